@@ -214,8 +214,8 @@ int genga_accel(genga_ctx *ctx, const genga_bodies *b, double *ax, double *ay, d
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): genga_accel for one system of n bodies, all massive
- * (0 <= n <= GENGA_NOALLOC_MAX_BODIES), with no context and no allocation.  Its scratch (source
- * records, launch plan, split shares; about 8.4 MB) is one static device array per GPU, held
+ * (0 <= n <= GENGA_NOALLOC_MAX_BODIES), with no context and no allocation.  Its scratch (launch
+ * plan, the tasks' shares; about 27 MB) is one static device array per GPU, held
  * until the process ends; its address is looked up on the first call on a device (or by
  * genga_create).  Reads b->x, b->y, b->z, b->m, b->rcrit (device, n entries; b may be NULL when
  * n = 0).  Writes ax, ay, az [n] (device), the encounter pairs (i < j, unordered, as the kick
@@ -290,7 +290,8 @@ int genga_graph_capture(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
 /* Launch the captured graph `repeats` times on `stream`. */
 int genga_graph_launch(genga_ctx *ctx, int repeats, void *stream);
 
-/* Time the kick's launch shapes (waves per workgroup x source split) on the current layout
+/* Time the kick's launch shapes (waves per workgroup x source split, the layout's own split
+ * among them) on the current layout
  * and keep the fastest for `prec` (synchronises `stream`; computes accelerations only, the
  * velocities are not changed).  cache_path (host string, may be NULL): a text file of earlier
  * results, one line per (device, precision, layout); a line matching the device's
@@ -302,8 +303,10 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
 
 /* Launch shape of the kick for `prec`: `waves` per workgroup (4, 8 or 16; 0 = default) and
  * `split`, the number of workgroups that share one block of 64 targets' sources (1..4;
- * 0 = chosen from the layout; > 1 adds a small finishing kernel that sums the shares in a
- * fixed order). */
+ * 0 = chosen from the layout, for each block by its own number of sources; more than one share
+ * per block adds a small finishing kernel that sums the shares in a fixed order).  Until it is
+ * set or tuned the shape is the layout's own (as after 0, 0); genga_get_kick_shape then gives
+ * the nearest uniform split. */
 int genga_set_kick_shape(genga_ctx *ctx, int prec, int waves, int split);
 int genga_get_kick_shape(genga_ctx *ctx, int prec, int *waves, int *split);
 

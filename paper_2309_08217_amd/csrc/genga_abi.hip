@@ -64,16 +64,19 @@ struct genga_ctx {
     std::vector<int32_t> n_massive_h; // per system; bodies beyond are TP2 test bodies
     size_t max_items = 0;
     // launch plan
-    WorkItem *items = nullptr;  // kick items, largest systems first
+    WorkItem *items = nullptr;  // kick and energy items, in system order
     int32_t n_items = 0;
-    WorkItem *eitems = nullptr; // energy items, in system order
     int32_t *item_first = nullptr;
-    int waves[2] = {default_kick_waves(0), default_kick_waves(1)}; // [prec] waves per workgroup of the kick
-    int grid[2] = {0, 0};       // 0: one workgroup per task
+    int4 *tasks = nullptr;      // the layout's own kick plan: (item, first source, end, 0)
+    int32_t *task_first = nullptr; // [n_items + 1] an item's tasks
+    int32_t n_tasks = 0;
+    int waves[2] = {0, 0};      // [prec] waves per workgroup of the kick (0: default_kick_waves)
     int split[2] = {1, 1};      // [prec] workgroups sharing an item's sources
-    double *kpart = nullptr;    // [KICK_MAX_SPLIT][3][n_total]
+    bool own_plan[2] = {true, true}; // [prec] the layout's own plan instead of `split`
+    double *kpart = nullptr;    // [tasks][3][64], at least KICK_MAX_SPLIT tasks per item
     // scratch
-    uint8_t *jrec = nullptr;    // 32 B per body
+    float *m32 = nullptr;       // [n_total] masses in FP32
+    double *chunk_mass = nullptr; // [n_chunks]
     double *rc2_part = nullptr;   // [n_chunks]
     double *mom_part = nullptr;   // [n_chunks][3]
     double *acc = nullptr;      // a_i of the last kick: [3][n_total]
@@ -228,9 +231,11 @@ struct genga_ctx {
         dfree(L.sys_of);
         dfree(L.mstar);
         dfree(items);
-        dfree(eitems);
         dfree(item_first);
-        dfree(jrec);
+        dfree(tasks);
+        dfree(task_first);
+        dfree(m32);
+        dfree(chunk_mass);
         dfree(rc2_part);
         dfree(mom_part);
         dfree(L.chunks);
@@ -293,6 +298,11 @@ int default_split(const genga_ctx *ctx)
     return default_kick_split(ctx->n_items, ctx->n_cu);
 }
 
+int kick_waves(const genga_ctx *ctx, int fp32)
+{
+    return ctx->waves[fp32] ? ctx->waves[fp32] : default_kick_waves(ctx->n_items, ctx->n_tasks, ctx->n_cu);
+}
+
 int check_prec(int prec)
 {
     if (prec != GENGA_KICK_FP32 && prec != GENGA_KICK_FP64) return fail(GENGA_ERR_ARG, "bad precision %d", prec);
@@ -305,17 +315,10 @@ int check_acc(int acc)
     return GENGA_OK;
 }
 
-// shift_tau != 0: the source-record pass first applies the pending second half of a Sun drift
-// (see enqueue_drift with defer_shift)
-int enqueue_kick(genga_ctx *ctx, const genga_bodies *b, double tau, int update_v, int prec, int acc, double *ax,
-                 double *ay, double *az, hipStream_t s, double shift_tau = 0.0)
+// What every launch over the kick's items takes from the context and the bodies.
+KickArgs kick_args(const genga_ctx *ctx, const genga_bodies *b)
 {
     const Layout &L = ctx->L;
-    ctx->list_valid = true;
-    if (L.n_total == 0) return GENGA_OK;
-    const int fp32 = prec == GENGA_KICK_FP32;
-    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, ctx->jrec, fp32, ctx->rc2_part, ctx->pair_count,
-                        ctx->mom_part, shift_tau, s));
     KickArgs a{};
     a.items = ctx->items;
     a.n_items = ctx->n_items;
@@ -328,23 +331,47 @@ int enqueue_kick(genga_ctx *ctx, const genga_bodies *b, double tau, int update_v
     a.vz = b->vz;
     a.m = b->m;
     a.rc = b->rcrit;
-    a.jrec = ctx->jrec;
+    a.m32 = ctx->m32;
     a.rc2_part = ctx->rc2_part;
+    a.chunk_mass = ctx->chunk_mass;
     a.chunk_first = L.chunk_first;
+    a.pairs = ctx->pairs;
+    a.pair_count = ctx->pair_count;
+    a.pair_cap = ctx->pair_cap;
+    a.flags = ctx->flags;
+    a.tasks = ctx->tasks;
+    a.task_first = ctx->task_first;
+    a.n_tasks = ctx->n_tasks;
+    a.split = 1;
+    a.direct = ctx->n_tasks == ctx->n_items;
+    a.part = ctx->kpart;
+    a.status = ctx->col.mass ? ctx->col.status : nullptr;
+    return a;
+}
+
+// shift_tau != 0: the pass before the kick first applies the pending second half of a Sun drift
+// (see enqueue_drift with defer_shift)
+int enqueue_kick(genga_ctx *ctx, const genga_bodies *b, double tau, int update_v, int prec, int acc, double *ax,
+                 double *ay, double *az, hipStream_t s, double shift_tau = 0.0)
+{
+    const Layout &L = ctx->L;
+    ctx->list_valid = true;
+    if (L.n_total == 0) return GENGA_OK;
+    const int fp32 = prec == GENGA_KICK_FP32;
+    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, fp32 ? ctx->m32 : nullptr, ctx->rc2_part,
+                        ctx->chunk_mass, ctx->pair_count, ctx->mom_part, shift_tau, s));
+    KickArgs a = kick_args(ctx, b);
     a.ax = ax;
     a.ay = ay;
     a.az = az;
     a.tau = tau;
     a.update_v = update_v;
-    a.pairs = ctx->pairs;
-    a.pair_count = ctx->pair_count;
-    a.pair_cap = ctx->pair_cap;
-    a.flags = ctx->flags;
-    a.split = ctx->split[fp32];
-    a.n_total = L.n_total;
-    a.part = ctx->kpart;
-    a.status = ctx->col.mass ? ctx->col.status : nullptr;
-    HIP_TRY(launch_kick(a, fp32, acc == GENGA_ACC_KAHAN32, ctx->waves[fp32], ctx->grid[fp32], s));
+    if (!ctx->own_plan[fp32]) {
+        a.tasks = nullptr;
+        a.split = ctx->split[fp32];
+        a.direct = a.split == 1;
+    }
+    HIP_TRY(launch_kick(a, fp32, acc == GENGA_ACC_KAHAN32, kick_waves(ctx, fp32), s));
     return GENGA_OK;
 }
 
@@ -357,28 +384,9 @@ int enqueue_pair_list(genga_ctx *ctx, const genga_bodies *b, hipStream_t s)
         HIP_TRY(hipMemsetAsync(ctx->pair_count, 0, sizeof(int32_t), s));
         return GENGA_OK;
     }
-    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, ctx->jrec, 0, ctx->rc2_part, ctx->pair_count, nullptr,
-                        0.0, s));
-    KickArgs a{};
-    a.items = ctx->items;
-    a.n_items = ctx->n_items;
-    a.sys_off = L.sys_off;
-    a.x = b->x;
-    a.y = b->y;
-    a.z = b->z;
-    a.m = b->m;
-    a.rc = b->rcrit;
-    a.jrec = ctx->jrec;
-    a.rc2_part = ctx->rc2_part;
-    a.chunk_first = L.chunk_first;
-    a.pairs = ctx->pairs;
-    a.pair_count = ctx->pair_count;
-    a.pair_cap = ctx->pair_cap;
-    a.flags = ctx->flags;
-    a.split = 1;
-    a.n_total = L.n_total;
-    a.status = ctx->col.mass ? ctx->col.status : nullptr;
-    HIP_TRY(launch_pair_list(a, 0, s));
+    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, nullptr, ctx->rc2_part, ctx->chunk_mass,
+                        ctx->pair_count, nullptr, 0.0, s));
+    HIP_TRY(launch_pair_list(kick_args(ctx, b), s));
     return GENGA_OK;
 }
 
@@ -924,7 +932,7 @@ int enqueue_energy(genga_ctx *ctx, const genga_bodies *b, double vshift, double 
 {
     const Layout &L = ctx->L;
     const size_t n = (size_t)L.n_total;
-    HIP_TRY(launch_energy(L, ctx->eitems, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, ctx->acc,
+    HIP_TRY(launch_energy(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, ctx->acc,
                           ctx->acc + n, ctx->acc + 2 * n, vshift, ctx->epartial, ctx->item_first, out, s));
     return GENGA_OK;
 }
@@ -956,13 +964,14 @@ int enqueue_step(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, int pre
 }
 
 // Work items: 64 consecutive bodies of one system, never mixing massive and test bodies;
-// massive targets visit every body of their system, test targets only the massive ones.
-// Kick items are ordered by work (largest first), energy items by system.
+// massive targets visit every body of their system, test targets only the massive ones.  The
+// kick's tasks: every item's sources in runs of about the layout's run length.
 int upload_plan(genga_ctx *ctx)
 {
     const int n_sys = ctx->L.n_sys;
     std::vector<WorkItem> it;
     std::vector<int32_t> first(n_sys + 1, 0);
+    int64_t visits = 0;
     for (int s = 0; s < n_sys; ++s) {
         first[s] = (int32_t)it.size();
         const int b = ctx->sys_off_h[s], e = ctx->sys_off_h[s + 1];
@@ -972,13 +981,27 @@ int upload_plan(genga_ctx *ctx)
     }
     first[n_sys] = (int32_t)it.size();
     if (it.size() > ctx->max_items) return fail(GENGA_ERR_STATE, "work plan larger than its allocation");
-    std::vector<WorkItem> kit = it;
-    std::stable_sort(kit.begin(), kit.end(), [](const WorkItem &a, const WorkItem &b) { return a.nsrc > b.nsrc; });
-    ctx->n_items = (int32_t)it.size();
-    if (!it.empty()) {
-        HIP_TRY(hipMemcpy(ctx->items, kit.data(), kit.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(ctx->eitems, it.data(), it.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
+    for (const WorkItem &w : it) visits += w.nsrc;
+    const int len = kick_run_len(visits, ctx->n_cu);
+    std::vector<int4> tasks;
+    std::vector<int32_t> tfirst(it.size() + 1, 0);
+    for (size_t k = 0; k < it.size(); ++k) {
+        const int parts = kick_runs(it[k].nsrc, len), per = kick_run(it[k].nsrc, parts);
+        const int b = ctx->sys_off_h[it[k].sys], e = b + it[k].nsrc;
+        for (int p = 0; p < parts; ++p)
+            tasks.push_back(make_int4((int)k, std::min(b + p * per, e), std::min(b + (p + 1) * per, e), 0));
+        tfirst[k + 1] = (int32_t)tasks.size();
     }
+    ctx->n_items = (int32_t)it.size();
+    ctx->n_tasks = (int32_t)tasks.size();
+    HIP_TRY(dalloc(ctx->tasks, tasks.size()));
+    HIP_TRY(dalloc(ctx->task_first, tfirst.size()));
+    HIP_TRY(dalloc(ctx->kpart, 192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size())));
+    if (!it.empty()) {
+        HIP_TRY(hipMemcpy(ctx->items, it.data(), it.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy(ctx->tasks, tasks.data(), tasks.size() * sizeof(int4), hipMemcpyHostToDevice));
+    }
+    HIP_TRY(hipMemcpy(ctx->task_first, tfirst.data(), tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->item_first, first.data(), (n_sys + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->L.n_massive, ctx->n_massive_h.data(), n_sys * sizeof(int32_t), hipMemcpyHostToDevice));
     std::vector<int32_t> seg(2 * (size_t)n_sys + 1);
@@ -1090,10 +1113,10 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     for (int s = 0; s < n_sys; ++s) max_items += (size_t)(sys_off_host[s + 1] - sys_off_host[s] + 63) / 64 + 1;
     ctx->max_items = max_items;
     HIP_TRY(dalloc(ctx->items, max_items));
-    HIP_TRY(dalloc(ctx->eitems, max_items));
     HIP_TRY(dalloc(ctx->item_first, n_sys + 1));
     HIP_TRY(dalloc(ctx->L.n_massive, n_sys));
-    HIP_TRY(dalloc(ctx->jrec, nt * 32));
+    HIP_TRY(dalloc(ctx->m32, nt));
+    HIP_TRY(dalloc(ctx->chunk_mass, chunks.size()));
     HIP_TRY(dalloc(ctx->L.chunks, chunks.size()));
     HIP_TRY(dalloc(ctx->L.chunk_first, n_sys + 1));
     HIP_TRY(dalloc(ctx->rc2_part, chunks.size()));
@@ -1112,7 +1135,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     HIP_TRY(dalloc(ctx->member_slot, nt));
     HIP_TRY(dalloc(ctx->wg_list, (size_t)std::max(ctx->ce_cap, n_total) / 2 + 2));
     HIP_TRY(dalloc(ctx->epartial, 9 * (size_t)ENERGY_SPLIT * max_items));
-    HIP_TRY(dalloc(ctx->kpart, (size_t)KICK_MAX_SPLIT * 3 * nt));
     HIP_TRY(dalloc(ctx->import_bad, 1));
     HIP_TRY(hipMemset(ctx->import_bad, 0, sizeof(int32_t)));
     HIP_TRY(order_work_alloc(ctx->sw, std::max(n_total, 2 * n_sys)));
@@ -1399,7 +1421,7 @@ int genga_sort_bodies(genga_ctx *ctx, genga_bodies *b, int32_t *perm_out, void *
     HIP_TRY(launch_ring_order(nullptr, ctx->sort_seg, ctx->sort_seg, 2 * ctx->L.n_sys, n, b->x, b->y, ctx->sw,
                               ctx->sort_perm, s));
     // every per-body array the context knows, staged through the kick's share buffer (at least
-    // 3 n_total doubles; no kick is in flight between calls on the context's stream)
+    // n_total doubles; no kick is in flight between calls on the context's stream)
     double *tmp = ctx->kpart;
     std::vector<double *> arr = {b->x, b->y, b->z, b->vx, b->vy, b->vz, const_cast<double *>(b->m),
                                  const_cast<double *>(b->rcrit)};
@@ -1598,12 +1620,14 @@ int genga_set_kick_shape(genga_ctx *ctx, int prec, int waves, int split)
     if (!ctx) return fail(GENGA_ERR_ARG, "null context");
     int rc = check_prec(prec);
     if (rc) return rc;
-    if (waves == 0) waves = prec == GENGA_KICK_FP32 ? 16 : 8;
-    if (waves != 4 && waves != 8 && waves != 16) return fail(GENGA_ERR_ARG, "waves must be 4, 8 or 16");
-    if (split == 0) split = default_split(ctx);
+    const int fp32 = prec == GENGA_KICK_FP32;
+    if (waves != 0 && waves != 4 && waves != 8 && waves != 16) return fail(GENGA_ERR_ARG, "waves must be 4, 8 or 16");
+    const bool own = split == 0;
+    if (own) split = default_split(ctx);
     if (split < 1 || split > KICK_MAX_SPLIT) return fail(GENGA_ERR_ARG, "split must be 1..%d", KICK_MAX_SPLIT);
-    ctx->waves[prec == GENGA_KICK_FP32] = waves;
-    ctx->split[prec == GENGA_KICK_FP32] = split;
+    ctx->waves[fp32] = waves;
+    ctx->split[fp32] = split;
+    ctx->own_plan[fp32] = own;
     return GENGA_OK;
 }
 
@@ -1612,7 +1636,7 @@ int genga_get_kick_shape(genga_ctx *ctx, int prec, int *waves, int *split)
     if (!ctx || !waves || !split) return fail(GENGA_ERR_ARG, "null argument");
     int rc = check_prec(prec);
     if (rc) return rc;
-    *waves = ctx->waves[prec == GENGA_KICK_FP32];
+    *waves = kick_waves(ctx, prec == GENGA_KICK_FP32);
     *split = ctx->split[prec == GENGA_KICK_FP32];
     return GENGA_OK;
 }
@@ -1644,13 +1668,20 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
                  ctx->L.n_sys, ctx->L.n_total, (unsigned long long)h);
         if (FILE *f = fopen(cache_path, "r")) {
             char line[512];
-            bool hit = false;
+            bool hit = false, own = false;
             int cw = 0, cs = 0;
             const size_t kl = strlen(key);
             while (fgets(line, sizeof(line), f)) {
-                if (strncmp(line, key, kl) == 0 && line[kl] == ' ' && sscanf(line + kl, "%d %d", &cw, &cs) == 2 &&
-                    (cw == 4 || cw == 8 || cw == 16) && cs >= 1 && cs <= KICK_MAX_SPLIT)
+                if (strncmp(line, key, kl) != 0 || line[kl] != ' ') continue;
+                int w = 0, sp = 0;
+                const bool o = sscanf(line + kl, " own %d %d", &w, &sp) == 2;
+                if (!o && sscanf(line + kl, "%d %d", &w, &sp) != 2) continue;
+                if ((w == 4 || w == 8 || w == 16) && sp >= 1 && sp <= KICK_MAX_SPLIT) {
                     hit = true; // the last matching line wins
+                    own = o;
+                    cw = w;
+                    cs = sp;
+                }
             }
             const bool read_err = ferror(f) != 0;
             fclose(f);
@@ -1658,6 +1689,7 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
             if (hit) {
                 ctx->waves[fp32] = cw;
                 ctx->split[fp32] = cs;
+                ctx->own_plan[fp32] = own;
                 return GENGA_OK;
             }
         }
@@ -1666,11 +1698,12 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     float best = 1e30f;
-    int best_w = ctx->waves[fp32], best_s = ctx->split[fp32];
+    int best_w = ctx->waves[fp32], best_s = 0;
     for (int w : {4, 8, 16}) {
-        for (int sp = 1; sp <= KICK_MAX_SPLIT && !rc; ++sp) {
+        for (int sp = 0; sp <= KICK_MAX_SPLIT && !rc; ++sp) { // 0: the layout's own plan
             ctx->waves[fp32] = w;
-            ctx->split[fp32] = sp;
+            ctx->split[fp32] = sp > 0 ? sp : default_split(ctx);
+            ctx->own_plan[fp32] = sp == 0;
             // accelerations only (velocities untouched); one warm-up then three timed launches
             rc = enqueue_kick(ctx, b, 0.0, 0, prec, GENGA_ACC_FP64, ctx->acc, ctx->acc + n, ctx->acc + 2 * n, s);
             if (rc) break;
@@ -1688,14 +1721,17 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
             }
         }
     }
+    const bool own = best_s == 0;
+    if (own) best_s = default_split(ctx);
     ctx->waves[fp32] = best_w;
     ctx->split[fp32] = best_s;
+    ctx->own_plan[fp32] = own;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc || !cache_path) return rc;
     FILE *f = fopen(cache_path, "a");
     if (!f) return fail(GENGA_ERR_ARG, "cannot write the autotune cache %s", cache_path);
-    const bool ok = fprintf(f, "%s %d %d\n", key, best_w, best_s) > 0;
+    const bool ok = fprintf(f, "%s%s %d %d\n", key, own ? " own" : "", best_w, best_s) > 0;
     if (fclose(f) != 0 || !ok) return fail(GENGA_ERR_ARG, "cannot write the autotune cache %s", cache_path);
     return GENGA_OK;
 }

@@ -18,17 +18,6 @@ struct WorkItem {
                   // for test-body targets)
 };
 
-// Source ("j") records, rebuilt from the SoA state before each kick; 32 bytes so that one
-// scalar load brings a whole record into SGPRs for the wave-uniform inner loop.
-struct JRec32 {
-    double x, y, z;
-    float m;
-    float pad;
-};
-struct JRec64 {
-    double x, y, z, m;
-};
-
 enum DeviceFlag : int32_t {
     FLAG_CAPACITY = 1,
     FLAG_NONFINITE = 2,
@@ -44,8 +33,9 @@ constexpr int CE_MAX_GROUP = 64;
 constexpr int BS_KMAX = 8;
 
 // A run of at most CHUNK consecutive bodies of one system: the unit of the O(N) kernels
-// (source records, momentum sums, Sun drift), so block reductions never mix systems.
-constexpr int CHUNK = 1024;
+// (r_crit maxima, momentum sums, Sun drift; one body per thread), so block reductions never mix
+// systems.
+constexpr int CHUNK = 256;
 struct Chunk {
     int32_t sys, b, e, pad;
 };
@@ -69,8 +59,9 @@ struct KickArgs {
     const double *x, *y, *z;
     double *vx, *vy, *vz;         // updated when update_v != 0
     const double *m, *rc;
-    const void *jrec;             // JRec32[] or JRec64[]
+    const float *m32;             // masses in FP32 (FP32 kick)
     const double *rc2_part;       // [n_chunks] max r_crit^2 per chunk
+    const double *chunk_mass;     // [n_chunks] the mass a chunk's bodies share, NaN if they differ
     const int32_t *chunk_first;   // [n_sys + 1]
     double *ax, *ay, *az;         // a_i out (FP64), always written
     double tau;
@@ -79,9 +70,13 @@ struct KickArgs {
     int32_t *pair_count;
     int32_t pair_cap;
     int32_t *flags;
-    int32_t split;                // workgroups sharing one item's sources (>= 1)
-    int32_t n_total;
-    double *part;                 // [split][3][n_total] shares when split > 1
+    const int4 *tasks;            // [n_tasks] (item, first source, end, -), items in order; null: every
+                                  //   item's sources in `split` runs, task = item * split + run
+    const int32_t *task_first;    // [n_items + 1] an item's tasks (with tasks)
+    int32_t n_tasks;
+    int32_t split;
+    int32_t direct;               // one task per item: it writes the bodies itself
+    double *part;                 // [tasks][3][64] shares of the targets (else)
     const int32_t *status;        // with collisions: bodies with status != 0 are in no pair
 };
 
@@ -90,8 +85,8 @@ constexpr int KICK_MAX_SPLIT = 4;
 // Error message for genga_last_error(); returns code.
 int fail(int code, const char *fmt, ...);
 
-// Source split that best fills the chip: the kick's workgroups run about one per CU at a
-// time, so pick the split whose number of workgroups wastes the least of the last round.
+// Source split reported for a layout (genga_get_kick_shape) before any tuning: the number of
+// workgroups per item that wastes the least of the last round at one workgroup per CU.
 inline int default_kick_split(int n_items, int n_cu)
 {
     int best = 1;
@@ -108,8 +103,33 @@ inline int default_kick_split(int n_items, int n_cu)
     return best;
 }
 
-// Waves per workgroup of the kick before any tuning.
-inline int default_kick_waves(int fp32) { return fp32 ? 16 : 8; }
+// The layout's own task plan.  Run length of a task's sources: the shortest of KICK_RUN_MIN,
+// 2 KICK_RUN_MIN, .. that keeps the layout within KICK_TASKS_PER_CU tasks per CU (source visits
+// = sum over the items of their sources).  Long runs spare prologues, short ones even out the
+// CUs' shares: FP32 kick of 40000 bodies 620 / 576 / 562 us, of 64 discs of 2000-8000 bodies
+// 611 / 614 / 567 us with 16 / 32 / 64 tasks per CU; a shortest run of 512 costs 2048 bodies
+// 19.4 against 15.1 us, one of 128 gives 40 massive among 20000 test bodies 52 against 35 us.
+constexpr int KICK_RUN_MIN = 256;
+constexpr int KICK_TASKS_PER_CU = 64;
+inline int kick_run_len(int64_t source_visits, int n_cu)
+{
+    int len = KICK_RUN_MIN;
+    n_cu = n_cu < 256 ? n_cu : 256;
+    while (len < (1 << 20) && source_visits / len > (int64_t)KICK_TASKS_PER_CU * n_cu) len *= 2;
+    return len;
+}
+// Tasks of an item of nsrc sources at that run length, and the length of each task's run when
+// nsrc sources are cut into `parts` (a multiple of four, so that whole quads stay whole).
+inline int kick_runs(int nsrc, int len) { return nsrc < len + len / 2 ? 1 : (nsrc + len / 2) / len; }
+__host__ __device__ inline int kick_run(int nsrc, int parts) { return ((nsrc + parts - 1) / parts + 3) / 4 * 4; }
+
+// Waves per workgroup of the kick before any tuning: 4, of which 7 workgroups share a CU; 16 when
+// the plan has one task per item and leaves CUs idle, where only shorter runs per wave help
+// (257 bodies, FP64: 13.3 us with 8 waves, 16.0 with 4).
+inline int default_kick_waves(int n_items, int n_tasks, int n_cu)
+{
+    return n_tasks == n_items && n_items <= n_cu ? 16 : 4;
+}
 
 // Address of the allocation-free entry point's scratch array on `device` (looked up once).
 int noalloc_prepare(int device, unsigned char **ptr_out, int *n_cu_out);
@@ -117,17 +137,17 @@ int noalloc_prepare(int device, unsigned char **ptr_out, int *n_cu_out);
 constexpr int ENERGY_SPLIT = 4;   // workgroups sharing one item's sources in the energy sum
 
 // Kernel launchers (each enqueues on `stream`; return hipError_t of the launch).
-// Source records and r_crit^2 maxima for the kick.  With shift_tau != 0 the launch first
-// finishes a Sun drift: x += shift_tau P / Mstar per system, P summed from mom_part (the
-// per-chunk partials of a preceding launch_momentum).
+// What the kick takes per chunk (r_crit^2 maxima, common masses), the masses in FP32 (m32 may be
+// null) and a cleared pair count.  With shift_tau != 0 the launch first finishes a Sun drift:
+// x += shift_tau P / Mstar per system, P summed from mom_part (the per-chunk partials of a
+// preceding launch_momentum).
 hipError_t launch_prep(const Layout &L, double *x, double *y, double *z, const double *m,
-                       const double *rc, void *jrec, int fp32, double *rc2_part, int32_t *pair_count,
+                       const double *rc, float *m32, double *rc2_part, double *chunk_mass, int32_t *pair_count,
                        const double *mom_part, double shift_tau, hipStream_t stream);
 // kahan: the FP32 kick's blocks are summed with Kahan compensation in FP32 (else in FP64)
-hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, int grid, hipStream_t stream);
-// The encounter pairs of the state only (FP64 source records from launch_prep; no forces,
-// nothing written but a.pairs / a.pair_count), 8 waves per workgroup.
-hipError_t launch_pair_list(const KickArgs &a, int grid, hipStream_t stream);
+hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream);
+// The encounter pairs of the state only (no forces, nothing written but a.pairs / a.pair_count).
+hipError_t launch_pair_list(const KickArgs &a, hipStream_t stream);
 hipError_t launch_rcrit(const Layout &L, const double *x, const double *y, const double *z,
                         const double *vx, const double *vy, const double *vz, const double *m,
                         double n1, double n2, double dt, double *rc, hipStream_t stream);

@@ -1,5 +1,5 @@
 // Allocation-free long-range accelerations of one system (genga_accel_noalloc): the kick's
-// source records, launch plan and split shares live in one file-scope device array instead of
+// FP32 masses, launch plan and split shares live in one file-scope device array instead of
 // a context's allocations, for callers that cannot allocate device memory (graph capture,
 // serving loops).  The kernels are the kick's own (kick.hip), launched with the shape a
 // context picks by default for the same single system, so the results equal genga_accel's.
@@ -15,15 +15,18 @@ constexpr int NA_MAX_N = GENGA_NOALLOC_MAX_BODIES;
 constexpr int NA_MAX_ITEMS = NA_MAX_N / 64;
 constexpr int NA_MAX_CHUNKS = NA_MAX_N / CHUNK;
 constexpr int NA_MAX_DEVICES = 64;
+// tasks of the kick: at most KICK_TASKS_PER_CU per CU, and half a run more per item
+constexpr int NA_MAX_TASKS = KICK_TASKS_PER_CU * 256 + NA_MAX_ITEMS;
 
 // byte offsets of the parts of the scratch array (each a multiple of 256)
 constexpr size_t align256(size_t v) { return (v + 255) / 256 * 256; }
-constexpr size_t OFF_JREC = 0;                                                 // 32 B per body
-constexpr size_t OFF_PART = OFF_JREC + align256((size_t)NA_MAX_N * 32);       // [split][3][n] FP64
-constexpr size_t OFF_ITEMS = OFF_PART + align256((size_t)KICK_MAX_SPLIT * 3 * NA_MAX_N * sizeof(double));
+constexpr size_t OFF_M32 = 0;
+constexpr size_t OFF_PART = OFF_M32 + align256((size_t)NA_MAX_N * sizeof(float)); // [tasks][3][64] FP64
+constexpr size_t OFF_ITEMS = OFF_PART + align256((size_t)NA_MAX_TASKS * 192 * sizeof(double));
 constexpr size_t OFF_CHUNKS = OFF_ITEMS + align256((size_t)NA_MAX_ITEMS * sizeof(WorkItem));
 constexpr size_t OFF_RC2 = OFF_CHUNKS + align256((size_t)NA_MAX_CHUNKS * sizeof(Chunk));
-constexpr size_t OFF_SMALL = OFF_RC2 + align256((size_t)NA_MAX_CHUNKS * sizeof(double)); // sys_off[2], chunk_first[2]
+constexpr size_t OFF_MASS = OFF_RC2 + align256((size_t)NA_MAX_CHUNKS * sizeof(double));
+constexpr size_t OFF_SMALL = OFF_MASS + align256((size_t)NA_MAX_CHUNKS * sizeof(double)); // sys_off[2], chunk_first[2]
 constexpr size_t SCRATCH_BYTES = OFF_SMALL + 256;
 
 // Each GPU the library runs on holds its own copy until the process ends; host code takes its
@@ -37,8 +40,8 @@ struct DeviceScratch {
 DeviceScratch g_dev[NA_MAX_DEVICES];
 std::mutex g_mu;
 
-// Launch plan of one system of n bodies, all massive: the chunks of the O(N) source-record
-// pass and the kick's items of 64 targets; clears the caller's count and status words.
+// Launch plan of one system of n bodies, all massive: the chunks of the O(N) pass before the
+// kick and the kick's items of 64 targets; clears the caller's count and status words.
 __global__ __launch_bounds__(256) void noalloc_plan_kernel(int n, Chunk *chunks, WorkItem *items, int32_t *small,
                                                            int32_t *d_count, int32_t *d_status)
 {
@@ -124,10 +127,11 @@ extern "C" int genga_accel_noalloc(const genga_bodies *b, int32_t n, double *ax,
     L.sys_off = small;
     L.chunks = chunks;
     L.chunk_first = small + 2;
-    double *rc2_part = (double *)(base + OFF_RC2);
-    void *jrec = base + OFF_JREC;
-    e = launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, jrec, fp32, rc2_part, d_count, nullptr, 0.0, s);
-    if (e != hipSuccess) return fail(GENGA_ERR_HIP, "source records: %s", hipGetErrorString(e));
+    double *rc2_part = (double *)(base + OFF_RC2), *chunk_mass = (double *)(base + OFF_MASS);
+    float *m32 = (float *)(base + OFF_M32);
+    e = launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, fp32 ? m32 : nullptr, rc2_part, chunk_mass, d_count, nullptr,
+                    0.0, s);
+    if (e != hipSuccess) return fail(GENGA_ERR_HIP, "pass before the kick: %s", hipGetErrorString(e));
 
     KickArgs a{};
     a.items = items;
@@ -138,8 +142,9 @@ extern "C" int genga_accel_noalloc(const genga_bodies *b, int32_t n, double *ax,
     a.z = b->z;
     a.m = b->m;
     a.rc = b->rcrit;
-    a.jrec = jrec;
+    a.m32 = m32;
     a.rc2_part = rc2_part;
+    a.chunk_mass = chunk_mass;
     a.chunk_first = small + 2;
     a.ax = ax;
     a.ay = ay;
@@ -149,10 +154,13 @@ extern "C" int genga_accel_noalloc(const genga_bodies *b, int32_t n, double *ax,
     a.pair_count = d_count;
     a.pair_cap = pair_cap;
     a.flags = d_status;
-    a.split = default_kick_split(a.n_items, n_cu);
-    a.n_total = n;
+    // a context's own plan: every item has the same sources, so the same number of runs
+    a.split = kick_runs(n, kick_run_len((int64_t)a.n_items * n, n_cu));
+    a.direct = a.split == 1;
+    if ((int64_t)a.n_items * a.split > NA_MAX_TASKS)
+        return fail(GENGA_ERR_STATE, "kick plan of %d bodies larger than the scratch", n);
     a.part = (double *)(base + OFF_PART);
-    e = launch_kick(a, fp32, acc == GENGA_ACC_KAHAN32, default_kick_waves(fp32), 0, s);
+    e = launch_kick(a, fp32, acc == GENGA_ACC_KAHAN32, default_kick_waves(a.n_items, a.n_items * a.split, n_cu), s);
     if (e != hipSuccess) return fail(GENGA_ERR_HIP, "kick launch: %s", hipGetErrorString(e));
     return GENGA_OK;
 }

@@ -8,10 +8,10 @@
 // doubled / kept / halved, rejected steps shrunk by shrink_factor.
 //
 // One attempt is a fixed sequence of launches over all large groups at once: a force
-// evaluation and midpoint update per sub-step (64 targets per workgroup, 8 or 16 waves that
-// split the group's members as sources), then per column an error launch and a decision
-// launch.  A group that has accepted a column, or reached dt, skips the rest.  The host
-// repeats attempts until no group is active.
+// evaluation and midpoint update per sub-step (64 targets per workgroup), on the list path of
+// several columns side by side, on the tile path of one column after another.  A group that has
+// accepted a column, or reached dt, skips the rest.  The host repeats attempts until no group is
+// active.
 //
 // The members of a group are ordered by ring and azimuth about the star (by the host, once per
 // step), so a tile of 64 consecutive members is compact in space.  Each state buffer carries the
@@ -31,6 +31,10 @@ using CI = const __attribute__((address_space(4))) int32_t;
 
 constexpr int GB_TILE = 64;
 constexpr int GB_THREADS = 256;
+// Up to this launch grid all eight columns of an attempt run side by side, above it the first six:
+// 6600 bodies (104 tiles) 1.42 against 1.47 ms a pass of two steps, 40322 bodies (631 tiles) 17.1
+// against 15.9 ms a step.
+constexpr int BIG_SIDE_TILES = 256;
 
 __device__ __forceinline__ unsigned long long dbits(double v) { return (unsigned long long)__double_as_longlong(v); }
 __device__ __forceinline__ double bitsd(unsigned long long b) { return __longlong_as_double((long long)b); }
@@ -107,6 +111,9 @@ __global__ __launch_bounds__(64) void big_setup_kernel(BigBs b, const int32_t *s
             b.skin[body] = 2.0;
             b.crossed[f] = 0;
             b.amut[f] = 0.0;
+            const double i9 = 1.0 / (0.9 * rc[body]);
+            b.cr[f] = make_double2(rc[body], body - sys_off[s] >= n_massive[s] ? -i9 : i9);
+            for (int k = 0; k < 1 + 2 * BS_KMAX; ++k) b.P[(size_t)k * b.cap_M + f].w = m[body];
         }
         // candidate radius: the deepest level's r_crit
         double rd = rc[body];
@@ -433,57 +440,83 @@ __device__ __forceinline__ ListMember list_member(double skin, double ms, double
     return m;
 }
 
-// The source records of the list sub-steps: the constant words of every state buffer's records
-// and the positions of Y (the sub-steps write those of B1 and B2).
-__global__ __launch_bounds__(GB_THREADS) void big_src_kernel(BigBs b)
-{
-    const int f = blockIdx.x * GB_THREADS + threadIdx.x;
-    if (f >= b.dims[1]) return;
-    const size_t M = (size_t)b.dims[1], cm = (size_t)b.cap_M;
-    const double2 c = make_double2(b.rc[f], b.test[f] ? -b.i09[f] : b.i09[f]);
-    for (int i = 0; i < 3; ++i) reinterpret_cast<double2 *>(b.rec + (i * cm + f) * 8)[2] = c;
-    reinterpret_cast<double4 *>(b.rec + (size_t)f * 8)[0] = make_double4(b.Y[f], b.Y[M + f], b.Y[2 * M + f], b.mass[f]);
-}
-
-// Per tile: the box swept by its members' straight lines over [0, H], and the largest
+// Start of an attempt on the list path, one wave per tile: the positions of Y as source records,
+// the group's position and velocity scales (max |r|, max |v|: one atomic per workgroup whose
+// tiles share a group, as 631 tiles' atomics on one address took 10 us), and, unless the lists
+// still hold, the box swept by the tile's straight lines over [0, H] and the largest
 // S + |A| H^2 / 2 of its members.
-__global__ __launch_bounds__(64) void big_sweep_kernel(BigBs b)
+__global__ __launch_bounds__(GB_THREADS) void big_prepare_kernel(BigBs b)
 {
-    for (int me = blockIdx.x; me < b.dims[2]; me += gridDim.x) {
-        const int4 tile = b.tiles[me];
+    constexpr int NW = GB_THREADS / 64;
+    __shared__ unsigned long long red[2][NW];
+    __shared__ int grp[NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const size_t M = (size_t)b.dims[1];
+    for (int m0 = blockIdx.x * NW; m0 < b.dims[2]; m0 += gridDim.x * NW) {
+        const int me = m0 + wave;
+        const bool tile_on = me < b.dims[2];
+        const int4 tile = tile_on ? b.tiles[me] : make_int4(0, 0, 0, 0);
         const int g = tile.x;
-        if (b.done[g] || b.keep[g]) continue;
-        const size_t M = (size_t)b.dims[1];
-        const bool v = (int)threadIdx.x < tile.z;
-        const int f = tile.y + (v ? (int)threadIdx.x : 0);
+        const bool on = tile_on && !b.done[g];
+        const bool v = on && lane < tile.z;
+        const int f = tile.y + (v ? lane : 0);
         const double H = b.H[g];
         const double x = b.Y[f], y = b.Y[M + f], z = b.Y[2 * M + f];
         const double u = b.Y[3 * M + f], vy = b.Y[4 * M + f], w = b.Y[5 * M + f];
-        const double x1 = fma(u, H, x), y1 = fma(vy, H, y), z1 = fma(w, H, z);
-        double sk = 2.0;
         if (v) {
-            const int body = b.body[f];
-            sk = b.skin[body];
-            if (b.crossed[f]) { // the member left its bound in the last attempt: four times wider
-                sk *= 4.0;
-                b.skin[body] = sk;
-                b.crossed[f] = 0;
+            double *p = reinterpret_cast<double *>(b.P + f);
+            p[0] = x;
+            p[1] = y;
+            p[2] = z;
+        }
+        const double sr = wave_maxv(v ? sqrt(sep2_rn(x, y, z)) : 0.0);
+        const double sv = wave_maxv(v ? sqrt(sep2_rn(u, vy, w)) : 0.0);
+        if (lane == 0) {
+            grp[wave] = on ? g : -1;
+            red[0][wave] = dbits(sr);
+            red[1][wave] = dbits(sv);
+        }
+        __syncthreads();
+        if (threadIdx.x < 2) {
+            // waves of one group in a row combine before the atomic
+            unsigned long long *slot = threadIdx.x == 0 ? b.sr : b.sv;
+            unsigned long long mx = 0;
+            for (int k = 0; k < NW; ++k) {
+                if (grp[k] < 0) continue;
+                const unsigned long long t = red[threadIdx.x][k];
+                mx = t > mx ? t : mx;
+                if (k + 1 == NW || grp[k + 1] != grp[k]) {
+                    atomicMax(&slot[grp[k]], mx);
+                    mx = 0;
+                }
             }
         }
-        const ListMember lm = list_member(sk, b.mstar[g], H, x, y, z, u, vy, w, v ? b.amut[f] : 0.0);
-        if (v) b.pred[f] = make_double4(lm.ax, lm.ay, lm.az, lm.s);
-        const double lo[3] = {wave_minv(v ? fmin(x, x1) : INFINITY), wave_minv(v ? fmin(y, y1) : INFINITY),
-                              wave_minv(v ? fmin(z, z1) : INFINITY)};
-        const double hi[3] = {wave_maxv(v ? fmax(x, x1) : -INFINITY), wave_maxv(v ? fmax(y, y1) : -INFINITY),
-                              wave_maxv(v ? fmax(z, z1) : -INFINITY)};
-        const double ext =
-            wave_maxv(v ? lm.s + 0.5 * sqrt(sep2_rn(lm.ax, lm.ay, lm.az)) * H * H : 0.0);
-        const int lane = threadIdx.x;
-        if (lane < 3) {
-            b.sbb[me * 8 + lane] = lo[lane];
-            b.sbb[me * 8 + 3 + lane] = hi[lane];
+        if (on && !b.keep[g]) {
+            const double x1 = fma(u, H, x), y1 = fma(vy, H, y), z1 = fma(w, H, z);
+            double sk = 2.0;
+            if (v) {
+                const int body = b.body[f];
+                sk = b.skin[body];
+                if (b.crossed[f]) { // the member left its bound in the last attempt: four times wider
+                    sk *= 4.0;
+                    b.skin[body] = sk;
+                    b.crossed[f] = 0;
+                }
+            }
+            const ListMember lm = list_member(sk, b.mstar[g], H, x, y, z, u, vy, w, v ? b.amut[f] : 0.0);
+            if (v) b.pred[f] = make_double4(lm.ax, lm.ay, lm.az, lm.s);
+            const double lo[3] = {wave_minv(v ? fmin(x, x1) : INFINITY), wave_minv(v ? fmin(y, y1) : INFINITY),
+                                  wave_minv(v ? fmin(z, z1) : INFINITY)};
+            const double hi[3] = {wave_maxv(v ? fmax(x, x1) : -INFINITY), wave_maxv(v ? fmax(y, y1) : -INFINITY),
+                                  wave_maxv(v ? fmax(z, z1) : -INFINITY)};
+            const double ext = wave_maxv(v ? lm.s + 0.5 * sqrt(sep2_rn(lm.ax, lm.ay, lm.az)) * H * H : 0.0);
+            if (lane < 3) {
+                b.sbb[me * 8 + lane] = lo[lane];
+                b.sbb[me * 8 + 3 + lane] = hi[lane];
+            }
+            if (lane == 0) b.sbb[me * 8 + 6] = ext;
         }
-        if (lane == 0) b.sbb[me * 8 + 6] = ext;
+        __syncthreads(); // red is rewritten by the next tiles
     }
 }
 
@@ -691,83 +724,43 @@ __device__ __forceinline__ int decided(const BigBs &b, int g, int k, double tol)
     return (e != ~0ull && bitsd(e) <= tol) ? k : -1;
 }
 
-// What follows a member's pair sum in a sub-step: the star's pull, then the midpoint update of
-// OUT (modes 0 and 1, with the positions of OUT's source records) or, in mode 2, T(k, 0) and
-// the group's error estimate of column k.  Every lane of the wave calls it; `lead` marks the
-// member's first lane, `act` the members of an active group.
-__device__ __forceinline__ void member_tail(const BigBs &b, int k, int mode, int g, int fa, bool act, bool lead,
-                                            double xa, double ya, double za, double ax, double ay, double az,
-                                            const double *Z, const double *ZM, double *OUT, double *ROUT)
+// Column kv's verdict for the launches after its last sub-step: true when the group has
+// accepted it (or an earlier column), from the same words in every workgroup.  No workgroup of an
+// accepted group goes on to write stale, so all of them agree; the group's first one stores acc.
+__device__ __forceinline__ bool group_accepted(const BigBs &b, int g, int kv, double tol, bool store)
 {
-    const size_t M = (size_t)b.dims[1];
-    if (mode == 0 && k == 0 && lead) {
-        b.amut[fa] = sqrt(sep2_rn(ax, ay, az));
-        b.a0[fa] = ax;
-        b.a0[M + fa] = ay;
-        b.a0[2 * M + fa] = az;
-    }
-    const double ri = inv_sqrt64(sep2_rn(xa, ya, za));
-    const double s = -b.mstar[g] * (ri * ri) * ri;
-    double d[6] = {Z[3 * M + fa], Z[4 * M + fa], Z[5 * M + fa], s * xa + ax, s * ya + ay, s * za + az};
-    const double h = b.H[g] / (2 * (k + 1));
-    if (mode == 2) {
-        double tk[6];
-        for (int q = 0; q < 6; ++q) tk[q] = 0.5 * (ZM[q * M + fa] + Z[q * M + fa] + h * d[q]);
-        if (lead) {
-            double *T0 = b.tcol + (size_t)k * 6 * M;
-            for (int q = 0; q < 6; ++q) T0[q * M + fa] = tk[q];
-        }
-        if (k == 0) return;
-        double dp = 0.0, dvv = 0.0;
-        bool bad = false;
-        if (lead) {
-            for (int q = 0; q < 6; ++q) {
-                const double tz = b.tcol[q * M + fa];
-                double sum = 0.0;
-                for (int jj = 1; jj <= k; ++jj) {
-                    const double v = jj == k ? tk[q] : b.tcol[((size_t)jj * 6 + q) * M + fa];
-                    sum = fma(LAGRANGE.d[k][jj], v - tz, sum);
-                }
-                if (q < 3) dp = fmax(dp, fabs(sum));
-                else dvv = fmax(dvv, fabs(sum));
-                bad |= !(sum == sum);
-            }
-        }
-        const double e = fmax(dp / bitsd(b.sr[g]), dvv / bitsd(b.sv[g]));
-        wave_atomic_max(b.err + k, g * BS_KMAX, lead, (bad || !(e == e)) ? ~0ull : dbits(e));
-        return;
-    }
-    if (lead) {
-        double o[6];
-        for (int q = 0; q < 6; ++q) {
-            o[q] = (mode == 0 ? Z[q * M + fa] : ZM[q * M + fa]) + (mode == 0 ? h : 2.0 * h) * d[q];
-            OUT[q * M + fa] = o[q];
-        }
-        reinterpret_cast<double4 *>(ROUT + (size_t)fa * 8)[0] = make_double4(o[0], o[1], o[2], b.mass[fa]);
-    }
+    const int a = b.acc[g], ka = kv < 0 ? a : decided(b, g, kv, tol);
+    if (store && ka != a) b.acc[g] = ka;
+    return ka >= 0;
 }
 
-// One sub-step on the list path (modes and outputs as substep_tile; jstep: Z is the state at
-// tau = jstep * H / (2 (k + 1))), one workgroup per target tile: the records of the tile's
-// slots (the sources of RZ, Z's records) are staged in LDS, then BIG_LIST_LANES lanes share a
-// member, each summing every BIG_LIST_LANES-th entry of its list in order, and the parts are
-// added in a fixed tree.  48 bytes per staged source and at most 80 VGPRs: three workgroups
-// fit a CU.
+// Pass i of the columns k0, k0 + 1, .. (blockIdx.y) on the list path, one workgroup per target
+// tile (blockIdx.x): sub-step i of column k reads its states z_i (buffer B1 for odd i, B2 for
+// even) and z_(i-1) and writes z_(i+1) = z_(i-1) + 2 h f(z_i), or, as its last (i = 2 (k + 1)),
+// T(k, 0) and the group's error estimate.  Pass 0 evaluates f(Y) once and writes z_1 of every
+// column.  The records of the tile's slots are staged in LDS, then BIG_LIST_LANES lanes share a
+// member, each summing every BIG_LIST_LANES-th entry of its list in order; the parts are added in
+// a fixed tree whose result every lane has, so that the update's six components (in pass 0 the
+// columns) go to one lane each.
+//
+// Latency bound: two rounds of loads, a barrier, the list's chain of terms.  A launch per
+// sub-step and column ran 104 tiles (6600 bodies) on 104 CUs for 6.6 us each, 72 of them an
+// attempt; side by side the columns fill the chip and an attempt is 17 launches.  48 bytes per
+// staged source and at most 80 VGPRs: three workgroups fit a CU.
 template <bool LV>
-__global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_per_eu(6))) void big_substep_list_kernel(BigBs b, int k, int mode, int jstep,
-                                                                               const double *Z, const double *ZM,
-                                                                               double *OUT, const double *RZ,
-                                                                               double *ROUT)
+__global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_per_eu(6))) void big_pass_kernel(
+    BigBs b, int i, int k0, int kv, double tol)
 {
     constexpr int P = BIG_LIST_LANES;
     constexpr int NS = BIG_LIST_SLOTS * 64;
+    static_assert(P == BS_KMAX && P >= 6, "one lane per column, and per component");
     __shared__ double2 sxy[NS], szm[NS], sri[NS]; // (x, y), (z, mass), (r_crit, signed 1 / (0.9 r_crit))
     __shared__ int sgi[LV ? NS : 1];               // member index, for the levels' radii
+    __shared__ unsigned long long ered[P];         // the waves' error maxima
     constexpr int PER = NS / (64 * P); // staged sources per thread
     static_assert(NS % (64 * P) == 0, "whole rounds of staging");
-    const size_t M = (size_t)b.dims[1];
-    // one target tile per workgroup (the grid covers the largest layout)
-    const int me = blockIdx.x;
+    const size_t M = (size_t)b.dims[1], cm = (size_t)b.cap_M;
+    const int me = blockIdx.x, k = k0 + (int)blockIdx.y, nsub = 2 * (k + 1);
     if (me >= b.dims[2]) return;
     // first round of loads: the tile, its slots
     const int4 tile = b.tiles[me];
@@ -780,106 +773,161 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
     const bool act = m < tile.z;
     const int fa = tile.y + (act ? m : 0);
     // second round: the group's state, the sources to stage and the member's own words
-    if (b.done[g] || b.acc[g] >= 0) return; // the whole workgroup
+    if (b.done[g]) return; // the whole workgroup
+    if (group_accepted(b, g, kv, tol, blockIdx.y == 0 && threadIdx.x == 0 && me == b.tfirst[g])) return;
+    const int bz = i == 0 ? 0 : (i & 1) ? 1 + 2 * k : 2 + 2 * k; // Z's buffer, and Z(i-1)'s
+    const int bm = i <= 1 ? 0 : (i & 1) ? 2 + 2 * k : 1 + 2 * k;
+    const double4 *PZ = b.P + bz * cm;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const int i = (int)threadIdx.x + u * 64 * P;
-        if (i < ns * 64 && (i & 63) < si[u].y) {
-            const size_t j = (size_t)(si[u].x + (i & 63));
-            const double4 p = reinterpret_cast<const double4 *>(RZ + j * 8)[0];
-            sxy[i] = make_double2(p.x, p.y);
-            szm[i] = make_double2(p.z, p.w);
-            sri[i] = reinterpret_cast<const double2 *>(RZ + j * 8)[2];
-            if constexpr (LV) sgi[i] = (int)j;
+        const int e = (int)threadIdx.x + u * 64 * P;
+        if (e < ns * 64 && (e & 63) < si[u].y) {
+            const size_t j = (size_t)(si[u].x + (e & 63));
+            const double4 p = PZ[j];
+            sxy[e] = make_double2(p.x, p.y);
+            szm[e] = make_double2(p.z, p.w);
+            sri[e] = b.cr[j];
+            if constexpr (LV) sgi[e] = (int)j;
         }
     }
-    const double xa = Z[fa], ya = Z[M + fa], za = Z[2 * M + fa];
-    const double2 ca = reinterpret_cast<const double2 *>(RZ + (size_t)fa * 8)[2];
+    const double4 pa = PZ[fa];
+    const double xa = pa.x, ya = pa.y, za = pa.z;
+    const double2 ca = b.cr[fa];
     const int tot = b.ltot[fa];
     const uint16_t *L = b.ll + (size_t)fa * BIG_LIST_CAP;
     int l0 = L[part], l1 = L[part + P]; // the first two positions (used only below tot)
+    // this lane's component of the update (part < 6: x, y, z, vx, vy, vz): Z's velocity and the
+    // component of z_(i-1) (velocities of buffer 0 stay in Y)
+    const int c = part % 3;
+    const auto vel = [&](int buf) {
+        return buf == 0 ? b.Y[(3 + c) * M + fa] : b.V[((size_t)(buf - 1) * 3 + c) * cm + fa];
+    };
+    const double vc = vel(bz);
+    const double zm = part < 3 ? reinterpret_cast<const double *>(b.P + bm * cm + fa)[c] : vel(bm);
     __syncthreads();
-    {
-        double ax = 0.0, ay = 0.0, az = 0.0;
-        if (act) {
-            // the bound of the lists: every member stays within S of its prediction
-            if (part == 0 && jstep > 0) {
-                const double H = b.H[g], hs = H / (2 * (k + 1)), tau = hs * jstep;
-                const double4 pm = b.pred[fa];
-                const double h2 = 0.5 * (tau * tau - ((jstep & 1) ? hs * hs : 0.0));
-                const double px = fma(pm.x, h2, fma(b.Y[3 * M + fa], tau, b.Y[fa]));
-                const double py = fma(pm.y, h2, fma(b.Y[4 * M + fa], tau, b.Y[M + fa]));
-                const double pz = fma(pm.z, h2, fma(b.Y[5 * M + fa], tau, b.Y[2 * M + fa]));
-                if (!(sep2_rn(xa - px, ya - py, za - pz) <= pm.w * pm.w * (1.0 - 0x1p-30))) {
-                    b.stale[g] = 1;
-                    b.crossed[fa] = 1;
-                }
-            }
-            const double rca = ca.x, i09a = fabs(ca.y);
-            const bool testa = signbit(ca.y);
-            const auto term = [&](int l) {
-                const double2 xy = sxy[l], zm = szm[l], cj = sri[l];
-                const double dx = xy.x - xa, dy = xy.y - ya, dz = zm.x - za;
-                const bool own = rca >= cj.x;
-                const double rcab = own ? rca : cj.x;
-                const double q = sep2_rn(dx, dy, dz);
-                const double rq = inv_sqrt64(q);
-                const double yv = (q * rq - 0.1 * rcab) * (own ? i09a : fabs(cj.y));
-                const double y2 = yv * yv;
-                const double kv = yv <= 0.0 ? 0.0 : (yv >= 1.0 ? 1.0 : y2 / (2.0 * y2 - 2.0 * yv + 1.0));
-                double w = 1.0 - kv, rdeep = rcab;
-                if constexpr (LV) {
-                    const int j = sgi[l];
-                    for (int lv = 1; lv < b.nlev; ++lv) {
-                        const double rcl_ab = fmax(b.rcl[(size_t)(lv - 1) * b.cap_M + fa],
-                                                   b.rcl[(size_t)(lv - 1) * b.cap_M + j]);
-                        w *= 1.0 - changeover_k((q * rq - 0.1 * rcl_ab) / (0.9 * rcl_ab));
-                        rdeep = rcl_ab;
-                    }
-                }
-                // the lists hold no member itself
-                const bool in = !(testa && signbit(cj.y)) && q < sq_rn(rdeep);
-                const double s = in ? zm.y * w * (rq * rq) * rq : 0.0;
-                ax = fma(s, dx, ax);
-                ay = fma(s, dy, ay);
-                az = fma(s, dz, az);
-            };
-            // lane `part` sums every P-th entry from `part` on, in order; the positions of the
-            // next two are loaded ahead (past the end: entry 0, unused)
-            const auto entry = [&](int e) { return (int)L[e < tot ? e : 0]; };
-            for (int e = part; e < tot; e += P) {
-                const int l = l0;
-                l0 = l1;
-                l1 = entry(e + 2 * P);
-                term(l);
+    double ax = 0.0, ay = 0.0, az = 0.0;
+    const double H = b.H[g];
+    if (act) {
+        // the bound of the lists: every member stays within S of its prediction
+        if (part == P - 1 && i > 0) {
+            const double hs = H / nsub, tau = hs * i;
+            const double4 pm = b.pred[fa];
+            const double h2 = 0.5 * (tau * tau - ((i & 1) ? hs * hs : 0.0));
+            const double px = fma(pm.x, h2, fma(b.Y[3 * M + fa], tau, b.Y[fa]));
+            const double py = fma(pm.y, h2, fma(b.Y[4 * M + fa], tau, b.Y[M + fa]));
+            const double pz = fma(pm.z, h2, fma(b.Y[5 * M + fa], tau, b.Y[2 * M + fa]));
+            if (!(sep2_rn(xa - px, ya - py, za - pz) <= pm.w * pm.w * (1.0 - 0x1p-30))) {
+                b.stale[g] = 1;
+                b.crossed[fa] = 1;
             }
         }
-        // the parts of a member, in a fixed order
-        for (int off = P / 2; off > 0; off >>= 1) {
-            ax += __shfl_xor(ax, off, 64);
-            ay += __shfl_xor(ay, off, 64);
-            az += __shfl_xor(az, off, 64);
+        const double rca = ca.x, i09a = fabs(ca.y);
+        const bool testa = signbit(ca.y);
+        const auto term = [&](int l) {
+            const double2 xy = sxy[l], zw = szm[l], cj = sri[l];
+            const double dx = xy.x - xa, dy = xy.y - ya, dz = zw.x - za;
+            const bool own = rca >= cj.x;
+            const double rcab = own ? rca : cj.x;
+            const double q = sep2_rn(dx, dy, dz);
+            const double rq = inv_sqrt64(q);
+            const double yv = (q * rq - 0.1 * rcab) * (own ? i09a : fabs(cj.y));
+            const double y2 = yv * yv;
+            const double kv1 = yv <= 0.0 ? 0.0 : (yv >= 1.0 ? 1.0 : y2 * inv64(2.0 * y2 - 2.0 * yv + 1.0));
+            double w = 1.0 - kv1, rdeep = rcab;
+            if constexpr (LV) {
+                const int j = sgi[l];
+                for (int lv = 1; lv < b.nlev; ++lv) {
+                    const double rcl_ab = fmax(b.rcl[(size_t)(lv - 1) * b.cap_M + fa],
+                                               b.rcl[(size_t)(lv - 1) * b.cap_M + j]);
+                    w *= 1.0 - changeover_k((q * rq - 0.1 * rcl_ab) / (0.9 * rcl_ab));
+                    rdeep = rcl_ab;
+                }
+            }
+            // the lists hold no member itself
+            const bool in = !(testa && signbit(cj.y)) && q < sq_rn(rdeep);
+            const double s = in ? zw.y * w * (rq * rq) * rq : 0.0;
+            ax = fma(s, dx, ax);
+            ay = fma(s, dy, ay);
+            az = fma(s, dz, az);
+        };
+        // lane `part` sums every P-th entry from `part` on, in order; the positions of the next
+        // two are loaded ahead (past the end: entry 0, unused)
+        const auto entry = [&](int e) { return (int)L[e < tot ? e : 0]; };
+        for (int e = part; e < tot; e += P) {
+            const int l = l0;
+            l0 = l1;
+            l1 = entry(e + 2 * P);
+            term(l);
         }
-        member_tail(b, k, mode, g, fa, act, act && part == 0, xa, ya, za, ax, ay, az, Z, ZM, OUT, ROUT);
     }
-}
-
-// The first sub-step of column k >= 1 on the list path: the pair sums at Y are column 0's
-// (a0), so only the update runs, one thread per member; it also takes column k - 1's verdict.
-__global__ __launch_bounds__(GB_THREADS) void big_substep_start_kernel(BigBs b, int k, double tol, double *OUT,
-                                                                      double *ROUT)
-{
-    const int f = blockIdx.x * GB_THREADS + threadIdx.x;
-    const bool valid = f < b.dims[1];
-    const int fa = valid ? f : 0;
-    const int g = b.grp[fa];
-    const int ka = decided(b, g, k - 1, tol); // column k - 1's verdict
-    if (valid && fa == b.off[g] && ka != b.acc[g]) b.acc[g] = ka;
-    const bool act = valid && !b.done[g] && ka < 0;
-    const size_t M = (size_t)b.dims[1];
-    const double *Y = b.Y;
-    member_tail(b, k, 0, g, fa, act, act, Y[fa], Y[M + fa], Y[2 * M + fa], act ? b.a0[fa] : 0.0,
-                act ? b.a0[M + fa] : 0.0, act ? b.a0[2 * M + fa] : 0.0, Y, Y, OUT, ROUT);
+    // the parts of a member, in a fixed order
+    for (int off = P / 2; off > 0; off >>= 1) {
+        ax += __shfl_xor(ax, off, 64);
+        ay += __shfl_xor(ay, off, 64);
+        az += __shfl_xor(az, off, 64);
+    }
+    if (i == 0 && act && part == 0) b.amut[fa] = sqrt(sep2_rn(ax, ay, az));
+    const double ri = inv_sqrt64(sep2_rn(xa, ya, za));
+    const double s = -b.mstar[g] * (ri * ri) * ri;
+    ax = s * xa + ax;
+    ay = s * ya + ay;
+    az = s * za + az;
+    if (i == 0) {
+        if (!act) return;
+        // lane `part`: z_1 of column `part`
+        const double h = H / (2 * (part + 1));
+        double *p = reinterpret_cast<double *>(b.P + (1 + 2 * part) * cm + fa);
+        double *v = b.V + (size_t)(2 * part) * 3 * cm + fa;
+        const double u0 = b.Y[3 * M + fa], u1 = b.Y[4 * M + fa], u2 = b.Y[5 * M + fa];
+        p[0] = xa + h * u0;
+        p[1] = ya + h * u1;
+        p[2] = za + h * u2;
+        v[0] = u0 + h * ax;
+        v[cm] = u1 + h * ay;
+        v[2 * cm] = u2 + h * az;
+        return;
+    }
+    const double pc = c == 0 ? xa : c == 1 ? ya : za;
+    const double d = part < 3 ? vc : c == 0 ? ax : c == 1 ? ay : az;
+    const double h = H / nsub;
+    if (i < nsub) {
+        if (!act || part >= 6) return;
+        const double o = zm + 2.0 * h * d;
+        const int bo = (i & 1) ? 2 + 2 * k : 1 + 2 * k;
+        if (part < 3) reinterpret_cast<double *>(b.P + bo * cm + fa)[c] = o;
+        else b.V[((size_t)(bo - 1) * 3 + c) * cm + fa] = o;
+        return;
+    }
+    const double tk = 0.5 * (zm + (part < 3 ? pc : vc) + h * d);
+    const bool use = act && part < 6;
+    double *T0 = b.tcol + part * M + fa; // T(j, 0) of this component: T0[6 j M]
+    if (use) T0[(size_t)k * 6 * M] = tk;
+    if (k == 0) return;
+    // the column's error estimate (Lagrange form of T(k, k) - T(k, k-1), relative to T(0, 0)):
+    // per position / velocity element over the group's scales; a non-finite one is kept as the
+    // all-ones pattern.  One atomic per workgroup, and only where it would raise the maximum.
+    unsigned long long e = 0;
+    if (use) {
+        const double tz = T0[0];
+        double tv[BS_KMAX], sum = 0.0;
+#pragma unroll
+        for (int j = 1; j < BS_KMAX; ++j) tv[j] = T0[(size_t)(j < k ? j : 0) * 6 * M];
+#pragma unroll
+        for (int j = 1; j < BS_KMAX; ++j)
+            if (j <= k) sum = fma(LAGRANGE.d[k][j], (j == k ? tk : tv[j]) - tz, sum);
+        const double err = fabs(sum) / bitsd(part < 3 ? b.sr[g] : b.sv[g]);
+        e = err == err ? dbits(err) : ~0ull;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        const unsigned long long w = __shfl_xor(e, off, 64);
+        e = w > e ? w : e;
+    }
+    if ((threadIdx.x & 63) == 0) ered[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < P; ++w) e = ered[w] > e ? ered[w] : e;
+    unsigned long long *slot = b.err + g * BS_KMAX + k;
+    if (e > __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(slot, e);
 }
 
 __global__ __launch_bounds__(64) void big_decide_kernel(BigBs b, int k, double tol)
@@ -902,25 +950,33 @@ __global__ __launch_bounds__(GB_THREADS) void big_accept_kernel(BigBs b, double 
     if (b.done[g] || ks < 0) return;
     const size_t M = (size_t)b.dims[1];
     for (int q = 0; q < 6; ++q) {
+        // every row's load in flight at once (rows above ks: T(0, 0) again, unused)
         const double t0 = b.tcol[q * M + f];
-        double s = 0.0;
-        for (int jj = 1; jj <= ks; ++jj) s = fma(LAGRANGE.w[ks][jj], b.tcol[((size_t)jj * 6 + q) * M + f] - t0, s);
+        double t[BS_KMAX], s = 0.0;
+#pragma unroll
+        for (int j = 1; j < BS_KMAX; ++j) t[j] = b.tcol[((size_t)(j <= ks ? j : 0) * 6 + q) * M + f];
+#pragma unroll
+        for (int j = 1; j < BS_KMAX; ++j)
+            if (j <= ks) s = fma(LAGRANGE.w[ks][j], t[j] - t0, s);
         b.Y[q * M + f] = t0 + s;
     }
 }
 
-// Step control per group, and the number of groups still short of dt.
+// Step control per group, and to the host the number of groups still short of dt, whether lists
+// overflowed, and how many attempts the slowest group still needs at least (each step at most
+// twice the one before it: the host enqueues that many without looking).
 __global__ __launch_bounds__(GB_THREADS) void big_control_kernel(BigBs b, double tol,
                                                                  int32_t *flags)
 {
-    __shared__ int cnt[GB_THREADS / 64];
+    __shared__ int cnt[GB_THREADS / 64], need[GB_THREADS / 64];
     const double dt = b.dtp[0];
-    int active = 0;
+    int active = 0, least = 0;
     for (int g = threadIdx.x; g < b.dims[0]; g += GB_THREADS) {
         if (b.done[g]) continue;
         if (b.skin && b.stale[g]) { // a void attempt: the same step again (with wider lists)
             b.keep[g] = 0;
             ++active;
+            least = max(least, 1);
             continue;
         }
         const int ks = decided(b, g, BS_KMAX - 1, tol);
@@ -942,15 +998,36 @@ __global__ __launch_bounds__(GB_THREADS) void big_control_kernel(BigBs b, double
                 b.H[g] = b.H[g] * shrink_factor(bitsd(e), tol);
             }
         }
-        active += !b.done[g];
+        if (!b.done[g]) {
+            ++active;
+            // H + 2 H + .. + 2^(n-1) H reaches dt - t
+            int n = 1;
+            const double rest = (dt - b.t[g]) * (1.0 - 0x1p-30);
+            for (double h = b.H[g], sum = h; sum < rest && n < BIG_AHEAD; ++n) {
+                h *= 2.0;
+                sum += h;
+            }
+            least = max(least, n);
+        }
     }
-    for (int s = 32; s > 0; s >>= 1) active += __shfl_xor(active, s, 64);
-    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = active;
+    for (int s = 32; s > 0; s >>= 1) {
+        active += __shfl_xor(active, s, 64);
+        least = max(least, __shfl_xor(least, s, 64));
+    }
+    if ((threadIdx.x & 63) == 0) {
+        cnt[threadIdx.x >> 6] = active;
+        need[threadIdx.x >> 6] = least;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         int total = 0;
-        for (int w = 0; w < GB_THREADS / 64; ++w) total += cnt[w];
-        *b.n_active = total;
+        for (int w = 0; w < GB_THREADS / 64; ++w) {
+            total += cnt[w];
+            least = max(least, need[w]);
+        }
+        b.status[0] = total;
+        b.status[1] = *b.ovf;
+        b.status[2] = least;
     }
 }
 
@@ -1028,34 +1105,31 @@ hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, i
     const int gg = (b.cap_G + 63) / 64, gm = (b.cap_M + GB_THREADS - 1) / GB_THREADS;
     const int nt = std::max(1, std::min(tile_grid, b.cap_T));
     const size_t M6 = 6 * (size_t)b.cap_M;
-    double *buf[3] = {b.Y, b.Y + M6, b.Y + 2 * M6}; // Y, B1, B2
-    double *rec[3] = {b.rec, b.rec + 8 * (size_t)b.cap_M, b.rec + 16 * (size_t)b.cap_M};
     const bool lv = b.nlev > 1;
-    auto substep = lv ? big_substep_list_kernel<true> : big_substep_list_kernel<false>;
+    auto pass = lv ? big_pass_kernel<true> : big_pass_kernel<false>;
     big_begin_kernel<<<gg, 64, 0, stream>>>(b, flags);
-    big_scale_kernel<<<gm, GB_THREADS, 0, stream>>>(b);
-    big_src_kernel<<<gm, GB_THREADS, 0, stream>>>(b);
-    big_sweep_kernel<<<nt, 64, 0, stream>>>(b);
+    big_prepare_kernel<<<(nt + 3) / 4, GB_THREADS, 0, stream>>>(b);
     const int nl = std::min(nt * BIG_LIST_SEGS, 65536);
     if (lv)
         big_list_kernel<true><<<nl, 64, 0, stream>>>(b);
     else
         big_list_kernel<false><<<nl, 64, 0, stream>>>(b);
     big_localize_kernel<<<nt, LOC_THREADS, 0, stream>>>(b);
-    for (int k = 0; k < BS_KMAX; ++k) {
-        const int nsub = 2 * (k + 1);
-        if (k == 0)
-            substep<<<nt, 64 * BIG_LIST_LANES, 0, stream>>>(b, k, 0, 0, buf[0], buf[0], buf[1], rec[0], rec[1]);
-        else
-            big_substep_start_kernel<<<gm, GB_THREADS, 0, stream>>>(b, k, tol, buf[1], rec[1]);
-        int zc = 1, zm = 0;
-        for (int i = 1; i < nsub; ++i) {
-            const int out = zm == 0 ? 2 : zm;
-            substep<<<nt, 64 * BIG_LIST_LANES, 0, stream>>>(b, k, 1, i, buf[zc], buf[zm], buf[out], rec[zc], rec[out]);
-            zm = zc;
-            zc = out;
+    const int threads = 64 * BIG_LIST_LANES;
+    pass<<<dim3(nt, 1), threads, 0, stream>>>(b, 0, 0, -1, tol);
+    // Columns in batches: side by side the columns above the accepted one have run for nothing.
+    // While the tiles leave CUs idle that costs nothing; beyond, the first six run together (the
+    // accepted column is mostly the fifth or sixth), and the last two only if they are needed.
+    const int split = nt <= BIG_SIDE_TILES ? BS_KMAX : 6;
+    int kv = -1; // the column whose verdict the launch takes: complete, but not yet decided
+    for (int k0 = 0; k0 < BS_KMAX; k0 = k0 == 0 ? split : BS_KMAX) {
+        const int k1 = k0 == 0 ? split : BS_KMAX;
+        for (int i = 1; i <= 2 * k1; ++i) {
+            const int kf = std::max(k0, (i + 1) / 2 - 1); // the first column that has a sub-step i
+            pass<<<dim3(nt, k1 - kf), threads, 0, stream>>>(b, i, kf, kv, tol);
+            // column i / 2 - 1 ends with pass i = 2 (k + 1)
+            kv = (i & 1) == 0 && i / 2 - 1 >= std::max(k0, 1) ? i / 2 - 1 : -1;
         }
-        substep<<<nt, 64 * BIG_LIST_LANES, 0, stream>>>(b, k, 2, nsub, buf[zc], buf[zm], nullptr, rec[zc], nullptr);
     }
     big_accept_kernel<<<gm, GB_THREADS, 0, stream>>>(b, tol);
     big_control_kernel<<<1, GB_THREADS, 0, stream>>>(b, tol, flags);

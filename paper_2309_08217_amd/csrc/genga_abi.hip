@@ -92,13 +92,13 @@ struct genga_ctx {
     // grid-wide Bulirsch-Stoer for groups of more than CE_MAX_GROUP members (opt-in)
     int32_t large_groups = 0;
     BigBs big;
-    int32_t *pin = nullptr;            // pinned host words for the per-attempt status reads
+    int32_t *pin = nullptr;            // pinned host words: [2] the union-find rounds, [4..6] the attempts' status
     hipStream_t big_stream = nullptr;  // private stream to capture one attempt
     DriftSide side;                    // the drift's second stream (groups of 9..64 members)
-    // the captured attempt, replayed on the caller's stream: one per tile-launch grid (a power
-    // of two that covers the layout's tiles)
-    hipGraphExec_t big_exec[32] = {};
-    hipGraphExec_t big_exec_list[32] = {}; // the same on the list path
+    // the captured attempt, replayed on the caller's stream: one per tile-launch grid (64 times
+    // a power of 2^(1/4) that covers the layout's tiles)
+    hipGraphExec_t big_exec[64] = {};
+    hipGraphExec_t big_exec_list[64] = {}; // the same on the list path
     int32_t *big_changed = nullptr;    // device word of the union-find rounds
     int32_t ce_cap = 0;                // members / group_start capacity
     std::vector<int32_t> gs_h;         // group_start copied to the host
@@ -161,12 +161,10 @@ struct genga_ctx {
         dfree(big.sr);
         dfree(big.sv);
         dfree(big.err);
-        dfree(big.n_active);
         dfree(big.rcl);
         dfree(big.nl);
         dfree(big.nlen);
         dfree(big.ltot);
-        dfree(big.a0);
         dfree(big.ll);
         dfree(big.slot);
         dfree(big.nslot);
@@ -177,7 +175,9 @@ struct genga_ctx {
         dfree(big.stale);
         dfree(big.keep);
         dfree(big.sbb);
-        dfree(big.rec);
+        dfree(big.P);
+        dfree(big.V);
+        dfree(big.cr);
         dfree(big.ovf);
         big.nlev = 1;
         dfree(rc_lv);
@@ -542,11 +542,9 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.sr, G));
     HIP_TRY(dalloc(b.sv, G));
     HIP_TRY(dalloc(b.err, G * BS_KMAX));
-    HIP_TRY(dalloc(b.n_active, 1));
     HIP_TRY(dalloc(b.nl, M * BIG_LIST_CAP));
     HIP_TRY(dalloc(b.nlen, M * BIG_LIST_SEGS));
     HIP_TRY(dalloc(b.ltot, M));
-    HIP_TRY(dalloc(b.a0, 3 * (size_t)M));
     HIP_TRY(dalloc(b.ll, M * BIG_LIST_CAP));
     HIP_TRY(dalloc(b.slot, (size_t)b.cap_T * BIG_LIST_SLOTS));
     HIP_TRY(dalloc(b.nslot, (size_t)b.cap_T));
@@ -560,14 +558,17 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.keep, G));
     HIP_TRY(hipMemset(b.keep, 0, G * sizeof(int32_t)));
     HIP_TRY(dalloc(b.sbb, 8 * (size_t)b.cap_T));
-    HIP_TRY(dalloc(b.rec, 3 * 8 * (size_t)M));
+    HIP_TRY(dalloc(b.P, (size_t)(1 + 2 * BS_KMAX) * M));
+    HIP_TRY(dalloc(b.V, (size_t)(2 * BS_KMAX) * 3 * M));
+    HIP_TRY(dalloc(b.cr, M));
     HIP_TRY(dalloc(b.ovf, 1));
     HIP_TRY(hipMemset(b.ovf, 0, sizeof(int32_t)));
     HIP_TRY(hipMemset(b.stale, 0, G * sizeof(int32_t)));
     HIP_TRY(dalloc(b.dims, 4));
     HIP_TRY(dalloc(b.dtp, 1));
     HIP_TRY(dalloc(ctx->big_changed, 1));
-    if (!ctx->pin) HIP_TRY(hipHostMalloc((void **)&ctx->pin, 4 * sizeof(int32_t), hipHostMallocDefault));
+    if (!ctx->pin) HIP_TRY(hipHostMalloc((void **)&ctx->pin, 8 * sizeof(int32_t), hipHostMallocDefault));
+    HIP_TRY(hipHostGetDevicePointer((void **)&b.status, ctx->pin + 4, 0));
     return GENGA_OK;
 }
 
@@ -879,8 +880,9 @@ int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, co
                              dt, s));
     // every attempt ends with the count of groups still short of dt; the device gives up on a
     // group after 20000 attempts, so the loop ends
-    int gl = 6;
-    while ((1 << gl) < bg.n_tiles && (1 << gl) < bg.cap_T) ++gl;
+    int gl = 0;
+    const auto grid_of = [](int q) { return (int)std::ceil(64.0 * std::exp2(0.25 * q)); };
+    while (gl < 63 && grid_of(gl) < bg.n_tiles) ++gl;
     // one attempt's launch sequence, captured once per context, path and grid (sizes and dt live
     // in device memory, every buffer address is fixed)
     const auto attempt_graph = [&](bool lists, hipGraphExec_t &exec) -> int {
@@ -890,7 +892,7 @@ int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, co
         // tile path: 16 waves per tile while the grid fits one workgroup per CU, else 8 (two
         // workgroups per CU: at N = 40322, 631 tiles, 20.5 steps/s against 18.0 with 16 and 19.4
         // with 4)
-        const int tg = 1 << gl, waves = tg <= ctx->n_cu ? 16 : 8;
+        const int tg = grid_of(gl), waves = tg <= ctx->n_cu ? 16 : 8;
         const hipError_t le = lists ? launch_big_attempt_list(bg, 1e-12, ctx->flags, tg, ctx->big_stream)
                                     : launch_big_attempt(bg, 1e-12, ctx->flags, tg, waves, ctx->big_stream);
         hipGraph_t g = nullptr;
@@ -911,18 +913,18 @@ int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, co
     // the list path; a list above its capacity sends the rest of the step to the tile path
     if ((rc = attempt_graph(true, ctx->big_exec_list[gl]))) return rc;
     bool lists = true;
-    for (int attempt = 0; attempt <= 20001; ++attempt) {
-        HIP_TRY(hipGraphLaunch(lists ? ctx->big_exec_list[gl] : ctx->big_exec[gl], s));
-        HIP_TRY(hipMemcpyAsync(ctx->pin + 1, bg.n_active, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        if (lists) HIP_TRY(hipMemcpyAsync(ctx->pin + 2, bg.ovf, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    volatile const int32_t *status = ctx->pin + 4; // written by the attempt's last kernel
+    for (int attempt = 0, ahead = 1; attempt <= 20001; attempt += ahead) {
+        for (int k = 0; k < ahead; ++k) HIP_TRY(hipGraphLaunch(lists ? ctx->big_exec_list[gl] : ctx->big_exec[gl], s));
         HIP_TRY(hipStreamSynchronize(s));
-        if (lists && ctx->pin[2]) {
+        if (lists && status[1]) {
             ctx->pin[2] = 0;
             HIP_TRY(hipMemcpyAsync(bg.ovf, ctx->pin + 2, sizeof(int32_t), hipMemcpyHostToDevice, s));
             if ((rc = attempt_graph(false, ctx->big_exec[gl]))) return rc;
             lists = false;
         }
-        if (ctx->pin[1] == 0) break;
+        if (status[0] == 0) break;
+        ahead = std::max(1, (int)status[2]);
     }
     HIP_TRY(launch_big_finish(bg, b->x, b->y, b->z, b->vx, b->vy, b->vz, s));
     return GENGA_OK;

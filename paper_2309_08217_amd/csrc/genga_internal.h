@@ -244,7 +244,6 @@ struct BigBs {
     int32_t *last = nullptr, *attempts = nullptr, *acc = nullptr, *done = nullptr; // [G]
     unsigned long long *sr = nullptr, *sv = nullptr; // [G] bit patterns of max |r|, max |v|
     unsigned long long *err = nullptr;               // [G][BS_KMAX] bit patterns of the estimates
-    int32_t *n_active = nullptr;   // groups not yet at dt after the last attempt
     // hierarchical levels: with nlev > 1 the pair weight is prod_{k<nlev} (1 - K_k), level 0
     // from rc, level k >= 1 from rcl[(k - 1) * cap_M + f]; the candidate radius is the deepest
     // level's.  Fixed when the attempt graph is captured.
@@ -266,17 +265,19 @@ struct BigBs {
     double *skin = nullptr;        // [cap_M] skin factor of each body's bound (indexed by body): 2 at the
                                    //   step's start, times 4 after each crossing
     int32_t *crossed = nullptr;    // [cap_M] the member crossed its bound in the last attempt
-    double *a0 = nullptr;          // [3][cap_M] the members' pair sums at the attempt's start state Y
-                                   //   (list path: column 0's first sub-step; the later columns reuse them)
     double *amut = nullptr;        // [cap_M] |pair acceleration| at the last attempt's start (column 0's
                                    //   first sub-step, on either path)
     int32_t *stale = nullptr;      // [G] a sub-step crossed a bound: the group's attempt is void
     int32_t *keep = nullptr;       // [G] the group's last attempt was rejected (not void): same start, a
                                    //   shorter step, so its lists and bounds still hold
     double *sbb = nullptr;         // [cap_T][8] box swept over the attempt by a tile, and its largest S
-    double *rec = nullptr;         // [3][cap_M][8] per state buffer (Y, B1, B2): a source's words in one
-                                   //   64-byte record (x, y, z, mass, r_crit, 1 / (0.9 r_crit), -, -),
-                                   //   the sign of 1 / (0.9 r_crit) set for TP2 bodies
+    // the list path's state buffers, so that the extrapolation columns advance side by side:
+    // buffer 0 holds Y's positions, buffers 1 + 2k and 2 + 2k column k's sub-step states
+    double4 *P = nullptr;          // [1 + 2 BS_KMAX][cap_M] (x, y, z, mass)
+    double *V = nullptr;           // [2 BS_KMAX][3][cap_M] velocities of buffers 1..
+    double2 *cr = nullptr;         // [cap_M] (r_crit, 1 / (0.9 r_crit)), the latter's sign set for TP2 bodies
+    int32_t *status = nullptr;     // pinned host words that big_control_kernel writes: groups not yet at dt,
+                                   //   lists overflowed, attempts the slowest group needs at least
     int32_t *ovf = nullptr;        // device word: a list exceeded BIG_LIST_CAP (the host falls back to tiles)
 };
 constexpr int BIG_TILES_PER_GROUP = 1024; // a workgroup of 1024 threads tests one source tile each
@@ -284,6 +285,7 @@ constexpr int BIG_LIST_SEGS = 8;          // segments of a member's list (built 
 constexpr int BIG_LIST_SEG = 128;         // sources per segment
 constexpr int BIG_LIST_CAP = BIG_LIST_SEGS * BIG_LIST_SEG; // sources per member on the list path
 constexpr int BIG_LIST_LANES = 8;         // lanes that share one member's list in a sub-step
+constexpr int BIG_AHEAD = 16;             // attempts enqueued without looking at most
 constexpr int BIG_LIST_SLOTS = 16;        // source tiles a target tile's sub-step stages in LDS
 constexpr int LEVELS_MAX = 4;             // symplectic levels of the hierarchical step
 
@@ -298,8 +300,9 @@ hipError_t launch_big_setup(const Layout &L, const BigBs &b, const int32_t *memb
 // or 16 per workgroup (the sources of a target tile split over them).
 hipError_t launch_big_attempt(const BigBs &b, double tol, int32_t *flags, int tile_grid, int waves,
                               hipStream_t stream);
-// The same attempt on the list path: lists built at its start (one wave per target tile), then
-// each sub-step sums every member's list (BIG_LIST_LANES lanes per member).
+// The same attempt on the list path: lists built at its start, then one launch per pass, in which
+// the columns that still have that sub-step sum every member's list (BIG_LIST_LANES lanes per
+// member) side by side.
 hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, int tile_grid, hipStream_t stream);
 hipError_t launch_big_finish(const BigBs &b, double *x, double *y, double *z, double *vx, double *vy,
                              double *vz, hipStream_t stream);

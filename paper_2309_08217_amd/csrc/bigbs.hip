@@ -111,8 +111,6 @@ __global__ __launch_bounds__(64) void big_setup_kernel(BigBs b, const int32_t *s
             b.skin[body] = 2.0;
             b.crossed[f] = 0;
             b.amut[f] = 0.0;
-            const double i9 = 1.0 / (0.9 * rc[body]);
-            b.cr[f] = make_double2(rc[body], body - sys_off[s] >= n_massive[s] ? -i9 : i9);
             for (int k = 0; k < 1 + 2 * BS_KMAX; ++k) b.P[(size_t)k * b.cap_M + f].w = m[body];
         }
         // candidate radius: the deepest level's r_crit
@@ -120,6 +118,7 @@ __global__ __launch_bounds__(64) void big_setup_kernel(BigBs b, const int32_t *s
         for (int k = 1; k < b.nlev; ++k) {
             rd = rc_lv[(size_t)(k - 1) * n_total + body];
             b.rcl[(size_t)(k - 1) * b.cap_M + f] = rd;
+            b.i9l[(size_t)(k - 1) * b.cap_M + f] = 1.0 / (0.9 * rd);
         }
         mx = sq_rn(rd);
     }
@@ -209,7 +208,6 @@ __device__ __forceinline__ void substep_tile(const BigBs &b, int me, int k, int 
     const bool valid = lane < tile.z;
     const int fa = tile.y + (valid ? lane : 0);
     const double xa = Z[fa], ya = Z[M + fa], za = Z[2 * M + fa];
-    const double rca = b.rc[fa];
     const bool testa = b.test[fa] != 0;
     // candidate radius: the group's largest r_crit^2, with a margin for the contracted r^2;
     // a source tile is skipped when the gap between the boxes exceeds it
@@ -218,7 +216,6 @@ __device__ __forceinline__ void substep_tile(const BigBs &b, int me, int k, int 
     CD *ZX = (CD *)Z;
     CD *ZY = (CD *)(Z + M);
     CD *ZZ = (CD *)(Z + 2 * M);
-    CD *RC = (CD *)b.rc;
     CD *MS = (CD *)b.mass;
     CI *TS = (CI *)b.test;
     CD *BB = (CD *)bbZ;
@@ -227,40 +224,35 @@ __device__ __forceinline__ void substep_tile(const BigBs &b, int me, int k, int 
     double ax = 0.0, ay = 0.0, az = 0.0;
     const double i09a = b.i09[fa];
     CD *I9 = (CD *)b.i09;
-    // levels 1..nlev-1: the target's radii, and the source radii through scalar loads
-    double rcal[LEVELS_MAX - 1] = {};
-    CD *RCL = (CD *)b.rcl;
+    // levels 1..nlev-1: the target's 1 / (0.9 radius), the sources' through scalar loads
+    double i9al[LEVELS_MAX - 1] = {};
+    CD *I9L = (CD *)b.i9l;
     if constexpr (LV)
-        for (int l = 1; l < b.nlev; ++l) rcal[l - 1] = b.rcl[(size_t)(l - 1) * b.cap_M + fa];
+        for (int l = 1; l < b.nlev; ++l) i9al[l - 1] = b.i9l[(size_t)(l - 1) * b.cap_M + fa];
     // the (1 - K) Newtonian terms of sources j .. j + cnt - 1 (cnt <= 4), side by side and
     // without branches: a pair outside r_crit,ab, the target itself and a test-test pair get
     // weight zero; the terms are added in source order
-    auto pairs4 = [&](int j, int cnt, const double (&dx)[4], const double (&dy)[4], const double (&dz)[4]) {
+    auto pairs4 = [&](int j, int cnt, const double (&dx)[4], const double (&dy)[4], const double (&dz)[4],
+                      const double (&q)[4]) {
         double t[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int jj = min(j + u, j + cnt - 1);
-            const double rcj = RC[jj], mj = MS[jj], i9j = I9[jj];
-            const bool tj = TS[jj] != 0;
-            const bool own = rca >= rcj;
-            const double rcab = own ? rca : rcj;
-            const double q = sep2_rn(dx[u], dy[u], dz[u]);
-            const double rq = inv_sqrt64(q);
-            const double yv = (q * rq - 0.1 * rcab) * (own ? i09a : i9j);
-            const double y2 = yv * yv;
-            const double kv = yv <= 0.0 ? 0.0 : (yv >= 1.0 ? 1.0 : y2 / (2.0 * y2 - 2.0 * yv + 1.0));
-            double w = 1.0 - kv, rdeep = rcab;
+            const bool skip = u >= cnt || j + u == fa || (testa && TS[jj] != 0);
+            const double qs = skip ? 1.0 : q[u];
+            const double rq = inv_sqrt64(qs), r = qs * rq;
+            const Changeover c0 = changeover_parts(r, fmin(i09a, I9[jj]));
+            double uu = c0.u, dd = c0.d;
             if constexpr (LV) {
-                // prod over the deeper levels of (1 - K_l); inside the deepest radius every
-                // level's radius holds the pair, as the radii do not grow with the level
+                // prod over the deeper levels of (1 - K_l): zero beyond the deepest radius
                 for (int l = 1; l < b.nlev; ++l) {
-                    const double rcl_ab = fmax(rcal[l - 1], RCL[(size_t)(l - 1) * b.cap_M + jj]);
-                    w *= 1.0 - changeover_k((q * rq - 0.1 * rcl_ab) / (0.9 * rcl_ab));
-                    rdeep = rcl_ab;
+                    const Changeover cl =
+                        changeover_parts(r, fmin(i9al[l - 1], I9L[(size_t)(l - 1) * b.cap_M + jj]));
+                    uu *= cl.u;
+                    dd *= cl.d;
                 }
             }
-            const bool in = u < cnt && j + u != fa && !(testa && tj) && q < sq_rn(rdeep);
-            t[u] = in ? mj * w * (rq * rq) * rq : 0.0;
+            t[u] = (skip ? 0.0 : MS[jj]) * (uu * uu) * inv64(dd) * ((rq * rq) * rq);
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -311,7 +303,7 @@ __device__ __forceinline__ void substep_tile(const BigBs &b, int me, int k, int 
                 dz[v] = ZZ[j + v] - za;
                 q[v] = fma(dx[v], dx[v], fma(dy[v], dy[v], dz[v] * dz[v]));
             }
-            if (fmin(fmin(q[0], q[1]), fmin(q[2], q[3])) < T) pairs4(j, 4, dx, dy, dz);
+            if (fmin(fmin(q[0], q[1]), fmin(q[2], q[3])) < T) pairs4(j, 4, dx, dy, dz, q);
         }
         if (j < je) {
             const int cnt = je - j;
@@ -324,7 +316,7 @@ __device__ __forceinline__ void substep_tile(const BigBs &b, int me, int k, int 
                 dz[v] = ZZ[jj] - za;
                 q[v] = v < cnt ? fma(dx[v], dx[v], fma(dy[v], dy[v], dz[v] * dz[v])) : INFINITY;
             }
-            if (fmin(fmin(q[0], q[1]), fmin(q[2], q[3])) < T) pairs4(j, cnt, dx, dy, dz);
+            if (fmin(fmin(q[0], q[1]), fmin(q[2], q[3])) < T) pairs4(j, cnt, dx, dy, dz, q);
         }
     }
     red[0][wave][lane] = ax;
@@ -745,7 +737,7 @@ __device__ __forceinline__ bool group_accepted(const BigBs &b, int g, int kv, do
 //
 // Latency bound: two rounds of loads, a barrier, the list's chain of terms.  A launch per
 // sub-step and column ran 104 tiles (6600 bodies) on 104 CUs for 6.6 us each, 72 of them an
-// attempt; side by side the columns fill the chip and an attempt is 17 launches.  48 bytes per
+// attempt; side by side the columns fill the chip and an attempt is 17 launches.  40 bytes per
 // staged source and at most 80 VGPRs: three workgroups fit a CU.
 template <bool LV>
 __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_per_eu(6))) void big_pass_kernel(
@@ -754,7 +746,8 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
     constexpr int P = BIG_LIST_LANES;
     constexpr int NS = BIG_LIST_SLOTS * 64;
     static_assert(P == BS_KMAX && P >= 6, "one lane per column, and per component");
-    __shared__ double2 sxy[NS], szm[NS], sri[NS]; // (x, y), (z, mass), (r_crit, signed 1 / (0.9 r_crit))
+    __shared__ double2 sxy[NS], szm[NS]; // (x, y), (z, mass)
+    __shared__ double si9[NS];           // 1 / (0.9 r_crit)
     __shared__ int sgi[LV ? NS : 1];               // member index, for the levels' radii
     __shared__ unsigned long long ered[P];         // the waves' error maxima
     constexpr int PER = NS / (64 * P); // staged sources per thread
@@ -786,13 +779,13 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
             const double4 p = PZ[j];
             sxy[e] = make_double2(p.x, p.y);
             szm[e] = make_double2(p.z, p.w);
-            sri[e] = b.cr[j];
+            si9[e] = b.i09[j];
             if constexpr (LV) sgi[e] = (int)j;
         }
     }
     const double4 pa = PZ[fa];
     const double xa = pa.x, ya = pa.y, za = pa.z;
-    const double2 ca = b.cr[fa];
+    const double i09a = b.i09[fa];
     const int tot = b.ltot[fa];
     const uint16_t *L = b.ll + (size_t)fa * BIG_LIST_CAP;
     int l0 = L[part], l1 = L[part + P]; // the first two positions (used only below tot)
@@ -821,31 +814,25 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
                 b.crossed[fa] = 1;
             }
         }
-        const double rca = ca.x, i09a = fabs(ca.y);
-        const bool testa = signbit(ca.y);
         const auto term = [&](int l) {
-            const double2 xy = sxy[l], zw = szm[l], cj = sri[l];
+            const double2 xy = sxy[l], zw = szm[l];
             const double dx = xy.x - xa, dy = xy.y - ya, dz = zw.x - za;
-            const bool own = rca >= cj.x;
-            const double rcab = own ? rca : cj.x;
-            const double q = sep2_rn(dx, dy, dz);
-            const double rq = inv_sqrt64(q);
-            const double yv = (q * rq - 0.1 * rcab) * (own ? i09a : fabs(cj.y));
-            const double y2 = yv * yv;
-            const double kv1 = yv <= 0.0 ? 0.0 : (yv >= 1.0 ? 1.0 : y2 * inv64(2.0 * y2 - 2.0 * yv + 1.0));
-            double w = 1.0 - kv1, rdeep = rcab;
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double rq = inv_sqrt64(q), r = q * rq;
+            // the lists hold neither the member itself nor two test bodies, and outside
+            // r_crit,ab the weight is zero
+            const Changeover c0 = changeover_parts(r, fmin(i09a, si9[l]));
+            double u = c0.u, dd = c0.d;
             if constexpr (LV) {
                 const int j = sgi[l];
                 for (int lv = 1; lv < b.nlev; ++lv) {
-                    const double rcl_ab = fmax(b.rcl[(size_t)(lv - 1) * b.cap_M + fa],
-                                               b.rcl[(size_t)(lv - 1) * b.cap_M + j]);
-                    w *= 1.0 - changeover_k((q * rq - 0.1 * rcl_ab) / (0.9 * rcl_ab));
-                    rdeep = rcl_ab;
+                    const Changeover cl = changeover_parts(r, fmin(b.i9l[(size_t)(lv - 1) * b.cap_M + fa],
+                                                                   b.i9l[(size_t)(lv - 1) * b.cap_M + j]));
+                    u *= cl.u;
+                    dd *= cl.d;
                 }
             }
-            // the lists hold no member itself
-            const bool in = !(testa && signbit(cj.y)) && q < sq_rn(rdeep);
-            const double s = in ? zw.y * w * (rq * rq) * rq : 0.0;
+            const double s = zw.y * (u * u) * inv64(dd) * ((rq * rq) * rq);
             ax = fma(s, dx, ax);
             ay = fma(s, dy, ay);
             az = fma(s, dz, az);

@@ -444,8 +444,8 @@ __device__ __forceinline__ double neville_c(int k, int l)
 struct BsShared {
     double pos[BS_LANES][4];                   // positions published for the pair forces
     double m[BS_LANES];                        // member masses
-    double rc[BS_LANES], r01[BS_LANES], i09[BS_LANES]; // r_crit, 0.1 r_crit, 1 / (0.9 r_crit)
-    double rcl[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1: r_crit of each
+    double i09[BS_LANES];                      // 1 / (0.9 r_crit)
+    double i9l[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1: the same of each
     int32_t test[BS_LANES];                    // member is a test body (TP2)
     int32_t nlev;                              // symplectic levels (1: the plain step)
 };
@@ -454,25 +454,28 @@ struct BsShared {
 struct BsMember {
     int a, nb, base; // member index, group size, lane of member 0 in pos[]
     bool act, test;
-    double mstar, rc, r01, i09;
+    double mstar, i09;
 };
 
-// With LV (hierarchical levels), the pair weight (1 - K) of level 0 times prod over levels
-// 1..nlev-1 of (1 - K_k) with the pair's level-k radius; the pair counts while closer than the
-// deepest level's radius (the radii do not grow with the level).  The factor of the deeper
-// levels, or 0 beyond the deepest radius; ra / rb give member a's / b's level radii.
+// m (1 - K) / r^3 of a pair at squared separation q: the factor of its difference vector in the
+// encounter force, zero outside r_crit,ab.  With LV (hierarchical levels) the weight is the
+// product over levels 0..nlev-1 of (1 - K_k), so zero beyond the deepest level's radius (the
+// radii do not grow with the level); ia / ib give the two members' 1 / (0.9 r_crit) of levels
+// 1.. with the given stride.
 template <bool LV>
-__device__ __forceinline__ double deeper_levels(double r, double q, int nlev, const double *ra, const double *rb,
-                                                int stride)
+__device__ __forceinline__ double encounter_factor(double q, double m, double i09, int nlev, const double *ia,
+                                                   const double *ib, int stride)
 {
-    if constexpr (!LV) return 1.0;
-    double w = 1.0;
-    for (int k = 1; k < nlev; ++k) {
-        const double rck = fmax(ra[(k - 1) * stride], rb[(k - 1) * stride]);
-        if (!(q < sq_rn(rck))) return 0.0;
-        w *= 1.0 - changeover_k((r - 0.1 * rck) / (0.9 * rck));
-    }
-    return w;
+    const double rq = inv_sqrt64(q), r = q * rq;
+    const Changeover c = changeover_parts(r, i09);
+    double u = c.u, d = c.d;
+    if constexpr (LV)
+        for (int k = 1; k < nlev; ++k) {
+            const Changeover ck = changeover_parts(r, fmin(ia[(k - 1) * stride], ib[(k - 1) * stride]));
+            u *= ck.u;
+            d *= ck.d;
+        }
+    return m * (u * u) * inv64(d) * ((rq * rq) * rq);
 }
 
 // dY/dt: Kepler term about the Sun plus the (1 - K) share of the Newtonian forces from the
@@ -488,21 +491,16 @@ __device__ void bs_forces(const BsMember &me, BsShared &S, int slot, const doubl
     const double ri = inv_sqrt64(z[0] * z[0] + z[1] * z[1] + z[2] * z[2]);
     const double s = -me.mstar * (ri * ri) * ri;
     double ax = s * z[0], ay = s * z[1], az = s * z[2];
-#pragma unroll 1
+    // two independent terms at a time; the member itself and a second test body get mass zero
+#pragma unroll 2
     for (int b = 0; b < me.nb; ++b) {
-        if (b == me.a || (me.test && S.test[b])) continue;
+        const bool skip = b == me.a || (me.test && S.test[b]);
         const double dx = S.pos[me.base + b][0] - z[0];
         const double dy = S.pos[me.base + b][1] - z[1];
         const double dz = S.pos[me.base + b][2] - z[2];
-        const double q = sep2_rn(dx, dy, dz);
-        // r_crit,ab = max(r_crit,a, r_crit,b), with that member's derived constants
-        const bool own = me.rc >= S.rc[b];
-        const double rcab = own ? me.rc : S.rc[b];
-        if (!(q < sq_rn(rcab))) continue;
-        const double rq = inv_sqrt64(q);
-        double w = 1.0 - changeover_k((q * rq - (own ? me.r01 : S.r01[b])) * (own ? me.i09 : S.i09[b]));
-        if constexpr (LV) w *= deeper_levels<LV>(q * rq, q, S.nlev, &S.rcl[0][me.a], &S.rcl[0][b], BS_LANES);
-        const double t = S.m[b] * w * (rq * rq) * rq;
+        const double q = skip ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
+        const double t = encounter_factor<LV>(q, skip ? 0.0 : S.m[b], fmin(me.i09, S.i09[b]), S.nlev, &S.i9l[0][me.a],
+                                              &S.i9l[0][b], BS_LANES);
         ax = fma(t, dx, ax);
         ay = fma(t, dy, ay);
         az = fma(t, dz, az);
@@ -615,8 +613,8 @@ constexpr int WG_THREADS = BS_KMAX * BS_LANES;
 
 struct BsWgShared {
     double pos[BS_KMAX][BS_LANES][3];          // each column's positions, for its pair forces
-    double m[BS_LANES], rc[BS_LANES], r01[BS_LANES], i09[BS_LANES];
-    double rcl[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1
+    double m[BS_LANES], i09[BS_LANES];
+    double i9l[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1
     double tab[BS_KMAX][6][BS_LANES];          // Neville rows, extended in place
     double err_last;                           // column BS_KMAX - 1's estimate
     int32_t test[BS_LANES];
@@ -628,7 +626,7 @@ struct BsWgShared {
 // between two barriers that every thread of the workgroup reaches.
 template <bool LV>
 __device__ void wg_forces(bool on, int k, int a, int part, int P, int nb, bool act, bool test, double mstar,
-                          double rc, double r01, double i09, BsWgShared &S, const double z[6], double d[6])
+                          double i09, BsWgShared &S, const double z[6], double d[6])
 {
     if (part == 0) {
         S.pos[k][a][0] = z[0];
@@ -645,21 +643,28 @@ __device__ void wg_forces(bool on, int k, int a, int part, int P, int nb, bool a
             ay = s * z[1];
             az = s * z[2];
         }
-#pragma unroll 1
-        for (int b = part; b < nb; b += P) {
-            if (b == a || (test && S.test[b])) continue;
+        // first the partners inside r_crit,ab, a bit each (in a chain of encounters most members
+        // are farther apart), then only their terms, every lane its own
+        unsigned long long near = 0;
+        for (int b = part, n = 0; b < nb; b += P, ++n) {
             const double dx = S.pos[k][b][0] - z[0];
             const double dy = S.pos[k][b][1] - z[1];
             const double dz = S.pos[k][b][2] - z[2];
-            const double q = sep2_rn(dx, dy, dz);
-            // r_crit,ab = max(r_crit,a, r_crit,b), with that member's derived constants
-            const bool own = rc >= S.rc[b];
-            const double rcab = own ? rc : S.rc[b];
-            if (!(q < sq_rn(rcab))) continue;
-            const double rq = inv_sqrt64(q);
-            double w = 1.0 - changeover_k((q * rq - (own ? r01 : S.r01[b])) * (own ? i09 : S.i09[b]));
-            if constexpr (LV) w *= deeper_levels<LV>(q * rq, q, S.nlev, &S.rcl[0][a], &S.rcl[0][b], BS_LANES);
-            const double t = S.m[b] * w * (rq * rq) * rq;
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double i = fmin(i09, S.i09[b]);
+            // r / (0.9 r_crit) < 10/9, with a margin for the rounding
+            const bool in = (q * i) * i < 100.0 / 81.0 * (1.0 + 0x1p-40);
+            near |= (unsigned long long)(in && b != a && !(test && S.test[b])) << n;
+        }
+        while (near) {
+            const int b = part + P * __builtin_ctzll(near);
+            near &= near - 1;
+            const double dx = S.pos[k][b][0] - z[0];
+            const double dy = S.pos[k][b][1] - z[1];
+            const double dz = S.pos[k][b][2] - z[2];
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double t = encounter_factor<LV>(q, S.m[b], fmin(i09, S.i09[b]), S.nlev, &S.i9l[0][a], &S.i9l[0][b],
+                                                  BS_LANES);
             ax = fma(t, dx, ax);
             ay = fma(t, dy, ay);
             az = fma(t, dz, az);
@@ -680,8 +685,8 @@ __device__ void wg_forces(bool on, int k, int a, int part, int P, int nb, bool a
 }
 
 template <bool LV>
-__device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bool test, double mstar, double rc,
-                             double r01, double i09, BsWgShared &S, double Y[6], double dt, double tol)
+__device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bool test, double mstar, double i09,
+                             BsWgShared &S, double Y[6], double dt, double tol)
 {
     const int nsub = 2 * (k + 1);
     const int lane = threadIdx.x & (BS_LANES - 1);
@@ -700,7 +705,7 @@ __device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bo
 #pragma unroll 1
         for (int i = 0; i <= 2 * BS_KMAX; ++i) {
             double dd[6];
-            wg_forces<LV>(i <= nsub, k, a, part, P, nb, act, test, mstar, rc, r01, i09, S, zc, dd);
+            wg_forces<LV>(i <= nsub, k, a, part, P, nb, act, test, mstar, i09, S, zc, dd);
             if (i == 0) {
                 for (int q = 0; q < 6; ++q) zc[q] = zm[q] + h * dd[q];
             } else if (i < nsub) {
@@ -772,10 +777,10 @@ template <int NB>
 struct SmallGroup {
     double mstar;
     double m[NB];
-    double rc2[NB][NB], r01[NB][NB], i09[NB][NB]; // per pair a < b, from r_crit,ab
+    double i09[NB][NB];                           // per pair a < b: 1 / (0.9 r_crit,ab)
     bool skip[NB][NB];                            // both are test bodies (TP2)
     int nlev;                                     // hierarchical levels
-    double rcl[LEVELS_MAX - 1][NB];               // levels 1..nlev-1: r_crit of each member
+    double i9l[LEVELS_MAX - 1][NB];               // levels 1..nlev-1: 1 / (0.9 r_crit) of each member
 };
 
 template <int NB, bool LV>
@@ -799,12 +804,8 @@ __device__ __forceinline__ void small_forces(const SmallGroup<NB> &g, const doub
         for (int b = a + 1; b < NB; ++b) {
             if (g.skip[a][b]) continue;
             const double dx = z[b][0] - z[a][0], dy = z[b][1] - z[a][1], dz = z[b][2] - z[a][2];
-            const double q = sep2_rn(dx, dy, dz);
-            if (!(q < g.rc2[a][b])) continue;
-            const double rq = inv_sqrt64(q);
-            double w = 1.0 - changeover_k((q * rq - g.r01[a][b]) * g.i09[a][b]);
-            if constexpr (LV) w *= deeper_levels<LV>(q * rq, q, g.nlev, &g.rcl[0][a], &g.rcl[0][b], NB);
-            const double u = w * (rq * rq) * rq;
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double u = encounter_factor<LV>(q, 1.0, g.i09[a][b], g.nlev, &g.i9l[0][a], &g.i9l[0][b], NB);
             const double ua = g.m[b] * u, ub = g.m[a] * u;
             d[a][3] = fma(ua, dx, d[a][3]);
             d[a][4] = fma(ua, dy, d[a][4]);
@@ -895,12 +896,12 @@ __device__ bool bs_small(const SmallGroup<NB> &g, int lane, double *ybuf, double
             const int kk = i / 2 - 1; // the column that has just completed
             __syncthreads();          // its T(kk, 0) is read by every lane
             if (kk == 0) continue;
-            const double err = fabs(lagrange_sum<E>(tcol, ld + kk * BS_KMAX, kk, e)) / scale;
-            if (!__ballot(lane < E && !(err <= tol))) {
+            const double diff = fabs(lagrange_sum<E>(tcol, ld + kk * BS_KMAX, kk, e));
+            if (!__ballot(lane < E && !(diff <= tol * scale))) {
                 kstar = kk;
                 break;
             }
-            if (kk == BS_KMAX - 1) err_last = wave_max(lane < E ? err : 0.0);
+            if (kk == BS_KMAX - 1) err_last = wave_max(lane < E ? diff / scale : 0.0);
         }
         if (kstar >= 0) {
             const double y = tcol[e] + lagrange_sum<E>(tcol, lw + kstar * BS_KMAX, kstar, e);
@@ -929,11 +930,7 @@ __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, dou
         g.m[a] = S.m[a];
 #pragma unroll
         for (int b = a + 1; b < NB; ++b) {
-            const bool own = S.rc[a] >= S.rc[b];
-            const double rcab = own ? S.rc[a] : S.rc[b];
-            g.rc2[a][b] = sq_rn(rcab);
-            g.r01[a][b] = own ? S.r01[a] : S.r01[b];
-            g.i09[a][b] = own ? S.i09[a] : S.i09[b];
+            g.i09[a][b] = fmin(S.i09[a], S.i09[b]);
             g.skip[a][b] = S.test[a] && S.test[b];
         }
     }
@@ -941,7 +938,7 @@ __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, dou
     if constexpr (LV)
         for (int k = 1; k < S.nlev; ++k)
 #pragma unroll
-            for (int a = 0; a < NB; ++a) g.rcl[k - 1][a] = S.rcl[k - 1][a];
+            for (int a = 0; a < NB; ++a) g.i9l[k - 1][a] = S.i9l[k - 1][a];
     if (lane < NB) {
         const int b = mem[lane];
         ybuf[6 * lane + 0] = x[b];
@@ -1015,12 +1012,10 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
         const int b = members[k0 + lane];
         const int sb = sys_of[b];
         S.m[lane] = m[b];
-        S.rc[lane] = rc[b];
-        S.r01[lane] = 0.1 * rc[b];
         S.i09[lane] = 1.0 / (0.9 * rc[b]);
         S.test[lane] = b - sys_off[sb] >= n_massive[sb];
         if constexpr (LV)
-            for (int l = 1; l < nlev; ++l) S.rcl[l - 1][lane] = rc_lv[(size_t)(l - 1) * n_total + b];
+            for (int l = 1; l < nlev; ++l) S.i9l[l - 1][lane] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
     }
     if (lane == 0) S.nlev = nlev;
     __syncthreads();
@@ -1042,8 +1037,6 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
     const int ai = me.act ? me.a : 0;
     me.test = S.test[ai] != 0;
     me.mstar = ms;
-    me.rc = S.rc[ai];
-    me.r01 = S.r01[ai];
     me.i09 = S.i09[ai];
     const int b = members[k0 + ai];
     double Y[6] = {x[b], y[b], z[b], vx[b], vy[b], vz[b]};
@@ -1106,12 +1099,10 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
             const int b = members[k0 + a];
             const int sb = sys_of[b];
             S.m[a] = m[b];
-            S.rc[a] = rc[b];
-            S.r01[a] = 0.1 * rc[b];
             S.i09[a] = 1.0 / (0.9 * rc[b]);
             S.test[a] = b - sys_off[sb] >= n_massive[sb];
             if constexpr (LV)
-                for (int l = 1; l < nlev; ++l) S.rcl[l - 1][a] = rc_lv[(size_t)(l - 1) * n_total + b];
+                for (int l = 1; l < nlev; ++l) S.i9l[l - 1][a] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
         }
         if (threadIdx.x == 0) {
             S.nlev = nlev;
@@ -1122,8 +1113,7 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
         const int ai = act ? a : 0;
         const int b = members[k0 + ai];
         double Y[6] = {x[b], y[b], z[b], vx[b], vy[b], vz[b]};
-        const bool ok = bs_workgroup<LV>(k, a, part, P, nb, act, S.test[ai] != 0, ms, S.rc[ai], S.r01[ai], S.i09[ai],
-                                         S, Y, dt, 1e-12);
+        const bool ok = bs_workgroup<LV>(k, a, part, P, nb, act, S.test[ai] != 0, ms, S.i09[ai], S, Y, dt, 1e-12);
         // every thread has read its member's state before the first force evaluation's barrier
         if (act && k == 0 && part == 0) store_state(x, y, z, vx, vy, vz, b, Y);
         if (!ok && threadIdx.x == 0) atomicOr(flags, FLAG_NOCONVERGE);

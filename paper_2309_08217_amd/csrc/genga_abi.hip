@@ -162,6 +162,7 @@ struct genga_ctx {
         dfree(big.sv);
         dfree(big.err);
         dfree(big.rcl);
+        dfree(big.i9l);
         dfree(big.nl);
         dfree(big.nlen);
         dfree(big.ltot);
@@ -177,7 +178,6 @@ struct genga_ctx {
         dfree(big.sbb);
         dfree(big.P);
         dfree(big.V);
-        dfree(big.cr);
         dfree(big.ovf);
         big.nlev = 1;
         dfree(rc_lv);
@@ -192,6 +192,7 @@ struct genga_ctx {
             dfree(t.Z);
             dfree(t.mass);
             dfree(t.rc);
+            dfree(t.i9);
             dfree(t.bb);
             dfree(t.cut2);
             dfree(t.tl);
@@ -480,6 +481,7 @@ int alloc_big(genga_ctx *ctx)
     if (lvl) {
         const size_t nt = (size_t)std::max(ctx->L.n_total, 1);
         HIP_TRY(dalloc(b.rcl, (size_t)(LEVELS_MAX - 1) * b.cap_M));
+        HIP_TRY(dalloc(b.i9l, (size_t)(LEVELS_MAX - 1) * b.cap_M));
         HIP_TRY(dalloc(ctx->rc_lv, (size_t)(LEVELS_MAX - 1) * nt));
         ctx->lt_cap_G = (int32_t)nt / 2 + 1;
         ctx->lt_cap_T = (int32_t)nt / 64 + ctx->lt_cap_G + 1;
@@ -496,6 +498,7 @@ int alloc_big(genga_ctx *ctx)
             HIP_TRY(dalloc(t.Z, nt));
             HIP_TRY(dalloc(t.mass, nt));
             HIP_TRY(dalloc(t.rc, (size_t)LEVELS_MAX * nt));
+            HIP_TRY(dalloc(t.i9, (size_t)LEVELS_MAX * nt));
             HIP_TRY(dalloc(t.bb, 8 * T));
             HIP_TRY(dalloc(t.cut2, G));
             HIP_TRY(dalloc(t.tl, T));
@@ -560,7 +563,6 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.sbb, 8 * (size_t)b.cap_T));
     HIP_TRY(dalloc(b.P, (size_t)(1 + 2 * BS_KMAX) * M));
     HIP_TRY(dalloc(b.V, (size_t)(2 * BS_KMAX) * 3 * M));
-    HIP_TRY(dalloc(b.cr, M));
     HIP_TRY(dalloc(b.ovf, 1));
     HIP_TRY(hipMemset(b.ovf, 0, sizeof(int32_t)));
     HIP_TRY(hipMemset(b.stale, 0, G * sizeof(int32_t)));

@@ -249,6 +249,7 @@ struct BigBs {
     // level's.  Fixed when the attempt graph is captured.
     int32_t nlev = 1;
     double *rcl = nullptr;         // [LEVELS_MAX - 1][cap_M]
+    double *i9l = nullptr;         // [LEVELS_MAX - 1][cap_M] 1 / (0.9 rcl)
     // neighbour lists (the list path), built at the start of every attempt (bigbs.hip): member
     // f's sources in BIG_LIST_SEGS segments, nl[f * BIG_LIST_CAP + s * BIG_LIST_SEG + e],
     // e < nlen[f * BIG_LIST_SEGS + s]
@@ -275,7 +276,6 @@ struct BigBs {
     // buffer 0 holds Y's positions, buffers 1 + 2k and 2 + 2k column k's sub-step states
     double4 *P = nullptr;          // [1 + 2 BS_KMAX][cap_M] (x, y, z, mass)
     double *V = nullptr;           // [2 BS_KMAX][3][cap_M] velocities of buffers 1..
-    double2 *cr = nullptr;         // [cap_M] (r_crit, 1 / (0.9 r_crit)), the latter's sign set for TP2 bodies
     int32_t *status = nullptr;     // pinned host words that big_control_kernel writes: groups not yet at dt,
                                    //   lists overflowed, attempts the slowest group needs at least
     int32_t *ovf = nullptr;        // device word: a list exceeded BIG_LIST_CAP (the host falls back to tiles)
@@ -316,6 +316,7 @@ struct LevelTiles {
     int32_t *body = nullptr, *test = nullptr;    // [M]
     double *X = nullptr, *Y = nullptr, *Z = nullptr, *mass = nullptr; // [M]
     double *rc = nullptr;                        // [LEVELS_MAX][cap_M]: radii of levels 0..
+    double *i9 = nullptr;                        // [LEVELS_MAX][cap_M]: 1 / (0.9 rc)
     double *bb = nullptr;                        // [n_tiles][8] tile boxes of X, Y, Z
     double *cut2 = nullptr;                      // [G] largest level-(l-1) radius^2 of the group
     int32_t *tl = nullptr;                       // [n_tiles] tile indices: the n_multi tiles of groups of

@@ -46,8 +46,11 @@ __global__ __launch_bounds__(64) void level_tiles_setup_kernel(LevelTiles t, con
         const int f = tile.y + threadIdx.x, body = t.body[f], s = sys_of[body];
         t.mass[f] = m[body];
         t.test[f] = body - sys_off[s] >= n_massive[s];
-        t.rc[f] = rc0[body];
-        for (int k = 1; k <= level; ++k) t.rc[(size_t)k * t.cap_M + f] = rcl[(size_t)(k - 1) * n_total + body];
+        for (int k = 0; k <= level; ++k) {
+            const double r = k == 0 ? rc0[body] : rcl[(size_t)(k - 1) * n_total + body];
+            t.rc[(size_t)k * t.cap_M + f] = r;
+            t.i9[(size_t)k * t.cap_M + f] = 1.0 / (0.9 * r);
+        }
         mx = fmax(0.0, sq_rn(t.rc[(size_t)(level - 1) * t.cap_M + f]));
     }
     mx = wave_maxv(mx);
@@ -72,23 +75,6 @@ __global__ __launch_bounds__(64) void level_tiles_pos_kernel(LevelTiles t, const
         t.Z[f] = pz;
     }
     tile_box(v, px, py, pz, t.bb, me);
-}
-
-// W_l K_l = prod_{k<l} (1 - K_k) times K_l (loops over the fixed bound, so the radii stay in
-// registers)
-__device__ __forceinline__ double level_share(double r, int l, const double *rcab)
-{
-    double w = 1.0, kl = 0.0;
-#pragma unroll
-    for (int k = 0; k < LEVELS_MAX; ++k) {
-        if (k > l) break;
-        const double kk = changeover_k((r - 0.1 * rcab[k]) / (0.9 * rcab[k]));
-        if (k < l)
-            w *= 1.0 - kk;
-        else
-            kl = kk;
-    }
-    return w * kl;
 }
 
 // The level's pairs found by a wave collect in its own LDS buffer and reach the list in
@@ -140,8 +126,8 @@ struct LvTarget {
     bool valid, test;
     int f, body;
     double x, y, z;
-    double rc[LEVELS_MAX]; // radii of levels 0..level (0 above)
-    double rc_up;          // the radius of level - 1
+    double i9[LEVELS_MAX]; // 1 / (0.9 radius) of levels 0..level (0 above)
+    double rc_up, rc_lv;   // the radii of level - 1 and level
 };
 
 __device__ __forceinline__ LvTarget lv_target(const LevelTiles &t, int4 tile, int lv)
@@ -156,8 +142,9 @@ __device__ __forceinline__ LvTarget lv_target(const LevelTiles &t, int4 tile, in
     me.z = t.Z[me.f];
     me.test = t.test[me.f] != 0;
 #pragma unroll
-    for (int k = 0; k < LEVELS_MAX; ++k) me.rc[k] = k <= lv ? t.rc[(size_t)k * t.cap_M + me.f] : 0.0;
+    for (int k = 0; k < LEVELS_MAX; ++k) me.i9[k] = k <= lv ? t.i9[(size_t)k * t.cap_M + me.f] : 0.0;
     me.rc_up = t.rc[(size_t)(lv - 1) * t.cap_M + me.f];
+    me.rc_lv = t.rc[(size_t)lv * t.cap_M + me.f];
     return me;
 }
 
@@ -169,24 +156,29 @@ __device__ __forceinline__ void lv_source(const LevelTiles &t, const LevelKickAr
 {
     CD *SM = (CD *)t.mass;
     CD *SR = (CD *)t.rc;
+    CD *S9 = (CD *)t.i9;
     CI *ST = (CI *)t.test;
     CI *SB = (CI *)t.body;
     const double q = sep2_rn(dx, dy, dz);
     const double rc_up = fmax(me.rc_up, rcj_up);
     bool em = false;
     if (me.valid && j != me.f && !(me.test && ST[j] != 0) && q < sq_rn(rc_up)) {
-        double rcab[LEVELS_MAX];
+        // W_l K_l = prod_{k<l} u_k^2 / d_k times y_l^2 / d_l (loops over the fixed bound, so the
+        // radii stay in registers)
+        const double rq = inv_sqrt64(q), r = q * rq;
+        double n = 1.0, d = 1.0;
 #pragma unroll
-        for (int k = 0; k < LEVELS_MAX; ++k) rcab[k] = k <= lv ? fmax(me.rc[k], SR[(size_t)k * t.cap_M + j]) : 1.0;
-        const double r = sqrt(q);
-        const double w = level_share(r, lv, rcab);
-        if (w > 0.0) {
-            const double s = SM[j] * w / (q * r);
-            ax += s * dx;
-            ay += s * dy;
-            az += s * dz;
+        for (int k = 0; k < LEVELS_MAX; ++k) {
+            if (k > lv) break;
+            const Changeover c = changeover_parts(r, fmin(me.i9[k], S9[(size_t)k * t.cap_M + j]));
+            n *= k < lv ? c.u : c.y;
+            d *= c.d;
         }
-        em = a.emit && me.body < SB[j] && q < sq_rn(fmax(t.rc[(size_t)lv * t.cap_M + me.f], SR[(size_t)lv * t.cap_M + j]));
+        const double s = SM[j] * (n * n) * inv64(d) * ((rq * rq) * rq);
+        ax = fma(s, dx, ax);
+        ay = fma(s, dy, ay);
+        az = fma(s, dz, az);
+        em = a.emit && me.body < SB[j] && q < sq_rn(fmax(me.rc_lv, SR[(size_t)lv * t.cap_M + j]));
     }
     lv_emit(a, buf, fill, em, me.body, SB[j]);
 }

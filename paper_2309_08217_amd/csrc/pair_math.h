@@ -45,13 +45,29 @@ __device__ __forceinline__ double inv_sqrt64(double q)
     return fma(y0 * e, p, y0);
 }
 
-// 1/x in FP64 for normal x well inside the range: v_rcp_f64 and two Newton steps (within an ulp
-// of the quotient, at a third of the instructions of a division)
+// 1/x in FP64 for normal x well inside the range: v_rcp_f64 (about 2^-24) and one third-order
+// correction; within an ulp of the quotient, at a third of the instructions of a division
 __device__ __forceinline__ double inv64(double x)
 {
-    double r = __builtin_amdgcn_rcp(x);
-    r = fma(fma(-x, r, 1.0), r, r);
-    return fma(fma(-x, r, 1.0), r, r);
+    const double r = __builtin_amdgcn_rcp(x);
+    const double e = fma(-x, r, 1.0);
+    return fma(r, fma(e, e, e), r);
+}
+
+// The changeover at separation r of a pair with i09 = 1 / (0.9 r_crit), without a division or a
+// branch: y = (r - 0.1 r_crit) i09 = r i09 - 1/9 cut to [0, 1] and u = 1 - y give K = y^2 / d and
+// 1 - K = u^2 / d with d = y^2 + u^2 (= 2 y^2 - 2 y + 1).  Outside r_crit u is 0, so 1 - K
+// vanishes by itself.  For the larger of two radii take the smaller i09.
+struct Changeover {
+    double y, u, d;
+};
+__device__ __forceinline__ Changeover changeover_parts(double r, double i09)
+{
+    Changeover c;
+    c.y = fmin(fmax(fma(r, i09, -1.0 / 9.0), 0.0), 1.0);
+    c.u = 1.0 - c.y;
+    c.d = fma(c.u, c.u, c.y * c.y);
+    return c;
 }
 
 // Step reduction after a rejected step: 0.9 (tol/err)^(1/15) from the last column's error,

@@ -104,11 +104,15 @@ __device__ void stumpff(double zz, double &c2, double &c3)
     }
 }
 
-// Advance (r, v) on the two-body orbit about mu by dt; returns false if not converged.
-__device__ bool kepler_universal(double &x, double &y, double &z, double &vx, double &vy,
-                                 double &vz, double mu, double dt)
+// (r, v) advanced on the two-body orbit about mu by dt; ok false if not converged.  Any orbit and
+// step: the root of the universal Kepler equation is bracketed first.
+struct KeplerState {
+    double x, y, z, vx, vy, vz;
+    bool ok;
+};
+__device__ __noinline__ KeplerState kepler_bracketed(double x, double y, double z, double vx, double vy, double vz,
+                                                     double mu, double dt)
 {
-    if (dt == 0.0) return true;
     const double r0 = sqrt(x * x + y * y + z * z);
     const double v2 = vx * vx + vy * vy + vz * vz;
     const double sig = (x * vx + y * vy + z * vz) / sqrt(mu); // r0 . v0 / sqrt(mu)
@@ -170,14 +174,88 @@ __device__ bool kepler_universal(double &x, double &y, double &z, double &vx, do
     const double r = sqrt(nxp * nxp + nyp * nyp + nzp * nzp);
     const double fd = smu / (r * r0) * chi * (zz * c3 - 1.0);
     const double gd = 1.0 - chi2 / r * c2;
-    const double nvx = fd * x + gd * vx, nvy = fd * y + gd * vy, nvz = fd * z + gd * vz;
-    x = nxp;
-    y = nyp;
-    z = nzp;
+    return KeplerState{nxp, nyp, nzp, fd * x + gd * vx, fd * y + gd * vy, fd * z + gd * vz, ok};
+}
+
+// c2 and c3 for |z| < 1 by Horner's rule: the first dropped terms are 1/22! and 1/23!
+__device__ __forceinline__ void stumpff_series(double z, double &c2, double &c3)
+{
+    constexpr double f[20] = {// 1 / (n + 2)!
+                              1.0 / 2, 1.0 / 6, 1.0 / 24, 1.0 / 120, 1.0 / 720, 1.0 / 5040, 1.0 / 40320, 1.0 / 362880,
+                              1.0 / 3628800, 1.0 / 39916800, 1.0 / 479001600, 1.0 / 6227020800.0,
+                              1.0 / 87178291200.0, 1.0 / 1307674368000.0, 1.0 / 20922789888000.0,
+                              1.0 / 355687428096000.0, 1.0 / 6402373705728000.0, 1.0 / 121645100408832000.0,
+                              1.0 / 2432902008176640000.0, 1.0 / 51090942171709440000.0};
+    c2 = f[18];
+    c3 = f[19];
+#pragma unroll
+    for (int k = 8; k >= 0; --k) {
+        c2 = fma(-z, c2, f[2 * k]);
+        c3 = fma(-z, c3, f[2 * k + 1]);
+    }
+}
+
+// The same for the steps a run takes, a fraction of an orbit (|alpha| chi^2 < 1): from the guess
+// of the third-order expansion in dt by Halley steps, whose error falls with its cube, so that a
+// correction below 1e-6 of chi is the last.  Latency bound (one wave per SIMD at most for a
+// disc): the bracketing and the Stumpff series' divisions took three times as long.  Whatever
+// does not converge goes to the bracketed solver.
+__device__ bool kepler_universal(double &x, double &y, double &z, double &vx, double &vy, double &vz, double mu,
+                                 double dt)
+{
+    if (dt == 0.0) return true;
+    const double q0 = fma(x, x, fma(y, y, z * z)), ir0 = inv_sqrt64(q0), r0 = q0 * ir0;
+    const double v2 = fma(vx, vx, fma(vy, vy, vz * vz));
+    const double ismu = inv_sqrt64(mu), smu = mu * ismu;
+    const double sig = fma(x, vx, fma(y, vy, z * vz)) * ismu; // r0 . v0 / sqrt(mu)
+    const double alpha = fma(2.0, ir0, -v2 * (ismu * ismu));  // 1 / a
+    const double beta = fma(-alpha, r0, 1.0);
+    const double M = smu * dt;
+    // r0 chi + sig chi^2 / 2 + beta chi^3 / 6 = M to third order in M / r0
+    const double w = M * ir0, p = 0.5 * sig * ir0, b = beta * ir0 * (1.0 / 6.0);
+    double chi = w * fma(w, fma(w, fma(2.0 * p, p, -b), -p), 1.0);
+    bool ok = false;
+    double c2, c3;
+    for (int it = 0; it < 8 && !ok; ++it) {
+        const double c = chi * chi, zz = alpha * c;
+        if (!(fabs(zz) < 1.0)) break;
+        stumpff_series(zz, c2, c3);
+        const double g1 = chi * fma(-zz, c3, 1.0), g2 = c * c2, g3 = c * chi * c3;
+        const double F = fma(sig, g2, fma(beta, g3, fma(r0, chi, -M)));
+        const double r = fma(sig, g1, fma(beta, g2, r0));       // dF / dchi
+        const double rp = fma(sig, fma(-zz, c2, 1.0), beta * g1); // d2F / dchi2
+        // Halley: F / (r - F r' / (2 r))
+        const double n = F * inv64(r);
+        const double step = n * inv64(fma(-0.5 * n, rp * inv64(r), 1.0));
+        chi -= step;
+        ok = fabs(step) <= 1e-6 * fabs(chi);
+    }
+    const double c = chi * chi, zz = alpha * c;
+    if (!ok || !(fabs(zz) < 1.0)) {
+        const KeplerState k = kepler_bracketed(x, y, z, vx, vy, vz, mu, dt);
+        x = k.x;
+        y = k.y;
+        z = k.z;
+        vx = k.vx;
+        vy = k.vy;
+        vz = k.vz;
+        return k.ok;
+    }
+    stumpff_series(zz, c2, c3);
+    const double g2 = c * c2;
+    const double f = fma(-g2, ir0, 1.0), g = fma(-c * chi * c3, ismu, dt);
+    const double nx = fma(f, x, g * vx), ny = fma(f, y, g * vy), nz = fma(f, z, g * vz);
+    const double ir = inv_sqrt64(fma(nx, nx, fma(ny, ny, nz * nz)));
+    const double fd = smu * (ir * ir0) * chi * fma(zz, c3, -1.0);
+    const double gd = fma(-g2, ir, 1.0);
+    const double nvx = fma(fd, x, gd * vx), nvy = fma(fd, y, gd * vy), nvz = fma(fd, z, gd * vz);
+    x = nx;
+    y = ny;
+    z = nz;
     vx = nvx;
     vy = nvy;
     vz = nvz;
-    return ok;
+    return true;
 }
 
 __device__ __forceinline__ void store_state(double *x, double *y, double *z, double *vx, double *vy,
@@ -768,7 +846,140 @@ __device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bo
     return true;
 }
 
-// Groups of 2 or 3 members (almost all groups when r_crit is a few Hill radii): lane k runs
+// Groups of two (almost all groups when r_crit is a few Hill radii): lane 8k + s runs column k for
+// one coordinate of one body, s = 0..3 the x, y, z and nothing of the first, 7..4 of the second,
+// so that a coordinate's partner is the lane mirrored within its eight and a body's coordinates
+// are a quad.  What a lane holds is a position and a velocity; a force evaluation is about 60
+// instructions, of which the sums over a quad and the partner's coordinate are DPP moves.
+// Latency bound (one wave per group, the slowest group sets the launch): with a column's whole
+// state in one lane a pass was about 200 instructions and 1.1 us.
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141; // quad_perm, row_half_mirror
+
+// (a + b) + (c + d) over the quad's lanes, the same in each of them
+__device__ __forceinline__ double quad_sum(double v)
+{
+    v += dpp64<DPP_XOR1>(v);
+    return v + dpp64<DPP_XOR2>(v);
+}
+
+struct PairGroup {
+    double mstar, mp, i09;      // mp: the partner's mass, 0 between two test bodies
+    double i9l[LEVELS_MAX - 1]; // hierarchical levels 1..nlev-1
+    int nlev;
+};
+
+template <bool LV>
+__device__ __forceinline__ double pair_accel(const PairGroup &g, double z)
+{
+    const double dz = dpp64<DPP_MIRROR8>(z) - z;
+    const double q0 = quad_sum(z * z), q1 = quad_sum(dz * dz);
+    const double ri = inv_sqrt64(q0);
+    const double f = g.mp != 0.0 ? encounter_factor<LV>(q1, g.mp, g.i09, g.nlev, g.i9l, g.i9l, 1) : 0.0;
+    return fma(f, dz, -g.mstar * (ri * ri) * ri * z);
+}
+
+// Sum over columns 1..k of c[j] (T(j, 0) - T(0, 0)) for one element (k wave-uniform): every
+// load is issued before the first use.
+__device__ __forceinline__ double pair_sum(const double *T, const double *c, int k)
+{
+    const double t0 = T[0];
+    double v[BS_KMAX], s = 0.0;
+#pragma unroll
+    for (int j = 1; j < BS_KMAX; ++j) v[j] = T[16 * j];
+#pragma unroll
+    for (int j = 1; j < BS_KMAX; ++j)
+        if (j <= k) s = fma(c[j], v[j] - t0, s);
+    return s;
+}
+
+// x, v: this lane's coordinate, in every column's lanes; tcol: LDS [BS_KMAX][16], T(j, 0) of the
+// positions (lanes 0..7) and velocities (8..15).
+template <bool LV>
+__device__ bool bs_pair(const PairGroup &g, int lane, double &x, double &v, double *tcol, double dt, double tol)
+{
+    const int k = lane >> 3, nsub = 2 * (k + 1);
+    double t = 0.0, H = dt;
+    int attempts = 0;
+    while (t < dt) {
+        const bool last = H >= (dt - t) * (1.0 - 0x1p-30); // ends the interval (exactly)
+        if (last) H = dt - t;
+        if (H < dt * 0x1p-40 || ++attempts > 20000) return false;
+        const double r1 = sqrt(quad_sum(x * x)), v1 = sqrt(quad_sum(v * v));
+        const double sr = fmax(r1, dpp64<DPP_MIRROR8>(r1)), sv = fmax(v1, dpp64<DPP_MIRROR8>(v1));
+        const double scale = lane & 8 ? sv : sr;
+        const double h = H / nsub, h2 = 2.0 * h;
+        // pass 0: z_1 of every column
+        double zm = x, um = v;
+        double zc = fma(h, v, x), uc = fma(h, pair_accel<LV>(g, x), v);
+        int kstar = -1;
+        double err_last = 0.0;
+#pragma unroll 1
+        for (int i = 1; i <= 2 * BS_KMAX; ++i) {
+            const double a = pair_accel<LV>(g, zc);
+            if (i == nsub) {
+                tcol[16 * k + (lane & 7)] = 0.5 * (zm + zc + h * uc); // T(k, 0)
+                tcol[16 * k + 8 + (lane & 7)] = 0.5 * (um + uc + h * a);
+            }
+            const double zn = fma(h2, uc, zm), un = fma(h2, a, um); // unused once i >= nsub
+            zm = zc;
+            um = uc;
+            zc = zn;
+            uc = un;
+            if (i < 4 || (i & 1)) continue;
+            const int kk = i / 2 - 1; // the column that has just completed
+            __syncthreads();
+            const double diff = fabs(pair_sum(tcol + (lane & 15), LAGRANGE.d[kk], kk));
+            if (!__ballot(!(diff <= tol * scale))) {
+                kstar = kk;
+                break;
+            }
+            if (kk == BS_KMAX - 1) err_last = wave_max(diff / scale);
+        }
+        if (kstar >= 0) {
+            x = tcol[lane & 7] + pair_sum(tcol + (lane & 7), LAGRANGE.w[kstar], kstar);
+            v = tcol[8 + (lane & 7)] + pair_sum(tcol + 8 + (lane & 7), LAGRANGE.w[kstar], kstar);
+            t = last ? dt : t + H;
+            if (kstar <= 4) H = 2.0 * H;
+            else if (kstar == BS_KMAX - 1) H = 0.5 * H;
+        } else {
+            H = H * shrink_factor(err_last, tol);
+        }
+        __syncthreads(); // every lane has read tcol
+    }
+    return true;
+}
+
+template <bool LV>
+__device__ bool run_pair(const BsShared &S, int lane, double ms, double *x, double *y, double *z, double *vx,
+                         double *vy, double *vz, const int32_t *mem, double *tcol, double dt)
+{
+    const int s = lane & 7, body = s >> 2, c = body ? 7 - s : s; // coordinate c (3: none)
+    PairGroup g;
+    g.mstar = ms;
+    g.mp = S.test[0] && S.test[1] ? 0.0 : S.m[1 - body];
+    g.i09 = fmin(S.i09[0], S.i09[1]);
+    g.nlev = S.nlev;
+    if constexpr (LV)
+        for (int l = 0; l + 1 < LEVELS_MAX; ++l) g.i9l[l] = l + 1 < S.nlev ? fmin(S.i9l[l][0], S.i9l[l][1]) : 0.0;
+    const int b = mem[body];
+    double *px = c == 0 ? x : c == 1 ? y : z, *pv = c == 0 ? vx : c == 1 ? vy : vz;
+    double X = c < 3 ? px[b] : 0.0, V = c < 3 ? pv[b] : 0.0;
+    const bool ok = bs_pair<LV>(g, lane, X, V, tcol, dt, 1e-12);
+    if (lane < 8 && c < 3) {
+        px[b] = X;
+        pv[b] = V;
+    }
+    return ok;
+}
+
+// Groups of three: lane k runs
 // extrapolation column k for the whole group, so a force evaluation is lane-local (the pair
 // force is formed once and applied to both members) and needs no exchange between lanes.
 // When column k completes, T(k, 0) goes to LDS and the wave forms T(k, k) - T(k, k-1) with
@@ -1022,7 +1233,7 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
     if (nb <= 3) {
         __shared__ double ybuf[3 * 6];
         double *lag = tab + BS_KMAX * 3 * 6;
-        const bool ok = nb == 2 ? run_small<2, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt)
+        const bool ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt)
                                 : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt);
         if (!ok && lane == 0) atomicOr(flags, FLAG_NOCONVERGE);
         return;

@@ -1,0 +1,74 @@
+"""The drift's solvers at the edges of their ranges, against the oracle: the Kepler drift on both
+sides of the step at which it turns to the bracketed solver, and encounter groups of two and three
+bodies at separations from deep inside the changeover zone to its rim."""
+import numpy as np
+import pytest
+
+import discs
+import oracle
+import paper_2309_08217_amd as genga
+from gpu_helpers import DT, System
+
+pytestmark = pytest.mark.gpu
+
+KEYS = ("x", "y", "z", "vx", "vy", "vz")
+
+
+def _disc(r, v, m):
+    st = {k: np.ascontiguousarray(a) for k, a in zip(KEYS, list(r.T) + list(v.T))}
+    return discs.Disc(**st, m=m)
+
+
+# from steps far below an orbit to several radians of it; |alpha| chi^2 = 1 lies near dt = 1 at 1 au
+@pytest.mark.parametrize("dt", [1e-9, 1e-3, 0.3, 0.98, 1.02, 5.0])
+@pytest.mark.parametrize("vfac", [(0.4, 1.0), (1.0, 1.41), (1.41, 1.43), (1.5, 3.0)])
+def test_kepler_drift(dt, vfac):
+    rng = np.random.default_rng(8)
+    n = 200
+    r, ang = rng.uniform(0.6, 2.0, n), rng.uniform(0, 2 * np.pi, n)
+    f, tilt = rng.uniform(*vfac, n) / np.sqrt(r), rng.uniform(-0.3, 0.3, n)
+    pos = np.stack([r * np.cos(ang), r * np.sin(ang), 0.05 * r * np.sin(3 * ang)], axis=1)
+    vel = np.stack([-f * np.sin(ang + tilt), f * np.cos(ang + tilt), 0.02 * f], axis=1)
+    d = _disc(pos, vel, np.zeros(n))
+    s = System([d], rcrit=np.zeros(n))
+    s.accel(genga.GENGA_KICK_FP64)
+    genga.genga_drift(s.ctx.handle, s.b, dt)
+    got = s.numpy_state()
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK
+    exp = oracle.drift(d.state(), np.zeros(n), 1.0, dt, np.zeros((0, 2), np.int32))
+    for k in KEYS:
+        err = np.max(np.abs(got[k] - exp[k]) / np.maximum(1.0, np.abs(exp[k])))
+        print(f"[kepler dt={dt} v={vfac}] {k} err {err:.2e}", flush=True)
+        assert err <= 5e-12     # the bound of the drifts over many orbits
+    s.close()
+
+
+@pytest.mark.parametrize("members", [2, 3])
+def test_groups_of_two_and_three(members):
+    rng = np.random.default_rng(9)
+    n, rc0 = 60, 4e-3
+    r, ang = rng.uniform(0.7, 1.5, n), np.linspace(0, 2 * np.pi, n, endpoint=False)
+    pos = np.stack([r * np.cos(ang), r * np.sin(ang), np.zeros(n)], axis=1)
+    vel = np.stack([-np.sin(ang), np.cos(ang), np.zeros(n)], axis=1) / np.sqrt(r)[:, None]
+    P, V = [pos], [vel]
+    for q in range(1, members):
+        u = rng.normal(size=(n, 3))
+        u /= np.linalg.norm(u, axis=1)[:, None]
+        P.append(pos + u * (rc0 * np.linspace(0.02, 0.95, n) / q)[:, None])
+        V.append(vel + 2e-3 * rng.normal(size=(n, 3)))
+    m = 10 ** rng.uniform(-10, -7, n * members)
+    d = _disc(np.concatenate(P), np.concatenate(V), m)
+    rc = np.where(np.arange(n * members) % 7 == 0, 1.1 * rc0, rc0)
+    s = System([d], rcrit=rc)
+    s.accel(genga.GENGA_KICK_FP64)
+    pairs, cnt = s.encounter_list()
+    assert cnt >= n
+    genga.genga_drift(s.ctx.handle, s.b, DT)
+    got = s.numpy_state()
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK
+    exp = oracle.drift(d.state(), rc, 1.0, DT, pairs)
+    for k in KEYS:
+        err = np.max(np.abs(got[k] - exp[k]))
+        print(f"[groups of {members}] {k} err {err:.2e}", flush=True)
+        assert err <= 1e-10     # the bound of the other encounter groups
+    s.close()

@@ -276,6 +276,15 @@ __device__ __forceinline__ void store_state(double *x, double *y, double *z, dou
 // sentinel), member_slot[body] = position in members[].
 // ------------------------------------------------------------------------------------------
 constexpr int CE_THREADS = 1024;
+constexpr int BS_LANES = 64;
+constexpr int CP_MEM = 8; // largest group whose extrapolation columns run side by side
+static_assert(CP_MEM * BS_KMAX == BS_LANES, "one lane per (column, member)");
+
+__device__ __forceinline__ double wave_sum(double v)
+{
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
 
 // lab[] is read with device-coherent atomic loads, so the hooks made by other waves through
 // atomicMin (performed in L2) are seen without cache maintenance.
@@ -364,68 +373,60 @@ __global__ __launch_bounds__(256) void uf_slots_kernel(const int32_t *members, c
     lab[b] = -1;
 }
 
-__global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(
-    const int32_t *pairs, const int32_t *pair_count, int32_t pair_cap, int32_t *lab, int32_t *mark,
-    int32_t *members, int32_t *group_start, int32_t *n_groups, int32_t *member_slot, int32_t *flags)
+// A list of up to GF_PAIRS pairs (a disc whose r_crit is a few Hill radii has tens to hundreds)
+// is joined in LDS: a thread per pair, a hash table of the bodies, union-find over its slots; the
+// rounds' dependent loads were most of the builder's 6-14 us when the labels were in global memory.
+constexpr int GF_PAIRS = CE_THREADS;
+constexpr int GF_SLOTS = 4096, GF_RANK = 256;
+static_assert(GF_SLOTS >= 2 * 2 * GF_PAIRS, "hash table at most half full");
+
+struct GroupFast {
+    int32_t body[GF_SLOTS], par[GF_SLOTS]; // a slot's body and its parent slot (a smaller body)
+    uint64_t keys[2 * GF_PAIRS];
+};
+struct GroupLds {
+    union {
+        uint64_t keys[CE_MAX_MEMBERS];
+        GroupFast f;
+        uint64_t sorted[2 * GF_PAIRS]; // over the hash table, which is then no longer used
+    };
+    int32_t nmem, changed, ng, cnt[CE_THREADS / 64];
+};
+static_assert(sizeof(GroupFast) <= CE_MAX_MEMBERS * sizeof(uint64_t), "the fast path's tables fit");
+static_assert(2 * GF_PAIRS * sizeof(uint64_t) <= 2 * GF_SLOTS * sizeof(int32_t), "sorted keys end before the keys");
+
+__device__ __forceinline__ int slot_root(const int32_t *par, int a)
 {
-    __shared__ uint64_t keys[CE_MAX_MEMBERS];
-    __shared__ int32_t s_nmem;
-    __shared__ int32_t s_changed;
-    __shared__ int32_t s_ng;
+    int r = ((volatile const int32_t *)par)[a];
+    while (r != a) {
+        a = r;
+        r = ((volatile const int32_t *)par)[a];
+    }
+    return r;
+}
+
+__device__ __forceinline__ int slot_of(GroupLds &S, int b)
+{
+    int h = (int)(((uint32_t)b * 2654435761u) >> 20);
+    for (;;) {
+        const int32_t old = atomicCAS(&S.f.body[h], -1, b);
+        if (old == b) return h;
+        if (old == -1) {
+            S.f.par[h] = h;
+            S.f.keys[atomicAdd(&S.nmem, 1)] = (uint64_t)h;
+            return h;
+        }
+        h = (h + 1) & (GF_SLOTS - 1);
+    }
+}
+
+// Bitonic sort of keys[0..n), padded with all-ones to a power of two.
+__device__ __forceinline__ void sort_keys(uint64_t *keys, int n)
+{
     const int tid = threadIdx.x;
-    const int np = min(*pair_count, pair_cap);
-    if (tid == 0) {
-        s_nmem = 0;
-        s_ng = 0;
-    }
-    __syncthreads();
-    if (np <= 0) {
-        if (tid == 0) *n_groups = 0;
-        return;
-    }
-    // collect distinct member bodies; each becomes its own root
-    for (int p = tid; p < np; p += CE_THREADS) {
-        for (int e = 0; e < 2; ++e) {
-            const int b = pairs[2 * p + e];
-            if (atomicCAS(&mark[b], 0, 1) == 0) {
-                const int k = atomicAdd(&s_nmem, 1);
-                if (k < CE_MAX_MEMBERS) keys[k] = (uint64_t)(uint32_t)b;
-                __hip_atomic_store(&lab[b], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
-    __syncthreads();
-    const int nmem_all = s_nmem;
-    const int nmem = min(nmem_all, CE_MAX_MEMBERS);
-    if (nmem_all > CE_MAX_MEMBERS) {
-        if (tid == 0) atomicOr(flags, FLAG_CAPACITY);
-    }
-    // union by hooking the larger root under the smaller until no pair spans two roots
-    for (int round = 0; round < 4096; ++round) {
-        if (tid == 0) s_changed = 0;
-        __syncthreads();
-        for (int p = tid; p < np; p += CE_THREADS) {
-            int a = find_root(lab, pairs[2 * p]);
-            int b = find_root(lab, pairs[2 * p + 1]);
-            if (a != b) {
-                const int lo = min(a, b), hi = max(a, b);
-                if (lab_load(lab, hi) > lo) atomicMin(&lab[hi], lo);
-                s_changed = 1;
-            }
-        }
-        __syncthreads();
-        if (!s_changed) break;
-        __syncthreads();
-    }
-    // sort members by (root, body) so each group is contiguous and in ascending order
-    for (int k = tid; k < nmem; k += CE_THREADS) {
-        const int b = (int)(keys[k] & 0xffffffffu);
-        const int r = find_root(lab, b);
-        keys[k] = ((uint64_t)(uint32_t)r << 32) | (uint32_t)b;
-    }
     int npow = 1;
-    while (npow < nmem) npow <<= 1;
-    for (int k = nmem + tid; k < npow; k += CE_THREADS) keys[k] = ~0ull;
+    while (npow < n) npow <<= 1;
+    for (int k = n + tid; k < npow; k += CE_THREADS) keys[k] = ~0ull;
     __syncthreads();
     for (int size = 2; size <= npow; size <<= 1) {
         for (int stride = size >> 1; stride > 0; stride >>= 1) {
@@ -443,15 +444,165 @@ __global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(
             __syncthreads();
         }
     }
+}
+
+// Members of the groups of np pairs as sorted keys (root body << 32 | body), their number.
+__device__ const uint64_t *group_keys_fast(const GroupBuild &g, GroupLds &S, int np, int &nmem)
+{
+    const int tid = threadIdx.x;
+    for (int k = tid; k < GF_SLOTS; k += CE_THREADS) S.f.body[k] = -1;
+    __syncthreads();
+    int sa = 0, sb = 0;
+    if (tid < np) {
+        sa = slot_of(S, g.pairs[2 * tid]);
+        sb = slot_of(S, g.pairs[2 * tid + 1]);
+    }
+    __syncthreads();
+    // the larger root's body hooks under the smaller; a hook that another thread's overwrites
+    // is made again in the next round
+    for (;;) {
+        if (tid == 0) S.changed = 0;
+        __syncthreads();
+        if (tid < np) {
+            const int a = slot_root(S.f.par, sa), b = slot_root(S.f.par, sb);
+            if (a != b) {
+                const bool less = S.f.body[a] < S.f.body[b];
+                S.f.par[less ? b : a] = less ? a : b;
+                S.changed = 1;
+            }
+        }
+        __syncthreads();
+        if (!S.changed) break;
+        __syncthreads();
+    }
+    nmem = S.nmem;
+    for (int k = tid; k < nmem; k += CE_THREADS) {
+        const int h = (int)S.f.keys[k], r = slot_root(S.f.par, h);
+        S.f.keys[k] = ((uint64_t)(uint32_t)S.f.body[r] << 32) | (uint32_t)S.f.body[h];
+    }
+    __syncthreads();
+    if (nmem > GF_RANK) {
+        sort_keys(S.f.keys, nmem);
+        return S.f.keys;
+    }
+    // few members: a key's place is the number of smaller ones
+    if (tid < nmem) {
+        const uint64_t key = S.f.keys[tid];
+        int rank = 0;
+        for (int k = 0; k < nmem; ++k) rank += S.f.keys[k] < key;
+        S.sorted[rank] = key;
+    }
+    __syncthreads();
+    return S.sorted;
+}
+
+__device__ const uint64_t *group_keys_global(const GroupBuild &g, GroupLds &S, int np, int &nmem)
+{
+    uint64_t *keys = S.keys;
+    const int tid = threadIdx.x;
+    int32_t *lab = g.lab, *mark = g.mark;
+    const int32_t *pairs = g.pairs;
+    // collect distinct member bodies; each becomes its own root
+    for (int p = tid; p < np; p += CE_THREADS) {
+        for (int e = 0; e < 2; ++e) {
+            const int b = pairs[2 * p + e];
+            if (atomicCAS(&mark[b], 0, 1) == 0) {
+                const int k = atomicAdd(&S.nmem, 1);
+                if (k < CE_MAX_MEMBERS) keys[k] = (uint64_t)(uint32_t)b;
+                __hip_atomic_store(&lab[b], b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+    __syncthreads();
+    const int nmem_all = S.nmem;
+    nmem = min(nmem_all, CE_MAX_MEMBERS);
+    if (nmem_all > CE_MAX_MEMBERS) {
+        if (tid == 0) atomicOr(g.flags, FLAG_CAPACITY);
+    }
+    // union by hooking the larger root under the smaller until no pair spans two roots
+    for (int round = 0; round < 4096; ++round) {
+        if (tid == 0) S.changed = 0;
+        __syncthreads();
+        for (int p = tid; p < np; p += CE_THREADS) {
+            int a = find_root(lab, pairs[2 * p]);
+            int b = find_root(lab, pairs[2 * p + 1]);
+            if (a != b) {
+                const int lo = min(a, b), hi = max(a, b);
+                if (lab_load(lab, hi) > lo) atomicMin(&lab[hi], lo);
+                S.changed = 1;
+            }
+        }
+        __syncthreads();
+        if (!S.changed) break;
+        __syncthreads();
+    }
+    // sort members by (root, body) so each group is contiguous and in ascending order
+    for (int k = tid; k < nmem; k += CE_THREADS) {
+        const int b = (int)(keys[k] & 0xffffffffu);
+        const int r = find_root(lab, b);
+        keys[k] = ((uint64_t)(uint32_t)r << 32) | (uint32_t)b;
+    }
+    sort_keys(keys, nmem);
+    // leave the marks clear for the next step (roots are re-initialised on marking)
+    for (int p = tid; p < np; p += CE_THREADS) {
+        mark[pairs[2 * p]] = 0;
+        mark[pairs[2 * p + 1]] = 0;
+    }
+    return keys;
+}
+
+// The groups of CP_MEM + 1 .. BS_LANES members in group order, by one workgroup (a ballot and a
+// scan per round of 1024 groups): list[0] their number, list[1 + i] the groups.
+__device__ __forceinline__ void list_wg_groups(const int32_t *group_start, int G, int32_t *list, int32_t *wsum)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int base = 0;
+    for (int c = 0; c < G; c += CE_THREADS) {
+        const int g = c + (int)threadIdx.x;
+        const int nb = g < G ? group_start[g + 1] - group_start[g] : 0;
+        const bool med = nb > CP_MEM && nb <= BS_LANES;
+        const unsigned long long bal = __ballot(med);
+        if (lane == 0) wsum[wave] = __popcll(bal);
+        __syncthreads();
+        int off = 0, tot = 0;
+        for (int w = 0; w < CE_THREADS / 64; ++w) {
+            off += w < wave ? wsum[w] : 0;
+            tot += wsum[w];
+        }
+        if (med) list[1 + base + off + __popcll(bal & ((1ull << lane) - 1))] = g;
+        base += tot;
+        __syncthreads(); // wsum is rewritten by the next round
+    }
+    if (threadIdx.x == 0) list[0] = base;
+}
+
+// One workgroup of CE_THREADS: members, group_start, n_groups, member_slot and wg_list.
+__device__ void build_groups(const GroupBuild &g, GroupLds &S)
+{
+    const int tid = threadIdx.x;
+    const int np = min(*g.pair_count, g.pair_cap);
+    if (tid == 0) {
+        S.nmem = 0;
+        S.ng = 0;
+    }
+    __syncthreads();
+    if (np <= 0) {
+        if (tid == 0) {
+            *g.n_groups = 0;
+            g.wg_list[0] = 0;
+        }
+        return;
+    }
+    int nmem = 0;
+    const uint64_t *keys = np <= GF_PAIRS ? group_keys_fast(g, S, np, nmem) : group_keys_global(g, S, np, nmem);
     // write members and slots; number the groups with a chunked scan of the start flags
-    __shared__ int32_t s_cnt[CE_THREADS / 64];
     const int per = (nmem + CE_THREADS - 1) / CE_THREADS;
     const int kb = min(tid * per, nmem), ke = min(kb + per, nmem);
     int nstart = 0;
     for (int k = kb; k < ke; ++k) {
         const int b = (int)(keys[k] & 0xffffffffu);
-        members[k] = b;
-        member_slot[b] = k;
+        g.members[k] = b;
+        g.member_slot[b] = k;
         if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) ++nstart;
     }
     // exclusive scan of the per-thread start counts: in-wave shuffles, then the wave totals
@@ -461,29 +612,116 @@ __global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(
         const int v = __shfl_up(incl, o, 64);
         if (lane >= o) incl += v;
     }
-    if (lane == 63) s_cnt[wave] = incl;
+    if (lane == 63) S.cnt[wave] = incl;
     __syncthreads();
-    if (tid == 0) {
-        int acc = 0;
-        for (int w = 0; w < CE_THREADS / 64; ++w) {
-            const int c = s_cnt[w];
-            s_cnt[w] = acc;
-            acc += c;
-        }
-        s_ng = acc;
+    int gi = incl - nstart, ng = 0;
+    for (int w = 0; w < CE_THREADS / 64; ++w) {
+        gi += w < wave ? S.cnt[w] : 0;
+        ng += S.cnt[w];
     }
-    __syncthreads();
-    int g = s_cnt[wave] + incl - nstart;
     for (int k = kb; k < ke; ++k)
-        if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) group_start[g++] = k;
+        if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) g.group_start[gi++] = k;
     if (tid == 0) {
-        group_start[s_ng] = nmem;
-        *n_groups = s_ng;
+        g.group_start[ng] = nmem;
+        *g.n_groups = ng;
     }
-    // leave the marks clear for the next step (roots are re-initialised on marking)
-    for (int p = tid; p < np; p += CE_THREADS) {
-        mark[pairs[2 * p]] = 0;
-        mark[pairs[2 * p + 1]] = 0;
+    __threadfence_block();
+    __syncthreads(); // group_start is read back by other threads
+    list_wg_groups(g.group_start, ng, g.wg_list, S.cnt);
+}
+
+__global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(GroupBuild g)
+{
+    __shared__ GroupLds S;
+    build_groups(g, S);
+}
+
+// A system's sum over part[3 first[s] ..), by every lane of a wave.
+__device__ __forceinline__ void wave_momentum(const int32_t *first, const double *part, int s, double P[3])
+{
+    P[0] = P[1] = P[2] = 0.0;
+    for (int k = first[s] + (int)(threadIdx.x & 63); k < first[s + 1]; k += 64)
+        for (int q = 0; q < 3; ++q) P[q] += part[3 * (size_t)k + q];
+    for (int q = 0; q < 3; ++q) P[q] = wave_sum(P[q]);
+}
+
+// The end of a kick inside a step (launch_kick_close).  Workgroup 0 builds the groups, the others
+// take a block of items each, one wave per item.
+__global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, double *x, double *y, double *z,
+                                                                const double *mstar, StepMomentum pm,
+                                                                const int32_t *item_first, GroupBuild g,
+                                                                int with_groups)
+{
+    __shared__ GroupLds S;
+    constexpr int NW = CE_THREADS / 64;
+    static_assert(NW == CLOSE_ITEMS, "one wave per item");
+    if (blockIdx.x == 0) {
+        if (with_groups) build_groups(g, S);
+        return;
+    }
+    double(*red)[NW] = reinterpret_cast<double(*)[NW]>(S.keys); // [3][NW]
+    const CloseBlock blk = pm.blocks[blockIdx.x - 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double sh[3] = {0.0, 0.0, 0.0};
+    if (pm.tau != 0.0) {
+        // P after the drift: the items' sums and the groups', from the system's first group on,
+        // so that the order of the sum depends on the system alone
+        double P[3] = {0.0, 0.0, 0.0};
+        for (int k = item_first[blk.sys] + tid; k < item_first[blk.sys + 1]; k += CE_THREADS)
+            for (int q = 0; q < 3; ++q) P[q] += pm.kepler[3 * (size_t)k + q];
+        const int G = *pm.group_n;
+        if (tid == 0) S.ng = G;
+        __syncthreads();
+        for (int k = tid; k < G; k += CE_THREADS)
+            if (pm.group_sys[k] == blk.sys) {
+                atomicMin(&S.ng, k);
+                break;
+            }
+        __syncthreads();
+        for (int k = S.ng + tid; k < G && pm.group_sys[k] == blk.sys; k += CE_THREADS)
+            for (int q = 0; q < 3; ++q) P[q] += pm.group[3 * (size_t)k + q];
+        for (int q = 0; q < 3; ++q) {
+            P[q] = wave_sum(P[q]);
+            if (lane == 0) red[q][wave] = P[q];
+        }
+        __syncthreads();
+        const double f = pm.tau / mstar[blk.sys];
+        for (int q = 0; q < 3; ++q) {
+            double t = 0.0;
+            for (int w = 0; w < NW; ++w) t += red[q][w];
+            sh[q] = f * t;
+        }
+        __syncthreads(); // red is rewritten below
+    }
+    double p[3] = {0.0, 0.0, 0.0};
+    if (wave < blk.n) {
+        const int it = blk.item + wave;
+        const WorkItem w = a.items[it];
+        if (lane < w.ni) {
+            const int i = w.i0 + lane;
+            double t[3];
+            item_shares(a, it, lane, t);
+            store_accel(a, i, t[0], t[1], t[2]);
+            if (pm.tau != 0.0) {
+                x[i] += sh[0];
+                y[i] += sh[1];
+                z[i] += sh[2];
+            }
+            const double mi = a.m[i];
+            p[0] = mi * a.vx[i];
+            p[1] = mi * a.vy[i];
+            p[2] = mi * a.vz[i];
+        }
+    }
+    for (int q = 0; q < 3; ++q) {
+        p[q] = wave_sum(p[q]);
+        if (lane == 0) red[q][wave] = p[q];
+    }
+    __syncthreads();
+    if (tid < 3) {
+        double t = 0.0;
+        for (int w = 0; w < NW; ++w) t += red[tid][w];
+        pm.kick[3 * (size_t)(blockIdx.x - 1) + tid] = t;
     }
 }
 
@@ -500,9 +738,6 @@ __global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(
 // published for the pair forces and the tableau rows, both in LDS.  Force evaluations are
 // plain loops over the members, so the code stays small and nothing spills.
 // ------------------------------------------------------------------------------------------
-constexpr int BS_LANES = 64;
-constexpr int CP_MEM = 8; // largest group whose extrapolation columns run side by side
-static_assert(CP_MEM * BS_KMAX == BS_LANES, "one lane per (column, member)");
 
 __device__ __forceinline__ double wave_max(double v)
 {
@@ -958,7 +1193,8 @@ __device__ bool bs_pair(const PairGroup &g, int lane, double &x, double &v, doub
 
 template <bool LV>
 __device__ bool run_pair(const BsShared &S, int lane, double ms, double *x, double *y, double *z, double *vx,
-                         double *vy, double *vz, const int32_t *mem, double *tcol, double dt)
+                         double *vy, double *vz, const int32_t *mem, double *tcol, double dt, const double sh[3],
+                         double p[3])
 {
     const int s = lane & 7, body = s >> 2, c = body ? 7 - s : s; // coordinate c (3: none)
     PairGroup g;
@@ -970,8 +1206,10 @@ __device__ bool run_pair(const BsShared &S, int lane, double ms, double *x, doub
         for (int l = 0; l + 1 < LEVELS_MAX; ++l) g.i9l[l] = l + 1 < S.nlev ? fmin(S.i9l[l][0], S.i9l[l][1]) : 0.0;
     const int b = mem[body];
     double *px = c == 0 ? x : c == 1 ? y : z, *pv = c == 0 ? vx : c == 1 ? vy : vz;
-    double X = c < 3 ? px[b] : 0.0, V = c < 3 ? pv[b] : 0.0;
+    double X = c < 3 ? px[b] + (c == 0 ? sh[0] : c == 1 ? sh[1] : sh[2]) : 0.0, V = c < 3 ? pv[b] : 0.0;
     const bool ok = bs_pair<LV>(g, lane, X, V, tcol, dt, 1e-12);
+    const double mv = lane < 8 ? S.m[body] * V : 0.0;
+    for (int q = 0; q < 3; ++q) p[q] = c == q ? mv : 0.0;
     if (lane < 8 && c < 3) {
         px[b] = X;
         pv[b] = V;
@@ -1132,7 +1370,7 @@ __device__ bool bs_small(const SmallGroup<NB> &g, int lane, double *ybuf, double
 template <int NB, bool LV>
 __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, double *y, double *z,
                           double *vx, double *vy, double *vz, const int32_t *mem, double *ybuf,
-                          double *tcol, double *lag, double dt)
+                          double *tcol, double *lag, double dt, const double sh[3], double p[3])
 {
     SmallGroup<NB> g;
     g.mstar = ms;
@@ -1152,9 +1390,9 @@ __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, dou
             for (int a = 0; a < NB; ++a) g.i9l[k - 1][a] = S.i9l[k - 1][a];
     if (lane < NB) {
         const int b = mem[lane];
-        ybuf[6 * lane + 0] = x[b];
-        ybuf[6 * lane + 1] = y[b];
-        ybuf[6 * lane + 2] = z[b];
+        ybuf[6 * lane + 0] = x[b] + sh[0];
+        ybuf[6 * lane + 1] = y[b] + sh[1];
+        ybuf[6 * lane + 2] = z[b] + sh[2];
         ybuf[6 * lane + 3] = vx[b];
         ybuf[6 * lane + 4] = vy[b];
         ybuf[6 * lane + 5] = vz[b];
@@ -1164,25 +1402,45 @@ __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, dou
     __syncthreads();
     const bool ok = bs_small<NB, LV>(g, lane, ybuf, tcol, lag, dt, 1e-12);
     __syncthreads();
+    for (int q = 0; q < 3; ++q) p[q] = lane < NB ? S.m[lane] * ybuf[6 * lane + 3 + q] : 0.0;
     if (lane < NB) store_state(x, y, z, vx, vy, vz, mem[lane], ybuf + 6 * lane);
     return ok;
 }
 
-// The drift over dt: blocks [0, bs_blocks) integrate one encounter group each with
-// Bulirsch-Stoer, the blocks after them Kepler-drift 64 bodies each and skip the group
-// members.  Each body is read and written by one block only.
+// The first half of a Sun drift in the drift launches: tau P / Mstar of system s (zero without pm).
+__device__ __forceinline__ void sun_shift_of(const StepMomentum &pm, const double *mstar, int s, double sh[3])
+{
+    sh[0] = sh[1] = sh[2] = 0.0;
+    if (!pm.kick) return;
+    double P[3];
+    wave_momentum(pm.block_first, pm.kick, s, P);
+    const double f = pm.tau / mstar[s];
+    for (int q = 0; q < 3; ++q) sh[q] = f * P[q];
+}
 
+// A wave's lanes' momenta p summed into out[3 k ..].
+__device__ __forceinline__ void store_momentum(double *out, int k, const double p[3])
+{
+    for (int q = 0; q < 3; ++q) {
+        const double t = wave_sum(p[q]);
+        if ((threadIdx.x & 63) == 0) out[3 * (size_t)k + q] = t;
+    }
+}
+
+// The drift over dt: blocks [0, bs_blocks) integrate the encounter groups with Bulirsch-Stoer, one
+// at a time, the blocks after them Kepler-drift an item of up to 64 bodies each and skip the group
+// members.  Each body is read and written by one block only.
 template <bool LV>
 __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, const int32_t *sys_off,
                                                          const int32_t *n_massive, const double *mstar,
-                                                         int n_total, double *x, double *y, double *z,
-                                                         double *vx, double *vy, double *vz,
+                                                         const WorkItem *items, int n_total, double *x, double *y,
+                                                         double *z, double *vx, double *vy, double *vz,
                                                          const double *m, const double *rc, double dt,
                                                          const int32_t *members,
                                                          const int32_t *group_start,
                                                          const int32_t *n_groups, int32_t *member_slot,
                                                          int32_t *flags, int big_groups, int bs_blocks,
-                                                         const double *rc_lv, int nlev)
+                                                         const double *rc_lv, int nlev, StepMomentum pm)
 {
     // the column path's two Neville rows; the small-group path's T(k, 0) table and Lagrange
     // weights fit in the same space.  The block's LDS sets how many share a CU.
@@ -1190,99 +1448,104 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
     static_assert(BS_KMAX * 3 * 6 + 2 * BS_LANES <= TAB, "small-group tables fit");
     __shared__ BsShared S;
     __shared__ double tab[TAB];
+    __shared__ double ybuf[3 * 6];
     const int lane = threadIdx.x;
+    double sh[3], p[3] = {0.0, 0.0, 0.0};
     if ((int)blockIdx.x >= bs_blocks) {
-        const int i = (blockIdx.x - bs_blocks) * BS_LANES + lane;
-        if (i >= n_total) return;
-        if (member_slot[i] >= 0) {
-            member_slot[i] = -1; // integrated by its group's block; leave the slot clear
-            return;
+        const int it = blockIdx.x - bs_blocks;
+        if (it == 0 && pm.clear && lane == 0) {
+            *pm.clear = 0;
+            *pm.group_n = *n_groups;
         }
-        double Y[6] = {x[i], y[i], z[i], vx[i], vy[i], vz[i]};
-        if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], mstar[sys_of[i]], dt)) atomicOr(flags, FLAG_KEPLER);
-        store_state(x, y, z, vx, vy, vz, i, Y);
+        const WorkItem w = items[it];
+        const int i = w.i0 + lane;
+        const bool on = lane < w.ni;
+        const bool group = on && member_slot[i] >= 0;
+        double Y[6] = {};
+        if (on)
+            for (int q = 0; q < 6; ++q) Y[q] = (q == 0 ? x : q == 1 ? y : q == 2 ? z : q == 3 ? vx : q == 4 ? vy : vz)[i];
+        sun_shift_of(pm, mstar, w.sys, sh);
+        if (group) member_slot[i] = -1; // integrated by its group's block; leave the slot clear
+        if (on && !group) {
+            for (int q = 0; q < 3; ++q) Y[q] += sh[q];
+            if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], mstar[w.sys], dt)) atomicOr(flags, FLAG_KEPLER);
+            store_state(x, y, z, vx, vy, vz, i, Y);
+            const double mi = m[i];
+            for (int q = 0; q < 3; ++q) p[q] = mi * Y[3 + q];
+        }
+        if (pm.kepler) store_momentum(pm.kepler, it, p);
         return;
     }
-    const int g = blockIdx.x;
-    if (g >= *n_groups) return;
-    const int k0 = group_start[g], nb = group_start[g + 1] - k0;
-    const double ms = mstar[sys_of[members[k0]]];
-    if (nb > BS_LANES) {
-        if (big_groups) return; // integrated by the grid-wide path
-        // larger than one wave: Kepler-drift the members instead and flag it
-        if (lane == 0) atomicOr(flags, FLAG_CAPACITY);
-        for (int k = lane; k < nb; k += BS_LANES) {
-            const int b = members[k0 + k];
-            double Y[6] = {x[b], y[b], z[b], vx[b], vy[b], vz[b]};
-            if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], ms, dt)) atomicOr(flags, FLAG_KEPLER);
-            store_state(x, y, z, vx, vy, vz, b, Y);
+    const int G = *n_groups;
+    for (int g = blockIdx.x; g < G; g += bs_blocks) {
+        const int k0 = group_start[g], nb = group_start[g + 1] - k0;
+        const int sys = sys_of[members[k0]];
+        const double ms = mstar[sys];
+        if (pm.group && lane == 0) pm.group_sys[g] = sys;
+        if (nb > BS_LANES && big_groups) continue;       // integrated by the grid-wide path
+        if (nb > CP_MEM && nb <= BS_LANES) continue;     // a workgroup of drift_wg_kernel integrates it
+        sun_shift_of(pm, mstar, sys, sh);
+        p[0] = p[1] = p[2] = 0.0;
+        if (nb > BS_LANES) {
+            // larger than one wave: Kepler-drift the members instead and flag it
+            if (lane == 0) atomicOr(flags, FLAG_CAPACITY);
+            for (int k = lane; k < nb; k += BS_LANES) {
+                const int b = members[k0 + k];
+                double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
+                if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], ms, dt)) atomicOr(flags, FLAG_KEPLER);
+                store_state(x, y, z, vx, vy, vz, b, Y);
+                for (int q = 0; q < 3; ++q) p[q] += m[b] * Y[3 + q];
+            }
+            if (pm.group) store_momentum(pm.group, g, p);
+            continue;
         }
-        return;
-    }
-    if (lane < nb) {
-        const int b = members[k0 + lane];
-        const int sb = sys_of[b];
-        S.m[lane] = m[b];
-        S.i09[lane] = 1.0 / (0.9 * rc[b]);
-        S.test[lane] = b - sys_off[sb] >= n_massive[sb];
-        if constexpr (LV)
-            for (int l = 1; l < nlev; ++l) S.i9l[l - 1][lane] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
-    }
-    if (lane == 0) S.nlev = nlev;
-    __syncthreads();
-    if (nb <= 3) {
-        __shared__ double ybuf[3 * 6];
-        double *lag = tab + BS_KMAX * 3 * 6;
-        const bool ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt)
-                                : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt);
+        __syncthreads(); // the previous group's LDS is no longer read
+        if (lane < nb) {
+            const int b = members[k0 + lane];
+            const int sb = sys_of[b];
+            S.m[lane] = m[b];
+            S.i09[lane] = 1.0 / (0.9 * rc[b]);
+            S.test[lane] = b - sys_off[sb] >= n_massive[sb];
+            if constexpr (LV)
+                for (int l = 1; l < nlev; ++l) S.i9l[l - 1][lane] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
+        }
+        if (lane == 0) S.nlev = nlev;
+        __syncthreads();
+        bool ok;
+        if (nb <= 3) {
+            double *lag = tab + BS_KMAX * 3 * 6;
+            ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt, sh, p)
+                         : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt, sh, p);
+        } else {
+            const int k = lane / CP_MEM;
+            BsMember me;
+            me.a = lane % CP_MEM;
+            me.nb = nb;
+            me.base = k * CP_MEM;
+            me.act = me.a < nb;
+            const int ai = me.act ? me.a : 0;
+            me.test = S.test[ai] != 0;
+            me.mstar = ms;
+            me.i09 = S.i09[ai];
+            const int b = members[k0 + ai];
+            double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
+            ok = bs_columns<LV>(me, k, S, (double(*)[BS_KMAX][CP_MEM][6])tab, Y, dt, 1e-12);
+            // every lane has read its member's state before the first force evaluation's barrier
+            if (me.act && k == 0) {
+                store_state(x, y, z, vx, vy, vz, b, Y);
+                for (int q = 0; q < 3; ++q) p[q] = S.m[ai] * Y[3 + q];
+            }
+        }
         if (!ok && lane == 0) atomicOr(flags, FLAG_NOCONVERGE);
-        return;
+        if (pm.group) store_momentum(pm.group, g, p);
     }
-    if (nb > CP_MEM) return; // a workgroup of drift_wg_kernel integrates it
-    const int k = lane / CP_MEM;
-    BsMember me;
-    me.a = lane % CP_MEM;
-    me.nb = nb;
-    me.base = k * CP_MEM;
-    me.act = me.a < nb;
-    const int ai = me.act ? me.a : 0;
-    me.test = S.test[ai] != 0;
-    me.mstar = ms;
-    me.i09 = S.i09[ai];
-    const int b = members[k0 + ai];
-    double Y[6] = {x[b], y[b], z[b], vx[b], vy[b], vz[b]};
-    const bool ok = bs_columns<LV>(me, k, S, (double(*)[BS_KMAX][CP_MEM][6])tab, Y, dt, 1e-12);
-    // every lane has read its member's state before the first force evaluation's barrier
-    if (me.act && k == 0) store_state(x, y, z, vx, vy, vz, b, Y);
-    if (!ok && lane == 0) atomicOr(flags, FLAG_NOCONVERGE);
 }
 
-// The groups of CP_MEM + 1 .. BS_LANES members in group order, from one workgroup (a ballot
-// and a scan per round of 1024 groups): list[0] their number, list[1 + i] the groups.
-__global__ __launch_bounds__(1024) void wg_list_kernel(const int32_t *group_start, const int32_t *n_groups,
-                                                       int bs_blocks, int32_t *list)
+__global__ __launch_bounds__(CE_THREADS) void wg_list_kernel(const int32_t *group_start, const int32_t *n_groups,
+                                                             int32_t *list)
 {
-    __shared__ int wsum[1024 / 64];
-    const int G = min(*n_groups, bs_blocks);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int base = 0;
-    for (int c = 0; c < G; c += 1024) {
-        const int g = c + (int)threadIdx.x;
-        const int nb = g < G ? group_start[g + 1] - group_start[g] : 0;
-        const bool med = nb > CP_MEM && nb <= BS_LANES;
-        const unsigned long long bal = __ballot(med);
-        if (lane == 0) wsum[wave] = __popcll(bal);
-        __syncthreads();
-        int off = 0, tot = 0;
-        for (int w = 0; w < 1024 / 64; ++w) {
-            off += w < wave ? wsum[w] : 0;
-            tot += wsum[w];
-        }
-        if (med) list[1 + base + off + __popcll(bal & ((1ull << lane) - 1))] = g;
-        base += tot;
-        __syncthreads(); // wsum is rewritten by the next round
-    }
-    if (threadIdx.x == 0) list[0] = base;
+    __shared__ int32_t wsum[CE_THREADS / 64];
+    list_wg_groups(group_start, *n_groups, list, wsum);
 }
 
 // The listed groups of CP_MEM + 1 .. BS_LANES members, one workgroup at a time each
@@ -1294,7 +1557,8 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
                                                               double *vx, double *vy, double *vz, const double *m,
                                                               const double *rc, double dt, const int32_t *members,
                                                               const int32_t *group_start, const int32_t *list,
-                                                              int32_t *flags, const double *rc_lv, int nlev)
+                                                              int32_t *flags, const double *rc_lv, int nlev,
+                                                              StepMomentum pm)
 {
     __shared__ BsWgShared S;
     const int n_list = list[0];
@@ -1304,7 +1568,10 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
         const int k = threadIdx.x / BS_LANES;
         const int P = nb <= 16 ? 4 : (nb <= 32 ? 2 : 1);
         const int a = (threadIdx.x % BS_LANES) / P, part = (threadIdx.x % BS_LANES) % P;
-        const double ms = mstar[sys_of[members[k0]]];
+        const int sys = sys_of[members[k0]];
+        const double ms = mstar[sys];
+        double sh[3];
+        sun_shift_of(pm, mstar, sys, sh);
         __syncthreads(); // the previous group's LDS is no longer read
         if (k == 0 && part == 0 && a < nb) {
             const int b = members[k0 + a];
@@ -1323,11 +1590,17 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
         const bool act = a < nb;
         const int ai = act ? a : 0;
         const int b = members[k0 + ai];
-        double Y[6] = {x[b], y[b], z[b], vx[b], vy[b], vz[b]};
+        double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
         const bool ok = bs_workgroup<LV>(k, a, part, P, nb, act, S.test[ai] != 0, ms, S.i09[ai], S, Y, dt, 1e-12);
         // every thread has read its member's state before the first force evaluation's barrier
-        if (act && k == 0 && part == 0) store_state(x, y, z, vx, vy, vz, b, Y);
+        const bool mine = act && k == 0 && part == 0;
+        if (mine) store_state(x, y, z, vx, vy, vz, b, Y);
         if (!ok && threadIdx.x == 0) atomicOr(flags, FLAG_NOCONVERGE);
+        if (pm.group && k == 0) {
+            double p[3];
+            for (int q = 0; q < 3; ++q) p[q] = mine ? S.m[a] * Y[3 + q] : 0.0;
+            store_momentum(pm.group, g, p);
+        }
     }
 }
 
@@ -1412,29 +1685,37 @@ hipError_t launch_uf_slots(int n_members_max, const int32_t *members, const int3
     return hipGetLastError();
 }
 
-hipError_t launch_ce_groups(const Layout &L, const int32_t *pairs, const int32_t *pair_count,
-                            int32_t pair_cap, int32_t *lab, int32_t *mark, int32_t *members,
-                            int32_t *group_start, int32_t *n_groups, int32_t *member_slot,
-                            int32_t *flags, hipStream_t stream)
+hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream)
 {
-    (void)L;
-    ce_groups_kernel<<<1, CE_THREADS, 0, stream>>>(pairs, pair_count, pair_cap, lab, mark, members,
-                                                   group_start, n_groups, member_slot, flags);
+    ce_groups_kernel<<<1, CE_THREADS, 0, stream>>>(g);
     return hipGetLastError();
 }
 
-hipError_t launch_drift(const Layout &L, double *x, double *y, double *z, double *vx, double *vy,
-                        double *vz, const double *m, const double *rc, double dt, const int32_t *members,
-                        const int32_t *group_start, const int32_t *n_groups, int32_t *member_slot,
-                        int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list, hipStream_t stream,
-                        const double *rc_lv, int nlev, bool kepler, const DriftSide *side)
+hipError_t launch_kick_close(const Layout &L, const KickArgs &a, double *x, double *y, double *z,
+                             const StepMomentum &pm, const int32_t *item_first, const GroupBuild *groups,
+                             hipStream_t stream)
+{
+    kick_close_kernel<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(a, x, y, z, L.mstar, pm, item_first,
+                                                                  groups ? *groups : GroupBuild{}, groups != nullptr);
+    return hipGetLastError();
+}
+
+hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, double *x, double *y, double *z,
+                        double *vx, double *vy, double *vz, const double *m, const double *rc, double dt,
+                        const int32_t *members, const int32_t *group_start, const int32_t *n_groups,
+                        int32_t *member_slot, int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list,
+                        hipStream_t stream, const double *rc_lv, int nlev, bool kepler, const DriftSide *side,
+                        const StepMomentum *pm_in, bool wg_listed)
 {
     if (L.n_total == 0) return hipSuccess;
-    // one block per possible group: every group has >= 2 members; bs_blocks < 0: no group
-    // blocks (the groups are integrated elsewhere), only the Kepler drift of non-members
+    const StepMomentum pm = pm_in ? *pm_in : StepMomentum{};
+    // groups have at least 2 members, so the one-workgroup builder makes at most half its
+    // members; bs_blocks < 0: no group blocks (the groups are integrated elsewhere), only the
+    // Kepler drift of non-members.  2048 blocks (two waves per SIMD) walk the groups.
     if (bs_blocks == 0) bs_blocks = CE_MAX_MEMBERS / 2;
     if (bs_blocks < 0) bs_blocks = 0;
-    const int grid = bs_blocks + (kepler ? (L.n_total + BS_LANES - 1) / BS_LANES : 0);
+    bs_blocks = std::min(bs_blocks, 2048);
+    const int grid = bs_blocks + (kepler ? n_items : 0);
     if (grid == 0) return hipSuccess;
     auto kern = nlev > 1 ? drift_kernel<true> : drift_kernel<false>;
     auto wg = nlev > 1 ? drift_wg_kernel<true> : drift_wg_kernel<false>;
@@ -1449,21 +1730,21 @@ hipError_t launch_drift(const Layout &L, double *x, double *y, double *z, double
     const bool fork = side && side->stream && bs_blocks > 0 && cs == hipStreamCaptureStatusNone;
     const int wg_grid = std::max(1, std::min(1024, bs_blocks));
     hipError_t e = hipSuccess;
-    if (bs_blocks > 0) wg_list_kernel<<<1, 1024, 0, stream>>>(group_start, n_groups, bs_blocks, wg_list);
+    if (bs_blocks > 0 && !wg_listed) wg_list_kernel<<<1, CE_THREADS, 0, stream>>>(group_start, n_groups, wg_list);
     if (fork) {
         if ((e = hipEventRecord(side->fork, stream)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(side->stream, side->fork, 0)) != hipSuccess) return e;
         wg<<<wg_grid, WG_THREADS, 0, side->stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, L.n_total, x, y, z, vx,
                                                      vy, vz, m, rc, dt, members, group_start, wg_list, flags, rc_lv,
-                                                     nlev);
+                                                     nlev, pm);
         if ((e = hipEventRecord(side->join, side->stream)) != hipSuccess) return e;
     }
-    kern<<<grid, BS_LANES, 0, stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, L.n_total, x, y, z, vx, vy, vz, m,
-                                        rc, dt, members, group_start, n_groups, member_slot, flags, big_groups,
-                                        bs_blocks, rc_lv, nlev);
+    kern<<<grid, BS_LANES, 0, stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, items, L.n_total, x, y, z, vx, vy, vz,
+                                        m, rc, dt, members, group_start, n_groups, member_slot, flags, big_groups,
+                                        bs_blocks, rc_lv, nlev, pm);
     if (bs_blocks > 0 && !fork)
         wg<<<wg_grid, WG_THREADS, 0, stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, L.n_total, x, y, z, vx, vy, vz,
-                                               m, rc, dt, members, group_start, wg_list, flags, rc_lv, nlev);
+                                               m, rc, dt, members, group_start, wg_list, flags, rc_lv, nlev, pm);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (fork && (e = hipStreamWaitEvent(stream, side->join, 0)) != hipSuccess) return e;
     return hipGetLastError();

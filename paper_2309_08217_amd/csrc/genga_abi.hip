@@ -73,6 +73,9 @@ struct genga_ctx {
     int waves[2] = {0, 0};      // [prec] waves per workgroup of the kick (0: default_kick_waves)
     int split[2] = {1, 1};      // [prec] workgroups sharing an item's sources
     bool own_plan[2] = {true, true}; // [prec] the layout's own plan instead of `split`
+    StepMomentum pm;            // momentum sums between the launches of a step (blocks: device)
+    CloseBlock *close_blocks = nullptr;
+    int32_t *close_first = nullptr;
     double *kpart = nullptr;    // [tasks][3][64], at least KICK_MAX_SPLIT tasks per item
     // scratch
     float *m32 = nullptr;       // [n_total] masses in FP32
@@ -235,6 +238,14 @@ struct genga_ctx {
         dfree(item_first);
         dfree(tasks);
         dfree(task_first);
+        dfree(close_blocks);
+        dfree(close_first);
+        dfree(pm.kick);
+        dfree(pm.kepler);
+        dfree(pm.group);
+        dfree(pm.group_sys);
+        dfree(pm.group_n);
+        pm = StepMomentum{};
         dfree(m32);
         dfree(chunk_mass);
         dfree(rc2_part);
@@ -391,6 +402,13 @@ int enqueue_pair_list(genga_ctx *ctx, const genga_bodies *b, hipStream_t s)
     return GENGA_OK;
 }
 
+// The context's arrays for the one-workgroup group builder.
+GroupBuild group_build(const genga_ctx *ctx)
+{
+    return GroupBuild{ctx->pairs,   ctx->pair_count,  ctx->pair_cap, ctx->lab,         ctx->mark,    ctx->members,
+                      ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->wg_list, ctx->flags};
+}
+
 int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, const std::vector<int32_t> &gs,
                    const std::vector<int32_t> &mem_h, const int32_t *members_dev, int min_nb,
                    const std::vector<int32_t> *prev = nullptr);
@@ -421,7 +439,8 @@ const DriftSide *drift_side(genga_ctx *ctx, hipStream_t s)
     return d.stream ? &d : nullptr;
 }
 
-int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, bool defer_shift = false)
+int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, bool defer_shift = false,
+                  bool groups_built = false)
 {
     const Layout &L = ctx->L;
     ctx->list_valid = false;
@@ -440,19 +459,17 @@ int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, boo
     if (ctx->large_groups) {
         // the groups depend on the pair list only; built first, so that a group too large
         // for the grid-wide path is refused before any part of the drift is enqueued
-        const int rc = build_groups_large(ctx, s);
+        const int rc = groups_built ? GENGA_OK : build_groups_large(ctx, s);
         if (rc) return rc;
         // with levels every group is integrated by the level steps: Kepler blocks only
         bs_blocks = ctx->n_levels > 1 ? -1 : std::max(1, (int)ctx->gs_h.size() - 1);
     }
     HIP_TRY(launch_sun_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, 0.5 * dt, ctx->mom_part, s));
-    if (!ctx->large_groups) {
-        HIP_TRY(launch_ce_groups(L, ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->lab, ctx->mark, ctx->members,
-                                 ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, s));
-    }
-    HIP_TRY(launch_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, dt, ctx->members,
+    if (!ctx->large_groups) HIP_TRY(launch_ce_groups(group_build(ctx), s));
+    HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, dt, ctx->members,
                          ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, ctx->large_groups,
-                         bs_blocks, ctx->wg_list, s, nullptr, 1, true, drift_side(ctx, s)));
+                         bs_blocks, ctx->wg_list, s, nullptr, 1, true, drift_side(ctx, s), nullptr,
+                         !ctx->large_groups));
     if (ctx->n_levels > 1) {
         const int rc = run_levels(ctx, b, dt, s);
         if (rc) return rc;
@@ -773,7 +790,7 @@ int run_level(genga_ctx *ctx, genga_bodies *b, int level, double tau, hipStream_
             if (deepest) {
                 // Bulirsch-Stoer with the product weight: one wave per group of up to 64 members
                 // (the group count read on the device), the grid-wide path for larger ones
-                HIP_TRY(launch_drift(ctx->L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, h, ctx->lv_mem,
+                HIP_TRY(launch_drift(ctx->L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, h, ctx->lv_mem,
                                      ctx->lv_gs, &ctx->gw.hdr->G, ctx->member_slot, ctx->flags, 1, hd.G, ctx->wg_list, s,
                                      ctx->rc_lv, ctx->n_levels, false, drift_side(ctx, s)));
                 if (hd.max_nb > CE_MAX_GROUP) {
@@ -941,9 +958,85 @@ int enqueue_energy(genga_ctx *ctx, const genga_bodies *b, double vshift, double 
     return GENGA_OK;
 }
 
+// A step's kick in two launches: the shares, then their sum with what the step needs around it
+// (the end of the preceding drift when shift_tau != 0, the momentum sums, with groups the
+// encounter groups of the kick's pairs).
+int enqueue_step_kick(genga_ctx *ctx, genga_bodies *b, double tau, int prec, int acc, double shift_tau, bool groups,
+                      hipStream_t s)
+{
+    const Layout &L = ctx->L;
+    const int fp32 = prec == GENGA_KICK_FP32;
+    ctx->list_valid = true;
+    const size_t n = (size_t)L.n_total;
+    KickArgs a = kick_args(ctx, b);
+    a.ax = ctx->acc;
+    a.ay = ctx->acc + n;
+    a.az = ctx->acc + 2 * n;
+    a.tau = tau;
+    a.update_v = 1;
+    if (!ctx->own_plan[fp32]) {
+        a.tasks = nullptr;
+        a.split = ctx->split[fp32];
+    }
+    a.direct = 0;
+    HIP_TRY(launch_kick_shares(a, fp32, acc == GENGA_ACC_KAHAN32, kick_waves(ctx, fp32), s));
+    StepMomentum pm = ctx->pm;
+    pm.tau = shift_tau;
+    const GroupBuild g = group_build(ctx);
+    HIP_TRY(launch_kick_close(L, a, b->x, b->y, b->z, pm, ctx->item_first, groups ? &g : nullptr, s));
+    return GENGA_OK;
+}
+
+// Steps without collisions: four launches each (kick shares, their sum with the groups, drift, the
+// groups of 9..64).  The kick sees the positions without the second half of the Sun drift, which is
+// one vector for all bodies of a system and so drops out of every difference; the launch that sums
+// the shares adds it.  r_crit and the masses are the call's, so what the kick takes from them is
+// formed once.  As launches of their own the momentum sums, shifts, groups and lists were seven
+// more of 4-6 us each.  With large groups on, a step whose list joins any bodies takes the drift
+// in its parts, with the host in between.
+int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, int prec, int acc, int cadence,
+                        double *d_energy, hipStream_t s)
+{
+    const Layout &L = ctx->L;
+    const bool large = ctx->large_groups != 0;
+    const auto prep = [&] {
+        return launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, prec == GENGA_KICK_FP32 ? ctx->m32 : nullptr,
+                           ctx->rc2_part, ctx->chunk_mass, ctx->pair_count, nullptr, 0.0, s);
+    };
+    HIP_TRY(prep());
+    int rc = enqueue_step_kick(ctx, b, 0.5 * dt, prec, acc, 0.0, !large, s);
+    if (rc) return rc;
+    StepMomentum pm = ctx->pm;
+    pm.tau = 0.5 * dt;
+    pm.clear = ctx->pair_count;
+    const DriftSide *side = large ? nullptr : drift_side(ctx, s);
+    for (int k = 1, rec = 0; k <= nsteps; ++k) {
+        const bool last = k == nsteps;
+        if (large && (rc = build_groups_large(ctx, s))) return rc;
+        const bool parts = large && ctx->gs_h.size() > 1;
+        if (parts) {
+            if ((rc = enqueue_drift(ctx, b, dt, s, false, true))) return rc;
+            HIP_TRY(prep()); // an empty pair list
+        } else {
+            HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit,
+                                 dt, ctx->members, ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, 0,
+                                 large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, side, &pm, true));
+        }
+        if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, parts ? 0.0 : 0.5 * dt, !last && !large, s)))
+            return rc;
+        if (cadence > 0 && d_energy && k % cadence == 0) {
+            rc = enqueue_energy(ctx, b, last ? 0.0 : 0.5 * dt, d_energy + (size_t)rec * 4 * L.n_sys, s);
+            if (rc) return rc;
+            ++rec;
+        }
+    }
+    return GENGA_OK;
+}
+
 int enqueue_step(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, int prec, int acc, int cadence,
                  double *d_energy, hipStream_t s)
 {
+    if (!ctx->col.mass && ctx->L.n_total > 0) return enqueue_steps_fused(ctx, b, dt, nsteps, prec, acc, cadence, d_energy, s);
     const size_t n = (size_t)ctx->L.n_total;
     double *ax = ctx->acc, *ay = ctx->acc + n, *az = ctx->acc + 2 * n;
     int rc = enqueue_kick(ctx, b, 0.5 * dt, 1, prec, acc, ax, ay, az, s);
@@ -1006,6 +1099,28 @@ int upload_plan(genga_ctx *ctx)
         HIP_TRY(hipMemcpy(ctx->tasks, tasks.data(), tasks.size() * sizeof(int4), hipMemcpyHostToDevice));
     }
     HIP_TRY(hipMemcpy(ctx->task_first, tfirst.data(), tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    // blocks of items of one system, for the end of a step's kick
+    std::vector<CloseBlock> cb;
+    std::vector<int32_t> cfirst(n_sys + 1, 0);
+    for (int s = 0; s < n_sys; ++s) {
+        cfirst[s] = (int32_t)cb.size();
+        for (int k = first[s]; k < first[s + 1]; k += CLOSE_ITEMS)
+            cb.push_back(CloseBlock{s, k, std::min(CLOSE_ITEMS, first[s + 1] - k), 0});
+    }
+    cfirst[n_sys] = (int32_t)cb.size();
+    HIP_TRY(dalloc(ctx->close_blocks, cb.size()));
+    HIP_TRY(dalloc(ctx->close_first, cfirst.size()));
+    HIP_TRY(dalloc(ctx->pm.kick, 3 * cb.size()));
+    HIP_TRY(dalloc(ctx->pm.kepler, 3 * it.size()));
+    HIP_TRY(dalloc(ctx->pm.group, 3 * (size_t)CE_MAX_MEMBERS / 2));
+    HIP_TRY(dalloc(ctx->pm.group_sys, (size_t)CE_MAX_MEMBERS / 2));
+    HIP_TRY(dalloc(ctx->pm.group_n, 1));
+    if (!cb.empty())
+        HIP_TRY(hipMemcpy(ctx->close_blocks, cb.data(), cb.size() * sizeof(CloseBlock), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(ctx->close_first, cfirst.data(), cfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    ctx->pm.blocks = ctx->close_blocks;
+    ctx->pm.block_first = ctx->close_first;
+    ctx->pm.n_blocks = (int32_t)cb.size();
     HIP_TRY(hipMemcpy(ctx->item_first, first.data(), (n_sys + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->L.n_massive, ctx->n_massive_h.data(), n_sys * sizeof(int32_t), hipMemcpyHostToDevice));
     std::vector<int32_t> seg(2 * (size_t)n_sys + 1);

@@ -80,6 +80,26 @@ struct KickArgs {
     const int32_t *status;        // with collisions: bodies with status != 0 are in no pair
 };
 
+// A run of at most CLOSE_ITEMS items of one system: a workgroup of launch_kick_close.
+constexpr int CLOSE_ITEMS = 16;
+struct CloseBlock {
+    int32_t sys, item, n, pad; // items [item, item + n)
+};
+
+// Momentum sums that the launches of a step hand on to each other instead of passes of their own.
+struct StepMomentum {
+    const CloseBlock *blocks = nullptr;  // [n_blocks], systems in order
+    const int32_t *block_first = nullptr; // [n_sys + 1]
+    int32_t n_blocks = 0;
+    double *kick = nullptr;    // [n_blocks][3] sum m v after the kick
+    double *kepler = nullptr;  // [n_items][3] sum m v after the drift, bodies outside groups
+    double *group = nullptr;   // [CE_MAX_MEMBERS / 2][3] the same of the groups, which are in system order
+    int32_t *group_sys = nullptr;
+    int32_t *group_n = nullptr; // the groups the drift had (n_groups is the next kick's while it closes)
+    double tau = 0.0;          // half a Sun drift: positions + tau P / Mstar
+    int32_t *clear = nullptr;  // pair count, cleared by the drift once the groups are built
+};
+
 constexpr int KICK_MAX_SPLIT = 4;
 
 // Error message for genga_last_error(); returns code.
@@ -146,6 +166,21 @@ hipError_t launch_prep(const Layout &L, double *x, double *y, double *z, const d
                        const double *mom_part, double shift_tau, hipStream_t stream);
 // kahan: the FP32 kick's blocks are summed with Kahan compensation in FP32 (else in FP64)
 hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream);
+// Arrays of the one-workgroup group builder.
+struct GroupBuild {
+    const int32_t *pairs, *pair_count;
+    int32_t pair_cap;
+    int32_t *lab, *mark, *members, *group_start, *n_groups, *member_slot, *wg_list, *flags;
+};
+// The kick without its finishing launch, for launch_kick_close.
+hipError_t launch_kick_shares(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream);
+// Finishes a kick inside a step: the tasks' shares summed, v += tau a; with pm.tau != 0 first the
+// second half of the preceding drift's Sun drift (from pm.kepler and pm.group); then the sums of
+// m v into pm.kick; and, from a workgroup of its own, with groups != null the encounter groups
+// of the kick's pairs.
+hipError_t launch_kick_close(const Layout &L, const KickArgs &a, double *x, double *y, double *z,
+                             const StepMomentum &pm, const int32_t *item_first, const GroupBuild *groups,
+                             hipStream_t stream);
 // The encounter pairs of the state only (no forces, nothing written but a.pairs / a.pair_count).
 hipError_t launch_pair_list(const KickArgs &a, hipStream_t stream);
 hipError_t launch_rcrit(const Layout &L, const double *x, const double *y, const double *z,
@@ -186,10 +221,7 @@ __device__ inline void system_momentum(const int32_t *chunk_first, const double 
         for (int q = 0; q < 3; ++q) P[q] += red[q][w];
     __syncthreads();
 }
-hipError_t launch_ce_groups(const Layout &L, const int32_t *pairs, const int32_t *pair_count,
-                            int32_t pair_cap, int32_t *lab, int32_t *mark, int32_t *members,
-                            int32_t *group_start, int32_t *n_groups, int32_t *member_slot,
-                            int32_t *flags, hipStream_t stream);
+hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream);
 // Kepler drift of the bodies outside encounter groups and Bulirsch-Stoer of each group of up
 // to CE_MAX_GROUP members (groups of 9 and more in a launch of their own, listed in wg_list:
 // [0] their number, then the groups; room for bs_blocks + 1); clears member_slot for the next
@@ -203,12 +235,14 @@ struct DriftSide {
     hipStream_t stream = nullptr;
     hipEvent_t fork = nullptr, join = nullptr;
 };
-hipError_t launch_drift(const Layout &L, double *x, double *y, double *z, double *vx, double *vy,
-                        double *vz, const double *m, const double *rc, double dt, const int32_t *members,
-                        const int32_t *group_start, const int32_t *n_groups, int32_t *member_slot,
-                        int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list, hipStream_t stream,
-                        const double *rc_lv = nullptr, int nlev = 1, bool kepler = true,
-                        const DriftSide *side = nullptr);
+// pm (may be null): the launch itself applies the first half of the Sun drift (pm->kick, pm->tau)
+// and leaves the sums of m v after the drift; wg_listed: wg_list is already there.
+hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, double *x, double *y, double *z,
+                        double *vx, double *vy, double *vz, const double *m, const double *rc, double dt,
+                        const int32_t *members, const int32_t *group_start, const int32_t *n_groups,
+                        int32_t *member_slot, int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list,
+                        hipStream_t stream, const double *rc_lv = nullptr, int nlev = 1, bool kepler = true,
+                        const DriftSide *side = nullptr, const StepMomentum *pm = nullptr, bool wg_listed = false);
 // Grid-wide union-find of the encounter pairs (large-group mode; the host reads lab back):
 // init (lab = body for the bodies of a pair), hook rounds (changed |= 1 while a round hooks),
 // compress (every member's lab = its root), slots (member_slot for members[0..n), lab = -1).

@@ -308,20 +308,6 @@ __device__ __forceinline__ void step64(CD *X, CD *Y, CD *Z, CD *M, int j, int jb
     }
 }
 
-// Body i's acceleration: out, checked, and v += tau a.
-__device__ __forceinline__ void store_accel(const KickArgs &a, int i, double tx, double ty, double tz)
-{
-    a.ax[i] = tx;
-    a.ay[i] = ty;
-    a.az[i] = tz;
-    if (!(isfinite(tx) && isfinite(ty) && isfinite(tz))) atomicOr(a.flags, FLAG_NONFINITE);
-    if (a.update_v) {
-        a.vx[i] += a.tau * tx;
-        a.vy[i] += a.tau * ty;
-        a.vz[i] += a.tau * tz;
-    }
-}
-
 // Sum the W waves' partial accelerations in a fixed order; then either finish the body or, when
 // its sources are split over tasks, store this task's share for kick_finish_kernel.
 template <int W>
@@ -354,29 +340,10 @@ __global__ __launch_bounds__(256) void kick_finish_kernel(KickArgs a)
     const int it = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (it >= a.n_items) return;
     const WorkItem w = a.items[it];
-    const int t0 = a.tasks ? a.task_first[it] : it * a.split, t1 = a.tasks ? a.task_first[it + 1] : t0 + a.split;
     if (lane >= w.ni) return;
-    double tx = 0.0, ty = 0.0, tz = 0.0;
-    const double *p = a.part + (size_t)t0 * 192 + lane;
-    int t = t0;
-    for (; t + 8 <= t1; t += 8, p += 8 * 192) { // eight tasks' loads in flight
-        double v[8][3];
-#pragma unroll
-        for (int u = 0; u < 8; ++u)
-            for (int q = 0; q < 3; ++q) v[u][q] = p[u * 192 + 64 * q];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            tx += v[u][0];
-            ty += v[u][1];
-            tz += v[u][2];
-        }
-    }
-    for (; t < t1; ++t, p += 192) {
-        tx += p[0];
-        ty += p[64];
-        tz += p[128];
-    }
-    store_accel(a, w.i0 + lane, tx, ty, tz);
+    double t[3];
+    item_shares(a, it, lane, t);
+    store_accel(a, w.i0 + lane, t[0], t[1], t[2]);
 }
 
 // Sources whose FP32 terms a wave adds up before it folds them into its accumulators: 32 of a
@@ -607,7 +574,7 @@ hipError_t launch_prep(const Layout &L, double *x, double *y, double *z, const d
     return hipGetLastError();
 }
 
-hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream)
+hipError_t launch_kick_shares(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream)
 {
     if (a.n_items == 0) return hipSuccess;
     const int grid = a.tasks ? a.n_tasks : a.n_items * a.split;
@@ -628,7 +595,14 @@ hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStr
         return hipErrorInvalidValue;
     }
 #undef GENGA_KICK_CASE
-    if (!a.direct) kick_finish_kernel<<<(a.n_items + 3) / 4, 256, 0, stream>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream)
+{
+    const hipError_t e = launch_kick_shares(a, fp32, kahan, waves, stream);
+    if (e != hipSuccess || a.direct || a.n_items == 0) return e;
+    kick_finish_kernel<<<(a.n_items + 3) / 4, 256, 0, stream>>>(a);
     return hipGetLastError();
 }
 

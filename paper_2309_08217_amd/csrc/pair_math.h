@@ -130,5 +130,38 @@ __device__ __forceinline__ void tile_box(bool v, double x, double y, double z, d
     }
 }
 
+// Body i's acceleration: out, checked, and v += tau a.
+__device__ __forceinline__ void store_accel(const KickArgs &a, int i, double tx, double ty, double tz)
+{
+    a.ax[i] = tx;
+    a.ay[i] = ty;
+    a.az[i] = tz;
+    if (!(isfinite(tx) && isfinite(ty) && isfinite(tz))) atomicOr(a.flags, FLAG_NONFINITE);
+    if (a.update_v) {
+        a.vx[i] += a.tau * tx;
+        a.vy[i] += a.tau * ty;
+        a.vz[i] += a.tau * tz;
+    }
+}
+
+// The tasks' shares of body `lane` of item `it`, added in task order.
+__device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane, double t[3])
+{
+    const int t0 = a.tasks ? a.task_first[it] : it * a.split, t1 = a.tasks ? a.task_first[it + 1] : t0 + a.split;
+    t[0] = t[1] = t[2] = 0.0;
+    const double *p = a.part + (size_t)t0 * 192 + lane;
+    int k = t0;
+    for (; k + 8 <= t1; k += 8, p += 8 * 192) { // eight tasks' loads in flight
+        double v[8][3];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            for (int q = 0; q < 3; ++q) v[u][q] = p[u * 192 + 64 * q];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            for (int q = 0; q < 3; ++q) t[q] += v[u][q];
+    }
+    for (; k < t1; ++k, p += 192)
+        for (int q = 0; q < 3; ++q) t[q] += p[64 * q];
+}
 
 } // namespace genga

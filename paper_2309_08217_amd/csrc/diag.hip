@@ -4,9 +4,11 @@
 // Energy of the democratic heliocentric Hamiltonian per system:
 //   E = sum m v^2/2 + |sum m v|^2/(2 Mstar) - sum Mstar m/r - sum_{i<j} m_i m_j / r_ij,
 //   L = sum m r x v.
-// The pair sum uses the kick's work items (64 targets per workgroup, W waves over the
-// sources j > i); per-item partial sums are reduced in a fixed order, so the result is
-// deterministic.  Velocities may be given half a kick ahead: v_sync = v - vshift * a.
+// The pair sum takes 64 targets per workgroup and a run of the sources j > i, split over its
+// waves; the runs' lengths come from the whole layout's work, as the kick's do, so that a few
+// massive bodies among many test bodies do not keep four workgroups busy alone (20040 bodies in
+// TP2 mode: 72 us when every block of targets had four parts).  The tasks' partial sums are
+// reduced in a fixed order, so the result is deterministic.  Velocities may be given half a kick ahead: v_sync = v - vshift * a.
 #include "genga_internal.h"
 #include "pair_math.h"
 
@@ -14,7 +16,7 @@ namespace genga {
 
 namespace {
 
-constexpr int EW = 8;      // waves per workgroup in the pair sum
+constexpr int EW = 4;      // waves per workgroup in the pair sum
 constexpr int NPART = 9;   // pairpot, kin, sunpot, px, py, pz, lx, ly, lz
 
 using CJ64 = const __attribute__((address_space(4))) double;
@@ -25,11 +27,11 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-__global__ __launch_bounds__(64 * EW) void energy_kernel(
-    const WorkItem *items, int n_items, const int32_t *sys_off, const double *mstar, const double *x,
-    const double *y, const double *z, const double *vx, const double *vy, const double *vz,
-    const double *m, const double *ax, const double *ay, const double *az, double vshift,
-    double *partial, int split)
+__global__ __launch_bounds__(64 * EW) void energy_kernel(const EnergyTask *tasks, const double *mstar, const double *x,
+                                                         const double *y, const double *z, const double *vx,
+                                                         const double *vy, const double *vz, const double *m,
+                                                         const double *ax, const double *ay, const double *az,
+                                                         double vshift, double *partial)
 {
     __shared__ double red[EW][64];
     const int lane = threadIdx.x & 63;
@@ -38,107 +40,119 @@ __global__ __launch_bounds__(64 * EW) void energy_kernel(
     CJ64 *Y = (CJ64 *)y;
     CJ64 *Z = (CJ64 *)z;
     CJ64 *M = (CJ64 *)m;
-    const int n_tasks = n_items * split;
-    for (int it = blockIdx.x; it < n_tasks; it += gridDim.x) {
-        const WorkItem w = items[it / split];
-        const int part = it % split;
-        const bool valid = lane < w.ni;
-        const int i = w.i0 + (valid ? lane : 0);
-        const double xi = x[i], yi = y[i], zi = z[i];
-        // sources j in [i0, end of system), split into `split` parts over workgroups and each
-        // part over the waves; only j > i counts
-        // test-body items have nsrc <= i0 - off: no pair terms (test pairs do not count)
-        const int jend = max(sys_off[w.sys] + w.nsrc, w.i0);
-        const int per = (jend - w.i0 + split - 1) / split;
-        const int p0 = min(w.i0 + part * per, jend);
-        const int p1 = min(p0 + per, jend);
-        const int chunk = (p1 - p0 + EW - 1) / EW;
-        const int jb = min(p0 + wave * chunk, p1), je = min(jb + chunk, p1);
-        double s = 0.0;
-        const int jmask = min(je, w.i0 + 64);
-        int j = jb;
-        for (; j < jmask; ++j) {
-            // sources inside the item's own range: only j > i counts (the self pair has q = 0,
-            // so it is replaced by a harmless q = 1 with zero weight)
-            const double dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
-            const bool take = j > i;
-            const double q = take ? fma(dx, dx, fma(dy, dy, dz * dz)) : 1.0;
-            const double mj = take ? M[j] : 0.0;
-            s = fma(mj, inv_sqrt64(q), s);
-        }
-        for (; j + 2 <= je; j += 2) {
-            const double dx0 = X[j] - xi, dy0 = Y[j] - yi, dz0 = Z[j] - zi;
-            const double dx1 = X[j + 1] - xi, dy1 = Y[j + 1] - yi, dz1 = Z[j + 1] - zi;
-            const double q0 = fma(dx0, dx0, fma(dy0, dy0, dz0 * dz0));
-            const double q1 = fma(dx1, dx1, fma(dy1, dy1, dz1 * dz1));
-            s = fma(M[j], inv_sqrt64(q0), s);
-            s = fma(M[j + 1], inv_sqrt64(q1), s);
-        }
-        for (; j < je; ++j) {
-            const double dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
-            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            s = fma(M[j], inv_sqrt64(q), s);
-        }
-        red[wave][lane] = s;
-        __syncthreads();
-        if (wave == 0) {
-            double tot = 0.0;
+    const EnergyTask w = tasks[blockIdx.x];
+    const bool valid = lane < w.ni;
+    const int i = w.i0 + (valid ? lane : 0);
+    const double xi = x[i], yi = y[i], zi = z[i];
+    const int chunk = (w.j1 - w.j0 + EW - 1) / EW;
+    const int jb = __builtin_amdgcn_readfirstlane(min(w.j0 + wave * chunk, w.j1));
+    const int je = __builtin_amdgcn_readfirstlane(min(jb + chunk, w.j1));
+    double s = 0.0;
+    const int jmask = min(je, w.i0 + 64);
+    int j = jb;
+    for (; j < jmask; ++j) {
+        // sources inside the item's own range: only j > i counts (the self pair has q = 0,
+        // so it is replaced by a harmless q = 1 with zero weight)
+        const double dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
+        const bool take = j > i;
+        const double q = take ? fma(dx, dx, fma(dy, dy, dz * dz)) : 1.0;
+        const double mj = take ? M[j] : 0.0;
+        s = fma(mj, inv_sqrt64(q), s);
+    }
+    for (; j + 4 <= je; j += 4) {
+        double q[4];
 #pragma unroll
-            for (int k = 0; k < EW; ++k) tot += red[k][lane];
-            double v[NPART];
-            if (valid && part > 0) {
-                v[0] = m[i] * tot;
-                for (int k = 1; k < NPART; ++k) v[k] = 0.0;
-            } else if (valid) {
-                const double mi = m[i];
-                const double ux = vx[i] - vshift * ax[i];
-                const double uy = vy[i] - vshift * ay[i];
-                const double uz = vz[i] - vshift * az[i];
-                v[0] = mi * tot;
-                v[1] = 0.5 * mi * (ux * ux + uy * uy + uz * uz);
-                v[2] = -mstar[w.sys] * mi / sqrt(xi * xi + yi * yi + zi * zi);
-                v[3] = mi * ux;
-                v[4] = mi * uy;
-                v[5] = mi * uz;
-                v[6] = mi * (yi * uz - zi * uy);
-                v[7] = mi * (zi * ux - xi * uz);
-                v[8] = mi * (xi * uy - yi * ux);
-            } else {
-#pragma unroll
-                for (int k = 0; k < NPART; ++k) v[k] = 0.0;
-            }
-#pragma unroll
-            for (int k = 0; k < NPART; ++k) {
-                const double t = wave_sum(v[k]);
-                if (lane == 0) partial[(size_t)it * NPART + k] = t;
-            }
+        for (int v = 0; v < 4; ++v) {
+            const double dx = X[j + v] - xi, dy = Y[j + v] - yi, dz = Z[j + v] - zi;
+            q[v] = fma(dx, dx, fma(dy, dy, dz * dz));
         }
-        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s = fma(M[j + v], inv_sqrt64(q[v]), s);
+    }
+    for (; j < je; ++j) {
+        const double dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
+        const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+        s = fma(M[j], inv_sqrt64(q), s);
+    }
+    red[wave][lane] = s;
+    __syncthreads();
+    if (wave != 0) return;
+    double tot = 0.0;
+#pragma unroll
+    for (int k = 0; k < EW; ++k) tot += red[k][lane];
+    const double mi = valid ? m[i] : 0.0;
+    tot = wave_sum(mi * tot);
+    if (lane == 0) partial[blockIdx.x] = tot;
+    if (!w.first) return;
+    double v[NPART - 1] = {};
+    if (valid) {
+        const double ux = vx[i] - vshift * ax[i];
+        const double uy = vy[i] - vshift * ay[i];
+        const double uz = vz[i] - vshift * az[i];
+        v[0] = 0.5 * mi * (ux * ux + uy * uy + uz * uz);
+        v[1] = -mstar[w.sys] * mi / sqrt(xi * xi + yi * yi + zi * zi);
+        v[2] = mi * ux;
+        v[3] = mi * uy;
+        v[4] = mi * uz;
+        v[5] = mi * (yi * uz - zi * uy);
+        v[6] = mi * (zi * ux - xi * uz);
+        v[7] = mi * (xi * uy - yi * ux);
+    }
+#pragma unroll
+    for (int k = 0; k < NPART - 1; ++k) {
+        const double t = wave_sum(v[k]);
+        if (lane == 0) partial[(size_t)(k + 1) * gridDim.x + blockIdx.x] = t;
     }
 }
 
-// One workgroup per system: each thread sums a strided subset of the system's item partials
-// in order, then a fixed tree in LDS combines the threads.
-constexpr int EF_THREADS = 256;
+// One workgroup per system: each thread sums a strided subset of the system's task partials
+// in order (the pair sum of every task, the other parts of the tasks that have them, which are
+// the system's first), then the lanes of a wave and the waves in fixed trees.  Bound by how fast
+// one CU reads what others wrote: 20040 bodies (12 thousand tasks) took 17 us with nine sums of
+// every task.
+constexpr int EF_THREADS = 1024, EF_AHEAD = 4;
 
-__global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t *item_first,
-                                                                   const double *mstar,
-                                                                   const double *partial, double *out,
-                                                                   int split)
+__device__ __forceinline__ double strided_sum(const double *p, int t0, int t1)
 {
-    __shared__ double red[NPART][EF_THREADS];
-    const int s = blockIdx.x;
-    double t[NPART];
-    for (int k = 0; k < NPART; ++k) t[k] = 0.0;
-    for (int it = item_first[s] * split + threadIdx.x; it < item_first[s + 1] * split; it += EF_THREADS)
-        for (int k = 0; k < NPART; ++k) t[k] += partial[(size_t)it * NPART + k];
-    for (int k = 0; k < NPART; ++k) red[k][threadIdx.x] = t[k];
-    __syncthreads();
-    for (int o = EF_THREADS / 2; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o)
-            for (int k = 0; k < NPART; ++k) red[k][threadIdx.x] += red[k][threadIdx.x + o];
-        __syncthreads();
+    double t = 0.0;
+    for (int it = t0 + threadIdx.x; it < t1; it += EF_AHEAD * EF_THREADS) {
+        double v[EF_AHEAD]; // all in flight
+#pragma unroll
+        for (int u = 0; u < EF_AHEAD; ++u) v[u] = p[min(it + u * EF_THREADS, t1 - 1)];
+#pragma unroll
+        for (int u = 0; u < EF_AHEAD; ++u) t += it + u * EF_THREADS < t1 ? v[u] : 0.0;
     }
+    return t;
+}
+
+__global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t *task_first,
+                                                                   const double *mstar,
+                                                                   const double *partial, int n_tasks, double *out)
+{
+    __shared__ double red[NPART][EF_THREADS / 64];
+    const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t0 = task_first[2 * s], tk = task_first[2 * s + 1], t1 = task_first[2 * s + 2];
+    double t[NPART];
+    // the usual number of first tasks in one load each, beside the pair sums
+    t[0] = strided_sum(partial, t0, t1);
+    for (int k = 1; k < NPART; ++k) {
+        const double *p = partial + (size_t)k * n_tasks;
+        const int it = t0 + (int)threadIdx.x;
+        t[k] = it < tk ? p[it] : 0.0;
+    }
+    for (int it = t0 + (int)threadIdx.x + EF_THREADS; it < tk; it += EF_THREADS)
+        for (int k = 1; k < NPART; ++k) t[k] += partial[(size_t)k * n_tasks + it];
+    for (int k = 0; k < NPART; ++k) {
+        t[k] = wave_sum(t[k]);
+        if (lane == 0) red[k][wave] = t[k];
+    }
+    __syncthreads();
+    if (threadIdx.x < NPART) {
+        double v = 0.0;
+        for (int w = 0; w < EF_THREADS / 64; ++w) v += red[threadIdx.x][w];
+        red[threadIdx.x][0] = v;
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
         const double p2 = red[3][0] * red[3][0] + red[4][0] * red[4][0] + red[5][0] * red[5][0];
         out[4 * s + 0] = red[1][0] + p2 / (2.0 * mstar[s]) + red[2][0] - red[0][0];
@@ -254,17 +268,15 @@ hipError_t launch_import_pairs(const Layout &L, const int32_t *src, const int32_
     return hipGetLastError();
 }
 
-hipError_t launch_energy(const Layout &L, const WorkItem *items, int32_t n_items, const double *x,
-                         const double *y, const double *z, const double *vx, const double *vy,
-                         const double *vz, const double *m, const double *ax, const double *ay,
-                         const double *az, double vshift, double *partial,
-                         const int32_t *item_first, double *out, hipStream_t stream)
+hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tasks, const int32_t *task_first,
+                         const double *x, const double *y, const double *z, const double *vx, const double *vy,
+                         const double *vz, const double *m, const double *ax, const double *ay, const double *az,
+                         double vshift, double *partial, double *out, hipStream_t stream)
 {
-    if (n_items > 0)
-        energy_kernel<<<n_items * ENERGY_SPLIT, 64 * EW, 0, stream>>>(items, n_items, L.sys_off, L.mstar, x, y,
-                                                                      z, vx, vy, vz, m, ax, ay, az, vshift,
-                                                                      partial, ENERGY_SPLIT);
-    energy_finish_kernel<<<L.n_sys, EF_THREADS, 0, stream>>>(item_first, L.mstar, partial, out, ENERGY_SPLIT);
+    if (n_tasks > 0)
+        energy_kernel<<<n_tasks, 64 * EW, 0, stream>>>(tasks, L.mstar, x, y, z, vx, vy, vz, m, ax, ay, az, vshift,
+                                                       partial);
+    energy_finish_kernel<<<L.n_sys, EF_THREADS, 0, stream>>>(task_first, L.mstar, partial, n_tasks, out);
     return hipGetLastError();
 }
 

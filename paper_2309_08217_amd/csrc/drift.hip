@@ -646,37 +646,66 @@ __device__ __forceinline__ void wave_momentum(const int32_t *first, const double
 }
 
 // The end of a kick inside a step (launch_kick_close).  Workgroup 0 builds the groups, the others
-// take a block of items each, one wave per item.
+// take a block of items each, pm.parts waves an item, which share its tasks (20040 bodies in FP64, 39
+// tasks an item: 14 us with four waves, 26 with one).  Latency bound, a chain of loads of what other launches wrote: everything a wave needs is loaded before
+// the first barrier, in three rounds.
 __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, double *x, double *y, double *z,
-                                                                const double *mstar, StepMomentum pm,
-                                                                const int32_t *item_first, GroupBuild g,
-                                                                int with_groups)
+                                                                StepMomentum pm, GroupBuild g, int with_groups)
 {
     __shared__ GroupLds S;
-    constexpr int NW = CE_THREADS / 64;
-    static_assert(NW == CLOSE_ITEMS, "one wave per item");
+    constexpr int NW = CLOSE_WAVES;
+    static_assert(NW == CE_THREADS / 64, "the block's waves");
+    const int parts = pm.parts;
     if (blockIdx.x == 0) {
         if (with_groups) build_groups(g, S);
         return;
     }
-    double(*red)[NW] = reinterpret_cast<double(*)[NW]>(S.keys); // [3][NW]
+    double(*red)[NW] = reinterpret_cast<double(*)[NW]>(S.keys);                     // [6][NW]
+    double(*share)[NW][64] = reinterpret_cast<double(*)[NW][64]>(S.keys + 6 * NW); // [3][NW][64]
+    static_assert((6 + 3 * 64) * NW <= CE_MAX_MEMBERS, "the sums fit");
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, part = wave % parts;
+    const bool shift = pm.tau != 0.0;
+    // first round: the block, the drift's groups (one per thread; more below)
     const CloseBlock blk = pm.blocks[blockIdx.x - 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    double sh[3] = {0.0, 0.0, 0.0};
-    if (pm.tau != 0.0) {
-        // P after the drift: the items' sums and the groups', from the system's first group on,
-        // so that the order of the sum depends on the system alone
-        double P[3] = {0.0, 0.0, 0.0};
-        for (int k = item_first[blk.sys] + tid; k < item_first[blk.sys + 1]; k += CE_THREADS)
+    const int G = shift ? *pm.group_n : 0;
+    int gs = shift ? pm.group_sys[tid] : -1;
+    // second round: the item, its tasks, P after the drift by item
+    const int it = blk.item + wave / parts;
+    const bool mine = wave / parts < blk.n;
+    const WorkItem w = mine ? a.items[it] : WorkItem{0, 0, 0, 0};
+    const bool on = lane < w.ni, lead = on && part == 0;
+    const int i = w.i0 + lane;
+    double P[3] = {0.0, 0.0, 0.0};
+    if (shift)
+        for (int k = blk.f0 + tid; k < blk.f1; k += CE_THREADS)
             for (int q = 0; q < 3; ++q) P[q] += pm.kepler[3 * (size_t)k + q];
-        const int G = *pm.group_n;
+    // third: the shares and the body
+    double t[3] = {0.0, 0.0, 0.0}, X[3] = {0.0, 0.0, 0.0}, V[3] = {0.0, 0.0, 0.0}, mi = 0.0;
+    if (lead) {
+        mi = a.m[i];
+        V[0] = a.vx[i];
+        V[1] = a.vy[i];
+        V[2] = a.vz[i];
+        if (shift) {
+            X[0] = x[i];
+            X[1] = y[i];
+            X[2] = z[i];
+        }
+    }
+    if (mine) item_shares(a, it, lane, t, part, parts);
+    for (int q = 0; q < 3; ++q) share[q][wave][lane] = t[q];
+    if (shift) {
+        // the groups' momenta, from the system's first group on, so that the order of the sum
+        // depends on the system alone (groups are in system order)
         if (tid == 0) S.ng = G;
         __syncthreads();
-        for (int k = tid; k < G; k += CE_THREADS)
-            if (pm.group_sys[k] == blk.sys) {
+        for (int k = tid; k < G; k += CE_THREADS) {
+            if (k != tid) gs = pm.group_sys[k];
+            if (gs == blk.sys) {
                 atomicMin(&S.ng, k);
                 break;
             }
+        }
         __syncthreads();
         for (int k = S.ng + tid; k < G && pm.group_sys[k] == blk.sys; k += CE_THREADS)
             for (int q = 0; q < 3; ++q) P[q] += pm.group[3 * (size_t)k + q];
@@ -685,43 +714,44 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
             if (lane == 0) red[q][wave] = P[q];
         }
         __syncthreads();
-        const double f = pm.tau / mstar[blk.sys];
+        const double f = pm.tau / blk.mstar;
         for (int q = 0; q < 3; ++q) {
-            double t = 0.0;
-            for (int w = 0; w < NW; ++w) t += red[q][w];
-            sh[q] = f * t;
+            double s = 0.0;
+            for (int k = 0; k < NW; ++k) s += red[q][k];
+            X[q] += f * s;
         }
-        __syncthreads(); // red is rewritten below
     }
+    __syncthreads();
     double p[3] = {0.0, 0.0, 0.0};
-    if (wave < blk.n) {
-        const int it = blk.item + wave;
-        const WorkItem w = a.items[it];
-        if (lane < w.ni) {
-            const int i = w.i0 + lane;
-            double t[3];
-            item_shares(a, it, lane, t);
-            store_accel(a, i, t[0], t[1], t[2]);
-            if (pm.tau != 0.0) {
-                x[i] += sh[0];
-                y[i] += sh[1];
-                z[i] += sh[2];
-            }
-            const double mi = a.m[i];
-            p[0] = mi * a.vx[i];
-            p[1] = mi * a.vy[i];
-            p[2] = mi * a.vz[i];
+    if (lead) {
+        for (int k = 1; k < parts; ++k)
+            for (int q = 0; q < 3; ++q) t[q] += share[q][wave + k][lane];
+        a.ax[i] = t[0];
+        a.ay[i] = t[1];
+        a.az[i] = t[2];
+        if (!(isfinite(t[0]) && isfinite(t[1]) && isfinite(t[2]))) atomicOr(a.flags, FLAG_NONFINITE);
+        for (int q = 0; q < 3; ++q) {
+            V[q] += a.tau * t[q];
+            p[q] = mi * V[q];
+        }
+        a.vx[i] = V[0];
+        a.vy[i] = V[1];
+        a.vz[i] = V[2];
+        if (shift) {
+            x[i] = X[0];
+            y[i] = X[1];
+            z[i] = X[2];
         }
     }
     for (int q = 0; q < 3; ++q) {
         p[q] = wave_sum(p[q]);
-        if (lane == 0) red[q][wave] = p[q];
+        if (lane == 0) red[3 + q][wave] = p[q];
     }
     __syncthreads();
     if (tid < 3) {
-        double t = 0.0;
-        for (int w = 0; w < NW; ++w) t += red[tid][w];
-        pm.kick[3 * (size_t)(blockIdx.x - 1) + tid] = t;
+        double s = 0.0;
+        for (int k = 0; k < NW; ++k) s += red[3 + tid][k];
+        pm.kick[3 * (size_t)(blockIdx.x - 1) + tid] = s;
     }
 }
 
@@ -1427,11 +1457,10 @@ __device__ __forceinline__ void store_momentum(double *out, int k, const double 
     }
 }
 
-// The drift over dt: blocks [0, bs_blocks) integrate the encounter groups with Bulirsch-Stoer, one
-// at a time, the blocks after them Kepler-drift an item of up to 64 bodies each and skip the group
+// The drift over dt: blocks [0, bs_blocks) integrate the encounter groups with Bulirsch-Stoer, the blocks after them Kepler-drift an item of up to 64 bodies each and skip the group
 // members.  Each body is read and written by one block only.
 template <bool LV>
-__global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, const int32_t *sys_off,
+__global__ __launch_bounds__(BS_LANES) __attribute__((amdgpu_waves_per_eu(2))) void drift_kernel(const int32_t *sys_of, const int32_t *sys_off,
                                                          const int32_t *n_massive, const double *mstar,
                                                          const WorkItem *items, int n_total, double *x, double *y,
                                                          double *z, double *vx, double *vy, double *vz,
@@ -1440,7 +1469,7 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
                                                          const int32_t *group_start,
                                                          const int32_t *n_groups, int32_t *member_slot,
                                                          int32_t *flags, int big_groups, int bs_blocks,
-                                                         const double *rc_lv, int nlev, StepMomentum pm)
+                                                         const double *rc_lv, int nlev, StepMomentum pm, int one_sys)
 {
     // the column path's two Neville rows; the small-group path's T(k, 0) table and Lagrange
     // weights fit in the same space.  The block's LDS sets how many share a CU.
@@ -1476,69 +1505,68 @@ __global__ __launch_bounds__(BS_LANES) void drift_kernel(const int32_t *sys_of, 
         if (pm.kepler) store_momentum(pm.kepler, it, p);
         return;
     }
-    const int G = *n_groups;
-    for (int g = blockIdx.x; g < G; g += bs_blocks) {
-        const int k0 = group_start[g], nb = group_start[g + 1] - k0;
-        const int sys = sys_of[members[k0]];
-        const double ms = mstar[sys];
-        if (pm.group && lane == 0) pm.group_sys[g] = sys;
-        if (nb > BS_LANES && big_groups) continue;       // integrated by the grid-wide path
-        if (nb > CP_MEM && nb <= BS_LANES) continue;     // a workgroup of drift_wg_kernel integrates it
-        sun_shift_of(pm, mstar, sys, sh);
-        p[0] = p[1] = p[2] = 0.0;
-        if (nb > BS_LANES) {
-            // larger than one wave: Kepler-drift the members instead and flag it
-            if (lane == 0) atomicOr(flags, FLAG_CAPACITY);
-            for (int k = lane; k < nb; k += BS_LANES) {
-                const int b = members[k0 + k];
-                double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
-                if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], ms, dt)) atomicOr(flags, FLAG_KEPLER);
-                store_state(x, y, z, vx, vy, vz, b, Y);
-                for (int q = 0; q < 3; ++q) p[q] += m[b] * Y[3 + q];
-            }
-            if (pm.group) store_momentum(pm.group, g, p);
-            continue;
-        }
-        __syncthreads(); // the previous group's LDS is no longer read
-        if (lane < nb) {
-            const int b = members[k0 + lane];
-            const int sb = sys_of[b];
-            S.m[lane] = m[b];
-            S.i09[lane] = 1.0 / (0.9 * rc[b]);
-            S.test[lane] = b - sys_off[sb] >= n_massive[sb];
-            if constexpr (LV)
-                for (int l = 1; l < nlev; ++l) S.i9l[l - 1][lane] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
-        }
-        if (lane == 0) S.nlev = nlev;
-        __syncthreads();
-        bool ok;
-        if (nb <= 3) {
-            double *lag = tab + BS_KMAX * 3 * 6;
-            ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt, sh, p)
-                         : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt, sh, p);
-        } else {
-            const int k = lane / CP_MEM;
-            BsMember me;
-            me.a = lane % CP_MEM;
-            me.nb = nb;
-            me.base = k * CP_MEM;
-            me.act = me.a < nb;
-            const int ai = me.act ? me.a : 0;
-            me.test = S.test[ai] != 0;
-            me.mstar = ms;
-            me.i09 = S.i09[ai];
-            const int b = members[k0 + ai];
+    // the group's bounds are loaded beside the count (the array has room for every block's), and a
+    // layout of one system looks up none
+    const int g = blockIdx.x, k0 = group_start[g], k1 = group_start[g + 1];
+    if (g >= *n_groups) return;
+    const int nb = k1 - k0;
+    const int sys = one_sys ? 0 : sys_of[members[k0]];
+    const double ms = mstar[sys];
+    if (pm.group && lane == 0) pm.group_sys[g] = sys;
+    if (nb > BS_LANES && big_groups) return;       // integrated by the grid-wide path
+    if (nb > CP_MEM && nb <= BS_LANES) return;     // a workgroup of drift_wg_kernel integrates it
+    sun_shift_of(pm, mstar, sys, sh);
+    p[0] = p[1] = p[2] = 0.0;
+    if (nb > BS_LANES) {
+        // larger than one wave: Kepler-drift the members instead and flag it
+        if (lane == 0) atomicOr(flags, FLAG_CAPACITY);
+        for (int k = lane; k < nb; k += BS_LANES) {
+            const int b = members[k0 + k];
             double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
-            ok = bs_columns<LV>(me, k, S, (double(*)[BS_KMAX][CP_MEM][6])tab, Y, dt, 1e-12);
-            // every lane has read its member's state before the first force evaluation's barrier
-            if (me.act && k == 0) {
-                store_state(x, y, z, vx, vy, vz, b, Y);
-                for (int q = 0; q < 3; ++q) p[q] = S.m[ai] * Y[3 + q];
-            }
+            if (!kepler_universal(Y[0], Y[1], Y[2], Y[3], Y[4], Y[5], ms, dt)) atomicOr(flags, FLAG_KEPLER);
+            store_state(x, y, z, vx, vy, vz, b, Y);
+            for (int q = 0; q < 3; ++q) p[q] += m[b] * Y[3 + q];
         }
-        if (!ok && lane == 0) atomicOr(flags, FLAG_NOCONVERGE);
         if (pm.group) store_momentum(pm.group, g, p);
+        return;
     }
+    if (lane < nb) {
+        const int b = members[k0 + lane];
+        S.m[lane] = m[b];
+        S.i09[lane] = 1.0 / (0.9 * rc[b]);
+        S.test[lane] = b - sys_off[sys] >= n_massive[sys];
+        if constexpr (LV)
+            for (int l = 1; l < nlev; ++l) S.i9l[l - 1][lane] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
+    }
+    if (lane == 0) S.nlev = nlev;
+    __syncthreads();
+    bool ok;
+    if (nb <= 3) {
+        double *lag = tab + BS_KMAX * 3 * 6;
+        ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt, sh, p)
+                     : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt, sh, p);
+    } else {
+        const int k = lane / CP_MEM;
+        BsMember me;
+        me.a = lane % CP_MEM;
+        me.nb = nb;
+        me.base = k * CP_MEM;
+        me.act = me.a < nb;
+        const int ai = me.act ? me.a : 0;
+        me.test = S.test[ai] != 0;
+        me.mstar = ms;
+        me.i09 = S.i09[ai];
+        const int b = members[k0 + ai];
+        double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
+        ok = bs_columns<LV>(me, k, S, (double(*)[BS_KMAX][CP_MEM][6])tab, Y, dt, 1e-12);
+        // every lane has read its member's state before the first force evaluation's barrier
+        if (me.act && k == 0) {
+            store_state(x, y, z, vx, vy, vz, b, Y);
+            for (int q = 0; q < 3; ++q) p[q] = S.m[ai] * Y[3 + q];
+        }
+    }
+    if (!ok && lane == 0) atomicOr(flags, FLAG_NOCONVERGE);
+    if (pm.group) store_momentum(pm.group, g, p);
 }
 
 __global__ __launch_bounds__(CE_THREADS) void wg_list_kernel(const int32_t *group_start, const int32_t *n_groups,
@@ -1575,10 +1603,9 @@ __global__ __launch_bounds__(WG_THREADS) void drift_wg_kernel(const int32_t *sys
         __syncthreads(); // the previous group's LDS is no longer read
         if (k == 0 && part == 0 && a < nb) {
             const int b = members[k0 + a];
-            const int sb = sys_of[b];
             S.m[a] = m[b];
             S.i09[a] = 1.0 / (0.9 * rc[b]);
-            S.test[a] = b - sys_off[sb] >= n_massive[sb];
+            S.test[a] = b - sys_off[sys] >= n_massive[sys];
             if constexpr (LV)
                 for (int l = 1; l < nlev; ++l) S.i9l[l - 1][a] = 1.0 / (0.9 * rc_lv[(size_t)(l - 1) * n_total + b]);
         }
@@ -1691,12 +1718,11 @@ hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream)
     return hipGetLastError();
 }
 
-hipError_t launch_kick_close(const Layout &L, const KickArgs &a, double *x, double *y, double *z,
-                             const StepMomentum &pm, const int32_t *item_first, const GroupBuild *groups,
-                             hipStream_t stream)
+hipError_t launch_kick_close(const KickArgs &a, double *x, double *y, double *z, const StepMomentum &pm,
+                             const GroupBuild *groups, hipStream_t stream)
 {
-    kick_close_kernel<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(a, x, y, z, L.mstar, pm, item_first,
-                                                                  groups ? *groups : GroupBuild{}, groups != nullptr);
+    kick_close_kernel<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(a, x, y, z, pm, groups ? *groups : GroupBuild{},
+                                                                  groups != nullptr);
     return hipGetLastError();
 }
 
@@ -1711,10 +1737,9 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
     const StepMomentum pm = pm_in ? *pm_in : StepMomentum{};
     // groups have at least 2 members, so the one-workgroup builder makes at most half its
     // members; bs_blocks < 0: no group blocks (the groups are integrated elsewhere), only the
-    // Kepler drift of non-members.  2048 blocks (two waves per SIMD) walk the groups.
+    // Kepler drift of non-members.
     if (bs_blocks == 0) bs_blocks = CE_MAX_MEMBERS / 2;
     if (bs_blocks < 0) bs_blocks = 0;
-    bs_blocks = std::min(bs_blocks, 2048);
     const int grid = bs_blocks + (kepler ? n_items : 0);
     if (grid == 0) return hipSuccess;
     auto kern = nlev > 1 ? drift_kernel<true> : drift_kernel<false>;
@@ -1741,7 +1766,7 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
     }
     kern<<<grid, BS_LANES, 0, stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, items, L.n_total, x, y, z, vx, vy, vz,
                                         m, rc, dt, members, group_start, n_groups, member_slot, flags, big_groups,
-                                        bs_blocks, rc_lv, nlev, pm);
+                                        bs_blocks, rc_lv, nlev, pm, L.n_sys == 1);
     if (bs_blocks > 0 && !fork)
         wg<<<wg_grid, WG_THREADS, 0, stream>>>(L.sys_of, L.sys_off, L.n_massive, L.mstar, L.n_total, x, y, z, vx, vy, vz,
                                                m, rc, dt, members, group_start, wg_list, flags, rc_lv, nlev, pm);

@@ -64,10 +64,12 @@ struct genga_ctx {
     std::vector<int32_t> n_massive_h; // per system; bodies beyond are TP2 test bodies
     size_t max_items = 0;
     // launch plan
-    WorkItem *items = nullptr;  // kick and energy items, in system order
+    WorkItem *items = nullptr;  // kick items, in system order
     int32_t n_items = 0;
-    int32_t *item_first = nullptr;
-    int4 *tasks = nullptr;      // the layout's own kick plan: (item, first source, end, 0)
+    EnergyTask *etasks = nullptr; // energy tasks, in system order
+    int32_t *etask_first = nullptr; // [n_sys + 1]
+    int32_t n_etasks = 0;
+    KickTask *tasks = nullptr;  // the layout's own kick plan
     int32_t *task_first = nullptr; // [n_items + 1] an item's tasks
     int32_t n_tasks = 0;
     int waves[2] = {0, 0};      // [prec] waves per workgroup of the kick (0: default_kick_waves)
@@ -235,7 +237,8 @@ struct genga_ctx {
         dfree(L.sys_of);
         dfree(L.mstar);
         dfree(items);
-        dfree(item_first);
+        dfree(etasks);
+        dfree(etask_first);
         dfree(tasks);
         dfree(task_first);
         dfree(close_blocks);
@@ -953,8 +956,8 @@ int enqueue_energy(genga_ctx *ctx, const genga_bodies *b, double vshift, double 
 {
     const Layout &L = ctx->L;
     const size_t n = (size_t)L.n_total;
-    HIP_TRY(launch_energy(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, ctx->acc,
-                          ctx->acc + n, ctx->acc + 2 * n, vshift, ctx->epartial, ctx->item_first, out, s));
+    HIP_TRY(launch_energy(L, ctx->etasks, ctx->n_etasks, ctx->etask_first, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m,
+                          ctx->acc, ctx->acc + n, ctx->acc + 2 * n, vshift, ctx->epartial, out, s));
     return GENGA_OK;
 }
 
@@ -983,7 +986,7 @@ int enqueue_step_kick(genga_ctx *ctx, genga_bodies *b, double tau, int prec, int
     StepMomentum pm = ctx->pm;
     pm.tau = shift_tau;
     const GroupBuild g = group_build(ctx);
-    HIP_TRY(launch_kick_close(L, a, b->x, b->y, b->z, pm, ctx->item_first, groups ? &g : nullptr, s));
+    HIP_TRY(launch_kick_close(a, b->x, b->y, b->z, pm, groups ? &g : nullptr, s));
     return GENGA_OK;
 }
 
@@ -1080,13 +1083,17 @@ int upload_plan(genga_ctx *ctx)
     if (it.size() > ctx->max_items) return fail(GENGA_ERR_STATE, "work plan larger than its allocation");
     for (const WorkItem &w : it) visits += w.nsrc;
     const int len = kick_run_len(visits, ctx->n_cu);
-    std::vector<int4> tasks;
+    std::vector<KickTask> tasks;
+    std::vector<int32_t> cfst(n_sys + 1, 0); // chunks of each system, as genga_set_systems lays them out
+    for (int s = 0; s < n_sys; ++s)
+        cfst[s + 1] = cfst[s] + (ctx->sys_off_h[s + 1] - ctx->sys_off_h[s] + CHUNK - 1) / CHUNK;
     std::vector<int32_t> tfirst(it.size() + 1, 0);
     for (size_t k = 0; k < it.size(); ++k) {
         const int parts = kick_runs(it[k].nsrc, len), per = kick_run(it[k].nsrc, parts);
-        const int b = ctx->sys_off_h[it[k].sys], e = b + it[k].nsrc;
+        const int sy = it[k].sys, b = ctx->sys_off_h[sy], e = b + it[k].nsrc;
         for (int p = 0; p < parts; ++p)
-            tasks.push_back(make_int4((int)k, std::min(b + p * per, e), std::min(b + (p + 1) * per, e), 0));
+            tasks.push_back(KickTask{sy, it[k].i0, it[k].ni, std::min(b + p * per, e), std::min(b + (p + 1) * per, e),
+                                     cfst[sy], cfst[sy + 1], b});
         tfirst[k + 1] = (int32_t)tasks.size();
     }
     ctx->n_items = (int32_t)it.size();
@@ -1096,16 +1103,18 @@ int upload_plan(genga_ctx *ctx)
     HIP_TRY(dalloc(ctx->kpart, 192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size())));
     if (!it.empty()) {
         HIP_TRY(hipMemcpy(ctx->items, it.data(), it.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(ctx->tasks, tasks.data(), tasks.size() * sizeof(int4), hipMemcpyHostToDevice));
+        HIP_TRY(hipMemcpy(ctx->tasks, tasks.data(), tasks.size() * sizeof(KickTask), hipMemcpyHostToDevice));
     }
     HIP_TRY(hipMemcpy(ctx->task_first, tfirst.data(), tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     // blocks of items of one system, for the end of a step's kick
     std::vector<CloseBlock> cb;
     std::vector<int32_t> cfirst(n_sys + 1, 0);
+    ctx->pm.parts = close_parts(ctx->n_items, ctx->n_cu);
+    const int citems = CLOSE_WAVES / ctx->pm.parts;
     for (int s = 0; s < n_sys; ++s) {
         cfirst[s] = (int32_t)cb.size();
-        for (int k = first[s]; k < first[s + 1]; k += CLOSE_ITEMS)
-            cb.push_back(CloseBlock{s, k, std::min(CLOSE_ITEMS, first[s + 1] - k), 0});
+        for (int k = first[s]; k < first[s + 1]; k += citems)
+            cb.push_back(CloseBlock{s, k, std::min(citems, first[s + 1] - k), first[s], first[s + 1], ctx->mstar_h[s]});
     }
     cfirst[n_sys] = (int32_t)cb.size();
     HIP_TRY(dalloc(ctx->close_blocks, cb.size()));
@@ -1121,7 +1130,32 @@ int upload_plan(genga_ctx *ctx)
     ctx->pm.blocks = ctx->close_blocks;
     ctx->pm.block_first = ctx->close_first;
     ctx->pm.n_blocks = (int32_t)cb.size();
-    HIP_TRY(hipMemcpy(ctx->item_first, first.data(), (n_sys + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
+    // energy tasks: the sources after an item's first body (a test item has none: test pairs have
+    // no energy), in runs as the kick's
+    std::vector<EnergyTask> et;
+    std::vector<int32_t> efirst(2 * n_sys + 1, 0);
+    const auto energy_end = [&](const WorkItem &w) { return std::max(ctx->sys_off_h[w.sys] + w.nsrc, w.i0); };
+    visits = 0;
+    for (const WorkItem &w : it) visits += energy_end(w) - w.i0;
+    const int elen = kick_run_len(visits, ctx->n_cu);
+    for (int s = 0; s < n_sys; ++s) {
+        for (const bool head : {true, false}) { // the items' first tasks, then the others
+            efirst[2 * s + !head] = (int32_t)et.size();
+            for (int k = first[s]; k < first[s + 1]; ++k) {
+                const WorkItem &w = it[k];
+                const int e = energy_end(w), parts = kick_runs(e - w.i0, elen), per = kick_run(e - w.i0, parts);
+                for (int p = head ? 0 : 1; p < (head ? 1 : parts); ++p)
+                    et.push_back(EnergyTask{s, w.i0, w.ni, std::min(w.i0 + p * per, e), std::min(w.i0 + (p + 1) * per, e), head});
+            }
+        }
+    }
+    efirst[2 * n_sys] = (int32_t)et.size();
+    ctx->n_etasks = (int32_t)et.size();
+    HIP_TRY(dalloc(ctx->etasks, et.size()));
+    HIP_TRY(dalloc(ctx->etask_first, efirst.size()));
+    HIP_TRY(dalloc(ctx->epartial, 9 * et.size()));
+    if (!et.empty()) HIP_TRY(hipMemcpy(ctx->etasks, et.data(), et.size() * sizeof(EnergyTask), hipMemcpyHostToDevice));
+    HIP_TRY(hipMemcpy(ctx->etask_first, efirst.data(), efirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     HIP_TRY(hipMemcpy(ctx->L.n_massive, ctx->n_massive_h.data(), n_sys * sizeof(int32_t), hipMemcpyHostToDevice));
     std::vector<int32_t> seg(2 * (size_t)n_sys + 1);
     for (int s = 0; s < n_sys; ++s) {
@@ -1207,6 +1241,8 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     // work items: 64 consecutive bodies of one system
     std::vector<Chunk> chunks;
     std::vector<int32_t> cfirst(n_sys + 1, 0);
+    ctx->pm.parts = close_parts(ctx->n_items, ctx->n_cu);
+    const int citems = CLOSE_WAVES / ctx->pm.parts;
     for (int s = 0; s < n_sys; ++s) {
         cfirst[s] = (int32_t)chunks.size();
         for (int b = sys_off_host[s]; b < sys_off_host[s + 1]; b += CHUNK)
@@ -1232,7 +1268,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     for (int s = 0; s < n_sys; ++s) max_items += (size_t)(sys_off_host[s + 1] - sys_off_host[s] + 63) / 64 + 1;
     ctx->max_items = max_items;
     HIP_TRY(dalloc(ctx->items, max_items));
-    HIP_TRY(dalloc(ctx->item_first, n_sys + 1));
     HIP_TRY(dalloc(ctx->L.n_massive, n_sys));
     HIP_TRY(dalloc(ctx->m32, nt));
     HIP_TRY(dalloc(ctx->chunk_mass, chunks.size()));
@@ -1253,7 +1288,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     HIP_TRY(dalloc(ctx->n_groups, 1));
     HIP_TRY(dalloc(ctx->member_slot, nt));
     HIP_TRY(dalloc(ctx->wg_list, (size_t)std::max(ctx->ce_cap, n_total) / 2 + 2));
-    HIP_TRY(dalloc(ctx->epartial, 9 * (size_t)ENERGY_SPLIT * max_items));
     HIP_TRY(dalloc(ctx->import_bad, 1));
     HIP_TRY(hipMemset(ctx->import_bad, 0, sizeof(int32_t)));
     HIP_TRY(order_work_alloc(ctx->sw, std::max(n_total, 2 * n_sys)));

@@ -52,6 +52,14 @@ struct Layout {
     int32_t *n_massive = nullptr;   // device [n_sys]: bodies [off, off + n_massive) are massive
 };
 
+// A task of the kick's own plan: the item's targets and a run of its sources, with what the kick
+// would otherwise look up one load after another.
+struct KickTask {
+    int32_t sys, i0, ni, j0, j1;
+    int32_t c0, c1; // the system's chunks
+    int32_t off;    // the system's first body
+};
+
 struct KickArgs {
     const WorkItem *items;
     int32_t n_items;
@@ -70,8 +78,8 @@ struct KickArgs {
     int32_t *pair_count;
     int32_t pair_cap;
     int32_t *flags;
-    const int4 *tasks;            // [n_tasks] (item, first source, end, -), items in order; null: every
-                                  //   item's sources in `split` runs, task = item * split + run
+    const KickTask *tasks;        // [n_tasks], items in order; null: every item's sources in `split`
+                                  //   runs, task = item * split + run
     const int32_t *task_first;    // [n_items + 1] an item's tasks (with tasks)
     int32_t n_tasks;
     int32_t split;
@@ -80,10 +88,21 @@ struct KickArgs {
     const int32_t *status;        // with collisions: bodies with status != 0 are in no pair
 };
 
-// A run of at most CLOSE_ITEMS items of one system: a workgroup of launch_kick_close.
-constexpr int CLOSE_ITEMS = 16;
+// A run of items of one system: a workgroup of launch_kick_close, of CLOSE_WAVES waves.  Each item
+// takes four waves, two or one, the most with which the blocks fit one per CU: 40000 bodies (625
+// items of 20 tasks) take 13 us with four and 18 with one, 64 systems of 4096 (4096 items of one
+// task) 21 with one and 39 with four.
+constexpr int CLOSE_WAVES = 16;
+inline int close_parts(int n_items, int n_cu)
+{
+    int p = 4;
+    while (p > 1 && (int64_t)n_items * p > (int64_t)CLOSE_WAVES * n_cu) p /= 2;
+    return p;
+}
 struct CloseBlock {
-    int32_t sys, item, n, pad; // items [item, item + n)
+    int32_t sys, item, n; // items [item, item + n)
+    int32_t f0, f1;       // the system's items
+    double mstar;
 };
 
 // Momentum sums that the launches of a step hand on to each other instead of passes of their own.
@@ -91,6 +110,7 @@ struct StepMomentum {
     const CloseBlock *blocks = nullptr;  // [n_blocks], systems in order
     const int32_t *block_first = nullptr; // [n_sys + 1]
     int32_t n_blocks = 0;
+    int32_t parts = 1;                   // waves per item
     double *kick = nullptr;    // [n_blocks][3] sum m v after the kick
     double *kepler = nullptr;  // [n_items][3] sum m v after the drift, bodies outside groups
     double *group = nullptr;   // [CE_MAX_MEMBERS / 2][3] the same of the groups, which are in system order
@@ -154,7 +174,12 @@ inline int default_kick_waves(int n_items, int n_tasks, int n_cu)
 // Address of the allocation-free entry point's scratch array on `device` (looked up once).
 int noalloc_prepare(int device, unsigned char **ptr_out, int *n_cu_out);
 
-constexpr int ENERGY_SPLIT = 4;   // workgroups sharing one item's sources in the energy sum
+// A task of the energy's pair sum: an item's targets and sources [j0, j1) of those after its first
+// body; the item's first task also sums its kinetic parts.  The tasks of system s are
+// [task_first[2 s], task_first[2 s + 2]), first tasks up to task_first[2 s + 1].
+struct EnergyTask {
+    int32_t sys, i0, ni, j0, j1, first;
+};
 
 // Kernel launchers (each enqueues on `stream`; return hipError_t of the launch).
 // What the kick takes per chunk (r_crit^2 maxima, common masses), the masses in FP32 (m32 may be
@@ -178,9 +203,8 @@ hipError_t launch_kick_shares(const KickArgs &a, int fp32, int kahan, int waves,
 // second half of the preceding drift's Sun drift (from pm.kepler and pm.group); then the sums of
 // m v into pm.kick; and, from a workgroup of its own, with groups != null the encounter groups
 // of the kick's pairs.
-hipError_t launch_kick_close(const Layout &L, const KickArgs &a, double *x, double *y, double *z,
-                             const StepMomentum &pm, const int32_t *item_first, const GroupBuild *groups,
-                             hipStream_t stream);
+hipError_t launch_kick_close(const KickArgs &a, double *x, double *y, double *z, const StepMomentum &pm,
+                             const GroupBuild *groups, hipStream_t stream);
 // The encounter pairs of the state only (no forces, nothing written but a.pairs / a.pair_count).
 hipError_t launch_pair_list(const KickArgs &a, hipStream_t stream);
 hipError_t launch_rcrit(const Layout &L, const double *x, const double *y, const double *z,
@@ -461,11 +485,10 @@ hipError_t launch_collide_resolve(const CollideArgs &c, int n_total, double *x, 
 hipError_t launch_gather(const int32_t *idx, int n, const double *src, double *dst, hipStream_t stream);
 hipError_t launch_gather(const int32_t *idx, int n, const int32_t *src, int32_t *dst, hipStream_t stream);
 
-hipError_t launch_energy(const Layout &L, const WorkItem *items, int32_t n_items, const double *x,
-                         const double *y, const double *z, const double *vx, const double *vy,
-                         const double *vz, const double *m, const double *ax, const double *ay,
-                         const double *az, double vshift, double *partial,
-                         const int32_t *item_first, double *out, hipStream_t stream);
+hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tasks, const int32_t *task_first,
+                         const double *x, const double *y, const double *z, const double *vx, const double *vy,
+                         const double *vz, const double *m, const double *ax, const double *ay, const double *az,
+                         double vshift, double *partial, double *out, hipStream_t stream);
 // A caller's pair list src[min(*src_count, cap)][2] checked (0 <= i < j < n_total, one system)
 // and copied to dst; *dst_count = *src_count, or 0 with FLAG_BADPAIR when a pair is invalid
 // (bad: a device word, zero on entry and left zero).

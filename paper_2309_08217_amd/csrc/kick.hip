@@ -151,47 +151,40 @@ __device__ __forceinline__ void near_block(const KickArgs &a, int jb, uint32_t m
     }
 }
 
-// What a task visits: its targets and sources [j0, j1).  With a task list (KickArgs::tasks) the
-// runs were laid out on the host; else every item's sources are cut into a.split runs.
-struct Task {
-    int sys, i0, ni, j0, j1;
-};
-
-__device__ __forceinline__ Task task_of(const KickArgs &a, int t)
+// What a task visits.  With a task list (KickArgs::tasks) the runs were laid out on the host; else
+// every item's sources are cut into a.split runs.
+__device__ __forceinline__ KickTask task_of(const KickArgs &a, int t)
 {
-    Task k;
-    if (a.tasks) {
-        const int4 e = a.tasks[t];
-        const WorkItem w = a.items[e.x];
-        k = Task{w.sys, w.i0, w.ni, e.y, e.z};
-    } else {
-        const WorkItem w = a.items[t / a.split];
-        const int part = t % a.split, b = a.sys_off[w.sys], e = b + w.nsrc;
-        const int per = kick_run(w.nsrc, a.split);
-        k.sys = w.sys;
-        k.i0 = w.i0;
-        k.ni = w.ni;
-        k.j0 = min(b + part * per, e);
-        k.j1 = min(k.j0 + per, e);
-    }
+    if (a.tasks) return a.tasks[t];
+    const WorkItem w = a.items[t / a.split];
+    const int part = t % a.split, b = a.sys_off[w.sys], e = b + w.nsrc;
+    const int per = kick_run(w.nsrc, a.split);
+    KickTask k;
+    k.sys = w.sys;
+    k.i0 = w.i0;
+    k.ni = w.ni;
+    k.j0 = min(b + part * per, e);
+    k.j1 = min(k.j0 + per, e);
+    k.c0 = a.chunk_first[w.sys];
+    k.c1 = a.chunk_first[w.sys + 1];
+    k.off = b;
     return k;
 }
 
-// largest r_crit^2 of system s, the chunks over the lanes
-__device__ __forceinline__ double system_rc2max(const KickArgs &a, int s)
+// largest r_crit^2 of the task's system, the chunks over the lanes
+__device__ __forceinline__ double system_rc2max(const KickArgs &a, const KickTask &t)
 {
     double mx = 0.0;
-    for (int k = a.chunk_first[s] + (int)(threadIdx.x & 63); k < a.chunk_first[s + 1]; k += 64)
+    for (int k = t.c0 + (int)(threadIdx.x & 63); k < t.c1; k += 64)
         mx = fmax(mx, a.rc2_part[k]);
     return wave_maxv(mx);
 }
 
-// The mass that all sources [j0, j1) of system s share, or NaN: from the chunks' common masses.
-__device__ __forceinline__ double common_mass(const KickArgs &a, int s, int j0, int j1)
+// The mass that all sources [j0, j1) of the task share, or NaN: from the chunks' common masses.
+__device__ __forceinline__ double common_mass(const KickArgs &a, const KickTask &t, int j0, int j1)
 {
     if (j0 >= j1) return 0.0;
-    const int c0 = a.chunk_first[s], b = a.sys_off[s];
-    const int k0 = c0 + (j0 - b) / CHUNK, k1 = c0 + (j1 - 1 - b) / CHUNK;
+    const int k0 = t.c0 + (j0 - t.off) / CHUNK, k1 = t.c0 + (j1 - 1 - t.off) / CHUNK;
     const double m = a.chunk_mass[k0];
     bool same = true;
     for (int k = k0 + (int)(threadIdx.x & 63); k <= k1; k += 64) same = same && a.chunk_mass[k] == m;
@@ -421,7 +414,7 @@ __device__ __forceinline__ void run64(const KickArgs &a, int jb, int je, int i, 
 
 // The wave's share of a task's sources.
 template <int W>
-__device__ __forceinline__ void wave_run(const Task &t, int wave, int &jb, int &je)
+__device__ __forceinline__ void wave_run(const KickTask &t, int wave, int &jb, int &je)
 {
     const int chunk = (t.j1 - t.j0 + W - 1) / W;
     jb = __builtin_amdgcn_readfirstlane(min(t.j0 + wave * chunk, t.j1));
@@ -439,17 +432,17 @@ __global__ __launch_bounds__(64 * W) void kick32_kernel(KickArgs a)
     const PairBuf pb{pair_slots[wave], &pair_fill[wave]};
     pair_fill[wave] = 0;
     wave_lds_sync();
-    const Task t = task_of(a, blockIdx.x);
+    const KickTask t = task_of(a, blockIdx.x);
     const bool valid = lane < t.ni;
     const int i = t.i0 + (valid ? lane : 0);
     const double xi = a.x[i], yi = a.y[i], zi = a.z[i], rci = a.rc[i];
     // candidate threshold: the system's largest r_crit^2 with a margin that covers the FP32
     // rounding of r^2; never zero, so that the self pair is always marked
-    const float T = (float)(system_rc2max(a, t.sys) * 1.0001) + 1e-24f;
+    const float T = (float)(system_rc2max(a, t) * 1.0001) + 1e-24f;
     int jb, je;
     wave_run<W>(t, wave, jb, je);
     double sx = 0.0, sy = 0.0, sz = 0.0;
-    const double mass = common_mass(a, t.sys, jb, je);
+    const double mass = common_mass(a, t, jb, je);
     if (mass == mass)
         run32<KAHAN, true>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     else
@@ -470,17 +463,17 @@ __global__ __launch_bounds__(64 * W) void kick64_kernel(KickArgs a)
     const PairBuf pb{pair_slots[wave], &pair_fill[wave]};
     pair_fill[wave] = 0;
     wave_lds_sync();
-    const Task t = task_of(a, blockIdx.x);
+    const KickTask t = task_of(a, blockIdx.x);
     const bool valid = lane < t.ni;
     const int i = t.i0 + (valid ? lane : 0);
     const double xi = a.x[i], yi = a.y[i], zi = a.z[i], rci = a.rc[i];
     // candidate threshold with a relative margin: q is formed with fused multiply-adds, the
     // exact decision without them
-    const double T = system_rc2max(a, t.sys) * (1.0 + 1e-12) + 1e-300;
+    const double T = system_rc2max(a, t) * (1.0 + 1e-12) + 1e-300;
     int jb, je;
     wave_run<W>(t, wave, jb, je);
     double sx = 0.0, sy = 0.0, sz = 0.0;
-    const double mass = LIST ? 0.0 : common_mass(a, t.sys, jb, je);
+    const double mass = LIST ? 0.0 : common_mass(a, t, jb, je);
     if (mass == mass)
         run64<true, LIST>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     else

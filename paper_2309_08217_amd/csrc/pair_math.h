@@ -144,10 +144,16 @@ __device__ __forceinline__ void store_accel(const KickArgs &a, int i, double tx,
     }
 }
 
-// The tasks' shares of body `lane` of item `it`, added in task order.
-__device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane, double t[3])
+// The tasks' shares of body `lane` of item `it`, added in task order; with parts > 1 those of part
+// `part` of its tasks.
+__device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane, double t[3], int part = 0, int parts = 1)
 {
-    const int t0 = a.tasks ? a.task_first[it] : it * a.split, t1 = a.tasks ? a.task_first[it + 1] : t0 + a.split;
+    int t0 = a.tasks ? a.task_first[it] : it * a.split, t1 = a.tasks ? a.task_first[it + 1] : t0 + a.split;
+    if (parts > 1) {
+        const int n = t1 - t0, b = t0;
+        t0 = b + n * part / parts;
+        t1 = b + n * (part + 1) / parts;
+    }
     t[0] = t[1] = t[2] = 0.0;
     const double *p = a.part + (size_t)t0 * 192 + lane;
     int k = t0;
@@ -159,6 +165,17 @@ __device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane,
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             for (int q = 0; q < 3; ++q) t[q] += v[u][q];
+    }
+    if (k + 4 <= t1) {
+        double v[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int q = 0; q < 3; ++q) v[u][q] = p[u * 192 + 64 * q];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int q = 0; q < 3; ++q) t[q] += v[u][q];
+        k += 4;
+        p += 4 * 192;
     }
     for (; k < t1; ++k, p += 192)
         for (int q = 0; q < 3; ++q) t[q] += p[64 * q];

@@ -108,7 +108,7 @@ int genga_set_test_bodies(genga_ctx *ctx, const int32_t *n_massive_host);
  * layout may be in an encounter group; one group holds at most 65536 bodies.  A larger group
  * makes genga_drift return GENGA_ERR_CAPACITY before it enqueues anything (genga_step: with
  * the bodies left after its last kick).
- * Allocates about 8 KB of device memory per body of the layout, resized by
+ * Allocates about 4 KB of device memory per body of the layout, resized by
  * genga_set_systems; the switch itself is kept across genga_set_systems.  Synchronises the
  * device. */
 int genga_set_large_groups(genga_ctx *ctx, int32_t enable);

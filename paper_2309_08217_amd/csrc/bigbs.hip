@@ -435,8 +435,7 @@ __device__ __forceinline__ ListMember list_member(double skin, double ms, double
 // Start of an attempt on the list path, one wave per tile: the positions of Y as source records,
 // the group's position and velocity scales (max |r|, max |v|: one atomic per workgroup whose
 // tiles share a group, as 631 tiles' atomics on one address took 10 us), and, unless the lists
-// still hold, the box swept by the tile's straight lines over [0, H] and the largest
-// S + |A| H^2 / 2 of its members.
+// still hold, the tile's boxes in position, velocity and A and the largest S of its members.
 __global__ __launch_bounds__(GB_THREADS) void big_prepare_kernel(BigBs b)
 {
     constexpr int NW = GB_THREADS / 64;
@@ -484,7 +483,6 @@ __global__ __launch_bounds__(GB_THREADS) void big_prepare_kernel(BigBs b)
             }
         }
         if (on && !b.keep[g]) {
-            const double x1 = fma(u, H, x), y1 = fma(vy, H, y), z1 = fma(w, H, z);
             double sk = 2.0;
             if (v) {
                 const int body = b.body[f];
@@ -497,210 +495,245 @@ __global__ __launch_bounds__(GB_THREADS) void big_prepare_kernel(BigBs b)
             }
             const ListMember lm = list_member(sk, b.mstar[g], H, x, y, z, u, vy, w, v ? b.amut[f] : 0.0);
             if (v) b.pred[f] = make_double4(lm.ax, lm.ay, lm.az, lm.s);
-            const double lo[3] = {wave_minv(v ? fmin(x, x1) : INFINITY), wave_minv(v ? fmin(y, y1) : INFINITY),
-                                  wave_minv(v ? fmin(z, z1) : INFINITY)};
-            const double hi[3] = {wave_maxv(v ? fmax(x, x1) : -INFINITY), wave_maxv(v ? fmax(y, y1) : -INFINITY),
-                                  wave_maxv(v ? fmax(z, z1) : -INFINITY)};
-            const double ext = wave_maxv(v ? lm.s + 0.5 * sqrt(sep2_rn(lm.ax, lm.ay, lm.az)) * H * H : 0.0);
-            if (lane < 3) {
-                b.sbb[me * 8 + lane] = lo[lane];
-                b.sbb[me * 8 + 3 + lane] = hi[lane];
+            const double c[9] = {x, y, z, u, vy, w, lm.ax, lm.ay, lm.az};
+            double lo[9], hi[9];
+#pragma unroll
+            for (int q = 0; q < 9; ++q) {
+                lo[q] = v ? c[q] : INFINITY;
+                hi[q] = v ? c[q] : -INFINITY;
             }
-            if (lane == 0) b.sbb[me * 8 + 6] = ext;
+            double ext = v ? lm.s : 0.0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    lo[q] = fmin(lo[q], __shfl_xor(lo[q], off, 64));
+                    hi[q] = fmax(hi[q], __shfl_xor(hi[q], off, 64));
+                }
+                ext = fmax(ext, __shfl_xor(ext, off, 64));
+            }
+            double *B = b.sbb + (size_t)me * BIG_BOX;
+            if (lane == 0) {
+#pragma unroll
+                for (int q = 0; q < 9; ++q) {
+                    B[q] = lo[q];
+                    B[9 + q] = hi[q];
+                }
+                B[18] = ext;
+            }
         }
         __syncthreads(); // red is rewritten by the next tiles
     }
 }
 
-// One source j for the target lane's list segment (wave-uniform j): listed when the straight
-// lines come within r = r_crit,ab + S_a + S_j + |A_a - A_j|_1 H^2 / 2 over [0, H] (the 1-norm
-// bounds the length of the difference).  The minimum of |d + v t|^2 over [0, H] is taken
-// without a division: at t = 0 when d.v >= 0, at t = H when -d.v >= |v|^2 H, else it is
-// |d|^2 - (d.v)^2 / |v|^2, compared as (|d|^2 - r^2) |v|^2 < (d.v)^2.
-__device__ __forceinline__ void list_source(const BigBs &b, bool valid, int fa, bool testa, double rfa,
-                                            double xa, double ya, double za, double ua, double va, double wa,
-                                            double4 pa, double H, int j, double xj, double yj, double zj, double uj,
-                                            double vj, double wj, double rj, bool testj, double4 pj, int32_t *row,
-                                            int &len, bool &over)
+// A body's words for the lists: the line from its state at the attempt's start, (A, S), the
+// deepest level's radius.
+struct ListBody {
+    double x, y, z, u, v, w, r;
+    double4 p;
+};
+
+// Whether the lines of target a and source j come within r = r_crit,ab + S_a + S_j
+// + |A_a - A_j|_1 H^2 / 2 over [0, H] (the 1-norm bounds the length of the difference).  The
+// minimum of |d + v t|^2 over [0, H] is taken without a division: at t = 0 when d.v >= 0, at t = H
+// when -d.v >= |v|^2 H, else it is |d|^2 - (d.v)^2 / |v|^2, compared as
+// (|d|^2 - r^2) |v|^2 < (d.v)^2.
+__device__ __forceinline__ bool list_close(const ListBody &a, const ListBody &j, double H)
 {
-    const double dx = xj - xa, dy = yj - ya, dz = zj - za;
-    const double du = uj - ua, dv = vj - va, dw = wj - wa;
+    const double dx = j.x - a.x, dy = j.y - a.y, dz = j.z - a.z;
+    const double du = j.u - a.u, dv = j.v - a.v, dw = j.w - a.w;
     const double dd = sep2_rn(dx, dy, dz), vv = sep2_rn(du, dv, dw);
     const double dp = (dx * du + dy * dv) + dz * dw;
-    const double r = fmax(rfa, rj) + pa.w + pj.w +
-                     0.5 * (fabs(pj.x - pa.x) + fabs(pj.y - pa.y) + fabs(pj.z - pa.z)) * (H * H);
+    const double r = fmax(a.r, j.r) + a.p.w + j.p.w +
+                     0.5 * (fabs(j.p.x - a.p.x) + fabs(j.p.y - a.p.y) + fabs(j.p.z - a.p.z)) * (H * H);
     // a margin of 2^-30 covers the rounding of the distance
     const double r2 = r * r * (1.0 + 0x1p-30);
-    bool close;
-    if (dp >= 0.0 || vv == 0.0) {
-        close = dd < r2;
-    } else if (-dp >= vv * H) {
-        close = sep2_rn(fma(du, H, dx), fma(dv, H, dy), fma(dw, H, dz)) < r2;
-    } else {
-        close = (dd - r2) * vv < dp * dp;
-    }
-    if (valid && close && j != fa && !(testa && testj)) {
-        if (len < BIG_LIST_SEG) row[len] = j;
-        else over = true;
-        ++len;
-    }
+    if (dp >= 0.0 || vv == 0.0) return dd < r2;
+    if (-dp >= vv * H) return sep2_rn(fma(du, H, dx), fma(dv, H, dy), fma(dw, H, dz)) < r2;
+    return (dd - r2) * vv < dp * dp;
 }
 
-// A segment of the lists of a target tile's members (one wave per tile and segment; segment s
-// takes the group's source tiles tt = s, s + BIG_LIST_SEGS, ...): the source tiles whose swept
-// boxes lie within the largest radius plus both tiles' largest extents, then their sources on
-// the straight lines, in quads whose words come through scalar loads.
-template <bool LV>
-__global__ __launch_bounds__(64) void big_list_kernel(BigBs b)
+// A component of the separation of what lies in box B from what lies in box A, over [0, H], when
+// both follow position + velocity t + A t^2 / 2: zero if the intervals meet, else their gap.
+// lo / hi: bounds in position (p), velocity (v) and A (w).
+__device__ __forceinline__ double gap_of(double alop, double ahip, double alov, double ahiv, double alow, double ahiw,
+                                         double blop, double bhip, double blov, double bhiv, double blow, double bhiw,
+                                         double H, double h2)
 {
+    const double lo = fma(fmin(blow - ahiw, 0.0), h2, fma(fmin(blov - ahiv, 0.0), H, blop - ahip));
+    const double hi = fma(fmax(bhiw - alow, 0.0), h2, fma(fmax(bhiv - alov, 0.0), H, bhip - alop));
+    return fmax(0.0, fmax(lo, -hi));
+}
+
+// The lists of a target tile's members, one workgroup of W waves per tile, in three passes that
+// each leave the next one little: the source tiles (a thread each) whose boxes come within the
+// largest radius and both largest S of the target tile's; of those, LIST_CAND at a time, the
+// sources (a lane each) that do; and these, four at a time per wave through scalar loads, against
+// the 64 members, as bits per member and tile in LDS.  The boxes bound the relative motion
+// (neighbours move together: boxes swept by either tile alone let three times the tiles through).
+// Then the source tiles with a bit become the tile's slots, in tile order (more than BIG_LIST_SLOTS
+// void the attempt and send the step to the tile path), and the bits the members' lists, in order,
+// as slot * 64 + the source's position in its tile.
+//
+// Bound by the arithmetic of the third pass (45 FP64 instructions a pair) on as many CUs as there
+// are target tiles.  With one wave per tile and eighth of the source tiles, and a second launch
+// that turned body lists into slot positions, 6600 bodies took 55 + 9 us an attempt and 40322
+// bodies 136 + 19 (mean over attempts); now 27 and 76.  W = 16 up to BIG_SIDE_TILES target tiles, where only more
+// waves per CU help; 8 beyond, two workgroups a CU.
+constexpr int LIST_CAND = 32;
+
+template <bool LV, int W>
+__global__ __launch_bounds__(64 * W) void big_list_kernel(BigBs b)
+{
+    static_assert(BIG_LIST_SLOTS * 64 <= 65536, "16-bit slot positions");
+    static_assert(LIST_CAND == 32 && LIST_CAND % W == 0, "a word of marks, whole shares per wave");
+    constexpr int SH = LIST_CAND / W; // candidate tiles per wave
+    __shared__ uint16_t cand[BIG_TILES_PER_GROUP];
+    __shared__ unsigned long long bits[LIST_CAND][64]; // sources of a candidate tile that a member lists
+    __shared__ uint16_t live[LIST_CAND * 64];          // (candidate, source) of the third pass
+    __shared__ int cnt[W][64];                         // a member's entries, by wave
+    __shared__ int wsum[W];
+    __shared__ uint32_t used;
     CD *YA = (CD *)b.Y;
-    CD *SB = (CD *)b.sbb;
-    CD *RC = (CD *)b.rc;
     CI *TS = (CI *)b.test;
-    CD *RL = (CD *)b.rcl;
     CD *PR = (CD *)b.pred; // (A, S) of member j at PR[4 j .. 4 j + 3]
-    for (int ms = blockIdx.x; ms < b.dims[2] * BIG_LIST_SEGS; ms += gridDim.x) {
-        const int me = ms / BIG_LIST_SEGS, seg = ms % BIG_LIST_SEGS;
-        const int4 tile = b.tiles[me];
-        const int g = tile.x;
-        if (b.done[g] || b.keep[g]) continue;
-        const size_t M = (size_t)b.dims[1];
-        const size_t lvo = LV ? (size_t)(b.nlev - 2) * b.cap_M : 0; // the deepest level's radii
-        const int lane = threadIdx.x;
-        const bool valid = lane < tile.z;
-        const int fa = tile.y + (valid ? lane : 0);
-        const int o = b.off[g], nb = b.off[g + 1] - o;
-        const int tf = b.tfirst[g], nt = b.tfirst[g + 1] - tf;
-        const double H = b.H[g];
-        const double xa = b.Y[fa], ya = b.Y[M + fa], za = b.Y[2 * M + fa];
-        const double ua = b.Y[3 * M + fa], va = b.Y[4 * M + fa], wa = b.Y[5 * M + fa];
-        const double4 pa = b.pred[fa];
-        const bool testa = b.test[fa] != 0;
-        const double rfa = LV ? b.rcl[lvo + fa] : b.rc[fa];
-        const double rmax = sqrt(b.rcmax2[g]);
-        const double tlx = SB[me * 8 + 0], tly = SB[me * 8 + 1], tlz = SB[me * 8 + 2];
-        const double thx = SB[me * 8 + 3], thy = SB[me * 8 + 4], thz = SB[me * 8 + 5], et = SB[me * 8 + 6];
-        int32_t *row = b.nl + (size_t)fa * BIG_LIST_CAP + seg * BIG_LIST_SEG;
-        int len = 0;
-        bool over = false;
-        for (int tt = seg; tt < nt; tt += BIG_LIST_SEGS) {
-            const int st = tf + tt;
-            const double gx = fmax(0.0, fmax(SB[st * 8 + 0] - thx, tlx - SB[st * 8 + 3]));
-            const double gy = fmax(0.0, fmax(SB[st * 8 + 1] - thy, tly - SB[st * 8 + 4]));
-            const double gz = fmax(0.0, fmax(SB[st * 8 + 2] - thz, tlz - SB[st * 8 + 5]));
-            const double cut = rmax + et + SB[st * 8 + 6];
-            if ((gx * gx + gy * gy) + gz * gz > cut * cut * (1.0 + 0x1p-30)) continue;
-            const int jb = o + 64 * tt, je = min(jb + 64, o + nb);
-            int j = jb;
-            for (; j + 4 <= je; j += 4) {
-                double X[4], Yv[4], Zv[4], U[4], V[4], W[4], R[4];
-                double4 Pj[4];
-                bool T[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    X[q] = YA[j + q];
-                    Yv[q] = YA[M + j + q];
-                    Zv[q] = YA[2 * M + j + q];
-                    U[q] = YA[3 * M + j + q];
-                    V[q] = YA[4 * M + j + q];
-                    W[q] = YA[5 * M + j + q];
-                    R[q] = LV ? RL[lvo + j + q] : RC[j + q];
-                    T[q] = TS[j + q] != 0;
-                    Pj[q] = make_double4(PR[4 * (j + q)], PR[4 * (j + q) + 1], PR[4 * (j + q) + 2],
-                                         PR[4 * (j + q) + 3]);
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    list_source(b, valid, fa, testa, rfa, xa, ya, za, ua, va, wa, pa, H, j + q, X[q], Yv[q], Zv[q],
-                                U[q], V[q], W[q], R[q], T[q], Pj[q], row, len, over);
-            }
-            for (; j < je; ++j)
-                list_source(b, valid, fa, testa, rfa, xa, ya, za, ua, va, wa, pa, H, j, YA[j], YA[M + j],
-                            YA[2 * M + j], YA[3 * M + j], YA[4 * M + j], YA[5 * M + j], LV ? RL[lvo + j] : RC[j],
-                            TS[j] != 0, make_double4(PR[4 * j], PR[4 * j + 1], PR[4 * j + 2], PR[4 * j + 3]),
-                            row, len, over);
+    const int me = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (me >= b.dims[2]) return;
+    const int4 tile = b.tiles[me];
+    const int g = tile.x;
+    if (b.done[g] || b.keep[g]) return; // the whole workgroup
+    const size_t M = (size_t)b.dims[1];
+    CD *RC = LV ? (CD *)(b.rcl + (size_t)(b.nlev - 2) * b.cap_M) : (CD *)b.rc; // the deepest level's radii
+    const int o = b.off[g], nb = b.off[g + 1] - o;
+    const int tf = b.tfirst[g], nt = b.tfirst[g + 1] - tf;
+    const double H = b.H[g], h2 = 0.5 * H * H;
+    CD *TB = (CD *)b.sbb + (size_t)me * BIG_BOX; // the target tile's boxes
+    const bool valid = lane < tile.z;
+    const int fa = tile.y + (valid ? lane : 0);
+    const ListBody A = {b.Y[fa], b.Y[M + fa], b.Y[2 * M + fa], b.Y[3 * M + fa], b.Y[4 * M + fa], b.Y[5 * M + fa],
+                        RC[fa], b.pred[fa]};
+    const bool testa = b.test[fa] != 0;
+    const double rmax = sqrt(b.rcmax2[g]) + TB[18];
+    const auto near = [&](const double *lo, const double *hi, double ext) {
+        double q = 0.0;
+        for (int c = 0; c < 3; ++c) {
+            const double gp = gap_of(TB[c], TB[9 + c], TB[3 + c], TB[12 + c], TB[6 + c], TB[15 + c], lo[c], hi[c],
+                                     lo[3 + c], hi[3 + c], lo[6 + c], hi[6 + c], H, h2);
+            q = fma(gp, gp, q);
         }
-        if (valid) b.nlen[(size_t)fa * BIG_LIST_SEGS + seg] = min(len, BIG_LIST_SEG);
-        if (__ballot(over) && lane == 0) {
+        const double cut = rmax + ext;
+        return !(q > cut * cut * (1.0 + 0x1p-30));
+    };
+    // the positions of this thread's item in the order of waves and lanes, and the number of all
+    const auto place = [&](bool is, int &n_all) {
+        const unsigned long long bal = __ballot(is);
+        if (lane == 0) wsum[wave] = __popcll(bal);
+        __syncthreads();
+        int pos = n_all + __popcll(bal & ((1ull << lane) - 1));
+        for (int w = 0; w < W; ++w) {
+            pos += w < wave ? wsum[w] : 0;
+            n_all += wsum[w];
+        }
+        __syncthreads(); // wsum is rewritten by the next call
+        return pos;
+    };
+    int n_cand = 0;
+    for (int t0 = 0; t0 < nt; t0 += 64 * W) {
+        const int tt = t0 + tid;
+        bool is = false;
+        if (tt < nt) {
+            const double *B = b.sbb + (size_t)(tf + tt) * BIG_BOX;
+            double w[19];
+            for (int q = 0; q < 19; ++q) w[q] = B[q];
+            is = near(w, w + 9, w[18]);
+        }
+        const int pos = place(is, n_cand);
+        if (is) cand[pos] = (uint16_t)tt;
+    }
+    __syncthreads();
+    int n_slots = 0, total = 0; // total: this lane's member's entries so far
+    uint16_t *out = b.ll + (size_t)fa * BIG_LIST_CAP;
+    for (int c0 = 0; c0 < n_cand; c0 += LIST_CAND) {
+        const int nc = min(LIST_CAND, n_cand - c0);
+        if (tid == 0) used = 0;
+        int n_live = 0;
+        for (int k = 0; k < SH; ++k) { // candidate k W + wave, source `lane`
+            const int c = k * W + wave;
+            bool is = false;
+            if (c < nc) {
+                bits[c][lane] = 0;
+                const int s = 64 * cand[c0 + c] + lane;
+                if (s < nb) {
+                    const int j = o + s;
+                    const double4 p = b.pred[j];
+                    const double w[9] = {b.Y[j], b.Y[M + j], b.Y[2 * M + j], b.Y[3 * M + j], b.Y[4 * M + j], b.Y[5 * M + j],
+                                         p.x, p.y, p.z};
+                    is = near(w, w, p.w);
+                }
+            }
+            const int pos = place(is, n_live);
+            if (is) live[pos] = (uint16_t)(c * 64 + lane);
+        }
+        __syncthreads();
+        for (int u = 4 * wave; u < n_live; u += 4 * W) {
+            int e[4], j[4];
+            ListBody S[4];
+            bool T[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) { // (the last quad repeats its last source)
+                e[q] = __builtin_amdgcn_readfirstlane(live[min(u + q, n_live - 1)]);
+                j[q] = o + 64 * __builtin_amdgcn_readfirstlane(cand[c0 + (e[q] >> 6)]) + (e[q] & 63);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int jq = j[q];
+                S[q] = {YA[jq], YA[M + jq], YA[2 * M + jq], YA[3 * M + jq], YA[4 * M + jq], YA[5 * M + jq], RC[jq],
+                        make_double4(PR[4 * jq], PR[4 * jq + 1], PR[4 * jq + 2], PR[4 * jq + 3])};
+                T[q] = TS[jq] != 0;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (valid && list_close(A, S[q], H) && j[q] != fa && !(testa && T[q]))
+                    atomicOr(&bits[e[q] >> 6][lane], 1ull << (e[q] & 63));
+        }
+        __syncthreads();
+        // this wave's share of the candidates: c = SH wave .. SH wave + SH - 1
+        unsigned long long mine[SH];
+        int n = 0;
+        for (int k = 0; k < SH; ++k) {
+            const int c = SH * wave + k;
+            mine[k] = c < nc ? bits[c][lane] : 0;
+            n += __popcll(mine[k]);
+            if (__ballot(mine[k] != 0) && lane == 0) atomicOr(&used, 1u << c);
+        }
+        cnt[wave][lane] = n;
+        __syncthreads();
+        const uint32_t in = used;
+        int at = total;
+        for (int w = 0; w < W; ++w) {
+            at += w < wave ? cnt[w][lane] : 0;
+            total += cnt[w][lane];
+        }
+        for (int k = 0; k < SH; ++k) {
+            const int c = SH * wave + k, slot = n_slots + __popc(in & ((1u << c) - 1));
+            if (!(in >> c & 1) || slot >= BIG_LIST_SLOTS) continue;
+            const int tt = cand[c0 + c];
+            if (lane == 0) b.slot[me * BIG_LIST_SLOTS + slot] = make_int2(o + 64 * tt, min(64, nb - 64 * tt));
+            for (unsigned long long q = mine[k]; q; q &= q - 1, ++at)
+                if (at < BIG_LIST_CAP) out[at] = (uint16_t)(slot * 64 + __builtin_ctzll(q));
+        }
+        n_slots += __popc(in);
+        __syncthreads(); // bits, cnt and used are rewritten by the next candidates
+    }
+    // a tile beyond the slots lists nothing (its attempt is void)
+    if (wave == 0) {
+        if (valid) b.ltot[fa] = n_slots <= BIG_LIST_SLOTS ? min(total, BIG_LIST_CAP) : 0;
+        if ((__ballot(valid && total > BIG_LIST_CAP) || n_slots > BIG_LIST_SLOTS) && lane == 0) {
             atomicOr(b.ovf, 1);
             b.stale[g] = 1;
         }
-    }
-}
-
-// Per target tile (thread = member m, segment s): the source tiles holding an entry of one of
-// its members' lists become the tile's slots, in tile order (more than BIG_LIST_SLOTS void the
-// attempt and send the step to the tile path), and each member's segments are written as one
-// run of slot positions, slot * 64 + the source's position in its tile.
-constexpr int LOC_THREADS = 64 * BIG_LIST_SEGS; // one thread per (member, segment) of a tile
-
-__global__ __launch_bounds__(LOC_THREADS) void big_localize_kernel(BigBs b)
-{
-    static_assert(BIG_LIST_SLOTS * 64 <= 65536, "16-bit slot positions");
-    __shared__ int mark[BIG_TILES_PER_GROUP];
-    __shared__ int wsum[LOC_THREADS / 64];
-    for (int me = blockIdx.x; me < b.dims[2]; me += gridDim.x) {
-        const int4 tile = b.tiles[me];
-        const int g = tile.x;
-        if (b.done[g] || b.keep[g]) continue; // the whole block
-        const int o = b.off[g], nb = b.off[g + 1] - o, nt = b.tfirst[g + 1] - b.tfirst[g];
-        for (int i = threadIdx.x; i < nt; i += LOC_THREADS) mark[i] = 0;
-        __syncthreads();
-        const int m = threadIdx.x / BIG_LIST_SEGS, s = threadIdx.x % BIG_LIST_SEGS;
-        const bool valid = m < tile.z;
-        const int f = tile.y + (valid ? m : 0);
-        const int32_t *nlen = b.nlen + (size_t)f * BIG_LIST_SEGS;
-        int start = 0, all = 0;
-        for (int q = 0; q < BIG_LIST_SEGS; ++q) {
-            const int l = nlen[q];
-            start += q < s ? l : 0;
-            all += l;
-        }
-        const int len = valid ? nlen[s] : 0;
-        const int32_t *row = b.nl + (size_t)f * BIG_LIST_CAP + s * BIG_LIST_SEG;
-        for (int e = 0; e < len; ++e) mark[(row[e] - o) >> 6] = 1;
-        __syncthreads();
-        // ordered compaction of the marks: thread t takes tiles [t per, (t + 1) per)
-        const int per = (nt + LOC_THREADS - 1) / LOC_THREADS;
-        const int t0 = (int)threadIdx.x * per, t1 = min(t0 + per, nt);
-        int cnt = 0;
-        for (int i = t0; i < t1; ++i) cnt += mark[i];
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-        int incl = cnt;
-        for (int d = 1; d < 64; d <<= 1) {
-            const int v = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += v;
-        }
-        if (lane == 63) wsum[wave] = incl;
-        __syncthreads();
-        int pos = incl - cnt, total = 0;
-        for (int w = 0; w < LOC_THREADS / 64; ++w) {
-            pos += w < wave ? wsum[w] : 0;
-            total += wsum[w];
-        }
-        for (int i = t0; i < t1; ++i)
-            if (mark[i]) {
-                if (pos < BIG_LIST_SLOTS) b.slot[me * BIG_LIST_SLOTS + pos] = make_int2(o + 64 * i, min(64, nb - 64 * i));
-                mark[i] = pos++;
-            }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            b.nslot[me] = min(total, BIG_LIST_SLOTS);
-            if (total > BIG_LIST_SLOTS) {
-                atomicOr(b.ovf, 1);
-                b.stale[g] = 1;
-            }
-        }
-        if (total <= BIG_LIST_SLOTS) {
-            uint16_t *out = b.ll + (size_t)f * BIG_LIST_CAP + start;
-            for (int e = 0; e < len; ++e) {
-                const int r = row[e] - o;
-                out[e] = (uint16_t)(mark[r >> 6] * 64 + (r & 63));
-            }
-        }
-        // a tile beyond the slots lists nothing (its attempt is void)
-        if (valid && s == 0) b.ltot[f] = total <= BIG_LIST_SLOTS ? all : 0;
-        __syncthreads(); // the marks are cleared for the next tile
+        if (lane == 0) b.nslot[me] = min(n_slots, BIG_LIST_SLOTS);
     }
 }
 
@@ -1096,12 +1129,10 @@ hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, i
     auto pass = lv ? big_pass_kernel<true> : big_pass_kernel<false>;
     big_begin_kernel<<<gg, 64, 0, stream>>>(b, flags);
     big_prepare_kernel<<<(nt + 3) / 4, GB_THREADS, 0, stream>>>(b);
-    const int nl = std::min(nt * BIG_LIST_SEGS, 65536);
-    if (lv)
-        big_list_kernel<true><<<nl, 64, 0, stream>>>(b);
+    if (nt <= BIG_SIDE_TILES)
+        (lv ? big_list_kernel<true, 16> : big_list_kernel<false, 16>)<<<nt, 1024, 0, stream>>>(b);
     else
-        big_list_kernel<false><<<nl, 64, 0, stream>>>(b);
-    big_localize_kernel<<<nt, LOC_THREADS, 0, stream>>>(b);
+        (lv ? big_list_kernel<true, 8> : big_list_kernel<false, 8>)<<<nt, 512, 0, stream>>>(b);
     const int threads = 64 * BIG_LIST_LANES;
     pass<<<dim3(nt, 1), threads, 0, stream>>>(b, 0, 0, -1, tol);
     // Columns in batches: side by side the columns above the accepted one have run for nothing.

@@ -168,8 +168,6 @@ struct genga_ctx {
         dfree(big.err);
         dfree(big.rcl);
         dfree(big.i9l);
-        dfree(big.nl);
-        dfree(big.nlen);
         dfree(big.ltot);
         dfree(big.ll);
         dfree(big.slot);
@@ -565,8 +563,6 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.sr, G));
     HIP_TRY(dalloc(b.sv, G));
     HIP_TRY(dalloc(b.err, G * BS_KMAX));
-    HIP_TRY(dalloc(b.nl, M * BIG_LIST_CAP));
-    HIP_TRY(dalloc(b.nlen, M * BIG_LIST_SEGS));
     HIP_TRY(dalloc(b.ltot, M));
     HIP_TRY(dalloc(b.ll, M * BIG_LIST_CAP));
     HIP_TRY(dalloc(b.slot, (size_t)b.cap_T * BIG_LIST_SLOTS));
@@ -580,7 +576,7 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.stale, G));
     HIP_TRY(dalloc(b.keep, G));
     HIP_TRY(hipMemset(b.keep, 0, G * sizeof(int32_t)));
-    HIP_TRY(dalloc(b.sbb, 8 * (size_t)b.cap_T));
+    HIP_TRY(dalloc(b.sbb, (size_t)BIG_BOX * b.cap_T));
     HIP_TRY(dalloc(b.P, (size_t)(1 + 2 * BS_KMAX) * M));
     HIP_TRY(dalloc(b.V, (size_t)(2 * BS_KMAX) * 3 * M));
     HIP_TRY(dalloc(b.ovf, 1));

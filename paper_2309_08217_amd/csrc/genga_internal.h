@@ -308,13 +308,9 @@ struct BigBs {
     int32_t nlev = 1;
     double *rcl = nullptr;         // [LEVELS_MAX - 1][cap_M]
     double *i9l = nullptr;         // [LEVELS_MAX - 1][cap_M] 1 / (0.9 rcl)
-    // neighbour lists (the list path), built at the start of every attempt (bigbs.hip): member
-    // f's sources in BIG_LIST_SEGS segments, nl[f * BIG_LIST_CAP + s * BIG_LIST_SEG + e],
-    // e < nlen[f * BIG_LIST_SEGS + s]
-    int32_t *nl = nullptr;         // [cap_M][BIG_LIST_CAP]
-    int32_t *nlen = nullptr;       // [cap_M][BIG_LIST_SEGS]
+    // neighbour lists (the list path), built at the start of every attempt (bigbs.hip)
     int32_t *ltot = nullptr;       // [cap_M] the list's length
-    uint16_t *ll = nullptr;        // [cap_M][BIG_LIST_CAP] the list as one run of slot positions
+    uint16_t *ll = nullptr;        // [cap_M][BIG_LIST_CAP] the list, as slot positions
                                    //   (slot * 64 + position in the slot's source tile)
     int2 *slot = nullptr;          // [cap_T][BIG_LIST_SLOTS] per target tile: the source tiles holding
                                    //   an entry of its members' lists, in tile order, as (first
@@ -329,7 +325,8 @@ struct BigBs {
     int32_t *stale = nullptr;      // [G] a sub-step crossed a bound: the group's attempt is void
     int32_t *keep = nullptr;       // [G] the group's last attempt was rejected (not void): same start, a
                                    //   shorter step, so its lists and bounds still hold
-    double *sbb = nullptr;         // [cap_T][8] box swept over the attempt by a tile, and its largest S
+    double *sbb = nullptr;         // [cap_T][BIG_BOX] per tile: the lowest position, velocity and A by
+                                   //   component, the highest, the largest S
     // the list path's state buffers, so that the extrapolation columns advance side by side:
     // buffer 0 holds Y's positions, buffers 1 + 2k and 2 + 2k column k's sub-step states
     double4 *P = nullptr;          // [1 + 2 BS_KMAX][cap_M] (x, y, z, mass)
@@ -339,9 +336,8 @@ struct BigBs {
     int32_t *ovf = nullptr;        // device word: a list exceeded BIG_LIST_CAP (the host falls back to tiles)
 };
 constexpr int BIG_TILES_PER_GROUP = 1024; // a workgroup of 1024 threads tests one source tile each
-constexpr int BIG_LIST_SEGS = 8;          // segments of a member's list (built by separate waves)
-constexpr int BIG_LIST_SEG = 128;         // sources per segment
-constexpr int BIG_LIST_CAP = BIG_LIST_SEGS * BIG_LIST_SEG; // sources per member on the list path
+constexpr int BIG_BOX = 20;
+constexpr int BIG_LIST_CAP = 1024;        // sources per member on the list path
 constexpr int BIG_LIST_LANES = 8;         // lanes that share one member's list in a sub-step
 constexpr int BIG_AHEAD = 16;             // attempts enqueued without looking at most
 constexpr int BIG_LIST_SLOTS = 16;        // source tiles a target tile's sub-step stages in LDS

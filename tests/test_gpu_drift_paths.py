@@ -1,6 +1,7 @@
 """The drift's solvers at the edges of their ranges, against the oracle: the Kepler drift on both
 sides of the step at which it turns to the bracketed solver, and encounter groups of two and three
-bodies at separations from the inner edge of the changeover zone to its rim."""
+bodies at separations from the inner edge of the changeover zone to its rim; neighbour lists of a
+large group with many candidate tiles."""
 import numpy as np
 import pytest
 
@@ -86,5 +87,34 @@ def test_groups_of_two_and_three(members):
     for k in KEYS:
         err = np.max(np.abs(got[k] - exp[k]))
         print(f"[groups of {members}] {k} err {err:.2e}", flush=True)
+        assert err <= 1e-10     # the bound of the other encounter groups
+    s.close()
+
+
+@pytest.mark.parametrize("tiles,last", [(31, 1), (41, 17)])
+def test_one_wide_radius_in_a_long_chain(tiles, last):
+    """A group along an arc, every body in reach of two neighbours on either side, and one body far
+    ahead on the same orbit whose wide r_crit reaches the arc's end only: the group's largest radius
+    makes most of its tiles candidates of each other (at most 32 of them, and more than 32), while
+    the lists stay short."""
+    n, step = 64 * tiles + last - 1, 1.5e-4
+    th = np.append(np.arange(n), n - 1 + 2000) * step
+    z = np.zeros(n + 1)
+    pos, vel = np.stack([np.cos(th), np.sin(th), z], axis=1), np.stack([-np.sin(th), np.cos(th), z], axis=1)
+    d = _disc(pos, vel, np.full(n + 1, 1e-10))
+    rc = np.append(np.full(n, 2.5 * step), 2004.5 * step)
+    s = System([d], rcrit=rc)
+    genga.genga_set_large_groups(s.ctx.handle, True)
+    s.accel(genga.GENGA_KICK_FP64)
+    pairs, cnt = s.encounter_list()
+    gid = oracle.groups(d.n, pairs)
+    assert np.bincount(gid[gid >= 0]).max() == n + 1
+    exp = oracle.drift(s.numpy_state(), rc, 1.0, DT, pairs)
+    genga.genga_drift(s.ctx.handle, s.b, DT)
+    got = s.numpy_state()
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK
+    for k in KEYS:
+        err = np.max(np.abs(got[k] - exp[k]))
+        print(f"[chain of {n}] {k} err {err:.2e}", flush=True)
         assert err <= 1e-10     # the bound of the other encounter groups
     s.close()

@@ -104,7 +104,6 @@ struct genga_ctx {
     // a power of 2^(1/4) that covers the layout's tiles)
     hipGraphExec_t big_exec[64] = {};
     hipGraphExec_t big_exec_list[64] = {}; // the same on the list path
-    int32_t *big_changed = nullptr;    // device word of the union-find rounds
     int32_t ce_cap = 0;                // members / group_start capacity
     std::vector<int32_t> gs_h;         // group_start copied to the host
     // host scratch of the grouping and tile ordering, kept so that the per-call vectors of
@@ -219,7 +218,6 @@ struct genga_ctx {
         big_stream = nullptr;
         dfree(big.dims);
         dfree(big.dtp);
-        dfree(big_changed);
         pin = nullptr;
         big.G = big.M = big.n_tiles = 0;
         large_groups = 0;
@@ -584,7 +582,6 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(hipMemset(b.stale, 0, G * sizeof(int32_t)));
     HIP_TRY(dalloc(b.dims, 4));
     HIP_TRY(dalloc(b.dtp, 1));
-    HIP_TRY(dalloc(ctx->big_changed, 1));
     if (!ctx->pin) HIP_TRY(hipHostMalloc((void **)&ctx->pin, 8 * sizeof(int32_t), hipHostMallocDefault));
     HIP_TRY(hipHostGetDevicePointer((void **)&b.status, ctx->pin + 4, 0));
     return GENGA_OK;
@@ -603,30 +600,11 @@ int build_groups_large(genga_ctx *ctx, hipStream_t s)
     out.off = ctx->group_start;
     const size_t ngs = (size_t)nt / 2 + 2; // groups have at least two members
     std::vector<int32_t> &gs = ctx->gs_h;
-    const auto layout = [&](bool union_find) -> int {
-        HIP_TRY(launch_group_layout(L, ctx->gw, ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->lab, ctx->iota, nt,
-                                    out, s, union_find));
-        gs.resize(ngs);
-        HIP_TRY(hipMemcpyAsync(ctx->ghdr, ctx->gw.hdr, sizeof(GroupHeader), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(gs.data(), ctx->group_start, ngs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        return GENGA_OK;
-    };
-    int rc = layout(true);
-    if (rc) return rc;
-    // a union-find not settled within the enqueued rounds: checked rounds, then the layout again
-    for (int round = 0; ctx->ghdr->unconverged; ++round) {
-        if (round > 4096) return fail(GENGA_ERR_STATE, "union-find of the encounter pairs did not settle");
-        ctx->pin[2] = 0;
-        HIP_TRY(hipMemcpyAsync(ctx->big_changed, ctx->pin + 2, sizeof(int32_t), hipMemcpyHostToDevice, s));
-        for (int rep = 0; rep < 2; ++rep) {
-            HIP_TRY(launch_uf_hook(ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->lab, ctx->big_changed, s));
-            HIP_TRY(launch_uf_compress(L, ctx->lab, s));
-        }
-        HIP_TRY(hipMemcpyAsync(ctx->pin + 2, ctx->big_changed, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (ctx->pin[2] == 0 && (rc = layout(false))) return rc;
-    }
+    HIP_TRY(launch_group_layout(L, ctx->gw, ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->lab, ctx->iota, nt, out, s));
+    gs.resize(ngs);
+    HIP_TRY(hipMemcpyAsync(ctx->ghdr, ctx->gw.hdr, sizeof(GroupHeader), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(gs.data(), ctx->group_start, ngs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
     const GroupHeader h = *ctx->ghdr;
     if (h.max_nb > 64 * BIG_TILES_PER_GROUP) {
         if (nt > 0) (void)hipMemsetAsync(ctx->lab, 0xff, (size_t)nt * sizeof(int32_t), s);
@@ -712,9 +690,7 @@ int level_kick(genga_ctx *ctx, genga_bodies *b, int level, const LevelTiles &T, 
 
 // The groups of the level-`level` pairs (ctx->lv_pairs), laid out on the device in the order of
 // the parent layout T (members of each group in T's order): into the child level's tiles, or,
-// for the deepest level, into lv_mem / lv_gs.  One host wait, for the header.  A union-find
-// that has not settled within the enqueued rounds is finished with checked rounds (one wait
-// each) and laid out again.
+// for the deepest level, into lv_mem / lv_gs.  One host wait, for the header.
 int group_level(genga_ctx *ctx, int level, const LevelTiles &T, bool deepest, hipStream_t s)
 {
     GroupOut out;
@@ -730,26 +706,9 @@ int group_level(genga_ctx *ctx, int level, const LevelTiles &T, bool deepest, hi
         out.tl = C.tl;
     }
     HIP_TRY(launch_group_layout(ctx->L, ctx->gw, ctx->lv_pairs, ctx->lv_count, ctx->pair_cap, ctx->lab, T.body, T.M,
-                                out, s, true));
+                                out, s));
     HIP_TRY(hipMemcpyAsync(ctx->ghdr, ctx->gw.hdr, sizeof(GroupHeader), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    for (int round = 0; ctx->ghdr->unconverged; ++round) {
-        if (round > 4096) return fail(GENGA_ERR_STATE, "union-find of the level pairs did not settle");
-        ctx->pin[2] = 0;
-        HIP_TRY(hipMemcpyAsync(ctx->big_changed, ctx->pin + 2, sizeof(int32_t), hipMemcpyHostToDevice, s));
-        for (int rep = 0; rep < 2; ++rep) {
-            HIP_TRY(launch_uf_hook(ctx->lv_pairs, ctx->lv_count, ctx->pair_cap, ctx->lab, ctx->big_changed, s));
-            HIP_TRY(launch_uf_compress(ctx->L, ctx->lab, s));
-        }
-        HIP_TRY(hipMemcpyAsync(ctx->pin + 2, ctx->big_changed, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (ctx->pin[2] == 0) {
-            HIP_TRY(launch_group_layout(ctx->L, ctx->gw, ctx->lv_pairs, ctx->lv_count, ctx->pair_cap, ctx->lab,
-                                        T.body, T.M, out, s, false));
-            HIP_TRY(hipMemcpyAsync(ctx->ghdr, ctx->gw.hdr, sizeof(GroupHeader), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-        }
-    }
     const GroupHeader &h = *ctx->ghdr;
     const auto refuse = [&](int status, const char *fmt, int a, int b) {
         if (ctx->L.n_total > 0)

@@ -267,16 +267,10 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
                         int32_t *member_slot, int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list,
                         hipStream_t stream, const double *rc_lv = nullptr, int nlev = 1, bool kepler = true,
                         const DriftSide *side = nullptr, const StepMomentum *pm = nullptr, bool wg_listed = false);
-// Grid-wide union-find of the encounter pairs (large-group mode; the host reads lab back):
-// init (lab = body for the bodies of a pair), hook rounds (changed |= 1 while a round hooks),
-// compress (every member's lab = its root), slots (member_slot for members[0..n), lab = -1).
-hipError_t launch_uf_init(const int32_t *pairs, const int32_t *pair_count, int32_t pair_cap, int32_t *lab,
-                          hipStream_t stream);
-// run_if (device word, may be null): the launch does nothing when *run_if == 0 (the previous
-// round changed nothing), so a fixed number of rounds can be enqueued without host waits.
-hipError_t launch_uf_hook(const int32_t *pairs, const int32_t *pair_count, int32_t pair_cap, int32_t *lab,
-                          int32_t *changed, hipStream_t stream, const int32_t *run_if = nullptr);
-hipError_t launch_uf_compress(const Layout &L, int32_t *lab, hipStream_t stream, const int32_t *run_if = nullptr);
+// Grid-wide union-find of the encounter pairs (large-group mode, levels; lab all -1 on entry), and
+// slots (member_slot for members[0..n), lab = -1).
+hipError_t launch_uf_union(const int32_t *pairs, const int32_t *pair_count, int32_t pair_cap, int32_t *lab,
+                           hipStream_t stream);
 hipError_t launch_uf_slots(int n_members_max, const int32_t *members, const int32_t *n_members,
                            int32_t *member_slot, int32_t *lab, hipStream_t stream);
 
@@ -402,14 +396,11 @@ hipError_t launch_kepler_list(const Layout &L, const int32_t *list, int32_t n, d
 
 // Encounter groups of a level's pair list laid out on the device (groups.hip).  The host reads
 // only the header, once per grouping.
-constexpr int UF_ROUNDS = 3; // union-find rounds enqueued at once; more only if the last still hooked
 struct GroupHeader {
     int32_t G, M;            // groups, members
     int32_t n_tiles, n_multi; // tiles of 64; of them in groups of several tiles
     int32_t max_nb;          // largest group
-    int32_t unconverged;     // the last union-find round still hooked: more rounds are needed
     int32_t pair_count;      // length of the pair list (may exceed its capacity)
-    int32_t pad;
 };
 // Where the layout goes: body[M] the members group by group, each group in the parent order;
 // off[G + 1]; with tiles != null also tfirst[G + 1], tiles[n_tiles] (group, first member, count,
@@ -421,11 +412,10 @@ struct GroupOut {
 };
 struct GroupWork {
     uint64_t *keys = nullptr, *keys_sorted = nullptr; // [cap]
-    int32_t *flag = nullptr, *gidx = nullptr;         // [cap]
-    uint64_t *tv = nullptr, *tscan = nullptr;         // [cap / 2 + 2]
-    int32_t *changed = nullptr;                       // [UF_ROUNDS]
+    int32_t *cnt = nullptr;                           // groups by block of 1024 members
+    uint64_t *tsum = nullptr;                         // tiles by block of 1024 groups
     GroupHeader *hdr = nullptr;                       // device
-    void *temp = nullptr;                             // sort / scan temporary storage
+    void *temp = nullptr;                             // sort temporary storage
     size_t temp_bytes = 0;
     int cap = 0;                                      // largest parent layout
 };
@@ -451,13 +441,12 @@ void order_work_free(OrderWork &w);
 hipError_t launch_ring_order(const int32_t *members, const int32_t *k0, const int32_t *off, int n_groups, int M,
                              const double *x, const double *y, OrderWork &w, int32_t *body_out, hipStream_t stream);
 void group_work_free(GroupWork &w);
-// With union_find: union-find of pairs (lab all -1 on entry; afterwards every body of a pair
-// holds its component's smallest body, the caller clears it); then the components' members in
-// the order of the parent layout pbody[Mp] into `out`, and the header.  Without: the layout of
-// the labels as they are (after further rounds by the caller).
+// Union-find of pairs (lab all -1 on entry; afterwards every body of a pair holds its component's
+// smallest body, the caller clears it); then the components' members in the order of the parent
+// layout pbody[Mp] into `out`, and the header.
 hipError_t launch_group_layout(const Layout &L, GroupWork &w, const int32_t *pairs, const int32_t *pair_count,
                                int32_t pair_cap, int32_t *lab, const int32_t *pbody, int Mp, const GroupOut &out,
-                               hipStream_t stream, bool union_find);
+                               hipStream_t stream);
 
 // Collisions (perfect mergers) and removal by distance: caller-owned mass (the bodies' m),
 // radius and status arrays; a list of the colliding pairs of the current drift.

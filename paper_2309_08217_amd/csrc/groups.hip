@@ -1,164 +1,174 @@
 // Encounter groups of a level's pair list laid out on the device (hierarchical levels,
 // Brasser et al. 2023, Sect. 1: the pairs closer than a level's critical radius form the groups
 // that the next level integrates).  The groups are the connected components of the pairs, found
-// by the grid-wide union-find (a fixed number of rounds, each skipped once the previous one
-// changed nothing); their members are taken in the order of the parent level's layout, grouped
-// by a stable radix sort of (root, parent position), and cut into tiles of 64 for the next
+// by a grid-wide union-find in one launch; their members are taken in the order of the parent
+// level's layout, grouped by a stable radix sort by root, and cut into tiles of 64 for the next
 // level's kick.  Everything stays on the device; the host reads one small header per grouping
-// (the sizes it needs to size the next launches).
+// (the sizes it needs to size the next launches).  A chain of small launches, bound by their
+// number: rounds of hooking and compressing, a sort by root and position and two library scans were
+// 32 launches, 167 us a grouping in the levels of 40322 bodies; now 13 launches, 109 us.
 #include <cstring>
 
 #include <rocprim/device/device_radix_sort.hpp>
-#include <rocprim/device/device_scan.hpp>
 
 #include "genga_internal.h"
+#include "union_find.h"
 
 namespace genga {
 
 namespace {
 
 constexpr int GL_THREADS = 256;
+constexpr int GS_THREADS = 1024; // the kernels that count and place: their block sums are few
 
-__device__ __forceinline__ int32_t lab_of(const int32_t *lab, int32_t b)
-{
-    return __hip_atomic_load(&lab[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Header cleared; with full, also the pair count of the list recorded and the round words cleared.
-__global__ __launch_bounds__(64) void group_begin_kernel(GroupHeader *hdr, const int32_t *pair_count,
-                                                         int32_t *changed, int full)
-{
-    if (threadIdx.x == 0) {
-        hdr->G = 0;
-        hdr->M = 0;
-        hdr->n_tiles = 0;
-        hdr->n_multi = 0;
-        hdr->max_nb = 0;
-        hdr->unconverged = 0;
-        if (full) hdr->pair_count = *pair_count;
-        hdr->pad = 0;
-    }
-    if (full && (int)threadIdx.x < UF_ROUNDS) changed[threadIdx.x] = 0;
-}
-
-// The round words: unconverged when the last round still hooked something.
-__global__ __launch_bounds__(64) void group_rounds_kernel(GroupHeader *hdr, const int32_t *changed)
-{
-    if (threadIdx.x == 0) hdr->unconverged = changed[UF_ROUNDS - 1] != 0;
-}
-
-// Sort key of parent position p: (root of its body) * Mp + p, or the sentinel for a body in no
-// pair.
-__global__ __launch_bounds__(GL_THREADS) void group_keys_kernel(const int32_t *pbody, int Mp, const int32_t *lab,
-                                                                uint64_t sentinel, uint64_t *keys)
+// Sort key of parent position p: the root of its body (n_total for a body in no pair) above p,
+// which is already in order.  The labels are left at their roots; the header is cleared for the
+// launches after this one.
+__global__ __launch_bounds__(GL_THREADS) void group_keys_kernel(const int32_t *pbody, int Mp, int n_total,
+                                                                const int32_t *pair_count, int32_t *lab,
+                                                                uint64_t *keys, GroupHeader *hdr)
 {
     const int p = blockIdx.x * GL_THREADS + threadIdx.x;
+    if (p == 0) *hdr = GroupHeader{0, 0, 0, 0, 0, *pair_count};
     if (p >= Mp) return;
-    const int32_t r = lab_of(lab, pbody[p]);
-    keys[p] = r >= 0 ? (uint64_t)(uint32_t)r * (uint64_t)Mp + (uint64_t)p : sentinel;
+    const int b = pbody[p], l = uf_load(lab, b);
+    int r = n_total;
+    if (l >= 0) {
+        r = uf_root(lab, l);
+        if (r != l) __hip_atomic_store(&lab[b], r, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    keys[p] = (uint64_t)(uint32_t)r << 32 | (uint32_t)p;
 }
 
-// Members in sorted order and the first member of each group.
-__global__ __launch_bounds__(GL_THREADS) void group_mark_kernel(const uint64_t *sorted, int Mp, uint64_t sentinel,
-                                                                const int32_t *pbody, int32_t *body_out,
-                                                                int32_t *flag)
+// Whether a group starts at sorted position q, and whether q holds a member at all.
+__device__ __forceinline__ bool group_start_at(const uint64_t *sorted, int q, int Mp, int n_total, bool &member)
 {
-    const int q = blockIdx.x * GL_THREADS + threadIdx.x;
-    if (q >= Mp) return;
-    const uint64_t k = sorted[q];
-    const bool valid = k < sentinel;
-    bool start = false;
-    if (valid) {
-        body_out[q] = pbody[(int)(k % (uint64_t)Mp)];
-        start = q == 0 || sorted[q - 1] / (uint64_t)Mp != k / (uint64_t)Mp;
+    const int r = q < Mp ? (int)(sorted[q] >> 32) : n_total;
+    member = r < n_total;
+    return member && (q == 0 || (int)(sorted[q - 1] >> 32) != r);
+}
+
+// The sum of v over the block's threads before this one; all: over the block (every thread).
+template <typename T>
+__device__ __forceinline__ T block_before(T v, T *wsum, T &all)
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    T incl = v;
+    for (int d = 1; d < 64; d <<= 1) {
+        const T u = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += u;
     }
-    flag[q] = start ? 1 : 0;
+    __syncthreads(); // wsum of an earlier call is no longer read
+    if (lane == 63) wsum[wave] = incl;
+    __syncthreads();
+    T before = incl - v;
+    all = 0;
+    for (int w = 0; w < GS_THREADS / 64; ++w) {
+        before += w < wave ? wsum[w] : 0;
+        all += wsum[w];
+    }
+    return before;
+}
+
+// Members in sorted order, and per block the number of groups that start in it.
+__global__ __launch_bounds__(GS_THREADS) void group_mark_kernel(const uint64_t *sorted, int Mp, int n_total,
+                                                                const int32_t *pbody, int32_t *body_out, int32_t *cnt)
+{
+    __shared__ int wsum[GS_THREADS / 64];
+    const int q = blockIdx.x * GS_THREADS + threadIdx.x;
+    bool member;
+    const bool start = group_start_at(sorted, q, Mp, n_total, member);
+    if (member) body_out[q] = pbody[(int)(uint32_t)sorted[q]];
+    int all;
+    block_before((int)start, wsum, all);
+    if (threadIdx.x == 0) cnt[blockIdx.x] = all;
 }
 
 // Group offsets; the last member writes the totals.
-__global__ __launch_bounds__(GL_THREADS) void group_offsets_kernel(const uint64_t *sorted, int Mp, uint64_t sentinel,
-                                                                   const int32_t *flag, const int32_t *gidx,
-                                                                   int32_t *off, GroupHeader *hdr)
+__global__ __launch_bounds__(GS_THREADS) void group_offsets_kernel(const uint64_t *sorted, int Mp, int n_total,
+                                                                   const int32_t *cnt, int32_t *off, GroupHeader *hdr)
 {
-    const int q = blockIdx.x * GL_THREADS + threadIdx.x;
-    if (q >= Mp) return;
-    const bool valid = sorted[q] < sentinel;
-    if (q == 0 && !valid) { // no member at all
-        off[0] = 0;
-        return;
-    }
-    if (!valid) return;
-    if (flag[q]) off[gidx[q]] = q;
-    if (q + 1 == Mp || sorted[q + 1] >= sentinel) {
-        const int G = gidx[q] + flag[q];
+    __shared__ int wsum[GS_THREADS / 64];
+    const int q = blockIdx.x * GS_THREADS + threadIdx.x;
+    bool member, next;
+    const bool start = group_start_at(sorted, q, Mp, n_total, member);
+    group_start_at(sorted, q + 1, Mp, n_total, next);
+    int part = 0, base, all;
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += GS_THREADS) part += cnt[k];
+    block_before(part, wsum, base);
+    const int g = base + block_before((int)start, wsum, all);
+    if (q == 0 && !member) off[0] = 0; // no member at all
+    if (start) off[g] = q;
+    if (member && !next) {
+        const int G = g + start;
         off[G] = q + 1;
         hdr->G = G;
         hdr->M = q + 1;
     }
 }
 
-// Per group: its size into the header's maximum and its tiles as (tiles of groups of several
-// tiles) << 32 | (1 for a group of one tile), for the scan below.
-__global__ __launch_bounds__(GL_THREADS) void group_sizes_kernel(const int32_t *off, GroupHeader *hdr, int Gcap,
-                                                                 uint64_t *tv)
+// A group's tiles of 64 members, as (tiles of a group of several tiles) << 32 | (1 for a group of
+// one tile), which the sums below count side by side.
+__device__ __forceinline__ uint64_t tiles_of(int nb)
 {
-    const int g = blockIdx.x * GL_THREADS + threadIdx.x;
-    if (g >= Gcap) return;
-    const int G = hdr->G;
-    uint64_t v = 0;
-    if (g < G) {
-        const int nb = off[g + 1] - off[g];
-        const int nt = (nb + 63) / 64;
-        v = nt > 1 ? (uint64_t)nt << 32 : 1ull;
-        atomicMax(&hdr->max_nb, nb);
-    }
-    tv[g] = v;
+    const int nt = (nb + 63) / 64;
+    return nt > 1 ? (uint64_t)nt << 32 : (uint64_t)nt;
 }
 
-// Tiles of 64 members, group by group: each group's first tile (tfirst) and the header's tile
-// counts; group_tile_fill_kernel then writes the tiles and the launch list tl (the tiles of
-// groups of several tiles first, a workgroup each, then the tile of every group of one tile, a
-// wave each).
-__global__ __launch_bounds__(GL_THREADS) void group_tiles_kernel(GroupHeader *hdr, int Gcap, const uint64_t *tv,
-                                                                 const uint64_t *tscan, int32_t *tfirst)
+// The largest group into the header, and per block the groups' tiles.
+__global__ __launch_bounds__(GS_THREADS) void group_sizes_kernel(const int32_t *off, GroupHeader *hdr, uint64_t *tsum)
 {
-    const int g = blockIdx.x * GL_THREADS + threadIdx.x;
-    if (g >= Gcap) return;
-    const int G = hdr->G;
-    if (g >= G) return;
-    const uint64_t tot = tscan[G - 1] + tv[G - 1];
-    const int n_multi = (int)(tot >> 32), n_tiles = n_multi + (int)(tot & 0xffffffffu);
-    const uint64_t e = tscan[g];
-    const int mo = (int)(e >> 32), so = (int)(e & 0xffffffffu);
-    tfirst[g] = mo + so;
+    __shared__ uint64_t wsum[GS_THREADS / 64];
+    const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G;
+    if ((int)blockIdx.x * GS_THREADS >= G) return; // the whole block
+    const int nb = g < G ? off[g + 1] - off[g] : 0;
+    int mx = nb;
+    for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(&hdr->max_nb, mx);
+    if (!tsum) return;
+    uint64_t all;
+    block_before(tiles_of(nb), wsum, all);
+    if (threadIdx.x == 0) tsum[blockIdx.x] = all;
+}
+
+// Tiles of 64 members, group by group: each group's first tile (tfirst), its tiles, their places
+// in the launch list tl (the tiles of groups of several tiles first, a workgroup each, then the
+// tile of every group of one tile, a wave each), and the header's tile counts.
+__global__ __launch_bounds__(GS_THREADS) void group_tiles_kernel(const int32_t *off, GroupHeader *hdr,
+                                                                 const uint64_t *tsum, int32_t *tfirst, int4 *tiles,
+                                                                 int32_t *tl)
+{
+    __shared__ uint64_t wsum[GS_THREADS / 64];
+    const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G, lane = threadIdx.x & 63;
+    const int nblk = (G + GS_THREADS - 1) / GS_THREADS;
+    if ((int)blockIdx.x >= nblk) return; // the whole block
+    uint64_t part = 0, rest = 0, base, after, all;
+    for (int k = threadIdx.x; k < nblk; k += GS_THREADS) (k < (int)blockIdx.x ? part : rest) += tsum[k];
+    block_before(part, wsum, base);
+    block_before(rest, wsum, after);
+    const int o = g < G ? off[g] : 0, nb = g < G ? off[g + 1] - o : 0, nt = (nb + 63) / 64;
+    const uint64_t e = base + block_before(tiles_of(nb), wsum, all), tot = base + after;
+    const int mo = (int)(e >> 32), so = (int)(uint32_t)e;
+    const int n_multi = (int)(tot >> 32), n_tiles = n_multi + (int)(uint32_t)tot;
+    if (g < G) tfirst[g] = mo + so;
     if (g == G - 1) {
         tfirst[G] = n_tiles;
         hdr->n_tiles = n_tiles;
         hdr->n_multi = n_multi;
     }
-}
-
-// The tiles themselves, one thread each (a group of many tiles would otherwise be one thread's
-// loop): tile t belongs to the last group whose first tile is at most t (every group has one).
-__global__ __launch_bounds__(GL_THREADS) void group_tile_fill_kernel(const int32_t *off, const GroupHeader *hdr,
-                                                                     const uint64_t *tscan, const int32_t *tfirst,
-                                                                     int4 *tiles, int32_t *tl, int Tcap)
-{
-    const int G = hdr->G, n_tiles = hdr->n_tiles, n_multi = hdr->n_multi;
-    if (G <= 0) return;
-    for (int t = blockIdx.x * GL_THREADS + threadIdx.x; t < min(n_tiles, Tcap); t += gridDim.x * GL_THREADS) {
-        int lo = 0, hi = G - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (tfirst[mid] <= t) lo = mid;
-            else hi = mid - 1;
+    if (nt == 1) {
+        tiles[mo + so] = make_int4(g, o, nb, 0);
+        tl[n_multi + so] = mo + so;
+    }
+    // the wave writes the tiles of its larger groups together, one group after the other
+    for (unsigned long long w = __ballot(nt > 1); w; w &= w - 1) {
+        const int src = __builtin_ctzll(w);
+        const int G1 = __shfl(g, src, 64), o1 = __shfl(o, src, 64), nb1 = __shfl(nb, src, 64);
+        const int t1 = __shfl(mo + so, src, 64), m1 = __shfl(mo, src, 64);
+        for (int k = lane; 64 * k < nb1; k += 64) {
+            tiles[t1 + k] = make_int4(G1, o1 + 64 * k, min(64, nb1 - 64 * k), 0);
+            tl[m1 + k] = t1 + k;
         }
-        const int g = lo, k = t - tfirst[g];
-        const int o = off[g], nb = off[g + 1] - o, nt = (nb + 63) / 64;
-        const uint64_t e = tscan[g];
-        const int mo = (int)(e >> 32), so = (int)(e & 0xffffffffu);
-        tiles[t] = make_int4(g, o + 64 * k, min(64, nb - 64 * k), 0);
-        tl[nt > 1 ? mo + k : n_multi + so] = t;
     }
 }
 
@@ -276,86 +286,51 @@ hipError_t group_work_alloc(GroupWork &w, int cap)
 {
     group_work_free(w);
     w.cap = cap > 1 ? cap : 2;
-    const size_t n = (size_t)w.cap, ng = n / 2 + 2;
+    const size_t n = (size_t)w.cap;
     hipError_t e;
     if ((e = hipMalloc((void **)&w.keys, n * sizeof(uint64_t))) != hipSuccess) return e;
     if ((e = hipMalloc((void **)&w.keys_sorted, n * sizeof(uint64_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&w.flag, n * sizeof(int32_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&w.gidx, n * sizeof(int32_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&w.tv, ng * sizeof(uint64_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&w.tscan, ng * sizeof(uint64_t))) != hipSuccess) return e;
-    if ((e = hipMalloc((void **)&w.changed, UF_ROUNDS * sizeof(int32_t))) != hipSuccess) return e;
+    const size_t nb = (n + GS_THREADS - 1) / GS_THREADS;
+    if ((e = hipMalloc((void **)&w.cnt, nb * sizeof(int32_t))) != hipSuccess) return e;
+    if ((e = hipMalloc((void **)&w.tsum, nb * sizeof(uint64_t))) != hipSuccess) return e;
     if ((e = hipMalloc((void **)&w.hdr, sizeof(GroupHeader))) != hipSuccess) return e;
-    // temporary storage of the sort and the two scans, for the largest sizes
-    size_t b0 = 0, b1 = 0, b2 = 0;
-    if ((e = rocprim::radix_sort_keys(nullptr, b0, w.keys, w.keys_sorted, (unsigned int)n, 0, 64)) != hipSuccess)
-        return e;
-    if ((e = rocprim::exclusive_scan(nullptr, b1, w.flag, w.gidx, 0, n, rocprim::plus<int32_t>())) != hipSuccess)
-        return e;
-    if ((e = rocprim::exclusive_scan(nullptr, b2, w.tv, w.tscan, (uint64_t)0, ng, rocprim::plus<uint64_t>())) !=
+    // temporary storage of the sort, for the largest size
+    if ((e = rocprim::radix_sort_keys(nullptr, w.temp_bytes, w.keys, w.keys_sorted, (unsigned int)n, 0, 64)) !=
         hipSuccess)
         return e;
-    w.temp_bytes = std::max(b0, std::max(b1, b2));
     if ((e = hipMalloc(&w.temp, w.temp_bytes ? w.temp_bytes : 1)) != hipSuccess) return e;
     return hipSuccess;
 }
 
 void group_work_free(GroupWork &w)
 {
-    for (void *p : {(void *)w.keys, (void *)w.keys_sorted, (void *)w.flag, (void *)w.gidx, (void *)w.tv,
-                    (void *)w.tscan, (void *)w.changed, (void *)w.hdr, w.temp})
+    for (void *p : {(void *)w.keys, (void *)w.keys_sorted, (void *)w.cnt, (void *)w.tsum, (void *)w.hdr, w.temp})
         if (p) (void)hipFree(p);
     w = GroupWork{};
 }
 
 hipError_t launch_group_layout(const Layout &L, GroupWork &w, const int32_t *pairs, const int32_t *pair_count,
                                int32_t pair_cap, int32_t *lab, const int32_t *pbody, int Mp, const GroupOut &out,
-                               hipStream_t stream, bool union_find)
+                               hipStream_t stream)
 {
     if (Mp > w.cap) return hipErrorInvalidValue;
-    group_begin_kernel<<<1, 64, 0, stream>>>(w.hdr, pair_count, w.changed, union_find ? 1 : 0);
+    if (Mp == 0) return hipMemsetAsync(w.hdr, 0, sizeof(GroupHeader), stream);
     hipError_t e;
-    if (union_find) {
-        if ((e = launch_uf_init(pairs, pair_count, pair_cap, lab, stream)) != hipSuccess) return e;
-        // rounds of two (hook, compress) passes; a round whose predecessor changed nothing is skipped
-        for (int r = 0; r < UF_ROUNDS; ++r) {
-            const int32_t *run_if = r > 0 ? w.changed + r - 1 : nullptr;
-            for (int rep = 0; rep < 2; ++rep) {
-                if ((e = launch_uf_hook(pairs, pair_count, pair_cap, lab, w.changed + r, stream, run_if)) !=
-                    hipSuccess)
-                    return e;
-                if ((e = launch_uf_compress(L, lab, stream, run_if)) != hipSuccess) return e;
-            }
-        }
-        group_rounds_kernel<<<1, 64, 0, stream>>>(w.hdr, w.changed);
-    }
-    if (Mp == 0) return hipGetLastError();
-    const uint64_t sentinel = (uint64_t)(uint32_t)L.n_total * (uint64_t)Mp;
-    const int nb = (Mp + GL_THREADS - 1) / GL_THREADS;
-    group_keys_kernel<<<nb, GL_THREADS, 0, stream>>>(pbody, Mp, lab, sentinel, w.keys);
+    if ((e = launch_uf_union(pairs, pair_count, pair_cap, lab, stream)) != hipSuccess) return e;
+    const int nb = (Mp + GL_THREADS - 1) / GL_THREADS, ns = (Mp + GS_THREADS - 1) / GS_THREADS;
+    group_keys_kernel<<<nb, GL_THREADS, 0, stream>>>(pbody, Mp, L.n_total, pair_count, lab, w.keys, w.hdr);
+    // the positions below the roots are in order: only the roots' bits are sorted
     size_t bytes = w.temp_bytes;
-    if ((e = rocprim::radix_sort_keys(w.temp, bytes, w.keys, w.keys_sorted, (unsigned int)Mp, 0, bits_for(sentinel),
-                                      stream)) != hipSuccess)
+    if ((e = rocprim::radix_sort_keys(w.temp, bytes, w.keys, w.keys_sorted, (unsigned int)Mp, 32,
+                                      32 + bits_for((uint64_t)L.n_total), stream)) != hipSuccess)
         return e;
-    group_mark_kernel<<<nb, GL_THREADS, 0, stream>>>(w.keys_sorted, Mp, sentinel, pbody, out.body, w.flag);
-    bytes = w.temp_bytes;
-    if ((e = rocprim::exclusive_scan(w.temp, bytes, w.flag, w.gidx, 0, (size_t)Mp, rocprim::plus<int32_t>(),
-                                     stream)) != hipSuccess)
-        return e;
-    group_offsets_kernel<<<nb, GL_THREADS, 0, stream>>>(w.keys_sorted, Mp, sentinel, w.flag, w.gidx, out.off, w.hdr);
+    group_mark_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, pbody, out.body, w.cnt);
+    group_offsets_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, w.cnt, out.off, w.hdr);
     // groups have at least two members
-    const int Gcap = Mp / 2 + 1, ng = (Gcap + GL_THREADS - 1) / GL_THREADS;
-    group_sizes_kernel<<<ng, GL_THREADS, 0, stream>>>(out.off, w.hdr, Gcap, w.tv);
-    if (out.tiles) {
-        bytes = w.temp_bytes;
-        if ((e = rocprim::exclusive_scan(w.temp, bytes, w.tv, w.tscan, (uint64_t)0, (size_t)Gcap,
-                                         rocprim::plus<uint64_t>(), stream)) != hipSuccess)
-            return e;
-        group_tiles_kernel<<<ng, GL_THREADS, 0, stream>>>(w.hdr, Gcap, w.tv, w.tscan, out.tfirst);
-        // at most one tile per member
-        group_tile_fill_kernel<<<std::min(nb, 1024), GL_THREADS, 0, stream>>>(out.off, w.hdr, w.tscan, out.tfirst,
-                                                                              out.tiles, out.tl, Mp);
-    }
+    const int ng = (Mp / 2 + GS_THREADS) / GS_THREADS;
+    group_sizes_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, out.tiles ? w.tsum : nullptr);
+    if (out.tiles)
+        group_tiles_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, w.tsum, out.tfirst, out.tiles, out.tl);
     return hipGetLastError();
 }
 

@@ -384,7 +384,7 @@ struct LevelKickArgs {
 // Constants of the members (mass, TP2 flag, radii of levels 0..level) and each group's cut-off.
 hipError_t launch_level_tiles_setup(const Layout &L, const LevelTiles &t, const double *m, const double *rc0,
                                     const double *rcl, int level, hipStream_t stream);
-// Gather the members' positions and tile boxes, then kick (waves: 8 or 16 per workgroup of a
+// Gather the members' positions and tile boxes, then kick (waves: 4 or 16 per workgroup of a
 // multi-tile group's target tile).  An emitting kick starts its pair count from zero.
 hipError_t launch_level_kick(const LevelTiles &t, const LevelKickArgs &a, const double *x, const double *y,
                              const double *z, int waves, hipStream_t stream);

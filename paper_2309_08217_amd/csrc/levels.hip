@@ -8,11 +8,12 @@
 //
 // Layout as in the grid-wide Bulirsch-Stoer: the members of the parent groups are ordered by
 // ring and azimuth (by the host, once per level interval) and cut into tiles of 64.  In a
-// group of several tiles a workgroup of 16 waves (8 when such tiles outnumber the CUs, so that
+// group of several tiles a workgroup of 16 waves (4 when such tiles outnumber the CUs, so that
 // several workgroups share a CU) takes one target tile, lists the source tiles
 // of the group whose box lies within the group's largest level-(l-1) radius of the target
-// tile's box (no pair beyond that radius carries weight at level l), and deals their quarters
-// out to its waves; a group of one tile is one wave, its members the sources in order.
+// tile's box (no pair beyond that radius carries weight at level l), then the sources in reach of
+// the box in them, and deals these out to its waves, four at a time; a group of one tile is one
+// wave, its members the sources in order.
 #include "genga_internal.h"
 #include "pair_math.h"
 
@@ -21,9 +22,6 @@ namespace genga {
 namespace {
 
 constexpr int LT_TILE = 64;
-
-using CD = const __attribute__((address_space(4))) double;
-using CI = const __attribute__((address_space(4))) int32_t;
 
 // Per member f: mass, TP2 flag, the radii of levels 0..level; per group: the largest
 // level-(level-1) radius squared, as the maximum over its tiles (bit patterns of non-negative
@@ -148,21 +146,30 @@ __device__ __forceinline__ LvTarget lv_target(const LevelTiles &t, int4 tile, in
     return me;
 }
 
-// Source member j (wave-uniform) for the target: its term if inside level (l-1)'s radius, and
-// the level's pair.  Every lane of the wave calls it.
-__device__ __forceinline__ void lv_source(const LevelTiles &t, const LevelKickArgs &a, const LvTarget &me, int lv,
-                                          int j, double dx, double dy, double dz, double rcj_up, double &ax,
-                                          double &ay, double &az, int2 *buf, int &fill)
+// A source member's words.
+struct LvSource {
+    double x, y, z, m;
+    double i9[LEVELS_MAX];
+    double rc_up, rc_lv;
+    int f, body, test;
+};
+
+// Whether the source is inside level (l-1)'s radius of the target.
+__device__ __forceinline__ bool lv_inside(const LvTarget &me, const LvSource &j)
 {
-    CD *SM = (CD *)t.mass;
-    CD *SR = (CD *)t.rc;
-    CD *S9 = (CD *)t.i9;
-    CI *ST = (CI *)t.test;
-    CI *SB = (CI *)t.body;
-    const double q = sep2_rn(dx, dy, dz);
-    const double rc_up = fmax(me.rc_up, rcj_up);
+    const double q = sep2_rn(j.x - me.x, j.y - me.y, j.z - me.z);
+    return me.valid && j.f != me.f && !(me.test && j.test != 0) && q < sq_rn(fmax(me.rc_up, j.rc_up));
+}
+
+// The term of a source inside (has) for the target, and the level's pair.  Every lane of the wave
+// calls it, with a source of its own.
+__device__ __forceinline__ void lv_source(const LevelKickArgs &a, const LvTarget &me, int lv, bool has,
+                                          const LvSource &j, double &ax, double &ay, double &az, int2 *buf, int &fill)
+{
     bool em = false;
-    if (me.valid && j != me.f && !(me.test && ST[j] != 0) && q < sq_rn(rc_up)) {
+    if (has) {
+        const double dx = j.x - me.x, dy = j.y - me.y, dz = j.z - me.z;
+        const double q = sep2_rn(dx, dy, dz);
         // W_l K_l = prod_{k<l} u_k^2 / d_k times y_l^2 / d_l (loops over the fixed bound, so the
         // radii stay in registers)
         const double rq = inv_sqrt64(q), r = q * rq;
@@ -170,54 +177,110 @@ __device__ __forceinline__ void lv_source(const LevelTiles &t, const LevelKickAr
 #pragma unroll
         for (int k = 0; k < LEVELS_MAX; ++k) {
             if (k > lv) break;
-            const Changeover c = changeover_parts(r, fmin(me.i9[k], S9[(size_t)k * t.cap_M + j]));
+            const Changeover c = changeover_parts(r, fmin(me.i9[k], j.i9[k]));
             n *= k < lv ? c.u : c.y;
             d *= c.d;
         }
-        const double s = SM[j] * (n * n) * inv64(d) * ((rq * rq) * rq);
+        const double s = j.m * (n * n) * inv64(d) * ((rq * rq) * rq);
         ax = fma(s, dx, ax);
         ay = fma(s, dy, ay);
         az = fma(s, dz, az);
-        em = a.emit && me.body < SB[j] && q < sq_rn(fmax(me.rc_lv, SR[(size_t)lv * t.cap_M + j]));
+        em = a.emit && me.body < j.body && q < sq_rn(fmax(me.rc_lv, j.rc_lv));
     }
-    lv_emit(a, buf, fill, em, me.body, SB[j]);
+    lv_emit(a, buf, fill, em, me.body, j.body);
 }
 
-// Sources [jb, je) of the group for the target: whole quads take the four sources' words in
-// one scalar load per array.
-__device__ __forceinline__ void lv_sources(const LevelTiles &t, const LevelKickArgs &a, const LvTarget &me, int lv,
-                                           int jb, int je, double &ax, double &ay, double &az, int2 *buf,
+// The words of member f.
+__device__ __forceinline__ LvSource lv_load(const LevelTiles &t, int lv, int f)
+{
+    LvSource s;
+    s.x = t.X[f];
+    s.y = t.Y[f];
+    s.z = t.Z[f];
+    s.m = t.mass[f];
+#pragma unroll
+    for (int k = 0; k < LEVELS_MAX; ++k) s.i9[k] = k <= lv ? t.i9[(size_t)k * t.cap_M + f] : 0.0;
+    s.rc_up = t.rc[(size_t)(lv - 1) * t.cap_M + f];
+    s.rc_lv = t.rc[(size_t)lv * t.cap_M + f];
+    s.f = f;
+    s.body = t.body[f];
+    s.test = t.test[f];
+    return s;
+}
+
+// Sources in LDS.
+template <int N>
+struct LvStage {
+    double2 xy[N], zm[N], rr[N], i9[N][LEVELS_MAX / 2];
+    int2 fb[N]; // member, body (a test body's bits flipped)
+    __device__ __forceinline__ void put(int e, const LvSource &s)
+    {
+        xy[e] = make_double2(s.x, s.y);
+        zm[e] = make_double2(s.z, s.m);
+        rr[e] = make_double2(s.rc_up, s.rc_lv);
+#pragma unroll
+        for (int k = 0; k < LEVELS_MAX; k += 2) i9[e][k / 2] = make_double2(s.i9[k], s.i9[k + 1]);
+        fb[e] = make_int2(s.f, s.test ? ~s.body : s.body);
+    }
+    __device__ __forceinline__ LvSource get(int e) const
+    {
+        LvSource s;
+        s.x = xy[e].x;
+        s.y = xy[e].y;
+        s.z = zm[e].x;
+        s.m = zm[e].y;
+        s.rc_up = rr[e].x;
+        s.rc_lv = rr[e].y;
+#pragma unroll
+        for (int k = 0; k < LEVELS_MAX; k += 2) {
+            s.i9[k] = i9[e][k / 2].x;
+            s.i9[k + 1] = i9[e][k / 2].y;
+        }
+        s.f = fb[e].x;
+        s.test = fb[e].y < 0;
+        s.body = s.test ? ~fb[e].y : fb[e].y;
+        return s;
+    }
+};
+static_assert(LEVELS_MAX % 2 == 0, "levels in pairs");
+
+// The terms of the staged sources e0, e0 + step, .. below n: the wave marks up to 64 of them per
+// target, then every lane works through its own marks.  (With the term behind the test a wave does
+// it for almost every source, for a quarter of its lanes.)
+template <int N>
+__device__ __forceinline__ void lv_sources(const LevelKickArgs &a, const LvTarget &me, int lv, const LvStage<N> &stage,
+                                           int e0, int step, int n, double &ax, double &ay, double &az, int2 *buf,
                                            int &fill)
 {
-    CD *SX = (CD *)t.X;
-    CD *SY = (CD *)t.Y;
-    CD *SZ = (CD *)t.Z;
-    CD *SR = (CD *)t.rc;
-    const size_t up = (size_t)(lv - 1) * t.cap_M;
-    int j = jb;
-    for (; j + 4 <= je; j += 4) {
-        double dx[4], dy[4], dz[4], ru[4];
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            dx[v] = SX[j + v] - me.x;
-            dy[v] = SY[j + v] - me.y;
-            dz[v] = SZ[j + v] - me.z;
-            ru[v] = SR[up + j + v];
+    for (int b = e0; b < n; b += 64 * step) {
+        unsigned long long m = 0;
+        for (int k = 0; k < 64 && b + k * step < n; ++k)
+            if (lv_inside(me, stage.get(b + k * step))) m |= 1ull << k;
+        while (__ballot(m != 0)) {
+            const bool has = m != 0;
+            const int k = has ? __builtin_ctzll(m) : 0;
+            m &= m - 1; // (zero stays zero)
+            lv_source(a, me, lv, has, stage.get(b + k * step), ax, ay, az, buf, fill);
         }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) lv_source(t, a, me, lv, j + v, dx[v], dy[v], dz[v], ru[v], ax, ay, az, buf, fill);
     }
-    for (; j < je; ++j)
-        lv_source(t, a, me, lv, j, SX[j] - me.x, SY[j] - me.y, SZ[j] - me.z, SR[up + j], ax, ay, az, buf, fill);
 }
 
 // Groups of more than one tile: one workgroup of W waves per target tile (tiles listed first
-// in t.tl).
+// in t.tl).  Bound by the FP64 arithmetic of the pairs.  A tile's own radius around its box holds
+// about half of the sources of the tiles it touches, so they are sorted out first, a lane each, and
+// staged in LDS for the marks and the terms (lv_sources).  Kicks of 40322 bodies: 62 us with every
+// source of the tiles through scalar loads and the term behind the test; 55 with the sources sorted
+// out; 42 with marks.
+constexpr int LV_CAND = 32; // source tiles at a time
 template <int W>
 __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles t, LevelKickArgs a)
 {
-    __shared__ double red[3][W][LT_TILE];
-    __shared__ int near_tile[BIG_TILES_PER_GROUP];
+    __shared__ uint16_t near_tile[BIG_TILES_PER_GROUP];
+    __shared__ uint16_t live[LV_CAND * LT_TILE]; // (source tile, source), in order
+    __shared__ union {
+        LvStage<W * LT_TILE> stage;
+        double red[3][W][LT_TILE]; // once the sources are done
+    } S;
     __shared__ int wave_cnt[W];
     __shared__ int2 pair_buf[W][LV_BUF];
     const int me = t.tl[blockIdx.x];
@@ -232,49 +295,82 @@ __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles
     const double cut = t.cut2[g] * (1.0 + 0x1p-30);
     const double *bt = t.bb + (size_t)me * 8;
     const double tlx = bt[0], tly = bt[1], tlz = bt[2], thx = bt[3], thy = bt[4], thz = bt[5];
-    // source tiles of the group in reach: one test per thread (in passes of W * 64 tiles),
-    // ordered compaction
-    int n_near = 0;
-    for (int t0 = 0; t0 < nt; t0 += W * LT_TILE) {
-        bool near = false;
-        const int tt = t0 + (int)threadIdx.x;
-        if (tt < nt) {
-            const double *bs = t.bb + (size_t)(tf + tt) * 8;
-            const double gx = fmax(0.0, fmax(bs[0] - thx, tlx - bs[3]));
-            const double gy = fmax(0.0, fmax(bs[1] - thy, tly - bs[4]));
-            const double gz = fmax(0.0, fmax(bs[2] - thz, tlz - bs[5]));
-            near = (gx * gx + gy * gy) + gz * gz <= cut;
-        }
-        const unsigned long long bal = __ballot(near);
+    const auto outside = [&](double lx, double ly, double lz, double hx, double hy, double hz) {
+        const double gx = fmax(0.0, fmax(lx - thx, tlx - hx));
+        const double gy = fmax(0.0, fmax(ly - thy, tly - hy));
+        const double gz = fmax(0.0, fmax(lz - thz, tlz - hz));
+        return (gx * gx + gy * gy) + gz * gz;
+    };
+    // the place of a thread's item in the order of the threads after n_all earlier ones
+    const auto place = [&](bool is, int &n_all) {
+        const unsigned long long bal = __ballot(is);
         if (lane == 0) wave_cnt[wave] = __popcll(bal);
         __syncthreads();
-        int base = n_near;
+        int pos = n_all + __popcll(bal & ((1ull << lane) - 1));
         for (int w = 0; w < W; ++w) {
-            if (w < wave) base += wave_cnt[w];
-            n_near += wave_cnt[w];
+            if (w < wave) pos += wave_cnt[w];
+            n_all += wave_cnt[w];
         }
-        if (near) near_tile[base + __popcll(bal & ((1ull << lane) - 1))] = tt;
         __syncthreads();
+        return pos;
+    };
+    // source tiles of the group in reach: one test per thread (in passes of W * 64 tiles)
+    int n_near = 0;
+    for (int t0 = 0; t0 < nt; t0 += W * LT_TILE) {
+        const int tt = t0 + (int)threadIdx.x;
+        bool near = false;
+        if (tt < nt) {
+            const double *bs = t.bb + (size_t)(tf + tt) * 8;
+            near = outside(bs[0], bs[1], bs[2], bs[3], bs[4], bs[5]) <= cut;
+        }
+        const int pos = place(near, n_near);
+        if (near) near_tile[pos] = (uint16_t)tt;
     }
+    __syncthreads();
     int2 *buf = pair_buf[wave];
     int fill = 0;
     double ax = 0.0, ay = 0.0, az = 0.0;
-    for (int u = wave; u < 4 * n_near; u += W) {
-        const int st = near_tile[u >> 2];
-        const int jb = o + LT_TILE * st + 16 * (u & 3), je = min(jb + 16, o + nb);
-        lv_sources(t, a, tg, lv, jb, je, ax, ay, az, buf, fill);
+    const double *up = t.rc + (size_t)(lv - 1) * t.cap_M;
+    const double up2 = wave_maxv(tg.valid ? sq_rn(tg.rc_up) : 0.0);
+    for (int c0 = 0; c0 < n_near; c0 += LV_CAND) {
+        int n_live = 0;
+        for (int c = 0; c < min(LV_CAND, n_near - c0); c += W) { // a source tile per wave, a source per lane
+            bool is = false;
+            if (c0 + c + wave < n_near && c + wave < LV_CAND) {
+                const int s = LT_TILE * near_tile[c0 + c + wave] + lane;
+                if (s < nb) {
+                    const int f = o + s;
+                    const double x = t.X[f], y = t.Y[f], z = t.Z[f];
+                    is = outside(x, y, z, x, y, z) <= fmax(up2, sq_rn(up[f])) * (1.0 + 0x1p-30);
+                }
+            }
+            const int pos = place(is, n_live);
+            if (is) live[pos] = (uint16_t)((c + wave) * LT_TILE + lane);
+        }
+        __syncthreads();
+        for (int l0 = 0; l0 < n_live; l0 += W * LT_TILE) {
+            const int n = min(W * LT_TILE, n_live - l0);
+            if ((int)threadIdx.x < n) {
+                const int e = live[l0 + threadIdx.x];
+                S.stage.put(threadIdx.x, lv_load(t, lv, o + LT_TILE * near_tile[c0 + e / LT_TILE] + e % LT_TILE));
+            }
+            __syncthreads();
+            lv_sources(a, tg, lv, S.stage, wave, W, n, ax, ay, az, buf, fill);
+            __syncthreads(); // stage (and at last live) is rewritten
+        }
+        if (n_live == 0) __syncthreads(); // near_tile has been read by every wave
     }
     lv_flush(a, buf, fill);
-    red[0][wave][lane] = ax;
-    red[1][wave][lane] = ay;
-    red[2][wave][lane] = az;
+    S.red[0][wave][lane] = ax;
+    S.red[1][wave][lane] = ay;
+    S.red[2][wave][lane] = az;
     __syncthreads();
     if (wave != 0 || !tg.valid) return;
     double sx = 0.0, sy = 0.0, sz = 0.0;
     for (int w = 0; w < W; ++w) {
-        sx += red[0][w][lane];
-        sy += red[1][w][lane];
-        sz += red[2][w][lane];
+        sx += S.red[0][w][lane];
+        sy += S.red[1][w][lane];
+        sz += S.red[2][w][lane];
     }
     a.vx[tg.body] += a.tau * sx;
     a.vy[tg.body] += a.tau * sy;
@@ -285,11 +381,14 @@ __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles
 __global__ __launch_bounds__(LT_TILE) void level_tile_one_kernel(LevelTiles t, LevelKickArgs a)
 {
     __shared__ int2 buf[LV_BUF];
+    __shared__ LvStage<LT_TILE> stage;
     const int4 tile = t.tiles[t.tl[t.n_multi + blockIdx.x]];
     const LvTarget tg = lv_target(t, tile, a.level);
+    if (tg.valid) stage.put(threadIdx.x, lv_load(t, a.level, tg.f));
+    __syncthreads();
     int fill = 0;
     double ax = 0.0, ay = 0.0, az = 0.0;
-    lv_sources(t, a, tg, a.level, tile.y, tile.y + tile.z, ax, ay, az, buf, fill);
+    lv_sources(a, tg, a.level, stage, 0, 1, tile.z, ax, ay, az, buf, fill);
     lv_flush(a, buf, fill);
     if (!tg.valid) return;
     a.vx[tg.body] += a.tau * ax;
@@ -317,8 +416,8 @@ hipError_t launch_level_kick(const LevelTiles &t, const LevelKickArgs &a, const 
     if (t.n_multi > 0) {
         if (waves == 16)
             level_tiles_kick_kernel<16><<<t.n_multi, LT_TILE * 16, 0, stream>>>(t, a);
-        else if (waves == 8)
-            level_tiles_kick_kernel<8><<<t.n_multi, LT_TILE * 8, 0, stream>>>(t, a);
+        else if (waves == 4)
+            level_tiles_kick_kernel<4><<<t.n_multi, LT_TILE * 4, 0, stream>>>(t, a);
         else
             return hipErrorInvalidValue;
     }

@@ -584,10 +584,135 @@ __device__ void build_groups(const GroupBuild &g, GroupLds &S)
     list_wg_groups(g.group_start, ng, g.wg_list, S.cnt);
 }
 
-__global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(GroupBuild g)
+// The end of a list's import: its length, or 0 with FLAG_BADPAIR when a pair was invalid.
+__device__ __forceinline__ void import_finish(const PairImport &p)
+{
+    const int c = *p.src_count;
+    const bool good = !*p.bad && c >= 0;
+    *p.dst_count = good ? c : 0;
+    if (!good) atomicOr(p.flags, FLAG_BADPAIR);
+    else if (c > p.cap) atomicOr(p.flags, FLAG_CAPACITY);
+    *p.bad = 0;
+}
+
+__global__ __launch_bounds__(64) void import_finish_kernel(PairImport p)
+{
+    if (threadIdx.x == 0) import_finish(p);
+}
+
+__global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(GroupBuild g, PairImport p)
 {
     __shared__ GroupLds S;
+    if (p.src) {
+        if (threadIdx.x == 0) import_finish(p);
+        __syncthreads();
+    }
     build_groups(g, S);
+}
+
+// What a drift outside a step starts from, in one launch: the momentum sums of the items' blocks,
+// and, from the workgroups after them, the check and copy of a caller's pair list.
+__global__ __launch_bounds__(CE_THREADS) void drift_open_kernel(const WorkItem *items, const double *vx,
+                                                                const double *vy, const double *vz, const double *m,
+                                                                StepMomentum pm, PairImport im)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if ((int)blockIdx.x >= pm.n_blocks) {
+        const int n = min(*im.src_count, im.cap), first = (blockIdx.x - pm.n_blocks) * CE_THREADS + tid;
+        bool ok = true;
+        for (int p = first; p < n; p += (gridDim.x - pm.n_blocks) * CE_THREADS) {
+            const int i = im.src[2 * p], j = im.src[2 * p + 1];
+            const bool good = i >= 0 && i < j && j < im.n_total && im.sys_of[i] == im.sys_of[j];
+            ok = ok && good;
+            im.dst[2 * p] = good ? i : 0;
+            im.dst[2 * p + 1] = good ? j : 0;
+        }
+        if (!ok) atomicOr(im.bad, 1);
+        return;
+    }
+    __shared__ double red[3][CLOSE_WAVES];
+    const CloseBlock blk = pm.blocks[blockIdx.x];
+    double p[3] = {0.0, 0.0, 0.0};
+    if (wave < blk.n) {
+        const WorkItem w = items[blk.item + wave];
+        if (lane < w.ni) {
+            const int i = w.i0 + lane;
+            const double mi = m[i];
+            p[0] = mi * vx[i];
+            p[1] = mi * vy[i];
+            p[2] = mi * vz[i];
+        }
+    }
+    for (int q = 0; q < 3; ++q) {
+        p[q] = wave_sum(p[q]);
+        if (lane == 0) red[q][wave] = p[q];
+    }
+    __syncthreads();
+    if (tid < 3) {
+        double s = 0.0;
+        for (int k = 0; k < CLOSE_WAVES; ++k) s += red[tid][k];
+        pm.kick[3 * (size_t)blockIdx.x + tid] = s;
+    }
+}
+
+// A thread's part of a system's momentum after the drift: by item, and by group from the system's
+// first group on, so that the order of the sum depends on the system alone (groups are in system
+// order).  gs: the system of group tid, loaded ahead; first: a word of LDS.
+__device__ __forceinline__ void drift_momentum(const StepMomentum &pm, const CloseBlock &blk, int G, int gs, int *first,
+                                               double P[3])
+{
+    const int tid = threadIdx.x;
+    if (tid == 0) *first = G;
+    __syncthreads();
+    for (int k = tid; k < G; k += CE_THREADS) {
+        if (k != tid) gs = pm.group_sys[k];
+        if (gs == blk.sys) {
+            atomicMin(first, k);
+            break;
+        }
+    }
+    __syncthreads();
+    for (int k = *first + tid; k < G && pm.group_sys[k] == blk.sys; k += CE_THREADS)
+        for (int q = 0; q < 3; ++q) P[q] += pm.group[3 * (size_t)k + q];
+}
+
+// The second half of the Sun drift after a drift outside a step: positions + tau P / Mstar.
+__global__ __launch_bounds__(CE_THREADS) void drift_close_kernel(const WorkItem *items, double *x, double *y, double *z,
+                                                                 StepMomentum pm)
+{
+    __shared__ double red[3][CLOSE_WAVES];
+    __shared__ int first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const CloseBlock blk = pm.blocks[blockIdx.x];
+    const int G = *pm.group_n, gs = pm.group_sys[tid];
+    const WorkItem w = wave < blk.n ? items[blk.item + wave] : WorkItem{0, 0, 0, 0};
+    const bool on = lane < w.ni;
+    const int i = w.i0 + lane;
+    double P[3] = {0.0, 0.0, 0.0}, X[3] = {0.0, 0.0, 0.0};
+    for (int k = blk.f0 + tid; k < blk.f1; k += CE_THREADS)
+        for (int q = 0; q < 3; ++q) P[q] += pm.kepler[3 * (size_t)k + q];
+    if (on) {
+        X[0] = x[i];
+        X[1] = y[i];
+        X[2] = z[i];
+    }
+    drift_momentum(pm, blk, G, gs, &first, P);
+    for (int q = 0; q < 3; ++q) {
+        P[q] = wave_sum(P[q]);
+        if (lane == 0) red[q][wave] = P[q];
+    }
+    __syncthreads();
+    const double f = pm.tau / blk.mstar;
+    for (int q = 0; q < 3; ++q) {
+        double s = 0.0;
+        for (int k = 0; k < CLOSE_WAVES; ++k) s += red[q][k];
+        X[q] += f * s;
+    }
+    if (on) {
+        x[i] = X[0];
+        y[i] = X[1];
+        z[i] = X[2];
+    }
 }
 
 // A system's sum over part[3 first[s] ..), by every lane of a wave.
@@ -622,7 +747,7 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
     // first round: the block, the drift's groups (one per thread; more below)
     const CloseBlock blk = pm.blocks[blockIdx.x - 1];
     const int G = shift ? *pm.group_n : 0;
-    int gs = shift ? pm.group_sys[tid] : -1;
+    const int gs = shift ? pm.group_sys[tid] : -1;
     // second round: the item, its tasks, P after the drift by item
     const int it = blk.item + wave / parts;
     const bool mine = wave / parts < blk.n;
@@ -649,20 +774,7 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
     if (mine) item_shares(a, it, lane, t, part, parts);
     for (int q = 0; q < 3; ++q) share[q][wave][lane] = t[q];
     if (shift) {
-        // the groups' momenta, from the system's first group on, so that the order of the sum
-        // depends on the system alone (groups are in system order)
-        if (tid == 0) S.ng = G;
-        __syncthreads();
-        for (int k = tid; k < G; k += CE_THREADS) {
-            if (k != tid) gs = pm.group_sys[k];
-            if (gs == blk.sys) {
-                atomicMin(&S.ng, k);
-                break;
-            }
-        }
-        __syncthreads();
-        for (int k = S.ng + tid; k < G && pm.group_sys[k] == blk.sys; k += CE_THREADS)
-            for (int q = 0; q < 3; ++q) P[q] += pm.group[3 * (size_t)k + q];
+        drift_momentum(pm, blk, G, gs, &S.ng, P);
         for (int q = 0; q < 3; ++q) {
             P[q] = wave_sum(P[q]);
             if (lane == 0) red[q][wave] = P[q];
@@ -1436,8 +1548,8 @@ __global__ __launch_bounds__(BS_LANES) __attribute__((amdgpu_waves_per_eu(2))) v
     double sh[3], p[3] = {0.0, 0.0, 0.0};
     if ((int)blockIdx.x >= bs_blocks) {
         const int it = blockIdx.x - bs_blocks;
-        if (it == 0 && pm.clear && lane == 0) {
-            *pm.clear = 0;
+        if (it == 0 && pm.group_n && lane == 0) {
+            if (pm.clear) *pm.clear = 0;
             *pm.group_n = *n_groups;
         }
         const WorkItem w = items[it];
@@ -1652,9 +1764,34 @@ hipError_t launch_uf_slots(int n_members_max, const int32_t *members, const int3
     return hipGetLastError();
 }
 
-hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream)
+static int import_blocks(const PairImport &p) { return std::max(1, std::min(256, (p.cap + CE_THREADS - 1) / CE_THREADS)); }
+
+hipError_t launch_import_pairs(const PairImport &p, hipStream_t stream)
 {
-    ce_groups_kernel<<<1, CE_THREADS, 0, stream>>>(g);
+    drift_open_kernel<<<import_blocks(p), CE_THREADS, 0, stream>>>(nullptr, nullptr, nullptr, nullptr, nullptr,
+                                                                   StepMomentum{}, p);
+    import_finish_kernel<<<1, 64, 0, stream>>>(p);
+    return hipGetLastError();
+}
+
+hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream, const PairImport *import)
+{
+    ce_groups_kernel<<<1, CE_THREADS, 0, stream>>>(g, import ? *import : PairImport{});
+    return hipGetLastError();
+}
+
+hipError_t launch_drift_open(const WorkItem *items, const double *vx, const double *vy, const double *vz,
+                             const double *m, const StepMomentum &pm, const PairImport *import, hipStream_t stream)
+{
+    const int grid = pm.n_blocks + (import ? import_blocks(*import) : 0);
+    drift_open_kernel<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
+    return hipGetLastError();
+}
+
+hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
+                              hipStream_t stream)
+{
+    drift_close_kernel<<<pm.n_blocks, CE_THREADS, 0, stream>>>(items, x, y, z, pm);
     return hipGetLastError();
 }
 

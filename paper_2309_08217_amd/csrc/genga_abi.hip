@@ -420,9 +420,13 @@ int run_levels(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s);
 
 // The drift's second stream and its events, made on first use outside graph capture; nullptr
 // while `s` is being captured or if making them fails (the drift's launches then stay on one
-// stream, with the same results).
+// stream, with the same results).  Only with large groups on, where groups of 9..64 members come by
+// the hundred (levels of 40322 bodies: 6.35 ms a step against 6.66 on one stream): the events cost
+// more than an empty launch takes (drift of 20040 bodies 76 us on one stream, 99 on two; 64 discs of
+// 2000 to 8000 bodies with some such groups 1.74 and 1.72 ms a step).
 const DriftSide *drift_side(genga_ctx *ctx, hipStream_t s)
 {
+    if (!ctx->large_groups) return nullptr;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) return nullptr;
     DriftSide &d = ctx->side;
@@ -968,7 +972,6 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
     StepMomentum pm = ctx->pm;
     pm.tau = 0.5 * dt;
     pm.clear = ctx->pair_count;
-    const DriftSide *side = large ? nullptr : drift_side(ctx, s);
     for (int k = 1, rec = 0; k <= nsteps; ++k) {
         const bool last = k == nsteps;
         if (large && (rc = build_groups_large(ctx, s))) return rc;
@@ -979,7 +982,7 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
         } else {
             HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit,
                                  dt, ctx->members, ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, 0,
-                                 large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, side, &pm, true));
+                                 large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, nullptr, &pm, true));
         }
         if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, parts ? 0.0 : 0.5 * dt, !last && !large, s)))
             return rc;
@@ -1654,9 +1657,26 @@ int genga_drift(genga_ctx *ctx, genga_bodies *b, double dt, const int32_t *pairs
     if (pairs && !d_count) return fail(GENGA_ERR_ARG, "a pair list needs its device count");
     hipStream_t s = (hipStream_t)stream;
     ctx->last_stream = s;
+    PairImport im;
     if (pairs)
-        HIP_TRY(launch_import_pairs(ctx->L, pairs, d_count, ctx->pairs, ctx->pair_count, ctx->pair_cap,
-                                    ctx->import_bad, ctx->flags, s));
+        im = PairImport{ctx->L.sys_of, ctx->L.n_total, pairs,         d_count,        ctx->pairs,
+                        ctx->pair_count, ctx->pair_cap, ctx->import_bad, ctx->flags};
+    if (!ctx->col.mass && !ctx->large_groups && ctx->L.n_total > 0) {
+        // four launches: the list and the momentum, the groups, the drift, the last shift (as
+        // launches of their own, and with a second stream, 20040 bodies with their list took 110 us, now 76)
+        ctx->list_valid = false;
+        StepMomentum pm = ctx->pm;
+        pm.tau = 0.5 * dt;
+        const PairImport *imp = pairs ? &im : nullptr;
+        HIP_TRY(launch_drift_open(ctx->items, b->vx, b->vy, b->vz, b->m, pm, imp, s));
+        HIP_TRY(launch_ce_groups(group_build(ctx), s, imp));
+        HIP_TRY(launch_drift(ctx->L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, dt,
+                             ctx->members, ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, 0, 0,
+                             ctx->wg_list, s, nullptr, 1, true, nullptr, &pm, true));
+        HIP_TRY(launch_drift_close(ctx->items, b->x, b->y, b->z, pm, s));
+        return GENGA_OK;
+    }
+    if (pairs) HIP_TRY(launch_import_pairs(im, s));
     return enqueue_drift(ctx, b, dt, s);
 }
 

@@ -245,7 +245,26 @@ __device__ inline void system_momentum(const int32_t *chunk_first, const double 
         for (int q = 0; q < 3; ++q) P[q] += red[q][w];
     __syncthreads();
 }
-hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream);
+// A caller's pair list src[min(*src_count, cap)][2] checked (0 <= i < j < n_total, one system)
+// and copied to dst; *dst_count = *src_count, or 0 with FLAG_BADPAIR when a pair is invalid
+// (bad: a device word, zero on entry and left zero).
+struct PairImport {
+    const int32_t *sys_of = nullptr;
+    int32_t n_total = 0;
+    const int32_t *src = nullptr, *src_count = nullptr;
+    int32_t *dst = nullptr, *dst_count = nullptr;
+    int32_t cap = 0;
+    int32_t *bad = nullptr, *flags = nullptr;
+};
+hipError_t launch_import_pairs(const PairImport &p, hipStream_t stream);
+// import (may be null): the end of an import that launch_drift_open began.
+hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream, const PairImport *import = nullptr);
+// A drift outside a step: what comes before launch_ce_groups and launch_drift (the momentum sums
+// for its first shift, the pairs of an import), and the second half of the Sun drift after it.
+hipError_t launch_drift_open(const WorkItem *items, const double *vx, const double *vy, const double *vz,
+                             const double *m, const StepMomentum &pm, const PairImport *import, hipStream_t stream);
+hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
+                              hipStream_t stream);
 // Kepler drift of the bodies outside encounter groups and Bulirsch-Stoer of each group of up
 // to CE_MAX_GROUP members (groups of 9 and more in a launch of their own, listed in wg_list:
 // [0] their number, then the groups; room for bs_blocks + 1); clears member_slot for the next
@@ -474,11 +493,6 @@ hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tas
                          const double *x, const double *y, const double *z, const double *vx, const double *vy,
                          const double *vz, const double *m, const double *ax, const double *ay, const double *az,
                          double vshift, double *partial, double *out, hipStream_t stream);
-// A caller's pair list src[min(*src_count, cap)][2] checked (0 <= i < j < n_total, one system)
-// and copied to dst; *dst_count = *src_count, or 0 with FLAG_BADPAIR when a pair is invalid
-// (bad: a device word, zero on entry and left zero).
-hipError_t launch_import_pairs(const Layout &L, const int32_t *src, const int32_t *src_count, int32_t *dst,
-                               int32_t *dst_count, int32_t cap, int32_t *bad, int32_t *flags, hipStream_t stream);
 hipError_t launch_sort_pairs(const int32_t *src, const int32_t *src_count, int32_t src_cap,
                              int32_t *dst, int32_t dst_cap, int32_t *dst_count, uint64_t *keys,
                              int32_t *flags, hipStream_t stream);

@@ -316,17 +316,6 @@ __global__ __launch_bounds__(256) void uf_union_kernel(const int32_t *pairs, con
     }
 }
 
-// members[k] -> member_slot, and lab back to -1 (clean for the next step)
-__global__ __launch_bounds__(256) void uf_slots_kernel(const int32_t *members, const int32_t *n_members,
-                                                       int32_t *member_slot, int32_t *lab)
-{
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= *n_members) return;
-    const int b = members[k];
-    member_slot[b] = k;
-    lab[b] = -1;
-}
-
 // A list of up to GF_PAIRS pairs (a disc whose r_crit is a few Hill radii has tens to hundreds)
 // is joined in LDS: a thread per pair, a hash table of the bodies, union-find over its slots; the
 // rounds' dependent loads were most of the builder's 6-14 us when the labels were in global memory.
@@ -1523,6 +1512,40 @@ __device__ __forceinline__ void store_momentum(double *out, int k, const double 
     }
 }
 
+// The Sun drift's halves around a drift in parts: the shift from the sums that the kick left, and
+// the sums for the shift after it, a wave per item.
+__global__ __launch_bounds__(64) void sun_shift_items_kernel(const WorkItem *items, const double *mstar, double *x,
+                                                             double *y, double *z, StepMomentum pm)
+{
+    const WorkItem w = items[blockIdx.x];
+    const int lane = threadIdx.x, i = w.i0 + lane;
+    double sh[3];
+    sun_shift_of(pm, mstar, w.sys, sh);
+    if (lane >= w.ni) return;
+    x[i] += sh[0];
+    y[i] += sh[1];
+    z[i] += sh[2];
+}
+
+__global__ __launch_bounds__(64) void drifted_kernel(const WorkItem *items, const double *vx, const double *vy,
+                                                     const double *vz, const double *m, StepMomentum pm)
+{
+    const WorkItem w = items[blockIdx.x];
+    const int lane = threadIdx.x, i = w.i0 + lane;
+    double p[3] = {0.0, 0.0, 0.0};
+    if (lane < w.ni) {
+        const double mi = m[i];
+        p[0] = mi * vx[i];
+        p[1] = mi * vy[i];
+        p[2] = mi * vz[i];
+    }
+    store_momentum(pm.kepler, blockIdx.x, p);
+    if (blockIdx.x == 0 && lane == 0) {
+        *pm.clear = 0;
+        *pm.group_n = 0;
+    }
+}
+
 // The drift over dt: blocks [0, bs_blocks) integrate the encounter groups with Bulirsch-Stoer, the blocks after them Kepler-drift an item of up to 64 bodies each and skip the group
 // members.  Each body is read and written by one block only.
 template <bool LV>
@@ -1756,14 +1779,6 @@ hipError_t launch_uf_union(const int32_t *pairs, const int32_t *pair_count, int3
     return hipGetLastError();
 }
 
-hipError_t launch_uf_slots(int n_members_max, const int32_t *members, const int32_t *n_members,
-                           int32_t *member_slot, int32_t *lab, hipStream_t stream)
-{
-    if (n_members_max <= 0) return hipSuccess;
-    uf_slots_kernel<<<(n_members_max + 255) / 256, 256, 0, stream>>>(members, n_members, member_slot, lab);
-    return hipGetLastError();
-}
-
 static int import_blocks(const PairImport &p) { return std::max(1, std::min(256, (p.cap + CE_THREADS - 1) / CE_THREADS)); }
 
 hipError_t launch_import_pairs(const PairImport &p, hipStream_t stream)
@@ -1785,6 +1800,20 @@ hipError_t launch_drift_open(const WorkItem *items, const double *vx, const doub
 {
     const int grid = pm.n_blocks + (import ? import_blocks(*import) : 0);
     drift_open_kernel<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
+    return hipGetLastError();
+}
+
+hipError_t launch_sun_shift(const WorkItem *items, int n_items, const double *mstar, double *x, double *y, double *z,
+                            const StepMomentum &pm, hipStream_t stream)
+{
+    sun_shift_items_kernel<<<n_items, 64, 0, stream>>>(items, mstar, x, y, z, pm);
+    return hipGetLastError();
+}
+
+hipError_t launch_drifted(const WorkItem *items, int n_items, const double *vx, const double *vy, const double *vz,
+                          const double *m, const StepMomentum &pm, hipStream_t stream)
+{
+    drifted_kernel<<<n_items, 64, 0, stream>>>(items, vx, vy, vz, m, pm);
     return hipGetLastError();
 }
 

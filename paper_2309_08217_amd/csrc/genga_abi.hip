@@ -105,7 +105,7 @@ struct genga_ctx {
     hipGraphExec_t big_exec[64] = {};
     hipGraphExec_t big_exec_list[64] = {}; // the same on the list path
     int32_t ce_cap = 0;                // members / group_start capacity
-    std::vector<int32_t> gs_h;         // group_start copied to the host
+    GroupHeader groups_h{};            // large mode: sizes of the groups of the last pair list
     // host scratch of the grouping and tile ordering, kept so that the per-call vectors of
     // n_total entries are not allocated (and faulted in) again on every call
     OrderWork ow;                      // the device ring / azimuth ordering of the large groups
@@ -408,15 +408,11 @@ GroupBuild group_build(const genga_ctx *ctx)
                       ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->wg_list, ctx->flags};
 }
 
-int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, const std::vector<int32_t> &gs,
-                   const std::vector<int32_t> &mem_h, const int32_t *members_dev, int min_nb,
-                   const std::vector<int32_t> *prev = nullptr);
+int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, const int32_t *members_dev);
+int upload_big_layout(genga_ctx *ctx, hipStream_t s, const std::vector<int32_t> &gs, const std::vector<int32_t> &mem,
+                      int min_nb, const std::vector<int32_t> &prev);
 int build_groups_large(genga_ctx *ctx, hipStream_t s);
 int run_levels(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s);
-
-// Sun drift (dt/2), Kepler / Bulirsch-Stoer (dt), Sun drift (dt/2).  With defer_shift the
-// last position shift is left to the next kick's source-record pass (only the momentum
-// partials are formed here); that kick must be given shift_tau = dt/2.
 
 // The drift's second stream and its events, made on first use outside graph capture; nullptr
 // while `s` is being captured or if making them fails (the drift's launches then stay on one
@@ -442,8 +438,34 @@ const DriftSide *drift_side(genga_ctx *ctx, hipStream_t s)
     return d.stream ? &d : nullptr;
 }
 
-int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, bool defer_shift = false,
-                  bool groups_built = false)
+// The Kepler drift, the groups' Bulirsch-Stoer steps and the levels, on groups already built.
+int enqueue_drift_parts(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s)
+{
+    const Layout &L = ctx->L;
+    const bool large = ctx->large_groups != 0;
+    // large mode: the group count is the layout's; with levels every group is integrated by the
+    // level steps (Kepler blocks only); else by default the one-workgroup group builder's maximum
+    const int bs_blocks = !large ? 0 : ctx->n_levels > 1 ? -1 : std::max(1, (int)ctx->groups_h.G);
+    HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, dt, ctx->members,
+                         ctx->group_start, large ? &ctx->gw.hdr->G : ctx->n_groups, ctx->member_slot, ctx->flags,
+                         ctx->large_groups, bs_blocks, ctx->wg_list, s, nullptr, 1, true, drift_side(ctx, s), nullptr,
+                         !large));
+    if (ctx->n_levels > 1) return run_levels(ctx, b, dt, s);
+    if (!large || ctx->groups_h.large_G == 0) return GENGA_OK;
+    BigBs &bg = ctx->big;
+    bg.G = ctx->groups_h.large_G;
+    bg.M = ctx->groups_h.large_M;
+    bg.n_tiles = ctx->groups_h.large_T;
+    if (bg.G > bg.cap_G || bg.M > bg.cap_M || bg.n_tiles > bg.cap_T)
+        return fail(GENGA_ERR_STATE, "large-group layout exceeds its allocation");
+    HIP_TRY(launch_ring_order(ctx->members, bg.k0, bg.off, bg.G, bg.M, b->x, b->y, ctx->ow, bg.body, s));
+    return run_big_groups(ctx, b, dt, s, ctx->members);
+}
+
+// Sun drift (dt/2), Kepler / Bulirsch-Stoer (dt), Sun drift (dt/2).  With defer_shift the
+// last position shift is left to the next kick's source-record pass (only the momentum
+// partials are formed here); that kick must be given shift_tau = dt/2.
+int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, bool defer_shift = false)
 {
     const Layout &L = ctx->L;
     ctx->list_valid = false;
@@ -458,28 +480,13 @@ int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, boo
         HIP_TRY(launch_collide_check(ctx->col, ctx->pairs, ctx->pair_count, ctx->pair_cap, b->x, b->y, b->z, b->vx,
                                      b->vy, b->vz, dt, s));
     }
-    int bs_blocks = 0; // default: the one-workgroup group builder's maximum
-    if (ctx->large_groups) {
-        // the groups depend on the pair list only; built first, so that a group too large
-        // for the grid-wide path is refused before any part of the drift is enqueued
-        const int rc = groups_built ? GENGA_OK : build_groups_large(ctx, s);
-        if (rc) return rc;
-        // with levels every group is integrated by the level steps: Kepler blocks only
-        bs_blocks = ctx->n_levels > 1 ? -1 : std::max(1, (int)ctx->gs_h.size() - 1);
-    }
+    int rc;
+    // the groups depend on the pair list only; built first, so that a group too large for the
+    // grid-wide path is refused before any part of the drift is enqueued
+    if (ctx->large_groups && (rc = build_groups_large(ctx, s))) return rc;
     HIP_TRY(launch_sun_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, 0.5 * dt, ctx->mom_part, s));
     if (!ctx->large_groups) HIP_TRY(launch_ce_groups(group_build(ctx), s));
-    HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, dt, ctx->members,
-                         ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, ctx->large_groups,
-                         bs_blocks, ctx->wg_list, s, nullptr, 1, true, drift_side(ctx, s), nullptr,
-                         !ctx->large_groups));
-    if (ctx->n_levels > 1) {
-        const int rc = run_levels(ctx, b, dt, s);
-        if (rc) return rc;
-    } else if (ctx->large_groups) {
-        const int rc = run_big_groups(ctx, b, dt, s, ctx->gs_h, {}, ctx->members, CE_MAX_GROUP + 1);
-        if (rc) return rc;
-    }
+    if ((rc = enqueue_drift_parts(ctx, b, dt, s))) return rc;
     if (defer_shift)
         HIP_TRY(launch_momentum(L, b->vx, b->vy, b->vz, b->m, ctx->mom_part, s));
     else
@@ -591,50 +598,53 @@ int alloc_big(genga_ctx *ctx)
     return GENGA_OK;
 }
 
-// The encounter groups of the context's pair list, for the large-group mode: members /
-// group_start / n_groups on the device, member_slot set for the drift launch.
+// The encounter groups of the context's pair list, for the large-group mode, laid out on the device
+// in body order (groups by their smallest member, members ascending) with everything the drift
+// takes from them: members / group_start / member_slot for its launch, and the tiles of every group
+// (levels) or the layout of the groups above CE_MAX_GROUP.  The host waits for the header only: with
+// the offsets read back, the layouts made on the host and sent in six copies, two steps of 6600
+// bodies in one group, of one attempt each, took 1.29 ms, now 1.10.
 int build_groups_large(genga_ctx *ctx, hipStream_t s)
 {
-    // the components of the pair list laid out on the device in body order (groups by their
-    // smallest member, members ascending), and the header and group offsets read in one wait
     const Layout &L = ctx->L;
     const int nt = L.n_total;
     GroupOut out;
     out.body = ctx->members;
     out.off = ctx->group_start;
-    const size_t ngs = (size_t)nt / 2 + 2; // groups have at least two members
-    std::vector<int32_t> &gs = ctx->gs_h;
+    out.member_slot = ctx->member_slot;
+    if (ctx->n_levels > 1) {
+        LevelTiles &T = ctx->lt[0];
+        out.off2 = T.off;
+        out.tfirst = T.tfirst;
+        out.tiles = T.tiles;
+        out.tl = T.tl;
+    } else {
+        BigBs &b = ctx->big;
+        out.large = LargeOut{b.k0, b.off, b.tfirst, b.dims, b.tiles, CE_MAX_GROUP + 1};
+    }
     HIP_TRY(launch_group_layout(L, ctx->gw, ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->lab, ctx->iota, nt, out, s));
-    gs.resize(ngs);
     HIP_TRY(hipMemcpyAsync(ctx->ghdr, ctx->gw.hdr, sizeof(GroupHeader), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(gs.data(), ctx->group_start, ngs * sizeof(int32_t), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
-    const GroupHeader h = *ctx->ghdr;
+    const GroupHeader h = ctx->groups_h = *ctx->ghdr;
     if (h.max_nb > 64 * BIG_TILES_PER_GROUP) {
-        if (nt > 0) (void)hipMemsetAsync(ctx->lab, 0xff, (size_t)nt * sizeof(int32_t), s);
-        gs.assign(1, 0);
+        ctx->groups_h = GroupHeader{};
+        if (nt > 0) (void)hipMemsetAsync(ctx->member_slot, 0xff, (size_t)nt * sizeof(int32_t), s);
         return fail(GENGA_ERR_CAPACITY, "an encounter group of %d bodies (at most %d)", h.max_nb,
                     64 * BIG_TILES_PER_GROUP);
     }
-    gs.resize((size_t)h.G + 1);
-    // the drift's group count and the members' slots (their labels back to -1)
-    HIP_TRY(hipMemcpyAsync(ctx->n_groups, &ctx->gw.hdr->G, sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(launch_uf_slots(nt, ctx->members, &ctx->gw.hdr->M, ctx->member_slot, ctx->lab, s));
     return GENGA_OK;
 }
-// The groups of gs / mem with at least min_nb members, cut into tiles of 64, each group's
-// members ordered so that 64 consecutive ones are close together and force tiles can skip
-// distant tiles.  With prev (an order of bodies that contains every member, e.g. the parent
-// level's): in that order, which keeps its locality, into o.body.  Without: o.body is left
-// empty and the caller orders the members on the device (launch_ring_order: rings of distance
-// to the star, then azimuth).
+
+// The groups of gs / mem with at least min_nb members, cut into tiles of 64, each group's members
+// in the order of prev (an order of bodies that contains every member, e.g. the parent level's,
+// where 64 consecutive ones are close together), into o.body.
 struct TileOrder {
     std::vector<int32_t> k0, off{0}, tfirst{0}, body;
     std::vector<int4> tiles;
 };
 
 int order_tiles(genga_ctx *ctx, const std::vector<int32_t> &gs, const std::vector<int32_t> &mem, int min_nb,
-                TileOrder &o, const std::vector<int32_t> *prev = nullptr)
+                TileOrder &o, const std::vector<int32_t> &prev)
 {
     const int ng = (int)gs.size() - 1;
     for (int g = 0; g < ng; ++g) {
@@ -649,7 +659,7 @@ int order_tiles(genga_ctx *ctx, const std::vector<int32_t> &gs, const std::vecto
     for (size_t gi = 0; gi + 1 < o.tfirst.size(); ++gi)
         if (o.tfirst[gi + 1] - o.tfirst[gi] > BIG_TILES_PER_GROUP)
             return fail(GENGA_ERR_CAPACITY, "an encounter group of more than %d bodies", 64 * BIG_TILES_PER_GROUP);
-    if (o.k0.empty() || !prev) return GENGA_OK;
+    if (o.k0.empty()) return GENGA_OK;
     const size_t nt = (size_t)ctx->L.n_total;
     o.body.resize((size_t)o.off.back());
     {
@@ -658,7 +668,7 @@ int order_tiles(genga_ctx *ctx, const std::vector<int32_t> &gs, const std::vecto
             for (int l = 0; l < o.off[gi + 1] - o.off[gi]; ++l) grp[mem[o.k0[gi] + l]] = (int32_t)gi;
             fill[gi] = o.off[gi];
         }
-        for (int32_t bi : *prev)
+        for (int32_t bi : prev)
             if (grp[bi] >= 0) o.body[fill[grp[bi]]++] = bi;
         for (size_t gi = 0; gi < o.k0.size(); ++gi)
             if (fill[gi] != o.off[gi + 1]) return fail(GENGA_ERR_STATE, "tile order misses group members");
@@ -766,7 +776,8 @@ int run_level(genga_ctx *ctx, genga_bodies *b, int level, double tau, hipStream_
                     HIP_TRY(hipMemcpyAsync(prev.data(), T.body, prev.size() * sizeof(int32_t),
                                            hipMemcpyDeviceToHost, s));
                     HIP_TRY(hipStreamSynchronize(s));
-                    if ((rc = run_big_groups(ctx, b, h, s, cgs, cmem, ctx->lv_mem, CE_MAX_GROUP + 1, &prev)))
+                    if ((rc = upload_big_layout(ctx, s, cgs, cmem, CE_MAX_GROUP + 1, prev)) ||
+                        (rc = run_big_groups(ctx, b, h, s, ctx->lv_mem)))
                         return rc;
                 }
             } else {
@@ -783,61 +794,33 @@ int run_level(genga_ctx *ctx, genga_bodies *b, int level, double tau, hipStream_
     return GENGA_OK;
 }
 
-// Level 1 over dt for the groups of the context's encounter list (built by enqueue_drift): the
-// groups are ordered by ring and azimuth on the host, once per step, and laid out in tiles; the
-// deeper levels inherit that order through the device layout.
+// Level 1 over dt for the groups of the context's encounter list (build_groups_large): their members
+// are ordered by ring and azimuth, once per step; the deeper levels inherit that order through the
+// device layout.
 int run_levels(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s)
 {
-    const std::vector<int32_t> &pgs = ctx->gs_h;
+    const GroupHeader &h = ctx->groups_h;
     LevelTiles &T = ctx->lt[0];
-    T.G = T.M = T.n_tiles = T.n_multi = 0;
-    if ((int)pgs.size() <= 1) return GENGA_OK;
-    TileOrder o;
-    int rc = order_tiles(ctx, pgs, {}, 2, o);
-    if (rc) return rc;
-    if ((int)o.k0.size() > ctx->lt_cap_G || o.off.back() > T.cap_M || (int)o.tiles.size() > ctx->lt_cap_T)
-        return fail(GENGA_ERR_STATE, "level layout exceeds its allocation");
-    T.G = (int32_t)o.k0.size();
-    T.M = o.off.back();
-    T.n_tiles = (int32_t)o.tiles.size();
+    T.G = h.G;
+    T.M = h.M;
+    T.n_tiles = h.n_tiles;
+    T.n_multi = h.n_multi;
     if (T.G == 0) return GENGA_OK;
-    // tiles of the groups of more than one tile first (a workgroup each), then the one tile of
-    // every smaller group (a wave each)
-    std::vector<int32_t> tl;
-    tl.reserve(o.tiles.size());
-    for (int pass = 0; pass < 2; ++pass) {
-        for (size_t gi = 0; gi < o.k0.size(); ++gi) {
-            const int t0 = o.tfirst[gi], t1 = o.tfirst[gi + 1];
-            if ((t1 - t0 > 1) == (pass == 0))
-                for (int k = t0; k < t1; ++k) tl.push_back(k);
-        }
-        if (pass == 0) T.n_multi = (int32_t)tl.size();
-    }
-    // the layout's uploads on the stream, one host wait after the last
-    if (!tl.empty())
-        HIP_TRY(hipMemcpyAsync(T.tl, tl.data(), tl.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(T.off, o.off.data(), o.off.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(T.tfirst, o.tfirst.data(), o.tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    if (!o.tiles.empty())
-        HIP_TRY(hipMemcpyAsync(T.tiles, o.tiles.data(), o.tiles.size() * sizeof(int4), hipMemcpyHostToDevice, s));
-    // the members in ring / azimuth order, on the device (the group offsets in the large-group
-    // layout's k0, free until run_big_groups lays out its own)
-    HIP_TRY(hipMemcpyAsync(ctx->big.k0, o.k0.data(), o.k0.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    HIP_TRY(launch_ring_order(ctx->members, ctx->big.k0, T.off, T.G, T.M, b->x, b->y, ctx->ow, T.body, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    if (T.G > ctx->lt_cap_G || T.M > T.cap_M || T.n_tiles > ctx->lt_cap_T)
+        return fail(GENGA_ERR_STATE, "level layout exceeds its allocation");
+    HIP_TRY(launch_ring_order(ctx->members, T.off, T.off, T.G, T.M, b->x, b->y, ctx->ow, T.body, s));
     return run_level(ctx, b, 1, dt, s);
 }
 
-// Grid-wide Bulirsch-Stoer over dt for the groups gs / mem (host copies; members_dev the
-// device copy of mem) of at least min_nb members.
-int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, const std::vector<int32_t> &gs,
-                   const std::vector<int32_t> &mem_h, const int32_t *members_dev, int min_nb,
-                   const std::vector<int32_t> *prev)
+// The layout of the groups gs / mem (host copies) of at least min_nb members, in the order of prev,
+// for run_big_groups.
+int upload_big_layout(genga_ctx *ctx, hipStream_t s, const std::vector<int32_t> &gs, const std::vector<int32_t> &mem,
+                      int min_nb, const std::vector<int32_t> &prev)
 {
     BigBs &bg = ctx->big;
     bg.G = bg.M = bg.n_tiles = 0;
     TileOrder o;
-    int rc = order_tiles(ctx, gs, mem_h, min_nb, o, prev);
+    int rc = order_tiles(ctx, gs, mem, min_nb, o, prev);
     if (rc) return rc;
     if (o.k0.empty()) return GENGA_OK;
     if ((int)o.k0.size() > bg.cap_G || o.off.back() > bg.cap_M || (int)o.tiles.size() > bg.cap_T)
@@ -852,11 +835,18 @@ int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, co
     HIP_TRY(hipMemcpyAsync(bg.tfirst, o.tfirst.data(), o.tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     const int32_t dims[4] = {bg.G, bg.M, bg.n_tiles, 0};
     HIP_TRY(hipMemcpyAsync(bg.dims, dims, sizeof(dims), hipMemcpyHostToDevice, s));
-    if (prev)
-        HIP_TRY(hipMemcpyAsync(bg.body, o.body.data(), o.body.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    else
-        HIP_TRY(launch_ring_order(members_dev, bg.k0, bg.off, bg.G, bg.M, b->x, b->y, ctx->ow, bg.body, s));
+    HIP_TRY(hipMemcpyAsync(bg.body, o.body.data(), o.body.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     HIP_TRY(hipStreamSynchronize(s));
+    return GENGA_OK;
+}
+
+// Grid-wide Bulirsch-Stoer over dt for the groups laid out in ctx->big (k0: their first members in
+// members_dev).
+int run_big_groups(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, const int32_t *members_dev)
+{
+    BigBs &bg = ctx->big;
+    if (bg.G == 0) return GENGA_OK;
+    int rc;
     const Layout &L = ctx->L;
     HIP_TRY(launch_big_setup(L, bg, members_dev, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit, ctx->rc_lv,
                              dt, s));
@@ -962,11 +952,8 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
 {
     const Layout &L = ctx->L;
     const bool large = ctx->large_groups != 0;
-    const auto prep = [&] {
-        return launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, prec == GENGA_KICK_FP32 ? ctx->m32 : nullptr,
-                           ctx->rc2_part, ctx->chunk_mass, ctx->pair_count, nullptr, 0.0, s);
-    };
-    HIP_TRY(prep());
+    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, prec == GENGA_KICK_FP32 ? ctx->m32 : nullptr, ctx->rc2_part,
+                        ctx->chunk_mass, ctx->pair_count, nullptr, 0.0, s));
     int rc = enqueue_step_kick(ctx, b, 0.5 * dt, prec, acc, 0.0, !large, s);
     if (rc) return rc;
     StepMomentum pm = ctx->pm;
@@ -975,16 +962,17 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
     for (int k = 1, rec = 0; k <= nsteps; ++k) {
         const bool last = k == nsteps;
         if (large && (rc = build_groups_large(ctx, s))) return rc;
-        const bool parts = large && ctx->gs_h.size() > 1;
-        if (parts) {
-            if ((rc = enqueue_drift(ctx, b, dt, s, false, true))) return rc;
-            HIP_TRY(prep()); // an empty pair list
+        if (large && ctx->groups_h.G > 0) {
+            ctx->list_valid = false;
+            HIP_TRY(launch_sun_shift(ctx->items, ctx->n_items, L.mstar, b->x, b->y, b->z, pm, s));
+            if ((rc = enqueue_drift_parts(ctx, b, dt, s))) return rc;
+            HIP_TRY(launch_drifted(ctx->items, ctx->n_items, b->vx, b->vy, b->vz, b->m, pm, s));
         } else {
             HIP_TRY(launch_drift(L, ctx->items, ctx->n_items, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, b->rcrit,
-                                 dt, ctx->members, ctx->group_start, ctx->n_groups, ctx->member_slot, ctx->flags, 0,
-                                 large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, nullptr, &pm, true));
+                                 dt, ctx->members, ctx->group_start, large ? &ctx->gw.hdr->G : ctx->n_groups,
+                                 ctx->member_slot, ctx->flags, 0, large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, nullptr, &pm, true));
         }
-        if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, parts ? 0.0 : 0.5 * dt, !last && !large, s)))
+        if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, 0.5 * dt, !last && !large, s)))
             return rc;
         if (cadence > 0 && d_energy && k % cadence == 0) {
             rc = enqueue_energy(ctx, b, last ? 0.0 : 0.5 * dt, d_energy + (size_t)rec * 4 * L.n_sys, s);
@@ -1200,8 +1188,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     // work items: 64 consecutive bodies of one system
     std::vector<Chunk> chunks;
     std::vector<int32_t> cfirst(n_sys + 1, 0);
-    ctx->pm.parts = close_parts(ctx->n_items, ctx->n_cu);
-    const int citems = CLOSE_WAVES / ctx->pm.parts;
     for (int s = 0; s < n_sys; ++s) {
         cfirst[s] = (int32_t)chunks.size();
         for (int b = sys_off_host[s]; b < sys_off_host[s + 1]; b += CHUNK)

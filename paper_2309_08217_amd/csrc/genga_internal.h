@@ -263,6 +263,12 @@ hipError_t launch_ce_groups(const GroupBuild &g, hipStream_t stream, const PairI
 // for its first shift, the pairs of an import), and the second half of the Sun drift after it.
 hipError_t launch_drift_open(const WorkItem *items, const double *vx, const double *vy, const double *vz,
                              const double *m, const StepMomentum &pm, const PairImport *import, hipStream_t stream);
+// launch_sun_shift: positions + tau P / Mstar, P from the sums a step's kick left.  launch_drifted:
+// the sums a step's drift leaves, when the drift ran in parts; pm.clear zeroed.
+hipError_t launch_sun_shift(const WorkItem *items, int n_items, const double *mstar, double *x, double *y, double *z,
+                            const StepMomentum &pm, hipStream_t stream);
+hipError_t launch_drifted(const WorkItem *items, int n_items, const double *vx, const double *vy, const double *vz,
+                          const double *m, const StepMomentum &pm, hipStream_t stream);
 hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
                               hipStream_t stream);
 // Kepler drift of the bodies outside encounter groups and Bulirsch-Stoer of each group of up
@@ -286,12 +292,9 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
                         int32_t *member_slot, int32_t *flags, int big_groups, int bs_blocks, int32_t *wg_list,
                         hipStream_t stream, const double *rc_lv = nullptr, int nlev = 1, bool kepler = true,
                         const DriftSide *side = nullptr, const StepMomentum *pm = nullptr, bool wg_listed = false);
-// Grid-wide union-find of the encounter pairs (large-group mode, levels; lab all -1 on entry), and
-// slots (member_slot for members[0..n), lab = -1).
+// Grid-wide union-find of the encounter pairs (large-group mode, levels; lab all -1 on entry).
 hipError_t launch_uf_union(const int32_t *pairs, const int32_t *pair_count, int32_t pair_cap, int32_t *lab,
                            hipStream_t stream);
-hipError_t launch_uf_slots(int n_members_max, const int32_t *members, const int32_t *n_members,
-                           int32_t *member_slot, int32_t *lab, hipStream_t stream);
 
 // Grid-wide Bulirsch-Stoer for the groups of more than CE_MAX_GROUP members.  Members of the G
 // large groups are numbered f = 0..M-1, group g holding [off[g], off[g+1]) (in an order the
@@ -420,19 +423,29 @@ struct GroupHeader {
     int32_t n_tiles, n_multi; // tiles of 64; of them in groups of several tiles
     int32_t max_nb;          // largest group
     int32_t pair_count;      // length of the pair list (may exceed its capacity)
+    int32_t large_G, large_M, large_T; // groups of the large layout, their members and tiles
 };
 // Where the layout goes: body[M] the members group by group, each group in the parent order;
 // off[G + 1]; with tiles != null also tfirst[G + 1], tiles[n_tiles] (group, first member, count,
 // 0) in group order, and tl[n_tiles]: the tiles of groups of several tiles first, then the one
 // tile of each smaller group.
-struct GroupOut {
-    int32_t *body = nullptr, *off = nullptr, *tfirst = nullptr, *tl = nullptr;
+// off2: a second copy of off; member_slot: the members' places in body, their labels then back to
+// -1; large: with k0 != null the groups of at least `least` members laid out as the grid-wide
+// Bulirsch-Stoer takes them, except for their members' order (k0[g] the group's first in body).
+struct LargeOut {
+    int32_t *k0 = nullptr, *off = nullptr, *tfirst = nullptr, *dims = nullptr;
     int4 *tiles = nullptr;
+    int32_t least = 0;
+};
+struct GroupOut {
+    int32_t *body = nullptr, *off = nullptr, *off2 = nullptr, *tfirst = nullptr, *tl = nullptr, *member_slot = nullptr;
+    int4 *tiles = nullptr;
+    LargeOut large;
 };
 struct GroupWork {
     uint64_t *keys = nullptr, *keys_sorted = nullptr; // [cap]
     int32_t *cnt = nullptr;                           // groups by block of 1024 members
-    uint64_t *tsum = nullptr;                         // tiles by block of 1024 groups
+    uint64_t *tsum = nullptr, *bsum = nullptr;        // tiles, large groups by block of 1024 groups
     GroupHeader *hdr = nullptr;                       // device
     void *temp = nullptr;                             // sort temporary storage
     size_t temp_bytes = 0;

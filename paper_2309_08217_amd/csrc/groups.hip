@@ -29,7 +29,11 @@ __global__ __launch_bounds__(GL_THREADS) void group_keys_kernel(const int32_t *p
                                                                 uint64_t *keys, GroupHeader *hdr)
 {
     const int p = blockIdx.x * GL_THREADS + threadIdx.x;
-    if (p == 0) *hdr = GroupHeader{0, 0, 0, 0, 0, *pair_count};
+    if (p == 0) {
+        GroupHeader h{};
+        h.pair_count = *pair_count;
+        *hdr = h;
+    }
     if (p >= Mp) return;
     const int b = pbody[p], l = uf_load(lab, b);
     int r = n_total;
@@ -70,15 +74,24 @@ __device__ __forceinline__ T block_before(T v, T *wsum, T &all)
     return before;
 }
 
-// Members in sorted order, and per block the number of groups that start in it.
+// Members in sorted order, and per block the number of groups that start in it; with slots the
+// members' slots, and their labels back to -1.
 __global__ __launch_bounds__(GS_THREADS) void group_mark_kernel(const uint64_t *sorted, int Mp, int n_total,
-                                                                const int32_t *pbody, int32_t *body_out, int32_t *cnt)
+                                                                const int32_t *pbody, int32_t *body_out, int32_t *cnt,
+                                                                int32_t *slots, int32_t *lab)
 {
     __shared__ int wsum[GS_THREADS / 64];
     const int q = blockIdx.x * GS_THREADS + threadIdx.x;
     bool member;
     const bool start = group_start_at(sorted, q, Mp, n_total, member);
-    if (member) body_out[q] = pbody[(int)(uint32_t)sorted[q]];
+    if (member) {
+        const int b = pbody[(int)(uint32_t)sorted[q]];
+        body_out[q] = b;
+        if (slots) {
+            slots[b] = q;
+            lab[b] = -1;
+        }
+    }
     int all;
     block_before((int)start, wsum, all);
     if (threadIdx.x == 0) cnt[blockIdx.x] = all;
@@ -86,7 +99,8 @@ __global__ __launch_bounds__(GS_THREADS) void group_mark_kernel(const uint64_t *
 
 // Group offsets; the last member writes the totals.
 __global__ __launch_bounds__(GS_THREADS) void group_offsets_kernel(const uint64_t *sorted, int Mp, int n_total,
-                                                                   const int32_t *cnt, int32_t *off, GroupHeader *hdr)
+                                                                   const int32_t *cnt, int32_t *off, int32_t *off2,
+                                                                   GroupHeader *hdr)
 {
     __shared__ int wsum[GS_THREADS / 64];
     const int q = blockIdx.x * GS_THREADS + threadIdx.x;
@@ -98,10 +112,14 @@ __global__ __launch_bounds__(GS_THREADS) void group_offsets_kernel(const uint64_
     block_before(part, wsum, base);
     const int g = base + block_before((int)start, wsum, all);
     if (q == 0 && !member) off[0] = 0; // no member at all
-    if (start) off[g] = q;
+    if (start) {
+        off[g] = q;
+        if (off2) off2[g] = q;
+    }
     if (member && !next) {
         const int G = g + start;
         off[G] = q + 1;
+        if (off2) off2[G] = q + 1;
         hdr->G = G;
         hdr->M = q + 1;
     }
@@ -115,8 +133,13 @@ __device__ __forceinline__ uint64_t tiles_of(int nb)
     return nt > 1 ? (uint64_t)nt << 32 : (uint64_t)nt;
 }
 
-// The largest group into the header, and per block the groups' tiles.
-__global__ __launch_bounds__(GS_THREADS) void group_sizes_kernel(const int32_t *off, GroupHeader *hdr, uint64_t *tsum)
+// A group among those of at least `least` members, as 1 << 32 | its members.
+__device__ __forceinline__ uint64_t large_of(int nb, int least) { return nb >= least ? 1ull << 32 | (uint32_t)nb : 0; }
+
+// The largest group into the header, and per block the groups' tiles, or the large groups and their
+// members (bsum[2 block]) and tiles.
+__global__ __launch_bounds__(GS_THREADS) void group_sizes_kernel(const int32_t *off, GroupHeader *hdr, uint64_t *tsum,
+                                                                 uint64_t *bsum, int least)
 {
     __shared__ uint64_t wsum[GS_THREADS / 64];
     const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G;
@@ -125,10 +148,69 @@ __global__ __launch_bounds__(GS_THREADS) void group_sizes_kernel(const int32_t *
     int mx = nb;
     for (int o = 32; o > 0; o >>= 1) mx = max(mx, __shfl_xor(mx, o, 64));
     if ((threadIdx.x & 63) == 0) atomicMax(&hdr->max_nb, mx);
-    if (!tsum) return;
     uint64_t all;
-    block_before(tiles_of(nb), wsum, all);
-    if (threadIdx.x == 0) tsum[blockIdx.x] = all;
+    if (tsum) {
+        block_before(tiles_of(nb), wsum, all);
+        if (threadIdx.x == 0) tsum[blockIdx.x] = all;
+    }
+    if (bsum) {
+        block_before(large_of(nb, least), wsum, all);
+        if (threadIdx.x == 0) bsum[2 * blockIdx.x] = all;
+        block_before((uint64_t)(nb >= least ? (nb + 63) / 64 : 0), wsum, all);
+        if (threadIdx.x == 0) bsum[2 * blockIdx.x + 1] = all;
+    }
+}
+
+// The tiles t0 .. of a group of nb members from member o on, by the wave, for every lane whose
+// group has any (want): tile k of a lane's group goes to put(tile index, tile, list place).
+template <typename Put>
+__device__ __forceinline__ void wave_tiles(bool want, int g, int o, int nb, int t0, int l0, Put put)
+{
+    const int lane = threadIdx.x & 63;
+    for (unsigned long long w = __ballot(want); w; w &= w - 1) {
+        const int src = __builtin_ctzll(w);
+        const int g1 = __shfl(g, src, 64), o1 = __shfl(o, src, 64), nb1 = __shfl(nb, src, 64);
+        const int t1 = __shfl(t0, src, 64), l1 = __shfl(l0, src, 64);
+        for (int k = lane; 64 * k < nb1; k += 64) put(t1 + k, make_int4(g1, o1 + 64 * k, min(64, nb1 - 64 * k), 0), l1 + k);
+    }
+}
+
+// The layout of the groups of at least `least` members for the grid-wide drift: their first members
+// in the layout of all (k0), their offsets in their own, tiles and sizes.
+__global__ __launch_bounds__(GS_THREADS) void group_large_kernel(const int32_t *off, GroupHeader *hdr,
+                                                                 const uint64_t *bsum, LargeOut out)
+{
+    __shared__ uint64_t wsum[GS_THREADS / 64];
+    const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G;
+    const int nblk = (G + GS_THREADS - 1) / GS_THREADS;
+    if ((int)blockIdx.x >= nblk) return; // the whole block
+    const int o = g < G ? off[g] : 0, nb = g < G ? off[g + 1] - o : 0;
+    const bool large = nb >= out.least;
+    uint64_t p = 0, tp = 0, base, tbase, all, tall;
+    for (int k = threadIdx.x; k < (int)blockIdx.x; k += GS_THREADS) {
+        p += bsum[2 * k];
+        tp += bsum[2 * k + 1];
+    }
+    block_before(p, wsum, base);
+    block_before(tp, wsum, tbase);
+    const uint64_t e = base + block_before(large_of(nb, out.least), wsum, all);
+    const int t0 = (int)(tbase + block_before((uint64_t)(large ? (nb + 63) / 64 : 0), wsum, tall));
+    const int gi = (int)(e >> 32), f0 = (int)(uint32_t)e;
+    if (large) {
+        out.k0[gi] = o;
+        out.off[gi] = f0;
+        out.tfirst[gi] = t0;
+    }
+    wave_tiles(large, gi, f0, nb, t0, 0, [&](int t, int4 tile, int) { out.tiles[t] = tile; });
+    if (g == G - 1) {
+        const uint64_t tot = base + all;
+        const int nG = (int)(tot >> 32), nM = (int)(uint32_t)tot, nT = (int)(tbase + tall);
+        out.off[nG] = nM;
+        out.tfirst[nG] = nT;
+        out.dims[0] = hdr->large_G = nG;
+        out.dims[1] = hdr->large_M = nM;
+        out.dims[2] = hdr->large_T = nT;
+    }
 }
 
 // Tiles of 64 members, group by group: each group's first tile (tfirst), its tiles, their places
@@ -139,7 +221,7 @@ __global__ __launch_bounds__(GS_THREADS) void group_tiles_kernel(const int32_t *
                                                                  int32_t *tl)
 {
     __shared__ uint64_t wsum[GS_THREADS / 64];
-    const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G, lane = threadIdx.x & 63;
+    const int g = blockIdx.x * GS_THREADS + threadIdx.x, G = hdr->G;
     const int nblk = (G + GS_THREADS - 1) / GS_THREADS;
     if ((int)blockIdx.x >= nblk) return; // the whole block
     uint64_t part = 0, rest = 0, base, after, all;
@@ -160,16 +242,10 @@ __global__ __launch_bounds__(GS_THREADS) void group_tiles_kernel(const int32_t *
         tiles[mo + so] = make_int4(g, o, nb, 0);
         tl[n_multi + so] = mo + so;
     }
-    // the wave writes the tiles of its larger groups together, one group after the other
-    for (unsigned long long w = __ballot(nt > 1); w; w &= w - 1) {
-        const int src = __builtin_ctzll(w);
-        const int G1 = __shfl(g, src, 64), o1 = __shfl(o, src, 64), nb1 = __shfl(nb, src, 64);
-        const int t1 = __shfl(mo + so, src, 64), m1 = __shfl(mo, src, 64);
-        for (int k = lane; 64 * k < nb1; k += 64) {
-            tiles[t1 + k] = make_int4(G1, o1 + 64 * k, min(64, nb1 - 64 * k), 0);
-            tl[m1 + k] = t1 + k;
-        }
-    }
+    wave_tiles(nt > 1, g, o, nb, mo + so, mo, [&](int t, int4 tile, int l) {
+        tiles[t] = tile;
+        tl[l] = t;
+    });
 }
 
 int bits_for(uint64_t v)
@@ -293,6 +369,7 @@ hipError_t group_work_alloc(GroupWork &w, int cap)
     const size_t nb = (n + GS_THREADS - 1) / GS_THREADS;
     if ((e = hipMalloc((void **)&w.cnt, nb * sizeof(int32_t))) != hipSuccess) return e;
     if ((e = hipMalloc((void **)&w.tsum, nb * sizeof(uint64_t))) != hipSuccess) return e;
+    if ((e = hipMalloc((void **)&w.bsum, 2 * nb * sizeof(uint64_t))) != hipSuccess) return e;
     if ((e = hipMalloc((void **)&w.hdr, sizeof(GroupHeader))) != hipSuccess) return e;
     // temporary storage of the sort, for the largest size
     if ((e = rocprim::radix_sort_keys(nullptr, w.temp_bytes, w.keys, w.keys_sorted, (unsigned int)n, 0, 64)) !=
@@ -304,7 +381,8 @@ hipError_t group_work_alloc(GroupWork &w, int cap)
 
 void group_work_free(GroupWork &w)
 {
-    for (void *p : {(void *)w.keys, (void *)w.keys_sorted, (void *)w.cnt, (void *)w.tsum, (void *)w.hdr, w.temp})
+    for (void *p : {(void *)w.keys, (void *)w.keys_sorted, (void *)w.cnt, (void *)w.tsum, (void *)w.bsum,
+                    (void *)w.hdr, w.temp})
         if (p) (void)hipFree(p);
     w = GroupWork{};
 }
@@ -314,7 +392,7 @@ hipError_t launch_group_layout(const Layout &L, GroupWork &w, const int32_t *pai
                                hipStream_t stream)
 {
     if (Mp > w.cap) return hipErrorInvalidValue;
-    if (Mp == 0) return hipMemsetAsync(w.hdr, 0, sizeof(GroupHeader), stream);
+    if (Mp <= 0) return hipMemsetAsync(w.hdr, 0, sizeof(GroupHeader), stream);
     hipError_t e;
     if ((e = launch_uf_union(pairs, pair_count, pair_cap, lab, stream)) != hipSuccess) return e;
     const int nb = (Mp + GL_THREADS - 1) / GL_THREADS, ns = (Mp + GS_THREADS - 1) / GS_THREADS;
@@ -324,13 +402,16 @@ hipError_t launch_group_layout(const Layout &L, GroupWork &w, const int32_t *pai
     if ((e = rocprim::radix_sort_keys(w.temp, bytes, w.keys, w.keys_sorted, (unsigned int)Mp, 32,
                                       32 + bits_for((uint64_t)L.n_total), stream)) != hipSuccess)
         return e;
-    group_mark_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, pbody, out.body, w.cnt);
-    group_offsets_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, w.cnt, out.off, w.hdr);
+    group_mark_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, pbody, out.body, w.cnt,
+                                                   out.member_slot, lab);
+    group_offsets_kernel<<<ns, GS_THREADS, 0, stream>>>(w.keys_sorted, Mp, L.n_total, w.cnt, out.off, out.off2, w.hdr);
     // groups have at least two members
     const int ng = (Mp / 2 + GS_THREADS) / GS_THREADS;
-    group_sizes_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, out.tiles ? w.tsum : nullptr);
+    group_sizes_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, out.tiles ? w.tsum : nullptr,
+                                                    out.large.k0 ? w.bsum : nullptr, out.large.least);
     if (out.tiles)
         group_tiles_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, w.tsum, out.tfirst, out.tiles, out.tl);
+    if (out.large.k0) group_large_kernel<<<ng, GS_THREADS, 0, stream>>>(out.off, w.hdr, w.bsum, out.large);
     return hipGetLastError();
 }
 

@@ -1201,7 +1201,9 @@ __device__ __forceinline__ double pair_accel(const PairGroup &g, double z)
     const double dz = dpp64<DPP_MIRROR8>(z) - z;
     const double q0 = quad_sum(z * z), q1 = quad_sum(dz * dz);
     const double ri = inv_sqrt64(q0);
-    const double f = g.mp != 0.0 ? encounter_factor<LV>(q1, g.mp, g.i09, g.nlev, g.i9l, g.i9l, 1) : 0.0;
+    // (two test bodies: a mass of zero at any separation; a branch here would keep the forces of a
+    // round from running side by side)
+    const double f = encounter_factor<LV>(g.mp != 0.0 ? q1 : 1.0, g.mp, g.i09, g.nlev, g.i9l, g.i9l, 1);
     return fma(f, dz, -g.mstar * (ri * ri) * ri * z);
 }
 
@@ -1221,6 +1223,12 @@ __device__ __forceinline__ double pair_sum(const double *T, const double *c, int
 
 // x, v: this lane's coordinate, in every column's lanes; tcol: LDS [BS_KMAX][16], T(j, 0) of the
 // positions (lanes 0..7) and velocities (8..15).
+//
+// A wave with a chain of some 25 dependent FP64 operations per force.  The midpoint rule is two
+// leapfrogs that meet only at the end: positions at even sub-steps take the velocities at odd
+// ones, and those the forces at even ones, so the forces at z_i and z_i+1, i = 2 j + 1, are
+// independent and run side by side: after f(x) eight rounds an attempt instead of 16 (a drift of 40000
+// bodies, set by a pair of 12 attempts: 57 -> 47 us).
 template <bool LV>
 __device__ bool bs_pair(const PairGroup &g, int lane, double &x, double &v, double *tcol, double dt, double tol)
 {
@@ -1235,25 +1243,24 @@ __device__ bool bs_pair(const PairGroup &g, int lane, double &x, double &v, doub
         const double sr = fmax(r1, dpp64<DPP_MIRROR8>(r1)), sv = fmax(v1, dpp64<DPP_MIRROR8>(v1));
         const double scale = lane & 8 ? sv : sr;
         const double h = H / nsub, h2 = 2.0 * h;
-        // pass 0: z_1 of every column
-        double zm = x, um = v;
-        double zc = fma(h, v, x), uc = fma(h, pair_accel<LV>(g, x), v);
+        // z_i, z_i+1, u_i, u_i-1 of every column
+        double ui = fma(h, pair_accel<LV>(g, x), v), up = v;
+        double zi = fma(h, v, x), zn = fma(h2, ui, x);
         int kstar = -1;
         double err_last = 0.0;
 #pragma unroll 1
-        for (int i = 1; i <= 2 * BS_KMAX; ++i) {
-            const double a = pair_accel<LV>(g, zc);
-            if (i == nsub) {
-                tcol[16 * k + (lane & 7)] = 0.5 * (zm + zc + h * uc); // T(k, 0)
-                tcol[16 * k + 8 + (lane & 7)] = 0.5 * (um + uc + h * a);
+        for (int kk = 0; kk < BS_KMAX; ++kk) {
+            const double ai = pair_accel<LV>(g, zi), an = pair_accel<LV>(g, zn);
+            const double un = fma(h2, ai, up); // u_i+1
+            if (kk == k) { // the column's last round
+                tcol[16 * k + (lane & 7)] = 0.5 * (zi + zn + h * un); // T(k, 0)
+                tcol[16 * k + 8 + (lane & 7)] = 0.5 * (ui + un + h * an);
             }
-            const double zn = fma(h2, uc, zm), un = fma(h2, a, um); // unused once i >= nsub
-            zm = zc;
-            um = uc;
-            zc = zn;
-            uc = un;
-            if (i < 4 || (i & 1)) continue;
-            const int kk = i / 2 - 1; // the column that has just completed
+            ui = fma(h2, an, ui);
+            up = un;
+            zi = fma(h2, un, zi);
+            zn = fma(h2, ui, zn);
+            if (kk == 0) continue;
             __syncthreads();
             const double diff = fabs(pair_sum(tcol + (lane & 15), LAGRANGE.d[kk], kk));
             if (!__ballot(!(diff <= tol * scale))) {

@@ -32,8 +32,8 @@ using CI = const __attribute__((address_space(4))) int32_t;
 constexpr int GB_TILE = 64;
 constexpr int GB_THREADS = 256;
 // Up to this launch grid all eight columns of an attempt run side by side, above it the first six:
-// 6600 bodies (104 tiles) 1.42 against 1.47 ms a pass of two steps, 40322 bodies (631 tiles) 17.1
-// against 15.9 ms a step.
+// 6600 bodies (104 tiles) 25.7 against 27.7 ms for two steps of some 40 attempts, 40322 bodies (631
+// tiles) 16.4 against 15.4 ms a step (five first: 16.1).
 constexpr int BIG_SIDE_TILES = 256;
 
 __device__ __forceinline__ unsigned long long dbits(double v) { return (unsigned long long)__double_as_longlong(v); }
@@ -111,7 +111,7 @@ __global__ __launch_bounds__(64) void big_setup_kernel(BigBs b, const int32_t *s
             b.skin[body] = 2.0;
             b.crossed[f] = 0;
             b.amut[f] = 0.0;
-            for (int k = 0; k < 1 + 2 * BS_KMAX; ++k) b.P[(size_t)k * b.cap_M + f].w = m[body];
+            b.P[f].w = m[body];
         }
         // candidate radius: the deepest level's r_crit
         double rd = rc[body];
@@ -759,28 +759,37 @@ __device__ __forceinline__ bool group_accepted(const BigBs &b, int g, int kv, do
     return ka >= 0;
 }
 
-// Pass i of the columns k0, k0 + 1, .. (blockIdx.y) on the list path, one workgroup per target
-// tile (blockIdx.x): sub-step i of column k reads its states z_i (buffer B1 for odd i, B2 for
-// even) and z_(i-1) and writes z_(i+1) = z_(i-1) + 2 h f(z_i), or, as its last (i = 2 (k + 1)),
-// T(k, 0) and the group's error estimate.  Pass 0 evaluates f(Y) once and writes z_1 of every
-// column.  The records of the tile's slots are staged in LDS, then BIG_LIST_LANES lanes share a
-// member, each summing every BIG_LIST_LANES-th entry of its list in order; the parts are added in
-// a fixed tree whose result every lane has, so that the update's six components (in pass 0 the
-// columns) go to one lane each.
+// The list path's force at one position: the share (1 - K) of a source's pull, in parts.
+struct BigPull {
+    double x = 0.0, y = 0.0, z = 0.0;
+};
+
+// Round j of the columns k0, k0 + 1, .. (blockIdx.y) on the list path, one workgroup per target
+// tile (blockIdx.x).  The midpoint rule is two leapfrogs that meet only at the end: positions at
+// even sub-steps take the velocities at odd ones, and those the forces at even ones.  So with the
+// state z_i, z_i+1, u_i, u_i-1 (i = 2 j + 1) the forces at z_i and z_i+1 are evaluated together:
+//   u_i+1 = u_i-1 + 2 h f(z_i), u_i+2 = u_i + 2 h f(z_i+1), z_i+2 = z_i + 2 h u_i+1, z_i+3 = ..,
+// or, in a column's last round (j = k), T(k, 0) and the group's error estimate.  The launch before
+// the first round (FIRST) evaluates f(Y) once and writes z_1, u_1, z_2 of every column.  Positions
+// are read by other tiles, so they alternate between two pairs of buffers; velocities are the
+// member's own.  The records of the tile's slots are staged in LDS, then BIG_LIST_LANES lanes share
+// a member, each summing every BIG_LIST_LANES-th entry of its list in order; the parts are added in
+// a fixed tree whose result every lane has, so that the update's components (before the first
+// round the columns) go to one lane each.
 //
-// Latency bound: two rounds of loads, a barrier, the list's chain of terms.  A launch per
-// sub-step and column ran 104 tiles (6600 bodies) on 104 CUs for 6.6 us each, 72 of them an
-// attempt; side by side the columns fill the chip and an attempt is 17 launches.  40 bytes per
-// staged source and at most 80 VGPRs: three workgroups fit a CU.
-template <bool LV>
-__global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_per_eu(6))) void big_pass_kernel(
-    BigBs b, int i, int k0, int kv, double tol)
+// Latency bound: two rounds of loads, a barrier, the list's chain of terms.  A launch per sub-step
+// and column ran 104 tiles (6600 bodies) on 104 CUs for 6.6 us each, 72 of them an attempt; side by
+// side the columns fill the chip, 17 launches of 9.2 us; two sub-steps a launch make it 9 of
+// 13 us.  64 bytes per staged source: two workgroups fit a CU.
+template <bool LV, bool FIRST>
+__global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_per_eu(4))) void big_round_kernel(
+    BigBs b, int j, int k0, int kv, double tol)
 {
-    constexpr int P = BIG_LIST_LANES;
+    constexpr int P = BIG_LIST_LANES, NZ = FIRST ? 1 : 2; // positions evaluated
     constexpr int NS = BIG_LIST_SLOTS * 64;
     static_assert(P == BS_KMAX && P >= 6, "one lane per column, and per component");
-    __shared__ double2 sxy[NS], szm[NS]; // (x, y), (z, mass)
-    __shared__ double si9[NS];           // 1 / (0.9 r_crit)
+    __shared__ double2 sxy[NZ][NS], szm[NZ][NS]; // (x, y), (z, mass or 1 / (0.9 r_crit))
+    __shared__ double si9[FIRST ? NS : 1];
     __shared__ int sgi[LV ? NS : 1];               // member index, for the levels' radii
     __shared__ unsigned long long ered[P];         // the waves' error maxima
     constexpr int PER = NS / (64 * P); // staged sources per thread
@@ -801,74 +810,88 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
     // second round: the group's state, the sources to stage and the member's own words
     if (b.done[g]) return; // the whole workgroup
     if (group_accepted(b, g, kv, tol, blockIdx.y == 0 && threadIdx.x == 0 && me == b.tfirst[g])) return;
-    const int bz = i == 0 ? 0 : (i & 1) ? 1 + 2 * k : 2 + 2 * k; // Z's buffer, and Z(i-1)'s
-    const int bm = i <= 1 ? 0 : (i & 1) ? 2 + 2 * k : 1 + 2 * k;
-    const double4 *PZ = b.P + bz * cm;
+    // z_i and z_i+1 of this round, and where the next round's go
+    double4 *const Z0 = b.P + (FIRST ? 0 : 1 + 4 * k + 2 * (j & 1)) * cm, *const Z1 = Z0 + cm;
+    double4 *const N0 = b.P + (1 + 4 * k + 2 * ((j + 1) & 1)) * cm, *const N1 = N0 + cm;
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int e = (int)threadIdx.x + u * 64 * P;
         if (e < ns * 64 && (e & 63) < si[u].y) {
-            const size_t j = (size_t)(si[u].x + (e & 63));
-            const double4 p = PZ[j];
-            sxy[e] = make_double2(p.x, p.y);
-            szm[e] = make_double2(p.z, p.w);
-            si9[e] = b.i09[j];
-            if constexpr (LV) sgi[e] = (int)j;
+            const size_t f = (size_t)(si[u].x + (e & 63));
+            const double4 p = Z0[f];
+            sxy[0][e] = make_double2(p.x, p.y);
+            szm[0][e] = make_double2(p.z, p.w);
+            if constexpr (FIRST) {
+                si9[e] = b.i09[f];
+            } else {
+                const double4 q = Z1[f];
+                sxy[NZ - 1][e] = make_double2(q.x, q.y);
+                szm[NZ - 1][e] = make_double2(q.z, q.w);
+            }
+            if constexpr (LV) sgi[e] = (int)f;
         }
     }
-    const double4 pa = PZ[fa];
-    const double xa = pa.x, ya = pa.y, za = pa.z;
-    const double i09a = b.i09[fa];
+    double4 pa[NZ];
+    pa[0] = Z0[fa];
+    if constexpr (!FIRST) pa[NZ - 1] = Z1[fa];
+    const double i09a = FIRST ? b.i09[fa] : pa[NZ - 1].w;
     const int tot = b.ltot[fa];
     const uint16_t *L = b.ll + (size_t)fa * BIG_LIST_CAP;
     int l0 = L[part], l1 = L[part + P]; // the first two positions (used only below tot)
-    // this lane's component of the update (part < 6: x, y, z, vx, vy, vz): Z's velocity and the
-    // component of z_(i-1) (velocities of buffer 0 stay in Y)
+    // this lane's component (part < 6: x, y, z of the positions, then of the velocities): u_i, u_i-1
     const int c = part % 3;
-    const auto vel = [&](int buf) {
-        return buf == 0 ? b.Y[(3 + c) * M + fa] : b.V[((size_t)(buf - 1) * 3 + c) * cm + fa];
-    };
-    const double vc = vel(bz);
-    const double zm = part < 3 ? reinterpret_cast<const double *>(b.P + bm * cm + fa)[c] : vel(bm);
+    double *const U0 = b.V + ((size_t)(2 * k) * 3 + c) * cm + fa, *const U1 = U0 + 3 * cm;
+    const double ui = FIRST ? 0.0 : *U0, up = FIRST ? 0.0 : j == 0 ? b.Y[(3 + c) * M + fa] : *U1;
     __syncthreads();
-    double ax = 0.0, ay = 0.0, az = 0.0;
-    const double H = b.H[g];
+    BigPull f[NZ];
+    const double H = b.H[g], h = H / nsub;
     if (act) {
         // the bound of the lists: every member stays within S of its prediction
-        if (part == P - 1 && i > 0) {
-            const double hs = H / nsub, tau = hs * i;
+        if (!FIRST && part >= P - 2) {
+            const int z = part - (P - 2), i = 2 * j + 1 + z;
+            const double tau = h * i;
             const double4 pm = b.pred[fa];
-            const double h2 = 0.5 * (tau * tau - ((i & 1) ? hs * hs : 0.0));
+            const double h2 = 0.5 * (tau * tau - ((i & 1) ? h * h : 0.0));
             const double px = fma(pm.x, h2, fma(b.Y[3 * M + fa], tau, b.Y[fa]));
             const double py = fma(pm.y, h2, fma(b.Y[4 * M + fa], tau, b.Y[M + fa]));
             const double pz = fma(pm.z, h2, fma(b.Y[5 * M + fa], tau, b.Y[2 * M + fa]));
-            if (!(sep2_rn(xa - px, ya - py, za - pz) <= pm.w * pm.w * (1.0 - 0x1p-30))) {
+            const double4 at = z ? pa[NZ - 1] : pa[0];
+            if (!(sep2_rn(at.x - px, at.y - py, at.z - pz) <= pm.w * pm.w * (1.0 - 0x1p-30))) {
                 b.stale[g] = 1;
                 b.crossed[fa] = 1;
             }
         }
         const auto term = [&](int l) {
-            const double2 xy = sxy[l], zw = szm[l];
-            const double dx = xy.x - xa, dy = xy.y - ya, dz = zw.x - za;
-            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double rq = inv_sqrt64(q), r = q * rq;
-            // the lists hold neither the member itself nor two test bodies, and outside
-            // r_crit,ab the weight is zero
-            const Changeover c0 = changeover_parts(r, fmin(i09a, si9[l]));
-            double u = c0.u, dd = c0.d;
-            if constexpr (LV) {
-                const int j = sgi[l];
-                for (int lv = 1; lv < b.nlev; ++lv) {
-                    const Changeover cl = changeover_parts(r, fmin(b.i9l[(size_t)(lv - 1) * b.cap_M + fa],
-                                                                   b.i9l[(size_t)(lv - 1) * b.cap_M + j]));
-                    u *= cl.u;
-                    dd *= cl.d;
-                }
+            double2 xy[NZ], zw[NZ];
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) {
+                xy[z] = sxy[z][l];
+                zw[z] = szm[z][l];
             }
-            const double s = zw.y * (u * u) * inv64(dd) * ((rq * rq) * rq);
-            ax = fma(s, dx, ax);
-            ay = fma(s, dy, ay);
-            az = fma(s, dz, az);
+            const double mj = zw[0].y, i9 = fmin(i09a, FIRST ? si9[l] : zw[NZ - 1].y);
+#pragma unroll
+            for (int z = 0; z < NZ; ++z) {
+                const double dx = xy[z].x - pa[z].x, dy = xy[z].y - pa[z].y, dz = zw[z].x - pa[z].z;
+                const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+                const double rq = inv_sqrt64(q), r = q * rq;
+                // the lists hold neither the member itself nor two test bodies, and outside
+                // r_crit,ab the weight is zero
+                const Changeover c0 = changeover_parts(r, i9);
+                double u = c0.u, dd = c0.d;
+                if constexpr (LV) {
+                    const int fj = sgi[l];
+                    for (int lv = 1; lv < b.nlev; ++lv) {
+                        const Changeover cl = changeover_parts(r, fmin(b.i9l[(size_t)(lv - 1) * b.cap_M + fa],
+                                                                       b.i9l[(size_t)(lv - 1) * b.cap_M + fj]));
+                        u *= cl.u;
+                        dd *= cl.d;
+                    }
+                }
+                const double s = mj * (u * u) * inv64(dd) * ((rq * rq) * rq);
+                f[z].x = fma(s, dx, f[z].x);
+                f[z].y = fma(s, dy, f[z].y);
+                f[z].z = fma(s, dz, f[z].z);
+            }
         };
         // lane `part` sums every P-th entry from `part` on, in order; the positions of the next
         // two are loaded ahead (past the end: entry 0, unused)
@@ -881,44 +904,63 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
         }
     }
     // the parts of a member, in a fixed order
-    for (int off = P / 2; off > 0; off >>= 1) {
-        ax += __shfl_xor(ax, off, 64);
-        ay += __shfl_xor(ay, off, 64);
-        az += __shfl_xor(az, off, 64);
+    for (int off = P / 2; off > 0; off >>= 1)
+#pragma unroll
+        for (int z = 0; z < NZ; ++z) {
+            f[z].x += __shfl_xor(f[z].x, off, 64);
+            f[z].y += __shfl_xor(f[z].y, off, 64);
+            f[z].z += __shfl_xor(f[z].z, off, 64);
+        }
+    if (FIRST && act && part == 0) b.amut[fa] = sqrt(sep2_rn(f[0].x, f[0].y, f[0].z));
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
+        const double ri = inv_sqrt64(sep2_rn(pa[z].x, pa[z].y, pa[z].z));
+        const double s = -b.mstar[g] * (ri * ri) * ri;
+        f[z].x = s * pa[z].x + f[z].x;
+        f[z].y = s * pa[z].y + f[z].y;
+        f[z].z = s * pa[z].z + f[z].z;
     }
-    if (i == 0 && act && part == 0) b.amut[fa] = sqrt(sep2_rn(ax, ay, az));
-    const double ri = inv_sqrt64(sep2_rn(xa, ya, za));
-    const double s = -b.mstar[g] * (ri * ri) * ri;
-    ax = s * xa + ax;
-    ay = s * ya + ay;
-    az = s * za + az;
-    if (i == 0) {
+    if constexpr (FIRST) {
         if (!act) return;
-        // lane `part`: z_1 of column `part`
-        const double h = H / (2 * (part + 1));
-        double *p = reinterpret_cast<double *>(b.P + (1 + 2 * part) * cm + fa);
+        // lane `part`: z_1, u_1 and z_2 of column `part`
+        const double hc = H / (2 * (part + 1));
+        double *p1 = reinterpret_cast<double *>(b.P + (1 + 4 * part) * cm + fa);
+        double *p2 = reinterpret_cast<double *>(b.P + (2 + 4 * part) * cm + fa);
         double *v = b.V + (size_t)(2 * part) * 3 * cm + fa;
-        const double u0 = b.Y[3 * M + fa], u1 = b.Y[4 * M + fa], u2 = b.Y[5 * M + fa];
-        p[0] = xa + h * u0;
-        p[1] = ya + h * u1;
-        p[2] = za + h * u2;
-        v[0] = u0 + h * ax;
-        v[cm] = u1 + h * ay;
-        v[2 * cm] = u2 + h * az;
+        const double y0[3] = {pa[0].x, pa[0].y, pa[0].z}, a0[3] = {f[0].x, f[0].y, f[0].z};
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            const double u0 = b.Y[(3 + q) * M + fa], u1 = u0 + hc * a0[q];
+            p1[q] = y0[q] + hc * u0;
+            p2[q] = y0[q] + 2.0 * hc * u1;
+            v[q * cm] = u1;
+        }
+        p1[3] = pa[0].w;
+        p2[3] = i09a;
         return;
     }
-    const double pc = c == 0 ? xa : c == 1 ? ya : za;
-    const double d = part < 3 ? vc : c == 0 ? ax : c == 1 ? ay : az;
-    const double h = H / nsub;
-    if (i < nsub) {
-        if (!act || part >= 6) return;
-        const double o = zm + 2.0 * h * d;
-        const int bo = (i & 1) ? 2 + 2 * k : 1 + 2 * k;
-        if (part < 3) reinterpret_cast<double *>(b.P + bo * cm + fa)[c] = o;
-        else b.V[((size_t)(bo - 1) * 3 + c) * cm + fa] = o;
+    // this lane's component
+    const double zi = c == 0 ? pa[0].x : c == 1 ? pa[0].y : pa[0].z;
+    const double zn = c == 0 ? pa[NZ - 1].x : c == 1 ? pa[NZ - 1].y : pa[NZ - 1].z;
+    const double ai = c == 0 ? f[0].x : c == 1 ? f[0].y : f[0].z;
+    const double an = c == 0 ? f[NZ - 1].x : c == 1 ? f[NZ - 1].y : f[NZ - 1].z;
+    const double un = up + 2.0 * h * ai; // u_i+1
+    if (j < k) {
+        if (!act) return;
+        const double u2 = ui + 2.0 * h * an; // u_i+2
+        if (part < 3) {
+            reinterpret_cast<double *>(N0 + fa)[c] = zi + 2.0 * h * un;
+            reinterpret_cast<double *>(N1 + fa)[c] = zn + 2.0 * h * u2;
+        } else if (part < 6) {
+            *U0 = u2;
+            *U1 = un;
+        } else if (part == 6 && j < 2) { // (later rounds find them there)
+            N0[fa].w = pa[0].w;
+            N1[fa].w = pa[NZ - 1].w;
+        }
         return;
     }
-    const double tk = 0.5 * (zm + (part < 3 ? pc : vc) + h * d);
+    const double tk = part < 3 ? 0.5 * (zi + zn + h * un) : 0.5 * (ui + un + h * an);
     const bool use = act && part < 6;
     double *T0 = b.tcol + part * M + fa; // T(j, 0) of this component: T0[6 j M]
     if (use) T0[(size_t)k * 6 * M] = tk;
@@ -931,10 +973,10 @@ __global__ __launch_bounds__(64 * BIG_LIST_LANES) __attribute__((amdgpu_waves_pe
         const double tz = T0[0];
         double tv[BS_KMAX], sum = 0.0;
 #pragma unroll
-        for (int j = 1; j < BS_KMAX; ++j) tv[j] = T0[(size_t)(j < k ? j : 0) * 6 * M];
+        for (int q = 1; q < BS_KMAX; ++q) tv[q] = T0[(size_t)(q < k ? q : 0) * 6 * M];
 #pragma unroll
-        for (int j = 1; j < BS_KMAX; ++j)
-            if (j <= k) sum = fma(LAGRANGE.d[k][j], (j == k ? tk : tv[j]) - tz, sum);
+        for (int q = 1; q < BS_KMAX; ++q)
+            if (q <= k) sum = fma(LAGRANGE.d[k][q], (q == k ? tk : tv[q]) - tz, sum);
         const double err = fabs(sum) / bitsd(part < 3 ? b.sr[g] : b.sv[g]);
         e = err == err ? dbits(err) : ~0ull;
     }
@@ -1126,7 +1168,8 @@ hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, i
     const int nt = std::max(1, std::min(tile_grid, b.cap_T));
     const size_t M6 = 6 * (size_t)b.cap_M;
     const bool lv = b.nlev > 1;
-    auto pass = lv ? big_pass_kernel<true> : big_pass_kernel<false>;
+    auto first = lv ? big_round_kernel<true, true> : big_round_kernel<false, true>;
+    auto round = lv ? big_round_kernel<true, false> : big_round_kernel<false, false>;
     big_begin_kernel<<<gg, 64, 0, stream>>>(b, flags);
     big_prepare_kernel<<<(nt + 3) / 4, GB_THREADS, 0, stream>>>(b);
     if (nt <= BIG_SIDE_TILES)
@@ -1134,7 +1177,7 @@ hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, i
     else
         (lv ? big_list_kernel<true, 8> : big_list_kernel<false, 8>)<<<nt, 512, 0, stream>>>(b);
     const int threads = 64 * BIG_LIST_LANES;
-    pass<<<dim3(nt, 1), threads, 0, stream>>>(b, 0, 0, -1, tol);
+    first<<<dim3(nt, 1), threads, 0, stream>>>(b, -1, 0, -1, tol);
     // Columns in batches: side by side the columns above the accepted one have run for nothing.
     // While the tiles leave CUs idle that costs nothing; beyond, the first six run together (the
     // accepted column is mostly the fifth or sixth), and the last two only if they are needed.
@@ -1142,11 +1185,10 @@ hipError_t launch_big_attempt_list(const BigBs &b, double tol, int32_t *flags, i
     int kv = -1; // the column whose verdict the launch takes: complete, but not yet decided
     for (int k0 = 0; k0 < BS_KMAX; k0 = k0 == 0 ? split : BS_KMAX) {
         const int k1 = k0 == 0 ? split : BS_KMAX;
-        for (int i = 1; i <= 2 * k1; ++i) {
-            const int kf = std::max(k0, (i + 1) / 2 - 1); // the first column that has a sub-step i
-            pass<<<dim3(nt, k1 - kf), threads, 0, stream>>>(b, i, kf, kv, tol);
-            // column i / 2 - 1 ends with pass i = 2 (k + 1)
-            kv = (i & 1) == 0 && i / 2 - 1 >= std::max(k0, 1) ? i / 2 - 1 : -1;
+        for (int j = 0; j < k1; ++j) { // column j ends with round j
+            const int kf = std::max(k0, j);
+            round<<<dim3(nt, k1 - kf), threads, 0, stream>>>(b, j, kf, kv, tol);
+            kv = j >= std::max(k0, 1) ? j : -1;
         }
     }
     big_accept_kernel<<<gm, GB_THREADS, 0, stream>>>(b, tol);

@@ -586,7 +586,7 @@ int alloc_big(genga_ctx *ctx)
     HIP_TRY(dalloc(b.keep, G));
     HIP_TRY(hipMemset(b.keep, 0, G * sizeof(int32_t)));
     HIP_TRY(dalloc(b.sbb, (size_t)BIG_BOX * b.cap_T));
-    HIP_TRY(dalloc(b.P, (size_t)(1 + 2 * BS_KMAX) * M));
+    HIP_TRY(dalloc(b.P, (size_t)(1 + 4 * BS_KMAX) * M));
     HIP_TRY(dalloc(b.V, (size_t)(2 * BS_KMAX) * 3 * M));
     HIP_TRY(dalloc(b.ovf, 1));
     HIP_TRY(hipMemset(b.ovf, 0, sizeof(int32_t)));

@@ -344,9 +344,10 @@ struct BigBs {
     double *sbb = nullptr;         // [cap_T][BIG_BOX] per tile: the lowest position, velocity and A by
                                    //   component, the highest, the largest S
     // the list path's state buffers, so that the extrapolation columns advance side by side:
-    // buffer 0 holds Y's positions, buffers 1 + 2k and 2 + 2k column k's sub-step states
-    double4 *P = nullptr;          // [1 + 2 BS_KMAX][cap_M] (x, y, z, mass)
-    double *V = nullptr;           // [2 BS_KMAX][3][cap_M] velocities of buffers 1..
+    // buffer 0 holds Y's positions, buffers 1 + 4k .. 4 + 4k column k's, two of one round and two of
+    // the next
+    double4 *P = nullptr;          // [1 + 4 BS_KMAX][cap_M] (x, y, z, mass), in a pair's second buffer (.., 1 / (0.9 r_crit))
+    double *V = nullptr;           // [2 BS_KMAX][3][cap_M] the columns' velocities
     int32_t *status = nullptr;     // pinned host words that big_control_kernel writes: groups not yet at dt,
                                    //   lists overflowed, attempts the slowest group needs at least
     int32_t *ovf = nullptr;        // device word: a list exceeded BIG_LIST_CAP (the host falls back to tiles)

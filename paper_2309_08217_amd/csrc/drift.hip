@@ -1010,7 +1010,7 @@ __device__ bool bs_columns(const BsMember &me, int k, BsShared &S, double (*row)
 constexpr int WG_THREADS = BS_KMAX * BS_LANES;
 
 struct BsWgShared {
-    double pos[BS_KMAX][BS_LANES][3];          // each column's positions, for its pair forces
+    double pos[2][BS_KMAX][BS_LANES][3];       // each column's positions, for its pair forces
     double m[BS_LANES], i09[BS_LANES];
     double i9l[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1
     double tab[BS_KMAX][6][BS_LANES];          // Neville rows, extended in place
@@ -1020,66 +1020,63 @@ struct BsWgShared {
     int32_t kstar, kstar_att;                  // converged column and the attempt it ended
 };
 
-// One pass of column k for part `part` of member a's P lanes: the forces at z (when `on`),
-// between two barriers that every thread of the workgroup reaches.
-template <bool LV>
-__device__ void wg_forces(bool on, int k, int a, int part, int P, int nb, bool act, bool test, double mstar,
-                          double i09, BsWgShared &S, const double z[6], double d[6])
+// The forces of column k on part `part` of member a's P lanes at the positions z (when `on`), after
+// a barrier that every thread of the workgroup reaches; the caller has another before the next call
+// overwrites pos.
+template <bool LV, int NZ>
+__device__ void wg_forces(bool on, int k, int a, int part, int P, int nb, bool test, double mstar, double i09,
+                          BsWgShared &S, const double (&z)[NZ][3], double (&f)[NZ][3])
 {
-    if (part == 0) {
-        S.pos[k][a][0] = z[0];
-        S.pos[k][a][1] = z[1];
-        S.pos[k][a][2] = z[2];
-    }
+    if (part == 0)
+#pragma unroll
+        for (int s = 0; s < NZ; ++s)
+            for (int q = 0; q < 3; ++q) S.pos[s][k][a][q] = z[s][q];
     __syncthreads();
-    if (on) {
-        double ax = 0.0, ay = 0.0, az = 0.0;
-        if (part == 0) {
-            const double ri = inv_sqrt64(z[0] * z[0] + z[1] * z[1] + z[2] * z[2]);
-            const double s = -mstar * (ri * ri) * ri;
-            ax = s * z[0];
-            ay = s * z[1];
-            az = s * z[2];
-        }
-        // first the partners inside r_crit,ab, a bit each (in a chain of encounters most members
-        // are farther apart), then only their terms, every lane its own
-        unsigned long long near = 0;
-        for (int b = part, n = 0; b < nb; b += P, ++n) {
-            const double dx = S.pos[k][b][0] - z[0];
-            const double dy = S.pos[k][b][1] - z[1];
-            const double dz = S.pos[k][b][2] - z[2];
-            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double i = fmin(i09, S.i09[b]);
-            // r / (0.9 r_crit) < 10/9, with a margin for the rounding
-            const bool in = (q * i) * i < 100.0 / 81.0 * (1.0 + 0x1p-40);
-            near |= (unsigned long long)(in && b != a && !(test && S.test[b])) << n;
-        }
-        while (near) {
-            const int b = part + P * __builtin_ctzll(near);
-            near &= near - 1;
-            const double dx = S.pos[k][b][0] - z[0];
-            const double dy = S.pos[k][b][1] - z[1];
-            const double dz = S.pos[k][b][2] - z[2];
-            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double t = encounter_factor<LV>(q, S.m[b], fmin(i09, S.i09[b]), S.nlev, &S.i9l[0][a], &S.i9l[0][b],
-                                                  BS_LANES);
-            ax = fma(t, dx, ax);
-            ay = fma(t, dy, ay);
-            az = fma(t, dz, az);
-        }
-        for (int o = 1; o < P; o <<= 1) {
-            ax += __shfl_xor(ax, o, 64);
-            ay += __shfl_xor(ay, o, 64);
-            az += __shfl_xor(az, o, 64);
-        }
-        d[0] = act ? z[3] : 0.0;
-        d[1] = act ? z[4] : 0.0;
-        d[2] = act ? z[5] : 0.0;
-        d[3] = act ? ax : 0.0;
-        d[4] = act ? ay : 0.0;
-        d[5] = act ? az : 0.0;
+    if (!on) return;
+#pragma unroll
+    for (int s = 0; s < NZ; ++s) {
+        const double ri = inv_sqrt64(z[s][0] * z[s][0] + z[s][1] * z[s][1] + z[s][2] * z[s][2]);
+        const double w = part == 0 ? -mstar * (ri * ri) * ri : 0.0;
+        for (int q = 0; q < 3; ++q) f[s][q] = w * z[s][q];
     }
-    __syncthreads(); // the next pass overwrites pos
+    // first the partners inside r_crit,ab at either position, a bit each (in a chain of encounters
+    // most members are farther apart), then only their terms, every lane its own (outside r_crit,ab
+    // a term is zero)
+    unsigned long long near = 0;
+    for (int b = part, n = 0; b < nb; b += P, ++n) {
+        const double i = fmin(i09, S.i09[b]);
+        bool in = false;
+#pragma unroll
+        for (int s = 0; s < NZ; ++s) {
+            const double dx = S.pos[s][k][b][0] - z[s][0];
+            const double dy = S.pos[s][k][b][1] - z[s][1];
+            const double dz = S.pos[s][k][b][2] - z[s][2];
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            // r / (0.9 r_crit) < 10/9, with a margin for the rounding
+            in |= (q * i) * i < 100.0 / 81.0 * (1.0 + 0x1p-40);
+        }
+        near |= (unsigned long long)(in && b != a && !(test && S.test[b])) << n;
+    }
+    while (near) {
+        const int b = part + P * __builtin_ctzll(near);
+        near &= near - 1;
+        const double mb = S.m[b], ib = fmin(i09, S.i09[b]);
+#pragma unroll
+        for (int s = 0; s < NZ; ++s) {
+            const double dx = S.pos[s][k][b][0] - z[s][0];
+            const double dy = S.pos[s][k][b][1] - z[s][1];
+            const double dz = S.pos[s][k][b][2] - z[s][2];
+            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
+            const double t = encounter_factor<LV>(q, mb, ib, S.nlev, &S.i9l[0][a], &S.i9l[0][b], BS_LANES);
+            f[s][0] = fma(t, dx, f[s][0]);
+            f[s][1] = fma(t, dy, f[s][1]);
+            f[s][2] = fma(t, dz, f[s][2]);
+        }
+    }
+    for (int o = 1; o < P; o <<= 1)
+#pragma unroll
+        for (int s = 0; s < NZ; ++s)
+            for (int q = 0; q < 3; ++q) f[s][q] += __shfl_xor(f[s][q], o, 64);
 }
 
 template <bool LV>
@@ -1096,24 +1093,39 @@ __device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bo
         if (H < dt * 0x1p-40 || ++attempts > 20000) return false;
         const double sr = wave_max(act ? sqrt(Y[0] * Y[0] + Y[1] * Y[1] + Y[2] * Y[2]) : 0.0);
         const double sv = wave_max(act ? sqrt(Y[3] * Y[3] + Y[4] * Y[4] + Y[5] * Y[5]) : 0.0);
-        const double h = H / nsub;
-        double zm[6], zc[6], T[6];
-        for (int q = 0; q < 6; ++q) zc[q] = zm[q] = T[q] = Y[q];
+        const double h = H / nsub, h2 = 2.0 * h;
+        // z_i and z_i+1, u_i, u_i-1, i = 2 kk + 1 (as in bs_pair)
+        double z[2][3], f[2][3] = {}, ui[3], up[3], T[6];
+        {
+            const double y0[1][3] = {{Y[0], Y[1], Y[2]}};
+            double f0[1][3] = {};
+            wg_forces<LV, 1>(act, k, a, part, P, nb, test, mstar, i09, S, y0, f0);
+            for (int q = 0; q < 3; ++q) {
+                up[q] = Y[3 + q];
+                ui[q] = up[q] + h * f0[0][q];
+                z[0][q] = Y[q] + h * up[q];
+                z[1][q] = Y[q] + h2 * ui[q];
+            }
+            __syncthreads(); // the first round overwrites pos
+        }
         int kstar = -1;
 #pragma unroll 1
-        for (int i = 0; i <= 2 * BS_KMAX; ++i) {
-            double dd[6];
-            wg_forces<LV>(i <= nsub, k, a, part, P, nb, act, test, mstar, i09, S, zc, dd);
-            if (i == 0) {
-                for (int q = 0; q < 6; ++q) zc[q] = zm[q] + h * dd[q];
-            } else if (i < nsub) {
-                for (int q = 0; q < 6; ++q) {
-                    const double tq = zm[q] + 2.0 * h * dd[q];
-                    zm[q] = zc[q];
-                    zc[q] = tq;
+        for (int kk = 0; kk < BS_KMAX; ++kk) {
+            wg_forces<LV, 2>(act && kk <= k, k, a, part, P, nb, test, mstar, i09, S, z, f);
+            double un[3]; // u_i+1
+            for (int q = 0; q < 3; ++q) un[q] = up[q] + h2 * f[0][q];
+            if (kk < k) {
+                for (int q = 0; q < 3; ++q) {
+                    up[q] = un[q];
+                    ui[q] = ui[q] + h2 * f[1][q];
+                    z[0][q] = z[0][q] + h2 * un[q];
+                    z[1][q] = z[1][q] + h2 * ui[q];
                 }
-            } else if (i == nsub) {
-                for (int q = 0; q < 6; ++q) T[q] = 0.5 * (zm[q] + zc[q] + h * dd[q]); // T(k, 0)
+            } else if (kk == k) {
+                for (int q = 0; q < 3; ++q) { // T(k, 0)
+                    T[q] = 0.5 * (z[0][q] + z[1][q] + h * un[q]);
+                    T[3 + q] = 0.5 * (ui[q] + un[q] + h * f[1][q]);
+                }
                 // Neville: row k - 1 is replaced by row k in place (T(k, l-1) goes into slot
                 // l-1 once T(k-1, l-1) has been read from it)
                 double dp = 0.0, dv = 0.0;
@@ -1146,8 +1158,7 @@ __device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bo
                     }
                 }
             }
-            if (i < 2 || (i & 1)) continue; // columns complete at even passes
-            __syncthreads();                // the completed column's verdict
+            __syncthreads(); // the completed column's verdict; the next round overwrites pos
             if (S.kstar_att == attempts) {
                 kstar = S.kstar;
                 break;

@@ -860,7 +860,12 @@ struct BsMember {
 // product over levels 0..nlev-1 of (1 - K_k), so zero beyond the deepest level's radius (the
 // radii do not grow with the level); ia / ib give the two members' 1 / (0.9 r_crit) of levels
 // 1.. with the given stride.
-template <bool LV>
+//
+// ALL (ia and ib in registers): every level there can be, those above nlev with 1 / (0.9 r_crit) = 0,
+// which leaves the product as it is; a loop to nlev would index the arrays, that is, keep them in
+// scratch memory (drifts in the levels of 40322
+// bodies 108 -> 88 us).
+template <bool LV, bool ALL = false>
 __device__ __forceinline__ double encounter_factor(double q, double m, double i09, int nlev, const double *ia,
                                                    const double *ib, int stride)
 {
@@ -868,7 +873,8 @@ __device__ __forceinline__ double encounter_factor(double q, double m, double i0
     const Changeover c = changeover_parts(r, i09);
     double u = c.u, d = c.d;
     if constexpr (LV)
-        for (int k = 1; k < nlev; ++k) {
+#pragma unroll
+        for (int k = 1; k < (ALL ? LEVELS_MAX : nlev); ++k) {
             const Changeover ck = changeover_parts(r, fmin(ia[(k - 1) * stride], ib[(k - 1) * stride]));
             u *= ck.u;
             d *= ck.d;
@@ -1202,8 +1208,7 @@ __device__ __forceinline__ double quad_sum(double v)
 
 struct PairGroup {
     double mstar, mp, i09;      // mp: the partner's mass, 0 between two test bodies
-    double i9l[LEVELS_MAX - 1]; // hierarchical levels 1..nlev-1
-    int nlev;
+    double i9l[LEVELS_MAX - 1]; // hierarchical levels 1.., 0 above nlev - 1
 };
 
 template <bool LV>
@@ -1214,7 +1219,7 @@ __device__ __forceinline__ double pair_accel(const PairGroup &g, double z)
     const double ri = inv_sqrt64(q0);
     // (two test bodies: a mass of zero at any separation; a branch here would keep the forces of a
     // round from running side by side)
-    const double f = encounter_factor<LV>(g.mp != 0.0 ? q1 : 1.0, g.mp, g.i09, g.nlev, g.i9l, g.i9l, 1);
+    const double f = encounter_factor<LV, true>(g.mp != 0.0 ? q1 : 1.0, g.mp, g.i09, LEVELS_MAX, g.i9l, g.i9l, 1);
     return fma(f, dz, -g.mstar * (ri * ri) * ri * z);
 }
 
@@ -1304,8 +1309,8 @@ __device__ bool run_pair(const BsShared &S, int lane, double ms, double *x, doub
     g.mstar = ms;
     g.mp = S.test[0] && S.test[1] ? 0.0 : S.m[1 - body];
     g.i09 = fmin(S.i09[0], S.i09[1]);
-    g.nlev = S.nlev;
     if constexpr (LV)
+#pragma unroll
         for (int l = 0; l + 1 < LEVELS_MAX; ++l) g.i9l[l] = l + 1 < S.nlev ? fmin(S.i9l[l][0], S.i9l[l][1]) : 0.0;
     const int b = mem[body];
     double *px = c == 0 ? x : c == 1 ? y : z, *pv = c == 0 ? vx : c == 1 ? vy : vz;
@@ -1331,8 +1336,7 @@ struct SmallGroup {
     double m[NB];
     double i09[NB][NB];                           // per pair a < b: 1 / (0.9 r_crit,ab)
     bool skip[NB][NB];                            // both are test bodies (TP2)
-    int nlev;                                     // hierarchical levels
-    double i9l[LEVELS_MAX - 1][NB];               // levels 1..nlev-1: 1 / (0.9 r_crit) of each member
+    double i9l[LEVELS_MAX - 1][NB];               // levels 1..: 1 / (0.9 r_crit) of each member, 0 above nlev - 1
 };
 
 template <int NB, bool LV>
@@ -1357,7 +1361,7 @@ __device__ __forceinline__ void small_forces(const SmallGroup<NB> &g, const doub
             if (g.skip[a][b]) continue;
             const double dx = z[b][0] - z[a][0], dy = z[b][1] - z[a][1], dz = z[b][2] - z[a][2];
             const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double u = encounter_factor<LV>(q, 1.0, g.i09[a][b], g.nlev, &g.i9l[0][a], &g.i9l[0][b], NB);
+            const double u = encounter_factor<LV, true>(q, 1.0, g.i09[a][b], LEVELS_MAX, &g.i9l[0][a], &g.i9l[0][b], NB);
             const double ua = g.m[b] * u, ub = g.m[a] * u;
             d[a][3] = fma(ua, dx, d[a][3]);
             d[a][4] = fma(ua, dy, d[a][4]);
@@ -1486,11 +1490,11 @@ __device__ bool run_small(const BsShared &S, int lane, double ms, double *x, dou
             g.skip[a][b] = S.test[a] && S.test[b];
         }
     }
-    g.nlev = S.nlev;
     if constexpr (LV)
-        for (int k = 1; k < S.nlev; ++k)
 #pragma unroll
-            for (int a = 0; a < NB; ++a) g.i9l[k - 1][a] = S.i9l[k - 1][a];
+        for (int k = 1; k < LEVELS_MAX; ++k)
+#pragma unroll
+            for (int a = 0; a < NB; ++a) g.i9l[k - 1][a] = k < S.nlev ? S.i9l[k - 1][a] : 0.0;
     if (lane < NB) {
         const int b = mem[lane];
         ybuf[6 * lane + 0] = x[b] + sh[0];

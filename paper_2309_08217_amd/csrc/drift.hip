@@ -840,7 +840,7 @@ __device__ __forceinline__ double neville_c(int k, int l)
 
 // Members' data shared by the lanes of the group's wave.
 struct BsShared {
-    double pos[BS_LANES][4];                   // positions published for the pair forces
+    double pos[2][BS_LANES][4];                // positions published for the pair forces
     double m[BS_LANES];                        // member masses
     double i09[BS_LANES];                      // 1 / (0.9 r_crit)
     double i9l[LEVELS_MAX - 1][BS_LANES];      // hierarchical levels 1..nlev-1: the same of each
@@ -854,6 +854,15 @@ struct BsMember {
     bool act, test;
     double mstar, i09;
 };
+
+template <int CTRL>
+__device__ __forceinline__ double dpp64(double v)
+{
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141; // quad_perm, row_half_mirror
 
 // m (1 - K) / r^3 of a pair at squared separation q: the factor of its difference vector in the
 // encounter force, zero outside r_crit,ab.  With LV (hierarchical levels) the weight is the
@@ -882,137 +891,147 @@ __device__ __forceinline__ double encounter_factor(double q, double m, double i0
     return m * (u * u) * inv64(d) * ((rq * rq) * rq);
 }
 
-// dY/dt: Kepler term about the Sun plus the (1 - K) share of the Newtonian forces from the
-// other members (K of Chambers 1999 over [0.1, 1] r_crit,ab; two test bodies do not
-// interact).  Every lane of the wave calls it.
-template <bool LV>
-__device__ void bs_forces(const BsMember &me, BsShared &S, int slot, const double z[6], double d[6])
+// The forces at the positions z: the Kepler term about the Sun plus the (1 - K) share of the
+// Newtonian forces from the other members (K of Chambers 1999 over [0.1, 1] r_crit,ab; two test
+// bodies do not interact).  Every lane of the wave calls it.
+template <bool LV, int NZ>
+__device__ __forceinline__ void bs_forces(const BsMember &me, BsShared &S, int slot, const double (&z)[NZ][3],
+                                          double (&f)[NZ][3])
 {
-    S.pos[slot][0] = z[0];
-    S.pos[slot][1] = z[1];
-    S.pos[slot][2] = z[2];
+#pragma unroll
+    for (int s = 0; s < NZ; ++s)
+        for (int q = 0; q < 3; ++q) S.pos[s][slot][q] = z[s][q];
     __syncthreads();
-    const double ri = inv_sqrt64(z[0] * z[0] + z[1] * z[1] + z[2] * z[2]);
-    const double s = -me.mstar * (ri * ri) * ri;
-    double ax = s * z[0], ay = s * z[1], az = s * z[2];
+#pragma unroll
+    for (int s = 0; s < NZ; ++s) {
+        const double ri = inv_sqrt64(z[s][0] * z[s][0] + z[s][1] * z[s][1] + z[s][2] * z[s][2]);
+        const double w = -me.mstar * (ri * ri) * ri;
+        for (int q = 0; q < 3; ++q) f[s][q] = w * z[s][q];
+    }
     // two independent terms at a time; the member itself and a second test body get mass zero
-#pragma unroll 2
+#pragma unroll(3 - NZ)
     for (int b = 0; b < me.nb; ++b) {
         const bool skip = b == me.a || (me.test && S.test[b]);
-        const double dx = S.pos[me.base + b][0] - z[0];
-        const double dy = S.pos[me.base + b][1] - z[1];
-        const double dz = S.pos[me.base + b][2] - z[2];
-        const double q = skip ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
-        const double t = encounter_factor<LV>(q, skip ? 0.0 : S.m[b], fmin(me.i09, S.i09[b]), S.nlev, &S.i9l[0][me.a],
-                                              &S.i9l[0][b], BS_LANES);
-        ax = fma(t, dx, ax);
-        ay = fma(t, dy, ay);
-        az = fma(t, dz, az);
+        const double mb = skip ? 0.0 : S.m[b], ib = fmin(me.i09, S.i09[b]);
+#pragma unroll
+        for (int s = 0; s < NZ; ++s) {
+            const double dx = S.pos[s][me.base + b][0] - z[s][0];
+            const double dy = S.pos[s][me.base + b][1] - z[s][1];
+            const double dz = S.pos[s][me.base + b][2] - z[s][2];
+            const double q = skip ? 1.0 : fma(dx, dx, fma(dy, dy, dz * dz));
+            const double t = encounter_factor<LV>(q, mb, ib, S.nlev, &S.i9l[0][me.a], &S.i9l[0][b], BS_LANES);
+            f[s][0] = fma(t, dx, f[s][0]);
+            f[s][1] = fma(t, dy, f[s][1]);
+            f[s][2] = fma(t, dz, f[s][2]);
+        }
     }
     __syncthreads(); // the next call overwrites pos
-    d[0] = me.act ? z[3] : 0.0;
-    d[1] = me.act ? z[4] : 0.0;
-    d[2] = me.act ? z[5] : 0.0;
-    d[3] = me.act ? ax : 0.0;
-    d[4] = me.act ? ay : 0.0;
-    d[5] = me.act ? az : 0.0;
 }
 
-// Groups of up to CP_MEM members.  Lane 8k + a runs extrapolation column k for member a, so
-// the columns advance side by side, one force evaluation per pass.  Column k's sub-steps end
-// after n_k + 1 passes; its lanes then extend the tableau by row k (reading row k-1 from LDS)
-// and the wave ends the attempt as soon as a column has converged.  The accepted column is
-// the first converged one, as in the sequential scheme.
+// Groups of 3 to CP_MEM: lane (k, a) runs member a in extrapolation column k, two sub-steps a round
+// (as in bs_pair).  When column k ends, its T(k, 0) go to LDS, and the wave forms T(k, k) -
+// T(k, k-1) with one lane per state element, from the Lagrange form of the extrapolation
+// (LAGRANGE).  tcol: LDS [BS_KMAX][6 CP_MEM]; ybuf: [6 CP_MEM].  (With a Neville row per column and
+// one sub-step a round, and groups of three on a lane per column, the drift of 20040 bodies in TP2
+// mode took 19.6 us, now 14.9; drifts in the levels of 40322 bodies 84 and 76.)
 template <bool LV>
-__device__ bool bs_columns(const BsMember &me, int k, BsShared &S, double (*row)[BS_KMAX][CP_MEM][6],
-                           double Y[6], double dt, double tol)
+__device__ bool bs_columns(const BsMember &me, int k, int lane, BsShared &S, double *tcol, double *ybuf, double Y[6],
+                           double dt, double tol)
 {
-    const int slot = me.base + me.a;
-    const int nsub = 2 * (k + 1);
+    constexpr int E = 6 * CP_MEM;
+    static_assert(E <= BS_LANES && CP_MEM == 8, "an element per lane, a member per lane of eight");
+    const int slot = me.base + me.a, nsub = 2 * (k + 1);
+    const int e = lane < 6 * me.nb ? lane : 0; // this lane's state element in the extrapolation
+    const auto column = [&](int kk, const double *c) { // sum over columns 1..kk of c[j] (T(j, 0) - T(0, 0))
+        double v[BS_KMAX], s = 0.0;
+#pragma unroll
+        for (int j = 0; j < BS_KMAX; ++j) v[j] = tcol[E * j + e];
+#pragma unroll
+        for (int j = 1; j < BS_KMAX; ++j)
+            if (j <= kk) s = fma(c[j], v[j] - v[0], s);
+        return s;
+    };
+    const auto members_max = [](double v) { // over the eight lanes of a column
+        v = fmax(v, dpp64<DPP_XOR1>(v));
+        v = fmax(v, dpp64<DPP_XOR2>(v));
+        return fmax(v, dpp64<DPP_MIRROR8>(v));
+    };
     double t = 0.0, H = dt;
     int attempts = 0;
     while (t < dt) {
         const bool last = H >= (dt - t) * (1.0 - 0x1p-30); // ends the interval (exactly)
         if (last) H = dt - t;
         if (H < dt * 0x1p-40 || ++attempts > 20000) return false;
-        const double sr = wave_max(me.act ? sqrt(Y[0] * Y[0] + Y[1] * Y[1] + Y[2] * Y[2]) : 0.0);
-        const double sv = wave_max(me.act ? sqrt(Y[3] * Y[3] + Y[4] * Y[4] + Y[5] * Y[5]) : 0.0);
-        const double h = H / nsub;
-        double zm[6], zc[6], T[6];
-        for (int q = 0; q < 6; ++q) zc[q] = zm[q] = T[q] = Y[q];
+        const double sr = members_max(me.act ? sqrt(Y[0] * Y[0] + Y[1] * Y[1] + Y[2] * Y[2]) : 0.0);
+        const double sv = members_max(me.act ? sqrt(Y[3] * Y[3] + Y[4] * Y[4] + Y[5] * Y[5]) : 0.0);
+        const double scale = e % 6 < 3 ? sr : sv;
+        const double h = H / nsub, h2 = 2.0 * h;
+        // z_i and z_i+1, u_i, u_i-1, i = 2 kk + 1
+        double z[2][3], f[2][3], ui[3], up[3];
+        {
+            const double y0[1][3] = {{Y[0], Y[1], Y[2]}};
+            double f0[1][3];
+            bs_forces<LV, 1>(me, S, slot, y0, f0);
+            for (int q = 0; q < 3; ++q) {
+                up[q] = Y[3 + q];
+                ui[q] = up[q] + h * f0[0][q];
+                z[0][q] = Y[q] + h * up[q];
+                z[1][q] = Y[q] + h2 * ui[q];
+            }
+        }
         int kstar = -1;
         double err_last = 0.0;
 #pragma unroll 1
-        for (int i = 0; i <= 2 * BS_KMAX; ++i) {
-            double dd[6];
-            bs_forces<LV>(me, S, slot, zc, dd);
-            if (i == 0) {
-                for (int q = 0; q < 6; ++q) zc[q] = zm[q] + h * dd[q];
-            } else if (i < nsub) {
-                for (int q = 0; q < 6; ++q) {
-                    const double tq = zm[q] + 2.0 * h * dd[q];
-                    zm[q] = zc[q];
-                    zc[q] = tq;
+        for (int kk = 0; kk < BS_KMAX; ++kk) {
+            bs_forces<LV, 2>(me, S, slot, z, f);
+            double un[3]; // u_i+1
+            for (int q = 0; q < 3; ++q) un[q] = up[q] + h2 * f[0][q];
+            if (kk == k && me.act)
+                for (int q = 0; q < 3; ++q) { // T(k, 0)
+                    tcol[E * k + 6 * me.a + q] = 0.5 * (z[0][q] + z[1][q] + h * un[q]);
+                    tcol[E * k + 6 * me.a + 3 + q] = 0.5 * (ui[q] + un[q] + h * f[1][q]);
                 }
-            } else if (i == nsub) {
-                for (int q = 0; q < 6; ++q) T[q] = 0.5 * (zm[q] + zc[q] + h * dd[q]); // T(k, 0)
-            }
-            if (i < 2 || (i & 1)) continue;
-            const int kk = i / 2 - 1; // the column whose sub-steps have just ended
-            double err = 0.0;
-            if (k == kk) {
-                double(*mine)[CP_MEM][6] = row[kk & 1];
-                const double(*below)[CP_MEM][6] = row[(kk + 1) & 1]; // row kk - 1
-                for (int q = 0; q < 6; ++q) mine[0][me.a][q] = T[q];
-                double dp = 0.0, dv = 0.0; // |T(kk, l) - T(kk, l-1)| of the last pass, l = kk
-#pragma unroll 1
-                for (int l = 1; l <= kk; ++l) {
-                    const double c = neville_c(kk, l);
-                    dp = dv = 0.0;
-                    double bl[6];
-                    for (int q = 0; q < 6; ++q) bl[q] = below[l - 1][me.a][q];
-                    for (int q = 0; q < 6; ++q) {
-                        const double nx = T[q] + (T[q] - bl[q]) * c;
-                        if (q < 3) dp = fmax(dp, fabs(nx - T[q]));
-                        else dv = fmax(dv, fabs(nx - T[q]));
-                        T[q] = nx;
-                    }
-                    for (int q = 0; q < 6; ++q) mine[l][me.a][q] = T[q];
-                }
-                // max over elements of |diff| / scale (the scale is common, so divide once)
-                err = me.act ? fmax(dp / sr, dv / sv) : 0.0;
+            for (int q = 0; q < 3; ++q) { // unused once kk >= k
+                up[q] = un[q];
+                ui[q] = ui[q] + h2 * f[1][q];
+                z[0][q] = z[0][q] + h2 * un[q];
+                z[1][q] = z[1][q] + h2 * ui[q];
             }
             if (kk == 0) continue;
-            for (int o = 1; o < CP_MEM; o <<= 1) err = fmax(err, __shfl_xor(err, o, 64));
-            if (__ballot(k == kk && me.a == 0 && err <= tol)) {
+            __syncthreads();
+            const double diff = fabs(column(kk, LAGRANGE.d[kk]));
+            if (!__ballot(!(diff <= tol * scale))) {
                 kstar = kk;
                 break;
             }
-            if (kk == BS_KMAX - 1) err_last = __shfl(err, kk * CP_MEM, 64);
+            if (kk == BS_KMAX - 1) err_last = wave_max(diff / scale);
         }
         if (kstar >= 0) {
-            __syncthreads(); // row kstar, written by its column's lanes, is read by all
-            for (int q = 0; q < 6; ++q) Y[q] = row[kstar & 1][kstar][me.a][q];
-            __syncthreads();
+            const double y = tcol[e] + column(kstar, LAGRANGE.w[kstar]);
+            if (lane < 6 * me.nb) ybuf[lane] = y;
+            __syncthreads(); // (tcol has been read, too)
+            for (int q = 0; q < 6; ++q) Y[q] = ybuf[6 * (me.act ? me.a : 0) + q];
             t = last ? dt : t + H;
             if (kstar <= 4) H = 2.0 * H;
             else if (kstar == BS_KMAX - 1) H = 0.5 * H;
         } else {
             H = H * shrink_factor(err_last, tol);
         }
+        __syncthreads(); // ybuf and tcol are rewritten
     }
     return true;
 }
 
 // Groups of CP_MEM + 1 .. BS_LANES members: one workgroup of BS_KMAX waves, wave k running
-// extrapolation column k for every member, so the columns advance side by side, one force
-// evaluation per pass, and an attempt takes at most 2 BS_KMAX + 1 passes.  A member has P
+// extrapolation column k for every member, so the columns advance side by side, two sub-steps a
+// round (as in bs_pair), and an attempt takes at most BS_KMAX + 1 rounds.  A member has P
 // lanes (4 for groups of up to 16, 2 up to 32, else 1) that share its sources, sum every
-// P-th one and add the parts in a fixed tree.  Column k completes at pass 2(k + 1) and
+// P-th one and add the parts in a fixed tree.  Column k completes with round k and
 // extends each member's Neville row in place in LDS: it reads row k - 1, which column k - 1
-// wrote two passes before, and replaces it by row k, which column k + 1 reads two passes
-// later.  The tableau arithmetic and the accepted column (the first converged one) are those
-// of the sequential scheme.
+// wrote the round before, and replaces it by row k, which column k + 1 reads the round
+// after.  The tableau arithmetic and the accepted column (the first converged one) are those
+// of the sequential scheme.  Latency bound: the barriers, and the chain of a round's forces (the
+// launch of a dense annulus of 1000 bodies 137 us with one sub-step a round, 104 with two).
 constexpr int WG_THREADS = BS_KMAX * BS_LANES;
 
 struct BsWgShared {
@@ -1190,15 +1209,6 @@ __device__ bool bs_workgroup(int k, int a, int part, int P, int nb, bool act, bo
 // instructions, of which the sums over a quad and the partner's coordinate are DPP moves.
 // Latency bound (one wave per group, the slowest group sets the launch): with a column's whole
 // state in one lane a pass was about 200 instructions and 1.1 us.
-template <int CTRL>
-__device__ __forceinline__ double dpp64(double v)
-{
-    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_MIRROR8 = 0x141; // quad_perm, row_half_mirror
-
 // (a + b) + (c + d) over the quad's lanes, the same in each of them
 __device__ __forceinline__ double quad_sum(double v)
 {
@@ -1325,195 +1335,6 @@ __device__ bool run_pair(const BsShared &S, int lane, double ms, double *x, doub
     return ok;
 }
 
-// Groups of three: lane k runs
-// extrapolation column k for the whole group, so a force evaluation is lane-local (the pair
-// force is formed once and applied to both members) and needs no exchange between lanes.
-// When column k completes, T(k, 0) goes to LDS and the wave forms T(k, k) - T(k, k-1) with
-// one lane per state element, from the Lagrange form of the extrapolation (LAGRANGE).
-template <int NB>
-struct SmallGroup {
-    double mstar;
-    double m[NB];
-    double i09[NB][NB];                           // per pair a < b: 1 / (0.9 r_crit,ab)
-    bool skip[NB][NB];                            // both are test bodies (TP2)
-    double i9l[LEVELS_MAX - 1][NB];               // levels 1..: 1 / (0.9 r_crit) of each member, 0 above nlev - 1
-};
-
-template <int NB, bool LV>
-__device__ __forceinline__ void small_forces(const SmallGroup<NB> &g, const double (&z)[NB][6],
-                                             double (&d)[NB][6])
-{
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-        const double ri = inv_sqrt64(z[a][0] * z[a][0] + z[a][1] * z[a][1] + z[a][2] * z[a][2]);
-        const double s = -g.mstar * (ri * ri) * ri;
-        d[a][0] = z[a][3];
-        d[a][1] = z[a][4];
-        d[a][2] = z[a][5];
-        d[a][3] = s * z[a][0];
-        d[a][4] = s * z[a][1];
-        d[a][5] = s * z[a][2];
-    }
-#pragma unroll
-    for (int a = 0; a < NB; ++a)
-#pragma unroll
-        for (int b = a + 1; b < NB; ++b) {
-            if (g.skip[a][b]) continue;
-            const double dx = z[b][0] - z[a][0], dy = z[b][1] - z[a][1], dz = z[b][2] - z[a][2];
-            const double q = fma(dx, dx, fma(dy, dy, dz * dz));
-            const double u = encounter_factor<LV, true>(q, 1.0, g.i09[a][b], LEVELS_MAX, &g.i9l[0][a], &g.i9l[0][b], NB);
-            const double ua = g.m[b] * u, ub = g.m[a] * u;
-            d[a][3] = fma(ua, dx, d[a][3]);
-            d[a][4] = fma(ua, dy, d[a][4]);
-            d[a][5] = fma(ua, dz, d[a][5]);
-            d[b][3] = fma(-ub, dx, d[b][3]);
-            d[b][4] = fma(-ub, dy, d[b][4]);
-            d[b][5] = fma(-ub, dz, d[b][5]);
-        }
-}
-
-// Sum over the completed columns 1..k of c[j] (T(j, 0) - T(0, 0)) for this lane's element,
-// tcol[j * E + e] holding T(j, 0); every load is issued before the first use.
-template <int E>
-__device__ __forceinline__ double lagrange_sum(const double *tcol, const double *c, int k, int e)
-{
-    const double t0 = tcol[e];
-    double v[BS_KMAX], cj[BS_KMAX];
-#pragma unroll
-    for (int j = 1; j < BS_KMAX; ++j) {
-        v[j] = tcol[j * E + e];
-        cj[j] = c[j];
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int j = 1; j < BS_KMAX; ++j) {
-        const double f = fma(cj[j], v[j] - t0, s);
-        s = j <= k ? f : s; // rows above k are stale
-    }
-    return s;
-}
-
-// ybuf: the group state [NB][6] in LDS (read at entry, holds the result on return);
-// tcol: LDS [BS_KMAX][NB * 6] for T(k, 0); lag: LAGRANGE copied to LDS (w, then d).
-template <int NB, bool LV>
-__device__ bool bs_small(const SmallGroup<NB> &g, int lane, double *ybuf, double *tcol, const double *lag,
-                         double dt, double tol)
-{
-    constexpr int E = NB * 6;
-    const double *lw = lag, *ld = lag + BS_KMAX * BS_KMAX;
-    const int k = lane & (BS_KMAX - 1);
-    const bool writer = lane < BS_KMAX;
-    const int nsub = 2 * (k + 1);
-    const int e = lane < E ? lane : 0; // state element of this lane in the extrapolation
-    double t = 0.0, H = dt;
-    int attempts = 0;
-    while (t < dt) {
-        const bool last = H >= (dt - t) * (1.0 - 0x1p-30); // ends the interval (exactly)
-        if (last) H = dt - t;
-        if (H < dt * 0x1p-40 || ++attempts > 20000) return false;
-        const double h = H / nsub;
-        double zm[NB][6], zc[NB][6];
-        double sr = 0.0, sv = 0.0;
-#pragma unroll
-        for (int a = 0; a < NB; ++a) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) zc[a][q] = zm[a][q] = ybuf[6 * a + q];
-            sr = fmax(sr, sqrt(zm[a][0] * zm[a][0] + zm[a][1] * zm[a][1] + zm[a][2] * zm[a][2]));
-            sv = fmax(sv, sqrt(zm[a][3] * zm[a][3] + zm[a][4] * zm[a][4] + zm[a][5] * zm[a][5]));
-        }
-        const double scale = e % 6 < 3 ? sr : sv;
-        int kstar = -1;
-        double err_last = 0.0;
-#pragma unroll 1
-        for (int i = 0; i <= 2 * BS_KMAX; ++i) {
-            double dd[NB][6];
-            small_forces<NB, LV>(g, zc, dd);
-            if (i == 0) {
-#pragma unroll
-                for (int a = 0; a < NB; ++a)
-#pragma unroll
-                    for (int q = 0; q < 6; ++q) zc[a][q] = zm[a][q] + h * dd[a][q];
-            } else if (i < nsub) {
-#pragma unroll
-                for (int a = 0; a < NB; ++a)
-#pragma unroll
-                    for (int q = 0; q < 6; ++q) {
-                        const double tq = zm[a][q] + 2.0 * h * dd[a][q];
-                        zm[a][q] = zc[a][q];
-                        zc[a][q] = tq;
-                    }
-            } else if (i == nsub && writer) {
-#pragma unroll
-                for (int a = 0; a < NB; ++a)
-#pragma unroll
-                    for (int q = 0; q < 6; ++q) tcol[k * E + 6 * a + q] = 0.5 * (zm[a][q] + zc[a][q] + h * dd[a][q]);
-            }
-            if (i < 2 || (i & 1)) continue;
-            const int kk = i / 2 - 1; // the column that has just completed
-            __syncthreads();          // its T(kk, 0) is read by every lane
-            if (kk == 0) continue;
-            const double diff = fabs(lagrange_sum<E>(tcol, ld + kk * BS_KMAX, kk, e));
-            if (!__ballot(lane < E && !(diff <= tol * scale))) {
-                kstar = kk;
-                break;
-            }
-            if (kk == BS_KMAX - 1) err_last = wave_max(lane < E ? diff / scale : 0.0);
-        }
-        if (kstar >= 0) {
-            const double y = tcol[e] + lagrange_sum<E>(tcol, lw + kstar * BS_KMAX, kstar, e);
-            __syncthreads(); // every lane has read ybuf and tcol
-            if (lane < E) ybuf[e] = y;
-            __syncthreads();
-            t = last ? dt : t + H;
-            if (kstar <= 4) H = 2.0 * H;
-            else if (kstar == BS_KMAX - 1) H = 0.5 * H;
-        } else {
-            H = H * shrink_factor(err_last, tol);
-        }
-    }
-    return true;
-}
-
-template <int NB, bool LV>
-__device__ bool run_small(const BsShared &S, int lane, double ms, double *x, double *y, double *z,
-                          double *vx, double *vy, double *vz, const int32_t *mem, double *ybuf,
-                          double *tcol, double *lag, double dt, const double sh[3], double p[3])
-{
-    SmallGroup<NB> g;
-    g.mstar = ms;
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-        g.m[a] = S.m[a];
-#pragma unroll
-        for (int b = a + 1; b < NB; ++b) {
-            g.i09[a][b] = fmin(S.i09[a], S.i09[b]);
-            g.skip[a][b] = S.test[a] && S.test[b];
-        }
-    }
-    if constexpr (LV)
-#pragma unroll
-        for (int k = 1; k < LEVELS_MAX; ++k)
-#pragma unroll
-            for (int a = 0; a < NB; ++a) g.i9l[k - 1][a] = k < S.nlev ? S.i9l[k - 1][a] : 0.0;
-    if (lane < NB) {
-        const int b = mem[lane];
-        ybuf[6 * lane + 0] = x[b] + sh[0];
-        ybuf[6 * lane + 1] = y[b] + sh[1];
-        ybuf[6 * lane + 2] = z[b] + sh[2];
-        ybuf[6 * lane + 3] = vx[b];
-        ybuf[6 * lane + 4] = vy[b];
-        ybuf[6 * lane + 5] = vz[b];
-    }
-    lag[lane] = (&LAGRANGE.w[0][0])[lane];
-    lag[BS_LANES + lane] = (&LAGRANGE.d[0][0])[lane];
-    __syncthreads();
-    const bool ok = bs_small<NB, LV>(g, lane, ybuf, tcol, lag, dt, 1e-12);
-    __syncthreads();
-    for (int q = 0; q < 3; ++q) p[q] = lane < NB ? S.m[lane] * ybuf[6 * lane + 3 + q] : 0.0;
-    if (lane < NB) store_state(x, y, z, vx, vy, vz, mem[lane], ybuf + 6 * lane);
-    return ok;
-}
-
 // The first half of a Sun drift in the drift launches: tau P / Mstar of system s (zero without pm).
 __device__ __forceinline__ void sun_shift_of(const StepMomentum &pm, const double *mstar, int s, double sh[3])
 {
@@ -1582,13 +1403,10 @@ __global__ __launch_bounds__(BS_LANES) __attribute__((amdgpu_waves_per_eu(2))) v
                                                          int32_t *flags, int big_groups, int bs_blocks,
                                                          const double *rc_lv, int nlev, StepMomentum pm, int one_sys)
 {
-    // the column path's two Neville rows; the small-group path's T(k, 0) table and Lagrange
-    // weights fit in the same space.  The block's LDS sets how many share a CU.
-    constexpr int TAB = 2 * BS_KMAX * CP_MEM * 6;
-    static_assert(BS_KMAX * 3 * 6 + 2 * BS_LANES <= TAB, "small-group tables fit");
+    // T(k, 0) of a group's state elements, and its state.  The block's LDS sets how many share a CU.
     __shared__ BsShared S;
-    __shared__ double tab[TAB];
-    __shared__ double ybuf[3 * 6];
+    __shared__ double tab[BS_KMAX * CP_MEM * 6];
+    __shared__ double ybuf[CP_MEM * 6];
     const int lane = threadIdx.x;
     double sh[3], p[3] = {0.0, 0.0, 0.0};
     if ((int)blockIdx.x >= bs_blocks) {
@@ -1652,10 +1470,8 @@ __global__ __launch_bounds__(BS_LANES) __attribute__((amdgpu_waves_per_eu(2))) v
     if (lane == 0) S.nlev = nlev;
     __syncthreads();
     bool ok;
-    if (nb <= 3) {
-        double *lag = tab + BS_KMAX * 3 * 6;
-        ok = nb == 2 ? run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt, sh, p)
-                     : run_small<3, LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, ybuf, tab, lag, dt, sh, p);
+    if (nb == 2) {
+        ok = run_pair<LV>(S, lane, ms, x, y, z, vx, vy, vz, members + k0, tab, dt, sh, p);
     } else {
         const int k = lane / CP_MEM;
         BsMember me;
@@ -1669,7 +1485,7 @@ __global__ __launch_bounds__(BS_LANES) __attribute__((amdgpu_waves_per_eu(2))) v
         me.i09 = S.i09[ai];
         const int b = members[k0 + ai];
         double Y[6] = {x[b] + sh[0], y[b] + sh[1], z[b] + sh[2], vx[b], vy[b], vz[b]};
-        ok = bs_columns<LV>(me, k, S, (double(*)[BS_KMAX][CP_MEM][6])tab, Y, dt, 1e-12);
+        ok = bs_columns<LV>(me, k, lane, S, tab, ybuf, Y, dt, 1e-12);
         // every lane has read its member's state before the first force evaluation's barrier
         if (me.act && k == 0) {
             store_state(x, y, z, vx, vy, vz, b, Y);

@@ -1,11 +1,12 @@
 // Drift part of the hybrid symplectic step (Brasser et al. 2023, Sect. 1), all FP64:
 //  * Sun drift: r_i += tau * (sum_j m_j v_j) / Mstar (democratic heliocentric split);
-//  * Kepler drift of every body not in a close encounter, by universal variables
-//    (Stumpff functions, safeguarded Newton on the universal Kepler equation);
+//  * Kepler drift of every body not in a close encounter, by universal variables (Stumpff
+//    functions; Halley's method on the universal Kepler equation, a bracketed solver where it
+//    does not settle);
 //  * close-encounter step: the encounter pairs are joined into groups (connected components,
-//    one workgroup, union-find in global memory, members sorted in LDS), and each group is
-//    integrated over dt by Gragg-Bulirsch-Stoer under the Sun's force plus the (1 - K) share
-//    of the members' mutual forces; the Kepler kernel then writes the group results back.
+//    one workgroup, in LDS for up to 1024 pairs), and each group is integrated over dt by
+//    Gragg-Bulirsch-Stoer under the Sun's force plus the (1 - K) share of the members' mutual
+//    forces, in the same launch as the Kepler drift (groups of 9-64 in one beside or after it).
 #include "genga_internal.h"
 #include "pair_math.h"
 #include "union_find.h"
@@ -19,7 +20,7 @@ namespace {
 // block reduction), then every chunk adds its system's partials in chunk order and shifts
 // its positions.  Deterministic.
 // ------------------------------------------------------------------------------------------
-constexpr int SUN_THREADS = SYS_P_THREADS;
+constexpr int SUN_THREADS = CHUNK;
 
 __global__ __launch_bounds__(SUN_THREADS) void momentum_kernel(const Chunk *chunks, const double *m,
                                                                const double *vx, const double *vy,
@@ -53,13 +54,41 @@ __global__ __launch_bounds__(SUN_THREADS) void momentum_kernel(const Chunk *chun
     }
 }
 
+// Momentum of system s for a block of SUN_THREADS threads: the chunk partials summed with a
+// stride, then a fixed tree, so every block of the system gets the same value.
+__device__ __forceinline__ void system_momentum(const int32_t *chunk_first, const double *mom_part, int s,
+                                                double (*red)[SUN_THREADS / 64], double P[3])
+{
+    double Px = 0.0, Py = 0.0, Pz = 0.0;
+    for (int k = chunk_first[s] + threadIdx.x; k < chunk_first[s + 1]; k += SUN_THREADS) {
+        Px += mom_part[3 * (size_t)k];
+        Py += mom_part[3 * (size_t)k + 1];
+        Pz += mom_part[3 * (size_t)k + 2];
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        Px += __shfl_xor(Px, o, 64);
+        Py += __shfl_xor(Py, o, 64);
+        Pz += __shfl_xor(Pz, o, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = Px;
+        red[1][threadIdx.x >> 6] = Py;
+        red[2][threadIdx.x >> 6] = Pz;
+    }
+    __syncthreads();
+    P[0] = P[1] = P[2] = 0.0;
+    for (int w = 0; w < SUN_THREADS / 64; ++w)
+        for (int q = 0; q < 3; ++q) P[q] += red[q][w];
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(SUN_THREADS) void sun_shift_kernel(const Chunk *chunks,
                                                                 const int32_t *chunk_first,
                                                                 const double *mstar,
                                                                 const double *mom_part, double tau,
                                                                 double *x, double *y, double *z)
 {
-    __shared__ double red[3][SYS_P_THREADS / 64];
+    __shared__ double red[3][SUN_THREADS / 64];
     const Chunk c = chunks[blockIdx.x];
     double P[3];
     system_momentum(chunk_first, mom_part, c.sys, red, P);
@@ -1597,14 +1626,6 @@ hipError_t launch_sun_drift(const Layout &L, double *x, double *y, double *z, co
     momentum_kernel<<<L.n_chunks, SUN_THREADS, 0, stream>>>(L.chunks, m, vx, vy, vz, mom_part);
     sun_shift_kernel<<<L.n_chunks, SUN_THREADS, 0, stream>>>(L.chunks, L.chunk_first, L.mstar, mom_part,
                                                              tau, x, y, z);
-    return hipGetLastError();
-}
-
-hipError_t launch_momentum(const Layout &L, const double *vx, const double *vy, const double *vz,
-                           const double *m, double *mom_part, hipStream_t stream)
-{
-    if (L.n_chunks == 0) return hipSuccess;
-    momentum_kernel<<<L.n_chunks, SUN_THREADS, 0, stream>>>(L.chunks, m, vx, vy, vz, mom_part);
     return hipGetLastError();
 }
 

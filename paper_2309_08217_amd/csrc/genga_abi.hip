@@ -360,17 +360,15 @@ KickArgs kick_args(const genga_ctx *ctx, const genga_bodies *b)
     return a;
 }
 
-// shift_tau != 0: the pass before the kick first applies the pending second half of a Sun drift
-// (see enqueue_drift with defer_shift)
 int enqueue_kick(genga_ctx *ctx, const genga_bodies *b, double tau, int update_v, int prec, int acc, double *ax,
-                 double *ay, double *az, hipStream_t s, double shift_tau = 0.0)
+                 double *ay, double *az, hipStream_t s)
 {
     const Layout &L = ctx->L;
     ctx->list_valid = true;
     if (L.n_total == 0) return GENGA_OK;
     const int fp32 = prec == GENGA_KICK_FP32;
-    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, fp32 ? ctx->m32 : nullptr, ctx->rc2_part,
-                        ctx->chunk_mass, ctx->pair_count, ctx->mom_part, shift_tau, s));
+    HIP_TRY(launch_prep(L, b->m, b->rcrit, fp32 ? ctx->m32 : nullptr, ctx->rc2_part,
+                        ctx->chunk_mass, ctx->pair_count, s));
     KickArgs a = kick_args(ctx, b);
     a.ax = ax;
     a.ay = ay;
@@ -395,8 +393,8 @@ int enqueue_pair_list(genga_ctx *ctx, const genga_bodies *b, hipStream_t s)
         HIP_TRY(hipMemsetAsync(ctx->pair_count, 0, sizeof(int32_t), s));
         return GENGA_OK;
     }
-    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, nullptr, ctx->rc2_part, ctx->chunk_mass,
-                        ctx->pair_count, nullptr, 0.0, s));
+    HIP_TRY(launch_prep(L, b->m, b->rcrit, nullptr, ctx->rc2_part, ctx->chunk_mass,
+                        ctx->pair_count, s));
     HIP_TRY(launch_pair_list(kick_args(ctx, b), s));
     return GENGA_OK;
 }
@@ -462,10 +460,8 @@ int enqueue_drift_parts(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t 
     return run_big_groups(ctx, b, dt, s, ctx->members);
 }
 
-// Sun drift (dt/2), Kepler / Bulirsch-Stoer (dt), Sun drift (dt/2).  With defer_shift the
-// last position shift is left to the next kick's source-record pass (only the momentum
-// partials are formed here); that kick must be given shift_tau = dt/2.
-int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, bool defer_shift = false)
+// Sun drift (dt/2), Kepler / Bulirsch-Stoer (dt), Sun drift (dt/2).
+int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s)
 {
     const Layout &L = ctx->L;
     ctx->list_valid = false;
@@ -475,7 +471,6 @@ int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, boo
         if (b->m != ctx->col.mass)
             return fail(GENGA_ERR_ARG, "with collisions on, the bodies' m must be the mass array given to "
                                        "genga_set_collisions");
-        if (defer_shift) return fail(GENGA_ERR_STATE, "collisions need the whole Sun drift inside the drift");
         // colliding encounter pairs, from the state at the start of the drift
         HIP_TRY(launch_collide_check(ctx->col, ctx->pairs, ctx->pair_count, ctx->pair_cap, b->x, b->y, b->z, b->vx,
                                      b->vy, b->vz, dt, s));
@@ -487,10 +482,7 @@ int enqueue_drift(genga_ctx *ctx, genga_bodies *b, double dt, hipStream_t s, boo
     HIP_TRY(launch_sun_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, 0.5 * dt, ctx->mom_part, s));
     if (!ctx->large_groups) HIP_TRY(launch_ce_groups(group_build(ctx), s));
     if ((rc = enqueue_drift_parts(ctx, b, dt, s))) return rc;
-    if (defer_shift)
-        HIP_TRY(launch_momentum(L, b->vx, b->vy, b->vz, b->m, ctx->mom_part, s));
-    else
-        HIP_TRY(launch_sun_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, 0.5 * dt, ctx->mom_part, s));
+    HIP_TRY(launch_sun_drift(L, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, 0.5 * dt, ctx->mom_part, s));
     if (collide) HIP_TRY(launch_collide_resolve(ctx->col, L.n_total, b->x, b->y, b->z, b->vx, b->vy, b->vz, s));
     return GENGA_OK;
 }
@@ -952,8 +944,8 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
 {
     const Layout &L = ctx->L;
     const bool large = ctx->large_groups != 0;
-    HIP_TRY(launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, prec == GENGA_KICK_FP32 ? ctx->m32 : nullptr, ctx->rc2_part,
-                        ctx->chunk_mass, ctx->pair_count, nullptr, 0.0, s));
+    HIP_TRY(launch_prep(L, b->m, b->rcrit, prec == GENGA_KICK_FP32 ? ctx->m32 : nullptr, ctx->rc2_part,
+                        ctx->chunk_mass, ctx->pair_count, s));
     int rc = enqueue_step_kick(ctx, b, 0.5 * dt, prec, acc, 0.0, !large, s);
     if (rc) return rc;
     StepMomentum pm = ctx->pm;
@@ -993,13 +985,10 @@ int enqueue_step(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, int pre
     if (rc) return rc;
     int rec = 0;
     for (int k = 1; k <= nsteps; ++k) {
-        // the second half Sun drift is left to the next kick's source pass, except with
-        // collisions, which are resolved on the drifted state
-        const bool defer = ctx->col.mass == nullptr;
-        rc = enqueue_drift(ctx, b, dt, s, defer);
+        rc = enqueue_drift(ctx, b, dt, s); // (collisions are resolved on the drifted state)
         if (rc) return rc;
         const bool last = k == nsteps;
-        rc = enqueue_kick(ctx, b, last ? 0.5 * dt : dt, 1, prec, acc, ax, ay, az, s, defer ? 0.5 * dt : 0.0);
+        rc = enqueue_kick(ctx, b, last ? 0.5 * dt : dt, 1, prec, acc, ax, ay, az, s);
         if (rc) return rc;
         if (cadence > 0 && d_energy && k % cadence == 0) {
             rc = enqueue_energy(ctx, b, last ? 0.0 : 0.5 * dt, d_energy + (size_t)rec * 4 * ctx->L.n_sys, s);
@@ -1201,8 +1190,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
 
     int32_t cap = pair_capacity > 0 ? pair_capacity : (int32_t)std::min<int64_t>(16 * (int64_t)n_total + 1024, INT32_MAX / 4);
     ctx->pair_cap = cap;
-    int64_t npow = 1;
-    while (npow < cap) npow <<= 1;
     const size_t nt = (size_t)n_total;
 
     HIP_TRY(dalloc(ctx->L.sys_off, n_sys + 1));
@@ -1223,7 +1210,7 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     HIP_TRY(dalloc(ctx->acc, 3 * nt));
     HIP_TRY(dalloc(ctx->pairs, 2 * (size_t)cap));
     HIP_TRY(dalloc(ctx->pair_count, 1));
-    HIP_TRY(dalloc(ctx->sort_keys, (size_t)npow));
+    HIP_TRY(dalloc(ctx->sort_keys, (size_t)cap));
     HIP_TRY(dalloc(ctx->flags, 1));
     HIP_TRY(dalloc(ctx->lab, nt));
     HIP_TRY(dalloc(ctx->mark, nt));
@@ -1629,8 +1616,8 @@ int genga_encounter_list(genga_ctx *ctx, const genga_bodies *b, int32_t *pairs, 
         return fail(GENGA_ERR_STATE, "no kick has run on the current positions: pass the bodies to list their "
                                      "encounter pairs");
     }
-    HIP_TRY(launch_sort_pairs(ctx->pairs, ctx->pair_count, ctx->pair_cap, pairs, cap, d_count, ctx->sort_keys,
-                              ctx->flags, s));
+    HIP_TRY(launch_sort_pairs(ctx->pairs, ctx->pair_count, ctx->pair_cap, ctx->L.n_total, pairs, cap, d_count,
+                              ctx->sort_keys, ctx->flags, s));
     return GENGA_OK;
 }
 

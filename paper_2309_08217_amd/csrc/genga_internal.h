@@ -183,12 +183,9 @@ struct EnergyTask {
 
 // Kernel launchers (each enqueues on `stream`; return hipError_t of the launch).
 // What the kick takes per chunk (r_crit^2 maxima, common masses), the masses in FP32 (m32 may be
-// null) and a cleared pair count.  With shift_tau != 0 the launch first finishes a Sun drift:
-// x += shift_tau P / Mstar per system, P summed from mom_part (the per-chunk partials of a
-// preceding launch_momentum).
-hipError_t launch_prep(const Layout &L, double *x, double *y, double *z, const double *m,
-                       const double *rc, float *m32, double *rc2_part, double *chunk_mass, int32_t *pair_count,
-                       const double *mom_part, double shift_tau, hipStream_t stream);
+// null) and a cleared pair count.
+hipError_t launch_prep(const Layout &L, const double *m, const double *rc, float *m32, double *rc2_part,
+                       double *chunk_mass, int32_t *pair_count, hipStream_t stream);
 // kahan: the FP32 kick's blocks are summed with Kahan compensation in FP32 (else in FP64)
 hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStream_t stream);
 // Arrays of the one-workgroup group builder.
@@ -213,38 +210,7 @@ hipError_t launch_rcrit(const Layout &L, const double *x, const double *y, const
 hipError_t launch_sun_drift(const Layout &L, double *x, double *y, double *z, const double *vx,
                             const double *vy, const double *vz, const double *m, double tau,
                             double *mom_part, hipStream_t stream);
-// Per-chunk partials of sum m v (the first half of launch_sun_drift).
-hipError_t launch_momentum(const Layout &L, const double *vx, const double *vy, const double *vz,
-                           const double *m, double *mom_part, hipStream_t stream);
 
-// Momentum of system s for a block of SYS_P_THREADS threads: the chunk partials summed with a
-// stride, then a fixed tree, so every block of the system gets the same value.
-constexpr int SYS_P_THREADS = 256;
-__device__ inline void system_momentum(const int32_t *chunk_first, const double *mom_part, int s,
-                                       double (*red)[SYS_P_THREADS / 64], double P[3])
-{
-    double Px = 0.0, Py = 0.0, Pz = 0.0;
-    for (int k = chunk_first[s] + threadIdx.x; k < chunk_first[s + 1]; k += SYS_P_THREADS) {
-        Px += mom_part[3 * (size_t)k];
-        Py += mom_part[3 * (size_t)k + 1];
-        Pz += mom_part[3 * (size_t)k + 2];
-    }
-    for (int o = 32; o > 0; o >>= 1) {
-        Px += __shfl_xor(Px, o, 64);
-        Py += __shfl_xor(Py, o, 64);
-        Pz += __shfl_xor(Pz, o, 64);
-    }
-    if ((threadIdx.x & 63) == 0) {
-        red[0][threadIdx.x >> 6] = Px;
-        red[1][threadIdx.x >> 6] = Py;
-        red[2][threadIdx.x >> 6] = Pz;
-    }
-    __syncthreads();
-    P[0] = P[1] = P[2] = 0.0;
-    for (int w = 0; w < SYS_P_THREADS / 64; ++w)
-        for (int q = 0; q < 3; ++q) P[q] += red[q][w];
-    __syncthreads();
-}
 // A caller's pair list src[min(*src_count, cap)][2] checked (0 <= i < j < n_total, one system)
 // and copied to dst; *dst_count = *src_count, or 0 with FLAG_BADPAIR when a pair is invalid
 // (bad: a device word, zero on entry and left zero).
@@ -507,7 +473,8 @@ hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tas
                          const double *x, const double *y, const double *z, const double *vx, const double *vy,
                          const double *vz, const double *m, const double *ax, const double *ay, const double *az,
                          double vshift, double *partial, double *out, hipStream_t stream);
-hipError_t launch_sort_pairs(const int32_t *src, const int32_t *src_count, int32_t src_cap,
+// The list src in lexicographic order in dst (keys: room for src_cap).
+hipError_t launch_sort_pairs(const int32_t *src, const int32_t *src_count, int32_t src_cap, int n_total,
                              int32_t *dst, int32_t dst_cap, int32_t *dst_count, uint64_t *keys,
                              int32_t *flags, hipStream_t stream);
 

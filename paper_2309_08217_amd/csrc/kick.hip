@@ -484,38 +484,18 @@ __global__ __launch_bounds__(64 * W) void kick64_kernel(KickArgs a)
 
 // Per chunk the largest r_crit^2 and the mass its bodies share (NaN: they differ), the masses in
 // FP32 (m32 may be null), and a cleared pair counter.
-__global__ __launch_bounds__(SYS_P_THREADS) void prep_kernel(const Chunk *chunks, const int32_t *chunk_first,
-                                                             const double *mstar, const double *mom_part,
-                                                             double shift_tau, double *x, double *y,
-                                                             double *z, const double *m,
-                                                             const double *rc, float *m32,
-                                                             double *rc2_part, double *chunk_mass, int32_t *pair_count)
+__global__ __launch_bounds__(CHUNK) void prep_kernel(const Chunk *chunks, const double *m, const double *rc,
+                                                     float *m32, double *rc2_part, double *chunk_mass,
+                                                     int32_t *pair_count)
 {
-    static_assert(CHUNK == SYS_P_THREADS, "one body per thread");
     const Chunk c = chunks[blockIdx.x];
     const int i = c.b + (int)threadIdx.x;
     const bool on = i < c.e;
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    if (shift_tau != 0.0) {
-        // the pending half of a Sun drift: x += tau P / Mstar (same arithmetic as sun_shift)
-        __shared__ double pred[3][SYS_P_THREADS / 64];
-        double P[3];
-        system_momentum(chunk_first, mom_part, c.sys, pred, P);
-        const double f = shift_tau / mstar[c.sys];
-        sx = f * P[0];
-        sy = f * P[1];
-        sz = f * P[2];
-        if (on) {
-            x[i] += sx;
-            y[i] += sy;
-            z[i] += sz;
-        }
-    }
     const double m0 = m[c.b], mi = on ? m[i] : m0, rci = on ? rc[i] : 0.0;
     if (on && m32) m32[i] = (float)mi;
     const double mx = wave_maxv(rci * rci);
-    __shared__ double red[SYS_P_THREADS / 64];
-    __shared__ int same[SYS_P_THREADS / 64];
+    __shared__ double red[CHUNK / 64];
+    __shared__ int same[CHUNK / 64];
     const bool eq = __all(mi == m0);
     if ((threadIdx.x & 63) == 0) {
         red[threadIdx.x >> 6] = mx;
@@ -525,7 +505,7 @@ __global__ __launch_bounds__(SYS_P_THREADS) void prep_kernel(const Chunk *chunks
     if (threadIdx.x == 0) {
         double r = 0.0;
         bool all = true;
-        for (int w = 0; w < SYS_P_THREADS / 64; ++w) {
+        for (int w = 0; w < CHUNK / 64; ++w) {
             r = fmax(r, red[w]);
             all = all && same[w] != 0;
         }
@@ -557,13 +537,11 @@ __global__ __launch_bounds__(256) void rcrit_kernel(int n_total, const int32_t *
 
 } // namespace
 
-hipError_t launch_prep(const Layout &L, double *x, double *y, double *z, const double *m,
-                       const double *rc, float *m32, double *rc2_part, double *chunk_mass, int32_t *pair_count,
-                       const double *mom_part, double shift_tau, hipStream_t stream)
+hipError_t launch_prep(const Layout &L, const double *m, const double *rc, float *m32, double *rc2_part,
+                       double *chunk_mass, int32_t *pair_count, hipStream_t stream)
 {
     if (L.n_chunks == 0) return hipSuccess;
-    prep_kernel<<<L.n_chunks, SYS_P_THREADS, 0, stream>>>(L.chunks, L.chunk_first, L.mstar, mom_part, shift_tau, x, y, z,
-                                                          m, rc, m32, rc2_part, chunk_mass, pair_count);
+    prep_kernel<<<L.n_chunks, CHUNK, 0, stream>>>(L.chunks, m, rc, m32, rc2_part, chunk_mass, pair_count);
     return hipGetLastError();
 }
 

@@ -129,8 +129,7 @@ extern "C" int genga_accel_noalloc(const genga_bodies *b, int32_t n, double *ax,
     L.chunk_first = small + 2;
     double *rc2_part = (double *)(base + OFF_RC2), *chunk_mass = (double *)(base + OFF_MASS);
     float *m32 = (float *)(base + OFF_M32);
-    e = launch_prep(L, b->x, b->y, b->z, b->m, b->rcrit, fp32 ? m32 : nullptr, rc2_part, chunk_mass, d_count, nullptr,
-                    0.0, s);
+    e = launch_prep(L, b->m, b->rcrit, fp32 ? m32 : nullptr, rc2_part, chunk_mass, d_count, s);
     if (e != hipSuccess) return fail(GENGA_ERR_HIP, "pass before the kick: %s", hipGetErrorString(e));
 
     KickArgs a{};

@@ -39,3 +39,25 @@ def test_accel_and_list_of_the_own_plan(n, rcrit):
     np.testing.assert_array_equal(s.encounter_list(cap=n * n, standalone=True)[0], exp)
     assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK
     s.close()
+
+
+@pytest.mark.parametrize("n,wide", [(700, 0), (2500, 0), (3000, 300), (8000, 7999)])
+def test_long_lists_in_order(n, wide):
+    """Lists on both sides of the length that one workgroup sorts (1024 pairs), with a body in the
+    middle of the order that has few partners, more than are ranked by counting (256) and more than
+    fit LDS (6144): the oracle's list, pair for pair."""
+    d = discs.disc_dense(n, seed=11)
+    rc = oracle.rcrit(d.state(), d.mstar, discs.DENSE_N1, discs.DENSE_N2, discs.DT_5_DAYS)
+    if wide:
+        st = d.state()
+        r = np.sort(np.sqrt(sum((st[k] - st[k][n // 2 if wide < n - 1 else 0]) ** 2 for k in ("x", "y", "z"))))
+        rc[n // 2 if wide < n - 1 else 0] = 2.0 * r[-1] if wide >= n - 1 else 0.5 * (r[2 * wide] + r[2 * wide + 1])
+    exp = oracle.encounters(d.state(), rc)
+    s = System([d], pair_capacity=len(exp) + 64, rcrit=rc)
+    got, cnt = s.encounter_list(cap=len(exp) + 64, standalone=True)
+    print(f"[list n={n}] {cnt} pairs, most of a body {np.bincount(exp[:, 0]).max()}", flush=True)
+    assert cnt == len(exp) and (cnt > 1024) == (n > 700)
+    if wide:
+        assert np.bincount(exp[:, 0]).max() > (256 if wide < n - 1 else 6144)
+    np.testing.assert_array_equal(got, exp)
+    s.close()

@@ -1801,8 +1801,11 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
     HIP_TRY(hipEventCreate(&e1));
     float best = 1e30f;
     int best_w = ctx->waves[fp32], best_s = 0;
-    for (int w : {4, 8, 16}) {
-        for (int sp = 0; sp <= KICK_MAX_SPLIT && !rc; ++sp) { // 0: the layout's own plan
+    // The layout's own plan (sp 0) last: an idle card takes some 30 ms of launches to reach its clock,
+    // and the first candidates are timed on the way (kick of 40000 bodies 654 us then, 560 after).
+    // Timed first, the plan lost that size to 8 waves in 4 shares, 582 us at the same clock.
+    for (int sp = KICK_MAX_SPLIT; sp >= 0 && !rc; --sp) {
+        for (int w : {16, 8, 4}) {
             ctx->waves[fp32] = w;
             ctx->split[fp32] = sp > 0 ? sp : default_split(ctx);
             ctx->own_plan[fp32] = sp == 0;

@@ -166,11 +166,12 @@ __global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t
 // Canonical (lexicographic) order of the encounter list, in one launch.  Up to SORT_SMALL pairs (a
 // list of a disc whose r_crit is a few Hill radii) the first workgroup sorts them in LDS, the others
 // return.  Above, each workgroup takes a run of bodies i, reads the whole list, and needs nothing
-// from the others: it counts the pairs below its run (where its output starts) and per body, keeps its
-// own in LDS (or reads the list again), places them by body and ranks each among its body's by counting.  The more bodies the more
-// workgroups, and each reads the list twice whatever its length.  Lists of dense annuli of 2049, 6600
-// and 12000 bodies (5700, 59000 and 197000 pairs) took 0.28, 3.7 and 15 ms, nearly all of it a
-// bitonic sort of one workgroup (in global memory above 8192 pairs), now 0.034, 0.12 and 0.32.
+// from the others: it counts the pairs below its run (where its output starts) and per body, keeps
+// its own in LDS (or reads the list again), places them by body and ranks each among its body's by
+// counting.  The more bodies the more workgroups, and each reads the list twice whatever its
+// length.  Lists of dense annuli of 2049, 6600 and 12000 bodies (5700, 59000 and 197000 pairs) took 0.28, 3.7
+// and 15 ms, nearly all of it a bitonic sort of one workgroup (in global memory above 8192 pairs),
+// now 0.034, 0.12 and 0.32.
 // ------------------------------------------------------------------------------------------
 constexpr int SORT_THREADS = 1024;
 constexpr int SORT_SMALL = 1024;  // pairs: 1659 take 41 us (with the listing) in one workgroup, 27 in all

@@ -1018,7 +1018,7 @@ int upload_plan(genga_ctx *ctx)
     first[n_sys] = (int32_t)it.size();
     if (it.size() > ctx->max_items) return fail(GENGA_ERR_STATE, "work plan larger than its allocation");
     for (const WorkItem &w : it) visits += w.nsrc;
-    const int len = kick_run_len(visits, ctx->n_cu);
+    const int len = kick_run_len(visits, (int64_t)it.size(), ctx->n_cu);
     std::vector<KickTask> tasks;
     std::vector<int32_t> cfst(n_sys + 1, 0); // chunks of each system, as genga_set_systems lays them out
     for (int s = 0; s < n_sys; ++s)
@@ -1073,7 +1073,7 @@ int upload_plan(genga_ctx *ctx)
     const auto energy_end = [&](const WorkItem &w) { return std::max(ctx->sys_off_h[w.sys] + w.nsrc, w.i0); };
     visits = 0;
     for (const WorkItem &w : it) visits += energy_end(w) - w.i0;
-    const int elen = kick_run_len(visits, ctx->n_cu);
+    const int elen = run_len(visits, ctx->n_cu);
     for (int s = 0; s < n_sys; ++s) {
         for (const bool head : {true, false}) { // the items' first tasks, then the others
             efirst[2 * s + !head] = (int32_t)et.size();

@@ -151,12 +151,26 @@ inline int default_kick_split(int n_items, int n_cu)
 // 19.4 against 15.1 us, one of 128 gives 40 massive among 20000 test bodies 52 against 35 us.
 constexpr int KICK_RUN_MIN = 256;
 constexpr int KICK_TASKS_PER_CU = 64;
-inline int kick_run_len(int64_t source_visits, int n_cu)
+inline int run_len(int64_t source_visits, int n_cu, int len = KICK_RUN_MIN)
 {
-    int len = KICK_RUN_MIN;
     n_cu = n_cu < 256 ? n_cu : 256;
     while (len < (1 << 20) && source_visits / len > (int64_t)KICK_TASKS_PER_CU * n_cu) len *= 2;
     return len;
+}
+// The kick's: runs of KICK_RUN_MIN only up to KICK_SHORT_PER_CU tasks per CU, where they fill it.
+// Above, their prologues cost more than the even shares bring (FP32 / FP64 kick of 8000 bodies
+// 42.5 / 56.4 us with 256, 38.2 / 53.5 with 512, of 16000 127 / 175 and 119 / 169, of 10 discs of
+// 2000-8000 109 / 149 and 99 / 141; of 6600, 10 tasks per CU, 34.2 / 45.3 and 34.0 / 46.8).  Not
+// where the items have few such runs each, whose lengths then differ too much (64 discs of
+// 500-1500 bodies 46.7 / 63.1 and 49.2 / 66.5 us).  The energy's pairs (half of the kick's) keep 256:
+// 8000 bodies 27 and 30 us, 64 discs of 1000 38 and 42.
+constexpr int KICK_SHORT_PER_CU = 14;
+inline int kick_run_len(int64_t source_visits, int64_t n_items, int n_cu)
+{
+    const int64_t cus = n_cu < 256 ? n_cu : 256;
+    const bool many = source_visits / KICK_RUN_MIN > KICK_SHORT_PER_CU * cus &&
+                      source_visits >= 6 * KICK_RUN_MIN * n_items;
+    return run_len(source_visits, n_cu, many ? 2 * KICK_RUN_MIN : KICK_RUN_MIN);
 }
 // Tasks of an item of nsrc sources at that run length, and the length of each task's run when
 // nsrc sources are cut into `parts` (a multiple of four, so that whole quads stay whole).

@@ -154,7 +154,7 @@ extern "C" int genga_accel_noalloc(const genga_bodies *b, int32_t n, double *ax,
     a.pair_cap = pair_cap;
     a.flags = d_status;
     // a context's own plan: every item has the same sources, so the same number of runs
-    a.split = kick_runs(n, kick_run_len((int64_t)a.n_items * n, n_cu));
+    a.split = kick_runs(n, kick_run_len((int64_t)a.n_items * n, a.n_items, n_cu));
     a.direct = a.split == 1;
     if ((int64_t)a.n_items * a.split > NA_MAX_TASKS)
         return fail(GENGA_ERR_STATE, "kick plan of %d bodies larger than the scratch", n);

@@ -61,3 +61,22 @@ def test_long_lists_in_order(n, wide):
         assert np.bincount(exp[:, 0]).max() > (256 if wide < n - 1 else 6144)
     np.testing.assert_array_equal(got, exp)
     s.close()
+
+
+@pytest.mark.parametrize("sizes", [[7647], [7648], [1535] * 40, [1537] * 40, [600, 7700, 1, 130]])
+def test_accel_on_both_sides_of_the_longer_runs(sizes):
+    """The first size of one disc whose runs are of 512 sources and the one before it; discs just
+    too small for them although there are tasks enough, and just large enough; uneven ones."""
+    ds = [discs.make_disc(n, 2.5, seed=900 + k, a_in=0.7, a_out=1.0) for k, n in enumerate(sizes)]
+    s = System(ds)
+    ref = oracle_accel_systems(s)
+    for prec, bar in ((FP64, 1e-12), (FP32, 1e-5)):
+        ax, ay, az = s.zeros(), s.zeros(), s.zeros()
+        genga.genga_accel(s.ctx.handle, s.b, ax, ay, az, prec, genga.GENGA_ACC_FP64)
+        s.torch.cuda.synchronize()
+        a = np.stack([v.cpu().numpy() for v in (ax, ay, az)], axis=1)
+        rms, mx = force_errors(a, ref)
+        print(f"[runs] sizes={sizes[:4]} prec={prec} rms={rms:.2e} max={mx:.2e}", flush=True)
+        assert rms <= bar
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK
+    s.close()

@@ -62,8 +62,9 @@ struct genga_ctx {
     Layout L;
     std::vector<int32_t> sys_off_h;
     std::vector<int32_t> n_massive_h; // per system; bodies beyond are TP2 test bodies
-    size_t max_items = 0;
-    // launch plan
+    // launch plan: one allocation, `plan`, that the pointers below (with L.n_massive, sort_seg and
+    // pm's) point into
+    char *plan = nullptr;
     WorkItem *items = nullptr;  // kick items, in system order
     int32_t n_items = 0;
     EnergyTask *etasks = nullptr; // energy tasks, in system order
@@ -76,8 +77,6 @@ struct genga_ctx {
     int split[2] = {1, 1};      // [prec] workgroups sharing an item's sources
     bool own_plan[2] = {true, true}; // [prec] the layout's own plan instead of `split`
     StepMomentum pm;            // momentum sums between the launches of a step (blocks: device)
-    CloseBlock *close_blocks = nullptr;
-    int32_t *close_first = nullptr;
     double *kpart = nullptr;    // [tasks][3][64], at least KICK_MAX_SPLIT tasks per item
     // scratch
     float *m32 = nullptr;       // [n_total] masses in FP32
@@ -232,18 +231,7 @@ struct genga_ctx {
         dfree(L.sys_off);
         dfree(L.sys_of);
         dfree(L.mstar);
-        dfree(items);
-        dfree(etasks);
-        dfree(etask_first);
-        dfree(tasks);
-        dfree(task_first);
-        dfree(close_blocks);
-        dfree(close_first);
-        dfree(pm.kick);
-        dfree(pm.kepler);
-        dfree(pm.group);
-        dfree(pm.group_sys);
-        dfree(pm.group_n);
+        dfree(plan);
         pm = StepMomentum{};
         dfree(m32);
         dfree(chunk_mass);
@@ -251,7 +239,6 @@ struct genga_ctx {
         dfree(mom_part);
         dfree(L.chunks);
         dfree(L.chunk_first);
-        dfree(L.n_massive);
         dfree(acc);
         dfree(pairs);
         dfree(pair_count);
@@ -264,11 +251,8 @@ struct genga_ctx {
         dfree(n_groups);
         dfree(member_slot);
         dfree(wg_list);
-        dfree(epartial);
-        dfree(kpart);
         dfree(import_bad);
         order_work_free(sw);
-        dfree(sort_seg);
         dfree(sort_perm);
         list_valid = false;
         dfree(col.list);
@@ -1016,7 +1000,6 @@ int upload_plan(genga_ctx *ctx)
         for (int i0 = b + nm; i0 < e; i0 += 64) it.push_back(WorkItem{s, i0, std::min(64, e - i0), nm});
     }
     first[n_sys] = (int32_t)it.size();
-    if (it.size() > ctx->max_items) return fail(GENGA_ERR_STATE, "work plan larger than its allocation");
     for (const WorkItem &w : it) visits += w.nsrc;
     const int len = kick_run_len(visits, (int64_t)it.size(), ctx->n_cu);
     std::vector<KickTask> tasks;
@@ -1032,40 +1015,16 @@ int upload_plan(genga_ctx *ctx)
                                      cfst[sy], cfst[sy + 1], b});
         tfirst[k + 1] = (int32_t)tasks.size();
     }
-    ctx->n_items = (int32_t)it.size();
-    ctx->n_tasks = (int32_t)tasks.size();
-    HIP_TRY(dalloc(ctx->tasks, tasks.size()));
-    HIP_TRY(dalloc(ctx->task_first, tfirst.size()));
-    HIP_TRY(dalloc(ctx->kpart, 192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size())));
-    if (!it.empty()) {
-        HIP_TRY(hipMemcpy(ctx->items, it.data(), it.size() * sizeof(WorkItem), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(ctx->tasks, tasks.data(), tasks.size() * sizeof(KickTask), hipMemcpyHostToDevice));
-    }
-    HIP_TRY(hipMemcpy(ctx->task_first, tfirst.data(), tfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     // blocks of items of one system, for the end of a step's kick
     std::vector<CloseBlock> cb;
     std::vector<int32_t> cfirst(n_sys + 1, 0);
-    ctx->pm.parts = close_parts(ctx->n_items, ctx->n_cu);
-    const int citems = CLOSE_WAVES / ctx->pm.parts;
+    const int cparts = close_parts((int)it.size(), ctx->n_cu), citems = CLOSE_WAVES / cparts;
     for (int s = 0; s < n_sys; ++s) {
         cfirst[s] = (int32_t)cb.size();
         for (int k = first[s]; k < first[s + 1]; k += citems)
             cb.push_back(CloseBlock{s, k, std::min(citems, first[s + 1] - k), first[s], first[s + 1], ctx->mstar_h[s]});
     }
     cfirst[n_sys] = (int32_t)cb.size();
-    HIP_TRY(dalloc(ctx->close_blocks, cb.size()));
-    HIP_TRY(dalloc(ctx->close_first, cfirst.size()));
-    HIP_TRY(dalloc(ctx->pm.kick, 3 * cb.size()));
-    HIP_TRY(dalloc(ctx->pm.kepler, 3 * it.size()));
-    HIP_TRY(dalloc(ctx->pm.group, 3 * (size_t)CE_MAX_MEMBERS / 2));
-    HIP_TRY(dalloc(ctx->pm.group_sys, (size_t)CE_MAX_MEMBERS / 2));
-    HIP_TRY(dalloc(ctx->pm.group_n, 1));
-    if (!cb.empty())
-        HIP_TRY(hipMemcpy(ctx->close_blocks, cb.data(), cb.size() * sizeof(CloseBlock), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(ctx->close_first, cfirst.data(), cfirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    ctx->pm.blocks = ctx->close_blocks;
-    ctx->pm.block_first = ctx->close_first;
-    ctx->pm.n_blocks = (int32_t)cb.size();
     // energy tasks: the sources after an item's first body (a test item has none: test pairs have
     // no energy), in runs as the kick's
     std::vector<EnergyTask> et;
@@ -1086,20 +1045,64 @@ int upload_plan(genga_ctx *ctx)
         }
     }
     efirst[2 * n_sys] = (int32_t)et.size();
-    ctx->n_etasks = (int32_t)et.size();
-    HIP_TRY(dalloc(ctx->etasks, et.size()));
-    HIP_TRY(dalloc(ctx->etask_first, efirst.size()));
-    HIP_TRY(dalloc(ctx->epartial, 9 * et.size()));
-    if (!et.empty()) HIP_TRY(hipMemcpy(ctx->etasks, et.data(), et.size() * sizeof(EnergyTask), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(ctx->etask_first, efirst.data(), efirst.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    HIP_TRY(hipMemcpy(ctx->L.n_massive, ctx->n_massive_h.data(), n_sys * sizeof(int32_t), hipMemcpyHostToDevice));
     std::vector<int32_t> seg(2 * (size_t)n_sys + 1);
     for (int s = 0; s < n_sys; ++s) {
         seg[2 * s] = ctx->sys_off_h[s];
         seg[2 * s + 1] = ctx->sys_off_h[s] + ctx->n_massive_h[s];
     }
     seg[2 * n_sys] = ctx->sys_off_h[n_sys];
-    HIP_TRY(hipMemcpy(ctx->sort_seg, seg.data(), seg.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    // One allocation and one copy: as 13 allocations and 8 copies a context of 257 / 20040 bodies took
+    // 318 / 465 us to make, so 183 / 320.  The plan that was there stays until the new one is complete.
+    size_t size = 0;
+    std::vector<char> host;
+    const auto place = [&](size_t bytes) { // 256-byte aligned sections
+        const size_t at = size;
+        size += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    const auto put = [&](const auto &v) {
+        const size_t bytes = v.size() * sizeof(v[0]), at = place(bytes);
+        host.resize(size);
+        if (bytes) std::copy_n(reinterpret_cast<const char *>(v.data()), bytes, host.data() + at);
+        return at;
+    };
+    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_cb = put(cb), o_cfirst = put(cfirst);
+    const size_t o_et = put(et), o_efirst = put(efirst), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
+    const size_t o_kick = place(3 * cb.size() * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
+    const size_t o_group = place(3 * (size_t)CE_MAX_MEMBERS / 2 * sizeof(double));
+    const size_t o_gsys = place((size_t)CE_MAX_MEMBERS / 2 * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
+    const size_t o_epart = place(9 * et.size() * sizeof(double));
+    const size_t o_kpart = place(192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size()) * sizeof(double));
+    char *plan = nullptr;
+    HIP_TRY(dalloc(plan, size));
+    const hipError_t copied = hipMemcpy(plan, host.data(), host.size(), hipMemcpyHostToDevice);
+    if (copied != hipSuccess) {
+        dfree(plan);
+        return fail(GENGA_ERR_HIP, "copy of the launch plan failed: %s", hipGetErrorString(copied));
+    }
+    dfree(ctx->plan);
+    ctx->plan = plan;
+    ctx->n_items = (int32_t)it.size();
+    ctx->n_tasks = (int32_t)tasks.size();
+    ctx->n_etasks = (int32_t)et.size();
+    ctx->items = reinterpret_cast<WorkItem *>(plan + o_items);
+    ctx->tasks = reinterpret_cast<KickTask *>(plan + o_tasks);
+    ctx->task_first = reinterpret_cast<int32_t *>(plan + o_tfirst);
+    ctx->etasks = reinterpret_cast<EnergyTask *>(plan + o_et);
+    ctx->etask_first = reinterpret_cast<int32_t *>(plan + o_efirst);
+    ctx->L.n_massive = reinterpret_cast<int32_t *>(plan + o_nm);
+    ctx->sort_seg = reinterpret_cast<int32_t *>(plan + o_seg);
+    ctx->pm.blocks = reinterpret_cast<CloseBlock *>(plan + o_cb);
+    ctx->pm.block_first = reinterpret_cast<int32_t *>(plan + o_cfirst);
+    ctx->pm.n_blocks = (int32_t)cb.size();
+    ctx->pm.parts = cparts;
+    ctx->pm.kick = reinterpret_cast<double *>(plan + o_kick);
+    ctx->pm.kepler = reinterpret_cast<double *>(plan + o_kepler);
+    ctx->pm.group = reinterpret_cast<double *>(plan + o_group);
+    ctx->pm.group_sys = reinterpret_cast<int32_t *>(plan + o_gsys);
+    ctx->pm.group_n = reinterpret_cast<int32_t *>(plan + o_gn);
+    ctx->epartial = reinterpret_cast<double *>(plan + o_epart);
+    ctx->kpart = reinterpret_cast<double *>(plan + o_kpart);
     HIP_TRY(hipDeviceSynchronize());
     return GENGA_OK;
 }
@@ -1195,12 +1198,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     HIP_TRY(dalloc(ctx->L.sys_off, n_sys + 1));
     HIP_TRY(dalloc(ctx->L.sys_of, nt));
     HIP_TRY(dalloc(ctx->L.mstar, n_sys));
-    // at most one more item per system when the massive / test boundary splits a block
-    size_t max_items = 0;
-    for (int s = 0; s < n_sys; ++s) max_items += (size_t)(sys_off_host[s + 1] - sys_off_host[s] + 63) / 64 + 1;
-    ctx->max_items = max_items;
-    HIP_TRY(dalloc(ctx->items, max_items));
-    HIP_TRY(dalloc(ctx->L.n_massive, n_sys));
     HIP_TRY(dalloc(ctx->m32, nt));
     HIP_TRY(dalloc(ctx->chunk_mass, chunks.size()));
     HIP_TRY(dalloc(ctx->L.chunks, chunks.size()));
@@ -1223,7 +1220,6 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     HIP_TRY(dalloc(ctx->import_bad, 1));
     HIP_TRY(hipMemset(ctx->import_bad, 0, sizeof(int32_t)));
     HIP_TRY(order_work_alloc(ctx->sw, std::max(n_total, 2 * n_sys)));
-    HIP_TRY(dalloc(ctx->sort_seg, 2 * (size_t)n_sys + 1));
     HIP_TRY(dalloc(ctx->sort_perm, std::max<size_t>(nt, 1)));
 
     HIP_TRY(hipMemcpy(ctx->L.sys_off, sys_off_host, (n_sys + 1) * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -1247,7 +1243,10 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
     ctx->n_massive_h.assign(sys_off_host, sys_off_host + n_sys);
     for (int s = 0; s < n_sys; ++s) ctx->n_massive_h[s] = sys_off_host[s + 1] - sys_off_host[s];
     rc = upload_plan(ctx);
-    if (rc) return rc;
+    if (rc) {
+        ctx->release();
+        return rc;
+    }
     ctx->split[0] = ctx->split[1] = default_split(ctx);
     if (keep_large) {
         if ((rc = alloc_big(ctx))) return rc;
@@ -1557,13 +1556,16 @@ int genga_set_test_bodies(genga_ctx *ctx, const int32_t *n_massive_host)
         if (nm < 0 || nm > ns) return fail(GENGA_ERR_ARG, "n_massive[%d] = %d outside [0, %d]", s, nm, ns);
     }
     HIP_TRY(hipDeviceSynchronize());
+    const std::vector<int32_t> before = ctx->n_massive_h;
     for (int s = 0; s < n_sys; ++s)
         ctx->n_massive_h[s] = n_massive_host ? n_massive_host[s] : ctx->sys_off_h[s + 1] - ctx->sys_off_h[s];
     if (ctx->graph_exec) (void)hipGraphExecDestroy(ctx->graph_exec);
     if (ctx->graph) (void)hipGraphDestroy(ctx->graph);
     ctx->graph_exec = nullptr;
     ctx->graph = nullptr;
-    return upload_plan(ctx);
+    rc = upload_plan(ctx);
+    if (rc) ctx->n_massive_h = before; // and the plan that goes with it
+    return rc;
 }
 
 int genga_rcrit(genga_ctx *ctx, const genga_bodies *b, double n1, double n2, double dt, double *rc_out,

@@ -174,7 +174,8 @@ __global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t
 // now 0.034, 0.12 and 0.32.
 // ------------------------------------------------------------------------------------------
 constexpr int SORT_THREADS = 1024;
-constexpr int SORT_SMALL = 1024;  // pairs: 1659 take 41 us (with the listing) in one workgroup, 27 in all
+constexpr int SORT_SMALL = 512;   // pairs: 592, 714, 1659 take 21.7, 23.2, 41 us (with the listing) in one
+                                  // workgroup, 19.7, 20.9, 27 in all; 439 and 489 the same, 142 18.6 and 20.6
 constexpr int SORT_LDS = 8192;    // keys
 constexpr int SORT_BLOCKS = 64;   // (6600 bodies with 32, 64, 128: 118, 122, 137 us; 12000: 352, 317, 325)
 constexpr int SORT_BODIES = 4096; // bodies at a time (counts in a quarter of the keys' space)

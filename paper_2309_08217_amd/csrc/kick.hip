@@ -100,12 +100,27 @@ __device__ __forceinline__ void emit_pair(const KickArgs &a, PairBuf pb, bool em
     wave_lds_sync();
 }
 
-// Empty the buffer (every lane of the wave calls this).
-__device__ __forceinline__ void flush_pairs(const KickArgs &a, PairBuf pb)
+// Empty the buffers of a workgroup's W waves (every lane of it calls this).  One counter update for
+// all of them: the updates of one address follow each other at about 10 ns, and on dense annuli each
+// wave has some pairs.  With one per wave the list of 6600 bodies in random order (59066 pairs, 10800
+// waves) took 118 us and their FP32 kick 84, so 73 and 44; sparse and sorted bodies the same.
+template <int W>
+__device__ __forceinline__ void flush_pairs(const KickArgs &a, const int2 (*slots)[PAIR_BUF], const int *fill, int wave,
+                                            int lane)
 {
-    wave_lds_sync();
-    const int n = *pb.n;
-    if (n > 0) spill_pairs(a, pb, n, 0ull, false, 0, 0);
+    __shared__ int base;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int n = fill[w];
+        if (w < wave) before += n;
+        all += n;
+    }
+    if (all == 0) return; // all of the workgroup
+    if (threadIdx.x == 0) base = atomicAdd(a.pair_count, all);
+    __syncthreads();
+    for (int k = lane; k < fill[wave]; k += 64) store_pair(a, base + before + k, slots[wave][k]);
 }
 
 // A marked pair (within the candidate radius of the system): exact FP64 decision; the term is
@@ -178,6 +193,13 @@ __device__ __forceinline__ double system_rc2max(const KickArgs &a, const KickTas
     for (int k = t.c0 + (int)(threadIdx.x & 63); k < t.c1; k += 64)
         mx = fmax(mx, a.rc2_part[k]);
     return wave_maxv(mx);
+}
+
+// The FP64 candidate threshold, with a relative margin: q is formed with fused multiply-adds, the
+// exact decision without them.
+__device__ __forceinline__ double candidate_rc2(const KickArgs &a, const KickTask &t)
+{
+    return system_rc2max(a, t) * (1.0 + 1e-12) + 1e-300;
 }
 
 // The mass that all sources [j0, j1) of the task share, or NaN: from the chunks' common masses.
@@ -447,12 +469,11 @@ __global__ __launch_bounds__(64 * W) void kick32_kernel(KickArgs a)
         run32<KAHAN, true>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     else
         run32<KAHAN, false>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
-    flush_pairs(a, pb);
+    flush_pairs<W>(a, pair_slots, pair_fill, wave, lane);
     finish<W>(a, red, wave, lane, valid, i, blockIdx.x, sx, sy, sz);
 }
 
-// LIST: the encounter pairs only (no far terms, nothing written but the list)
-template <int W, bool LIST>
+template <int W>
 __global__ __launch_bounds__(64 * W) void kick64_kernel(KickArgs a)
 {
     __shared__ double red[3][W][64];
@@ -467,19 +488,46 @@ __global__ __launch_bounds__(64 * W) void kick64_kernel(KickArgs a)
     const bool valid = lane < t.ni;
     const int i = t.i0 + (valid ? lane : 0);
     const double xi = a.x[i], yi = a.y[i], zi = a.z[i], rci = a.rc[i];
-    // candidate threshold with a relative margin: q is formed with fused multiply-adds, the
-    // exact decision without them
-    const double T = system_rc2max(a, t) * (1.0 + 1e-12) + 1e-300;
+    const double T = candidate_rc2(a, t);
     int jb, je;
     wave_run<W>(t, wave, jb, je);
     double sx = 0.0, sy = 0.0, sz = 0.0;
-    const double mass = LIST ? 0.0 : common_mass(a, t, jb, je);
+    const double mass = common_mass(a, t, jb, je);
     if (mass == mass)
-        run64<true, LIST>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
+        run64<true, false>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     else
-        run64<false, LIST>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
-    flush_pairs(a, pb);
-    if (!LIST) finish<W>(a, red, wave, lane, valid, i, blockIdx.x, sx, sy, sz);
+        run64<false, false>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
+    flush_pairs<W>(a, pair_slots, pair_fill, wave, lane);
+    finish<W>(a, red, wave, lane, valid, i, blockIdx.x, sx, sy, sz);
+}
+
+// The encounter pairs alone, in the layout's own tasks.  A pair is found from its lower body, so of
+// its sources an item looks at those from its first body on (all of them: list of 40000 bodies 343
+// us, so 216; of 64 discs of 2000-8000 391 and 270); bound by the FP64 issue of three differences and
+// r^2 per pair.  In the energy's tasks, which have just these sources, 200 and 269, but 700 bodies 24
+// against 21 and dense lists of 12000 181 against 160.
+constexpr int LIST_WAVES = 4;
+__global__ __launch_bounds__(64 * LIST_WAVES) void pair_list_kernel(KickArgs a)
+{
+    __shared__ int2 pair_slots[LIST_WAVES][PAIR_BUF];
+    __shared__ int pair_fill[LIST_WAVES];
+    KickTask t = a.tasks[blockIdx.x];
+    t.j0 = max(t.j0, t.i0);
+    if (t.j0 >= t.j1) return;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const PairBuf pb{pair_slots[wave], &pair_fill[wave]};
+    pair_fill[wave] = 0;
+    wave_lds_sync();
+    const bool valid = lane < t.ni;
+    const int i = t.i0 + (valid ? lane : 0);
+    const double xi = a.x[i], yi = a.y[i], zi = a.z[i], rci = a.rc[i];
+    const double T = candidate_rc2(a, t);
+    int jb, je;
+    wave_run<LIST_WAVES>(t, wave, jb, je);
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+    run64<true, true>(a, jb, je, i, valid, xi, yi, zi, rci, T, 0.0, sx, sy, sz, pb);
+    flush_pairs<LIST_WAVES>(a, pair_slots, pair_fill, wave, lane);
 }
 
 // Per chunk the largest r_crit^2 and the mass its bodies share (NaN: they differ), the masses in
@@ -556,7 +604,7 @@ hipError_t launch_kick_shares(const KickArgs &a, int fp32, int kahan, int waves,
         else if (fp32)                                                                        \
             kick32_kernel<Wv, false><<<grid, 64 * Wv, 0, stream>>>(a);                       \
         else                                                                                  \
-            kick64_kernel<Wv, false><<<grid, 64 * Wv, 0, stream>>>(a);                       \
+            kick64_kernel<Wv><<<grid, 64 * Wv, 0, stream>>>(a);                       \
         break;
     switch (waves) {
         GENGA_KICK_CASE(4)
@@ -579,9 +627,8 @@ hipError_t launch_kick(const KickArgs &a, int fp32, int kahan, int waves, hipStr
 
 hipError_t launch_pair_list(const KickArgs &a, hipStream_t stream)
 {
-    if (a.n_items == 0) return hipSuccess;
-    const int grid = a.tasks ? a.n_tasks : a.n_items * a.split;
-    kick64_kernel<4, true><<<grid, 64 * 4, 0, stream>>>(a);
+    if (a.n_tasks == 0) return hipSuccess;
+    pair_list_kernel<<<a.n_tasks, 64 * LIST_WAVES, 0, stream>>>(a);
     return hipGetLastError();
 }
 

@@ -169,15 +169,15 @@ __global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t
 // from the others: it counts the pairs below its run (where its output starts) and per body, keeps
 // its own in LDS (or reads the list again), places them by body and ranks each among its body's by
 // counting.  The more bodies the more workgroups, and each reads the list twice whatever its
-// length.  Lists of dense annuli of 2049, 6600 and 12000 bodies (5700, 59000 and 197000 pairs) took 0.28, 3.7
-// and 15 ms, nearly all of it a bitonic sort of one workgroup (in global memory above 8192 pairs),
-// now 0.034, 0.12 and 0.32.
+// length.  Lists (with the listing) of dense annuli of 2049, 6600 and 12000 bodies (5700, 59000 and
+// 197000 pairs) took 0.28, 3.7 and 15 ms, nearly all of it a bitonic sort of one workgroup (in global
+// memory above 8192 pairs), now 0.027, 0.072 and 0.145.
 // ------------------------------------------------------------------------------------------
 constexpr int SORT_THREADS = 1024;
 constexpr int SORT_SMALL = 512;   // pairs: 592, 714, 1659 take 21.7, 23.2, 41 us (with the listing) in one
                                   // workgroup, 19.7, 20.9, 27 in all; 439 and 489 the same, 142 18.6 and 20.6
 constexpr int SORT_LDS = 8192;    // keys
-constexpr int SORT_BLOCKS = 64;   // (6600 bodies with 32, 64, 128: 118, 122, 137 us; 12000: 352, 317, 325)
+constexpr int SORT_BLOCKS = 256;  // at most (40322 bodies with 64, 128, 256: 2055, 1382, 1101 us)
 constexpr int SORT_BODIES = 4096; // bodies at a time (counts in a quarter of the keys' space)
 constexpr int SORT_COUNT = 256;   // a body's pairs ranked by counting; more are sorted by the workgroup
 constexpr int SORT_AHEAD = 8;     // pairs in flight per thread
@@ -357,8 +357,11 @@ hipError_t launch_sort_pairs(const int32_t *src, const int32_t *src_count, int32
                              int32_t *dst, int32_t dst_cap, int32_t *dst_count, uint64_t *keys,
                              int32_t *flags, hipStream_t stream)
 {
-    // a workgroup per 64 bodies at most, and none but the first where the list cannot be long
-    const int blocks = src_cap > SORT_SMALL ? std::max(1, std::min(SORT_BLOCKS, n_total / 64)) : 1;
+    // a workgroup per 64 bodies up to 32, then one per 128 (4000 bodies, 22185 pairs, with 32 and 62
+    // workgroups 41 and 47 us, 12000, 197189 pairs, with 62, 64 and 93 160, 160 and 145); none but the
+    // first where the list cannot be long
+    const int most = std::max(std::min(n_total / 64, 32), std::min(n_total / 128, SORT_BLOCKS));
+    const int blocks = src_cap > SORT_SMALL ? std::max(1, most) : 1;
     sort_pairs_kernel<<<blocks, SORT_THREADS, 0, stream>>>(src, src_count, src_cap, n_total, dst, dst_cap, dst_count,
                                                            keys, flags);
     return hipGetLastError();

@@ -88,6 +88,16 @@ __device__ __forceinline__ void lv_wave_sync()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+__device__ __forceinline__ void lv_store(const LevelKickArgs &a, int idx, int2 p)
+{
+    if (idx < a.pair_cap) {
+        a.pairs[2 * idx] = p.x;
+        a.pairs[2 * idx + 1] = p.y;
+    } else {
+        atomicOr(a.flags, FLAG_CAPACITY);
+    }
+}
+
 __device__ __forceinline__ void lv_flush(const LevelKickArgs &a, int2 *buf, int &fill)
 {
     if (fill == 0) return;
@@ -96,15 +106,7 @@ __device__ __forceinline__ void lv_flush(const LevelKickArgs &a, int2 *buf, int 
     int base = 0;
     if (lane == 0) base = atomicAdd(a.pair_count, fill);
     base = __shfl(base, 0, 64);
-    for (int k = lane; k < fill; k += 64) {
-        const int idx = base + k;
-        if (idx < a.pair_cap) {
-            a.pairs[2 * idx] = buf[k].x;
-            a.pairs[2 * idx + 1] = buf[k].y;
-        } else {
-            atomicOr(a.flags, FLAG_CAPACITY);
-        }
-    }
+    for (int k = lane; k < fill; k += 64) lv_store(a, base + k, buf[k]);
     lv_wave_sync();
     fill = 0;
 }
@@ -270,7 +272,8 @@ __device__ __forceinline__ void lv_sources(const LevelKickArgs &a, const LvTarge
 // about half of the sources of the tiles it touches, so they are sorted out first, a lane each, and
 // staged in LDS for the marks and the terms (lv_sources).  Kicks of 40322 bodies: 62 us with every
 // source of the tiles through scalar loads and the term behind the test; 55 with the sources sorted
-// out; 42 with marks.
+// out; 42 with marks; 33 with one update of the pair counter a workgroup in place of one a wave (they
+// follow each other at about 10 ns).
 constexpr int LV_CAND = 32; // source tiles at a time
 template <int W>
 __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles t, LevelKickArgs a)
@@ -281,7 +284,7 @@ __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles
         LvStage<W * LT_TILE> stage;
         double red[3][W][LT_TILE]; // once the sources are done
     } S;
-    __shared__ int wave_cnt[W];
+    __shared__ int wave_cnt[W], pair_base;
     __shared__ int2 pair_buf[W][LV_BUF];
     const int me = t.tl[blockIdx.x];
     const int4 tile = t.tiles[me]; // (group, first member, count, -)
@@ -360,21 +363,31 @@ __global__ __launch_bounds__(LT_TILE *W) void level_tiles_kick_kernel(LevelTiles
         }
         if (n_live == 0) __syncthreads(); // near_tile has been read by every wave
     }
-    lv_flush(a, buf, fill);
+    // the sums, and the waves' pairs with one counter update for all of them
+    if (lane == 0) wave_cnt[wave] = fill;
     S.red[0][wave][lane] = ax;
     S.red[1][wave][lane] = ay;
     S.red[2][wave][lane] = az;
     __syncthreads();
-    if (wave != 0 || !tg.valid) return;
-    double sx = 0.0, sy = 0.0, sz = 0.0;
+    int before = 0, all = 0;
     for (int w = 0; w < W; ++w) {
-        sx += S.red[0][w][lane];
-        sy += S.red[1][w][lane];
-        sz += S.red[2][w][lane];
+        if (w < wave) before += wave_cnt[w];
+        all += wave_cnt[w];
     }
-    a.vx[tg.body] += a.tau * sx;
-    a.vy[tg.body] += a.tau * sy;
-    a.vz[tg.body] += a.tau * sz;
+    if (threadIdx.x == 0 && all > 0) pair_base = atomicAdd(a.pair_count, all);
+    if (wave == 0 && tg.valid) {
+        double sx = 0.0, sy = 0.0, sz = 0.0;
+        for (int w = 0; w < W; ++w) {
+            sx += S.red[0][w][lane];
+            sy += S.red[1][w][lane];
+            sz += S.red[2][w][lane];
+        }
+        a.vx[tg.body] += a.tau * sx;
+        a.vy[tg.body] += a.tau * sy;
+        a.vz[tg.body] += a.tau * sz;
+    }
+    __syncthreads();
+    for (int k = lane; k < fill; k += 64) lv_store(a, pair_base + before + k, buf[k]);
 }
 
 // Groups of one tile (up to 64 members): one wave per group, its members the sources in order.

@@ -303,7 +303,7 @@ __device__ __forceinline__ void store_state(double *x, double *y, double *z, dou
 // Encounter groups: one workgroup.  lab[] (init -1) and mark[] (init 0) are global arrays
 // over all bodies that this kernel leaves clean again for the next step.
 // Output: members[] sorted by (group root, body), group_start[g] (g < n_groups, plus an end
-// sentinel), member_slot[body] = position in members[].
+// sentinel), member_slot[body] = position in members[] (-1: in no group that is integrated).
 // ------------------------------------------------------------------------------------------
 constexpr int CE_THREADS = 1024;
 constexpr int BS_LANES = 64;
@@ -567,14 +567,12 @@ __device__ void build_groups(const GroupBuild &g, GroupLds &S)
     }
     int nmem = 0;
     const uint64_t *keys = np <= GF_PAIRS ? group_keys_fast(g, S, np, nmem) : group_keys_global(g, S, np, nmem);
-    // write members and slots; number the groups with a chunked scan of the start flags
+    // write members; number the groups with a chunked scan of the start flags
     const int per = (nmem + CE_THREADS - 1) / CE_THREADS;
     const int kb = min(tid * per, nmem), ke = min(kb + per, nmem);
     int nstart = 0;
     for (int k = kb; k < ke; ++k) {
-        const int b = (int)(keys[k] & 0xffffffffu);
-        g.members[k] = b;
-        g.member_slot[b] = k;
+        g.members[k] = (int)(keys[k] & 0xffffffffu);
         if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) ++nstart;
     }
     // exclusive scan of the per-thread start counts: in-wave shuffles, then the wave totals
@@ -591,12 +589,18 @@ __device__ void build_groups(const GroupBuild &g, GroupLds &S)
         gi += w < wave ? S.cnt[w] : 0;
         ng += S.cnt[w];
     }
-    for (int k = kb; k < ke; ++k)
-        if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) g.group_start[gi++] = k;
-    if (tid == 0) {
-        g.group_start[ng] = nmem;
-        *g.n_groups = ng;
+    // Members beyond CE_MAX_MEMBERS (flagged) can leave groups of one, and so more groups than the
+    // drift has blocks and sums for: the members of those get no slot and are Kepler-drifted.
+    for (int k = kb; k < ke; ++k) {
+        if (k == 0 || (keys[k - 1] >> 32) != (keys[k] >> 32)) {
+            if (gi <= CE_MAX_GROUPS) g.group_start[gi] = k;
+            ++gi;
+        }
+        if (gi <= CE_MAX_GROUPS) g.member_slot[(int)(keys[k] & 0xffffffffu)] = k; // in group gi - 1
     }
+    if (ng <= CE_MAX_GROUPS && tid == 0) g.group_start[ng] = nmem;
+    ng = min(ng, CE_MAX_GROUPS);
+    if (tid == 0) *g.n_groups = ng;
     __threadfence_block();
     __syncthreads(); // group_start is read back by other threads
     list_wg_groups(g.group_start, ng, g.wg_list, S.cnt);
@@ -1700,10 +1704,9 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
 {
     if (L.n_total == 0) return hipSuccess;
     const StepMomentum pm = pm_in ? *pm_in : StepMomentum{};
-    // groups have at least 2 members, so the one-workgroup builder makes at most half its
-    // members; bs_blocks < 0: no group blocks (the groups are integrated elsewhere), only the
-    // Kepler drift of non-members.
-    if (bs_blocks == 0) bs_blocks = CE_MAX_MEMBERS / 2;
+    // bs_blocks 0: what the one-workgroup builder makes at most; < 0: no group blocks (the groups
+    // are integrated elsewhere), only the Kepler drift of non-members.
+    if (bs_blocks == 0) bs_blocks = CE_MAX_GROUPS;
     if (bs_blocks < 0) bs_blocks = 0;
     const int grid = bs_blocks + (kepler ? n_items : 0);
     if (grid == 0) return hipSuccess;

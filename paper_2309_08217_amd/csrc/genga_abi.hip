@@ -1069,8 +1069,8 @@ int upload_plan(genga_ctx *ctx)
     const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_cb = put(cb), o_cfirst = put(cfirst);
     const size_t o_et = put(et), o_efirst = put(efirst), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
     const size_t o_kick = place(3 * cb.size() * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
-    const size_t o_group = place(3 * (size_t)CE_MAX_MEMBERS / 2 * sizeof(double));
-    const size_t o_gsys = place((size_t)CE_MAX_MEMBERS / 2 * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
+    const size_t o_group = place(3 * (size_t)CE_MAX_GROUPS * sizeof(double));
+    const size_t o_gsys = place((size_t)CE_MAX_GROUPS * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
     const size_t o_epart = place(9 * et.size() * sizeof(double));
     const size_t o_kpart = place(192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size()) * sizeof(double));
     char *plan = nullptr;

@@ -28,6 +28,7 @@ enum DeviceFlag : int32_t {
 
 // Maximum sizes of the close-encounter step (one workgroup builds the groups in LDS).
 constexpr int CE_MAX_MEMBERS = 8192;
+constexpr int CE_MAX_GROUPS = CE_MAX_MEMBERS / 2; // groups of at least two
 constexpr int COLLIDE_CAP = 4096;          // colliding pairs per drift
 constexpr int CE_MAX_GROUP = 64;
 constexpr int BS_KMAX = 8;
@@ -113,7 +114,7 @@ struct StepMomentum {
     int32_t parts = 1;                   // waves per item
     double *kick = nullptr;    // [n_blocks][3] sum m v after the kick
     double *kepler = nullptr;  // [n_items][3] sum m v after the drift, bodies outside groups
-    double *group = nullptr;   // [CE_MAX_MEMBERS / 2][3] the same of the groups, which are in system order
+    double *group = nullptr;   // [CE_MAX_GROUPS][3] the same of the groups, which are in system order
     int32_t *group_sys = nullptr;
     int32_t *group_n = nullptr; // the groups the drift had (n_groups is the next kick's while it closes)
     double tau = 0.0;          // half a Sun drift: positions + tau P / Mstar

@@ -1,0 +1,52 @@
+"""What a context does at its limits and carries (or must not carry) from one call to the next."""
+import numpy as np
+import pytest
+
+import discs
+import oracle
+import paper_2309_08217_amd as genga
+from gpu_helpers import DT, System
+
+pytestmark = pytest.mark.gpu
+
+FP64, FP32 = genga.GENGA_KICK_FP64, genga.GENGA_KICK_FP32
+KEYS = ("x", "y", "z", "vx", "vy", "vz")
+
+
+def _clusters(sizes, r_crit):
+    """Clusters of the given numbers of bodies on circular orbits far from each other, members 0.8
+    r_crit apart along the orbit, masses too small to matter (a pull of 2e-11 at most)."""
+    c = np.arange(len(sizes))
+    a0 = np.sqrt(0.25 + (16.0 - 0.25) * (c + 0.5) / len(sizes))
+    ph0 = c * np.pi * (3.0 - np.sqrt(5.0))
+    a = np.repeat(a0, sizes)
+    ph = np.repeat(ph0, sizes) + 0.8 * r_crit / a * np.concatenate([np.arange(s) for s in sizes])
+    v, zero = 1.0 / np.sqrt(a), np.zeros(len(a))
+    return discs.Disc(x=a * np.cos(ph), y=a * np.sin(ph), z=zero, vx=-v * np.sin(ph), vy=v * np.cos(ph),
+                      vz=zero.copy(), m=np.full(len(a), 1e-19))
+
+
+# more than 8192 bodies in encounters, so that some groups lose members: as pairs alone (about 4900
+# groups are left), and with groups of 12 last in the order
+@pytest.mark.parametrize("sizes", [[2] * 5000, [2] * 4600 + [12] * 20])
+@pytest.mark.parametrize("call", ["step", "drift"])
+def test_more_bodies_in_encounters_than_the_builder_takes(sizes, call):
+    """GENGA_ERR_CAPACITY, and every body moves: in its group or, left out, on its Kepler orbit.
+    The masses do not matter, so both are the Kepler orbit, to the group step's 1e-12 of 4 au."""
+    d = _clusters(sizes, 1e-4)
+    s = System([d], rcrit=np.full(d.n, 1e-4))
+    st = d.state()
+    for _ in range(2):
+        if call == "step":
+            genga.genga_step(s.ctx.handle, s.b, DT, 1, FP64)
+        else:
+            _, c = s.encounter_list(standalone=True)
+            assert c == sum(k - 1 for k in sizes)
+            genga.genga_drift(s.ctx.handle, s.b, DT)
+        assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_ERR_CAPACITY
+        st = oracle.kepler_drift(st, 1.0, DT)
+        got = s.numpy_state()
+        err = max(np.max(np.abs(got[k] - st[k])) for k in KEYS)
+        print(f"[capacity {call}] {d.n} bodies, error {err:.1e}", flush=True)
+        assert err <= 1e-10
+    s.close()

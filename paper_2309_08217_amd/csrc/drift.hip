@@ -301,7 +301,8 @@ __device__ __forceinline__ void store_state(double *x, double *y, double *z, dou
 
 // ------------------------------------------------------------------------------------------
 // Encounter groups: one workgroup.  lab[] (init -1) and mark[] (init 0) are global arrays
-// over all bodies that this kernel leaves clean again for the next step.
+// over all bodies that this kernel leaves clean again for the next step, and for uf_union_kernel,
+// which takes every label that is not -1 as a link of its own.
 // Output: members[] sorted by (group root, body), group_start[g] (g < n_groups, plus an end
 // sentinel), member_slot[body] = position in members[] (-1: in no group that is integrated).
 // ------------------------------------------------------------------------------------------
@@ -515,11 +516,13 @@ __device__ const uint64_t *group_keys_global(const GroupBuild &g, GroupLds &S, i
         keys[k] = ((uint64_t)(uint32_t)r << 32) | (uint32_t)b;
     }
     sort_keys(keys, nmem);
-    // leave the marks clear for the next step (roots are re-initialised on marking)
-    for (int p = tid; p < np; p += CE_THREADS) {
-        mark[pairs[2 * p]] = 0;
-        mark[pairs[2 * p + 1]] = 0;
-    }
+    // every root has been read (sort_keys has barriers): labels and marks are left as they were found
+    for (int p = tid; p < np; p += CE_THREADS)
+        for (int e = 0; e < 2; ++e) {
+            const int b = pairs[2 * p + e];
+            mark[b] = 0;
+            __hip_atomic_store(&lab[b], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     return keys;
 }
 

@@ -50,3 +50,31 @@ def test_more_bodies_in_encounters_than_the_builder_takes(sizes, call):
         print(f"[capacity {call}] {d.n} bodies, error {err:.1e}", flush=True)
         assert err <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("levels", [1, 2])
+def test_large_groups_on_a_context_with_a_history(levels):
+    """A step without large groups whose list has more than 1024 pairs, other positions, large groups
+    on: the next steps are those of a fresh context, bit for bit."""
+    first, second = discs.disc_dense(3000, seed=5), discs.disc_dense(3000, seed=6)
+    rc = oracle.rcrit(second.state(), 1.0, discs.DENSE_N1, discs.DENSE_N2, discs.DT_5_DAYS)
+    assert len(oracle.encounters(first.state(), rc)) > 1024
+    states = []
+    for used in (True, False):
+        s = System([first if used else second], rcrit=rc, pair_capacity=200000)
+        h, torch = s.ctx.handle, s.torch
+        if used:
+            genga.genga_step(h, s.b, discs.DT_5_DAYS, 2, FP64)
+            assert genga.genga_poll_status(h) == genga.GENGA_ERR_CAPACITY   # groups above 64 bodies
+            for k, v in second.state().items():
+                getattr(s.b, k).copy_(torch.as_tensor(v))
+        genga.genga_set_large_groups(h, True)
+        if levels > 1:
+            rcl = torch.as_tensor(0.5 * rc, device="cuda")
+            genga.genga_set_levels(h, levels, 2, rcl)
+        genga.genga_step(h, s.b, discs.DT_5_DAYS, 1, FP64)
+        assert genga.genga_poll_status(h) == genga.GENGA_OK, genga.genga_last_error()
+        states.append(s.numpy_state())
+        s.close()
+    for k in KEYS:
+        np.testing.assert_array_equal(states[0][k], states[1][k])

@@ -183,7 +183,8 @@ __device__ __forceinline__ void lv_source(const LevelKickArgs &a, const LvTarget
             n *= k < lv ? c.u : c.y;
             d *= c.d;
         }
-        const double s = j.m * (n * n) * inv64(d) * ((rq * rq) * rq);
+        // (a weight of zero is no term, also at zero separation, where r^-3 is not finite)
+        const double s = n > 0.0 ? j.m * (n * n) * inv64(d) * ((rq * rq) * rq) : 0.0;
         ax = fma(s, dx, ax);
         ay = fma(s, dy, ay);
         az = fma(s, dz, az);

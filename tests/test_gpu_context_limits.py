@@ -78,3 +78,25 @@ def test_large_groups_on_a_context_with_a_history(levels):
         s.close()
     for k in KEYS:
         np.testing.assert_array_equal(states[0][k], states[1][k])
+
+
+# a cluster of one tile and one of two
+@pytest.mark.parametrize("size", [3, 100])
+def test_coincident_bodies_under_the_levels(size):
+    """Two bodies of a level's group at one place: their level kick's weight is zero, so it adds
+    nothing; the Bulirsch-Stoer step of the two does not converge, is flagged and leaves them, and
+    no other body sees anything of it."""
+    d = _clusters([size, 2, 2], 1e-4)
+    for k in KEYS:
+        getattr(d, k)[1] = getattr(d, k)[0]
+    s = System([d], rcrit=np.full(d.n, 1e-4))
+    genga.genga_set_large_groups(s.ctx.handle, True)
+    rcl = s.torch.full((d.n,), 0.5e-4, dtype=s.torch.float64, device="cuda")
+    genga.genga_set_levels(s.ctx.handle, 2, 2, rcl)
+    genga.genga_step(s.ctx.handle, s.b, DT, 1, FP64)
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_ERR_NOCONVERGE
+    ref, got = oracle.kepler_drift(d.state(), 1.0, DT), s.numpy_state()
+    for k in KEYS:
+        assert np.all(np.isfinite(got[k]))
+        assert np.max(np.abs(got[k][2:] - ref[k][2:])) <= 1e-10
+    s.close()

@@ -919,7 +919,9 @@ int enqueue_step_kick(genga_ctx *ctx, genga_bodies *b, double tau, int prec, int
 // Steps without collisions: four launches each (kick shares, their sum with the groups, drift, the
 // groups of 9..64).  The kick sees the positions without the second half of the Sun drift, which is
 // one vector for all bodies of a system and so drops out of every difference; the launch that sums
-// the shares adds it.  r_crit and the masses are the call's, so what the kick takes from them is
+// the shares adds it.  Not before the call's last kick, whose list the caller can ask for: a pair
+// within the sum's rounding of r_crit would not be as the positions in the caller's arrays have it
+// (one more launch a call).  r_crit and the masses are the call's, so what the kick takes from them is
 // formed once.  As launches of their own the momentum sums, shifts, groups and lists were seven
 // more of 4-6 us each.  With large groups on, a step whose list joins any bodies takes the drift
 // in its parts, with the host in between.
@@ -948,7 +950,8 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
                                  dt, ctx->members, ctx->group_start, large ? &ctx->gw.hdr->G : ctx->n_groups,
                                  ctx->member_slot, ctx->flags, 0, large ? -1 : 0, ctx->wg_list, s, nullptr, 1, true, nullptr, &pm, true));
         }
-        if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, 0.5 * dt, !last && !large, s)))
+        if (last) HIP_TRY(launch_drift_close(ctx->items, b->x, b->y, b->z, pm, s));
+        if ((rc = enqueue_step_kick(ctx, b, last ? 0.5 * dt : dt, prec, acc, last ? 0.0 : 0.5 * dt, !last && !large, s)))
             return rc;
         if (cadence > 0 && d_energy && k % cadence == 0) {
             rc = enqueue_energy(ctx, b, last ? 0.0 : 0.5 * dt, d_energy + (size_t)rec * 4 * L.n_sys, s);

@@ -100,3 +100,43 @@ def test_coincident_bodies_under_the_levels(size):
         assert np.all(np.isfinite(got[k]))
         assert np.max(np.abs(got[k][2:] - ref[k][2:])) <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("large", [False, True])
+@pytest.mark.parametrize("steps", [1, 3])
+def test_list_after_steps_is_that_of_the_positions(steps, large):
+    """The list of a call's last kick is decided on the positions that the call returns: pairs whose
+    r_crit is their final separation are outside, with the next number above it inside."""
+    n = 800
+    d = _clusters([2] * n, 1e-3)
+    rng = np.random.default_rng(3)
+    # approaching pairs, outside r_crit at every earlier kick and without mass, so that r_crit does not
+    # change a bit of their motion; the last body's momentum gives the Sun shift
+    i, j = np.arange(0, 2 * n, 2), np.arange(1, 2 * n, 2)
+    for k in ("x", "y", "z"):
+        u = 1e-3 * rng.normal(size=n)
+        getattr(d, k)[j] = getattr(d, k)[i] + u
+        getattr(d, "v" + k)[j] = getattr(d, "v" + k)[i] - 0.8 * u / (steps * DT)
+    d.m[:] = 0.0
+    d.m[-1] = 1e-6
+    far = (np.hypot(d.x[i], d.y[i]) > 2.5) & (j < 2 * n - 1)   # little shear over the steps
+    inside = rng.random(n) < 0.5
+    rc = np.zeros(2 * n)
+    for rim in (False, True):   # first without encounters, for the final separations
+        s = System([d], rcrit=rc)
+        genga.genga_set_large_groups(s.ctx.handle, large)
+        genga.genga_step(s.ctx.handle, s.b, DT, steps, FP64)
+        st = s.numpy_state()
+        if not rim:
+            dx, dy, dz = (st[k][j] - st[k][i] for k in ("x", "y", "z"))
+            r2 = (dx * dx + dy * dy) + dz * dz
+            lo = np.sqrt(r2)
+            lo = np.where(lo * lo > r2, np.nextafter(lo, 0.0), lo)    # the largest r with r * r <= r2
+            rc[i] = np.where(far, np.where(inside, np.nextafter(lo, 1.0), lo), 0.0)
+        else:
+            exp = oracle.encounters(st, rc)
+            np.testing.assert_array_equal(exp[:, 0], i[far & inside])
+            np.testing.assert_array_equal(s.encounter_list(standalone=False)[0], exp)
+            np.testing.assert_array_equal(s.encounter_list(standalone=True)[0], exp)
+        assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK, genga.genga_last_error()
+        s.close()

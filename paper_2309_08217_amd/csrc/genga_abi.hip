@@ -1250,7 +1250,9 @@ int genga_set_systems(genga_ctx *ctx, int32_t n_sys, const int32_t *sys_off_host
         ctx->release();
         return rc;
     }
+    // a source split set or tuned for another layout does not carry over (the waves do)
     ctx->split[0] = ctx->split[1] = default_split(ctx);
+    ctx->own_plan[0] = ctx->own_plan[1] = true;
     if (keep_large) {
         if ((rc = alloc_big(ctx))) return rc;
         ctx->large_groups = 1;

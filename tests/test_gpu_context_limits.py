@@ -140,3 +140,18 @@ def test_list_after_steps_is_that_of_the_positions(steps, large):
             np.testing.assert_array_equal(s.encounter_list(standalone=True)[0], exp)
         assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK, genga.genga_last_error()
         s.close()
+
+
+@pytest.mark.parametrize("prec", [FP64, FP32])
+def test_a_new_layout_takes_its_own_kick_plan(prec):
+    """A source split set for one layout is not kept for the next: its kick is that of a fresh
+    context, bit for bit."""
+    d = discs.make_disc(5000, 2.5, seed=31)
+    s, fresh = System([d]), System([d])
+    genga.genga_set_kick_shape(s.ctx.handle, prec, 0, 3)
+    assert not np.array_equal(s.accel(prec), fresh.accel(prec))   # other runs, another rounding
+    genga.genga_set_systems(s.ctx.handle, s.off, s.mstar)
+    np.testing.assert_array_equal(s.accel(prec), fresh.accel(prec))
+    assert genga.genga_get_kick_shape(s.ctx.handle, prec) == genga.genga_get_kick_shape(fresh.ctx.handle, prec)
+    s.close()
+    fresh.close()

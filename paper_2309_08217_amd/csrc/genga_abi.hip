@@ -939,9 +939,9 @@ int enqueue_steps_fused(genga_ctx *ctx, genga_bodies *b, double dt, int nsteps, 
     pm.clear = ctx->pair_count;
     for (int k = 1, rec = 0; k <= nsteps; ++k) {
         const bool last = k == nsteps;
+        ctx->list_valid = false; // until the next kick, also where the groups are refused
         if (large && (rc = build_groups_large(ctx, s))) return rc;
         if (large && ctx->groups_h.G > 0) {
-            ctx->list_valid = false;
             HIP_TRY(launch_sun_shift(ctx->items, ctx->n_items, L.mstar, b->x, b->y, b->z, pm, s));
             if ((rc = enqueue_drift_parts(ctx, b, dt, s))) return rc;
             HIP_TRY(launch_drifted(ctx->items, ctx->n_items, b->vx, b->vy, b->vz, b->m, pm, s));

@@ -155,3 +155,23 @@ def test_a_new_layout_takes_its_own_kick_plan(prec):
     assert genga.genga_get_kick_shape(s.ctx.handle, prec) == genga.genga_get_kick_shape(fresh.ctx.handle, prec)
     s.close()
     fresh.close()
+
+
+def test_no_list_after_a_refused_step():
+    """genga_step refused for a group above 65536 bodies: the list of its last kick is no longer
+    handed out, as after a refused genga_drift; the standalone list is."""
+    n = 66000
+    ph = 2.0 * np.pi * np.arange(n) / n
+    zero = np.zeros(n)
+    d = discs.Disc(x=np.cos(ph), y=np.sin(ph), z=zero, vx=-np.sin(ph), vy=np.cos(ph), vz=zero.copy(),
+                   m=np.full(n, 1e-15))
+    s = System([d], rcrit=np.full(n, 3.0 * np.pi / n))   # one neighbour on either side
+    genga.genga_set_large_groups(s.ctx.handle, True)
+    with pytest.raises(genga.GengaError) as e:
+        genga.genga_step(s.ctx.handle, s.b, DT, 1, FP64)
+    assert e.value.status == genga.GENGA_ERR_CAPACITY
+    with pytest.raises(genga.GengaError) as e:
+        s.encounter_list()
+    assert e.value.status == genga.GENGA_ERR_STATE
+    assert s.encounter_list(standalone=True)[1] == n
+    s.close()

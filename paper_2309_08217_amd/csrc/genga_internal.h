@@ -155,7 +155,7 @@ constexpr int KICK_TASKS_PER_CU = 64;
 inline int run_len(int64_t source_visits, int n_cu, int len = KICK_RUN_MIN)
 {
     n_cu = n_cu < 256 ? n_cu : 256;
-    while (len < (1 << 20) && source_visits / len > (int64_t)KICK_TASKS_PER_CU * n_cu) len *= 2;
+    while (len < (1 << 30) && source_visits / len > (int64_t)KICK_TASKS_PER_CU * n_cu) len *= 2; // n <= 2^30
     return len;
 }
 // The kick's: runs of KICK_RUN_MIN only up to KICK_SHORT_PER_CU tasks per CU, where they fill it.

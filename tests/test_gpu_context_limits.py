@@ -175,3 +175,22 @@ def test_no_list_after_a_refused_step():
     assert e.value.status == genga.GENGA_ERR_STATE
     assert s.encounter_list(standalone=True)[1] == n
     s.close()
+
+
+@pytest.mark.parametrize("n_sys,n", [(1, 1 << 25)])
+def test_memory_of_a_layout(n_sys, n):
+    """A layout's device memory goes by its bodies: the tasks' shares 96 B a body (four shares of
+    three sums), the other arrays about 150 and some 400 a system."""
+    torch = pytest.importorskip("torch")
+    c = genga.Context()
+    off = np.arange(n_sys + 1, dtype=np.int64) * n
+    genga.genga_set_systems(c.handle, [0, 64], [1.0], 1024)   # (what a first layout leaves allocated)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    e = genga.Context()
+    genga.genga_set_systems(e.handle, off, np.ones(n_sys), 1024)
+    per_body = (before - torch.cuda.mem_get_info()[0]) / (n_sys * n)
+    print(f"[layout] {n_sys} systems of {n}: {per_body:.0f} B a body", flush=True)
+    assert per_body <= 400
+    e.close()
+    c.close()

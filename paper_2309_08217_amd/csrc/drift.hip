@@ -767,7 +767,7 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
     double(*red)[NW] = reinterpret_cast<double(*)[NW]>(S.keys);                     // [6][NW]
     double(*share)[NW][64] = reinterpret_cast<double(*)[NW][64]>(S.keys + 6 * NW); // [3][NW][64]
     static_assert((6 + 3 * 64) * NW <= CE_MAX_MEMBERS, "the sums fit");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, part = wave % parts;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), part = wave % parts;
     const bool shift = pm.tau != 0.0;
     // first round: the block, the drift's groups (one per thread; more below)
     const CloseBlock blk = pm.blocks[blockIdx.x - 1];
@@ -796,7 +796,7 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
             X[2] = z[i];
         }
     }
-    if (mine) item_shares(a, it, lane, t, part, parts);
+    if (on) item_shares(a, it, w, lane, t, part, parts);
     for (int q = 0; q < 3; ++q) share[q][wave][lane] = t[q];
     if (shift) {
         drift_momentum(pm, blk, G, gs, &S.ng, P);

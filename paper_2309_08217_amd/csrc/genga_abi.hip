@@ -72,12 +72,13 @@ struct genga_ctx {
     int32_t n_etasks = 0;
     KickTask *tasks = nullptr;  // the layout's own kick plan
     int32_t *task_first = nullptr; // [n_items + 1] an item's tasks
+    uint32_t *item_row = nullptr;  // [n_items] an item's first row of shares
     int32_t n_tasks = 0;
     int waves[2] = {0, 0};      // [prec] waves per workgroup of the kick (0: default_kick_waves)
     int split[2] = {1, 1};      // [prec] workgroups sharing an item's sources
     bool own_plan[2] = {true, true}; // [prec] the layout's own plan instead of `split`
     StepMomentum pm;            // momentum sums between the launches of a step (blocks: device)
-    double *kpart = nullptr;    // [tasks][3][64], at least KICK_MAX_SPLIT tasks per item
+    double *kpart = nullptr;    // [3][ni] per task, at least for KICK_MAX_SPLIT tasks per item
     // scratch
     float *m32 = nullptr;       // [n_total] masses in FP32
     double *chunk_mass = nullptr; // [n_chunks]
@@ -336,6 +337,7 @@ KickArgs kick_args(const genga_ctx *ctx, const genga_bodies *b)
     a.flags = ctx->flags;
     a.tasks = ctx->tasks;
     a.task_first = ctx->task_first;
+    a.item_row = ctx->item_row;
     a.n_tasks = ctx->n_tasks;
     a.split = 1;
     a.direct = ctx->n_tasks == ctx->n_items;
@@ -1010,12 +1012,15 @@ int upload_plan(genga_ctx *ctx)
     for (int s = 0; s < n_sys; ++s)
         cfst[s + 1] = cfst[s] + (ctx->sys_off_h[s + 1] - ctx->sys_off_h[s] + CHUNK - 1) / CHUNK;
     std::vector<int32_t> tfirst(it.size() + 1, 0);
+    std::vector<uint32_t> rows(it.size());
+    uint32_t row = 0; // at most 64 bodies of some 64 tasks per CU and of one and a half tasks per item
     for (size_t k = 0; k < it.size(); ++k) {
+        rows[k] = row;
         const int parts = kick_runs(it[k].nsrc, len), per = kick_run(it[k].nsrc, parts);
         const int sy = it[k].sys, b = ctx->sys_off_h[sy], e = b + it[k].nsrc;
-        for (int p = 0; p < parts; ++p)
+        for (int p = 0; p < parts; ++p, row += it[k].ni)
             tasks.push_back(KickTask{sy, it[k].i0, it[k].ni, std::min(b + p * per, e), std::min(b + (p + 1) * per, e),
-                                     cfst[sy], cfst[sy + 1], b});
+                                     cfst[sy], cfst[sy + 1], b, row});
         tfirst[k + 1] = (int32_t)tasks.size();
     }
     // blocks of items of one system, for the end of a step's kick
@@ -1069,13 +1074,14 @@ int upload_plan(genga_ctx *ctx)
         if (bytes) std::copy_n(reinterpret_cast<const char *>(v.data()), bytes, host.data() + at);
         return at;
     };
-    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_cb = put(cb), o_cfirst = put(cfirst);
+    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_cfirst = put(cfirst);
     const size_t o_et = put(et), o_efirst = put(efirst), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
     const size_t o_kick = place(3 * cb.size() * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
     const size_t o_group = place(3 * (size_t)CE_MAX_GROUPS * sizeof(double));
     const size_t o_gsys = place((size_t)CE_MAX_GROUPS * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
     const size_t o_epart = place(9 * et.size() * sizeof(double));
-    const size_t o_kpart = place(192 * std::max(tasks.size(), KICK_MAX_SPLIT * it.size()) * sizeof(double));
+    const size_t nt = (size_t)ctx->sys_off_h[n_sys];
+    const size_t o_kpart = place(3 * std::max((size_t)row, KICK_MAX_SPLIT * nt) * sizeof(double));
     char *plan = nullptr;
     HIP_TRY(dalloc(plan, size));
     const hipError_t copied = hipMemcpy(plan, host.data(), host.size(), hipMemcpyHostToDevice);
@@ -1091,6 +1097,7 @@ int upload_plan(genga_ctx *ctx)
     ctx->items = reinterpret_cast<WorkItem *>(plan + o_items);
     ctx->tasks = reinterpret_cast<KickTask *>(plan + o_tasks);
     ctx->task_first = reinterpret_cast<int32_t *>(plan + o_tfirst);
+    ctx->item_row = reinterpret_cast<uint32_t *>(plan + o_rows);
     ctx->etasks = reinterpret_cast<EnergyTask *>(plan + o_et);
     ctx->etask_first = reinterpret_cast<int32_t *>(plan + o_efirst);
     ctx->L.n_massive = reinterpret_cast<int32_t *>(plan + o_nm);

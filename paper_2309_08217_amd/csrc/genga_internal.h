@@ -59,6 +59,7 @@ struct KickTask {
     int32_t sys, i0, ni, j0, j1;
     int32_t c0, c1; // the system's chunks
     int32_t off;    // the system's first body
+    uint32_t row;   // where its share starts: the bodies of the tasks before it
 };
 
 struct KickArgs {
@@ -82,10 +83,11 @@ struct KickArgs {
     const KickTask *tasks;        // [n_tasks], items in order; null: every item's sources in `split`
                                   //   runs, task = item * split + run
     const int32_t *task_first;    // [n_items + 1] an item's tasks (with tasks)
+    const uint32_t *item_row;     // [n_items] its first task's row (with tasks)
     int32_t n_tasks;
     int32_t split;
     int32_t direct;               // one task per item: it writes the bodies itself
-    double *part;                 // [tasks][3][64] shares of the targets (else)
+    double *part;                 // shares of the targets (else): [3][ni] of a task at 3 row
     const int32_t *status;        // with collisions: bodies with status != 0 are in no pair
 };
 

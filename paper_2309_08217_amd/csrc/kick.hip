@@ -183,6 +183,7 @@ __device__ __forceinline__ KickTask task_of(const KickArgs &a, int t)
     k.c0 = a.chunk_first[w.sys];
     k.c1 = a.chunk_first[w.sys + 1];
     k.off = b;
+    k.row = (uint32_t)a.split * (uint32_t)w.i0 + (uint32_t)part * (uint32_t)w.ni;
     return k;
 }
 
@@ -327,7 +328,7 @@ __device__ __forceinline__ void step64(CD *X, CD *Y, CD *Z, CD *M, int j, int jb
 // its sources are split over tasks, store this task's share for kick_finish_kernel.
 template <int W>
 __device__ __forceinline__ void finish(const KickArgs &a, double (*red)[W][64], int wave, int lane, bool valid, int i,
-                                       int task, double sx, double sy, double sz)
+                                       const KickTask &k, double sx, double sy, double sz)
 {
     red[0][wave][lane] = sx;
     red[1][wave][lane] = sy;
@@ -339,25 +340,26 @@ __device__ __forceinline__ void finish(const KickArgs &a, double (*red)[W][64], 
     for (int w = 0; w < W; ++w)
 #pragma unroll
         for (int q = 0; q < 3; ++q) t[q] += red[q][w][lane];
+    if (!valid) return;
     if (a.direct) {
-        if (valid) store_accel(a, i, t[0], t[1], t[2]);
+        store_accel(a, i, t[0], t[1], t[2]);
         return;
     }
-    double *p = a.part + (size_t)task * 192 + lane;
+    double *p = a.part + 3 * (size_t)k.row + lane;
     p[0] = t[0];
-    p[64] = t[1];
-    p[128] = t[2];
+    p[k.ni] = t[1];
+    p[2 * k.ni] = t[2];
 }
 
 // Adds the tasks' shares of every body in task order, then as finish() above.  One wave per item.
 __global__ __launch_bounds__(256) void kick_finish_kernel(KickArgs a)
 {
-    const int it = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int it = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6)), lane = threadIdx.x & 63;
     if (it >= a.n_items) return;
     const WorkItem w = a.items[it];
     if (lane >= w.ni) return;
     double t[3];
-    item_shares(a, it, lane, t);
+    item_shares(a, it, w, lane, t);
     store_accel(a, w.i0 + lane, t[0], t[1], t[2]);
 }
 
@@ -470,7 +472,7 @@ __global__ __launch_bounds__(64 * W) void kick32_kernel(KickArgs a)
     else
         run32<KAHAN, false>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     flush_pairs<W>(a, pair_slots, pair_fill, wave, lane);
-    finish<W>(a, red, wave, lane, valid, i, blockIdx.x, sx, sy, sz);
+    finish<W>(a, red, wave, lane, valid, i, t, sx, sy, sz);
 }
 
 template <int W>
@@ -498,7 +500,7 @@ __global__ __launch_bounds__(64 * W) void kick64_kernel(KickArgs a)
     else
         run64<false, false>(a, jb, je, i, valid, xi, yi, zi, rci, T, mass, sx, sy, sz, pb);
     flush_pairs<W>(a, pair_slots, pair_fill, wave, lane);
-    finish<W>(a, red, wave, lane, valid, i, blockIdx.x, sx, sy, sz);
+    finish<W>(a, red, wave, lane, valid, i, t, sx, sy, sz);
 }
 
 // The encounter pairs alone, in the layout's own tasks.  A pair is found from its lower body, so of

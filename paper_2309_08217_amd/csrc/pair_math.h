@@ -144,24 +144,28 @@ __device__ __forceinline__ void store_accel(const KickArgs &a, int i, double tx,
     }
 }
 
-// The tasks' shares of body `lane` of item `it`, added in task order; with parts > 1 those of part
-// `part` of its tasks.
-__device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane, double t[3], int part = 0, int parts = 1)
+// The tasks' shares of body `lane` (below w.ni) of item `it`, added in task order; with parts > 1
+// those of part `part` of its tasks.
+__device__ __forceinline__ void item_shares(const KickArgs &a, int it, const WorkItem &w, int lane, double t[3],
+                                            int part = 0, int parts = 1)
 {
-    int t0 = a.tasks ? a.task_first[it] : it * a.split, t1 = a.tasks ? a.task_first[it + 1] : t0 + a.split;
+    const int first = a.tasks ? a.task_first[it] : it * a.split;
+    const uint32_t row = a.tasks ? a.item_row[it] : (uint32_t)a.split * (uint32_t)w.i0;
+    int t0 = first, t1 = a.tasks ? a.task_first[it + 1] : first + a.split;
     if (parts > 1) {
-        const int n = t1 - t0, b = t0;
-        t0 = b + n * part / parts;
-        t1 = b + n * (part + 1) / parts;
+        const int n = t1 - t0;
+        t0 = first + n * part / parts;
+        t1 = first + n * (part + 1) / parts;
     }
     t[0] = t[1] = t[2] = 0.0;
-    const double *p = a.part + (size_t)t0 * 192 + lane;
+    const int ni = w.ni, stride = 3 * ni;
+    const double *p = a.part + 3 * (size_t)row + (size_t)(t0 - first) * stride + lane;
     int k = t0;
-    for (; k + 8 <= t1; k += 8, p += 8 * 192) { // eight tasks' loads in flight
+    for (; k + 8 <= t1; k += 8, p += 8 * stride) { // eight tasks' loads in flight
         double v[8][3];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
-            for (int q = 0; q < 3; ++q) v[u][q] = p[u * 192 + 64 * q];
+            for (int q = 0; q < 3; ++q) v[u][q] = p[u * stride + q * ni];
 #pragma unroll
         for (int u = 0; u < 8; ++u)
             for (int q = 0; q < 3; ++q) t[q] += v[u][q];
@@ -170,15 +174,15 @@ __device__ __forceinline__ void item_shares(const KickArgs &a, int it, int lane,
         double v[4][3];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            for (int q = 0; q < 3; ++q) v[u][q] = p[u * 192 + 64 * q];
+            for (int q = 0; q < 3; ++q) v[u][q] = p[u * stride + q * ni];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             for (int q = 0; q < 3; ++q) t[q] += v[u][q];
         k += 4;
-        p += 4 * 192;
+        p += 4 * stride;
     }
-    for (; k < t1; ++k, p += 192)
-        for (int q = 0; q < 3; ++q) t[q] += p[64 * q];
+    for (; k < t1; ++k, p += stride)
+        for (int q = 0; q < 3; ++q) t[q] += p[q * ni];
 }
 
 } // namespace genga

@@ -177,7 +177,7 @@ def test_no_list_after_a_refused_step():
     s.close()
 
 
-@pytest.mark.parametrize("n_sys,n", [(1, 1 << 25)])
+@pytest.mark.parametrize("n_sys,n", [(1, 1 << 25), (200000, 10), (200000, 65)])
 def test_memory_of_a_layout(n_sys, n):
     """A layout's device memory goes by its bodies: the tasks' shares 96 B a body (four shares of
     three sums), the other arrays about 150 and some 400 a system."""

@@ -635,13 +635,55 @@ __global__ __launch_bounds__(CE_THREADS) void ce_groups_kernel(GroupBuild g, Pai
     build_groups(g, S);
 }
 
+// What a wave of a CloseBlock works on: an item of a system (item < 0: none), or a part of its tasks.
+struct CloseWave {
+    int sys, item, part, parts;
+    int f0, f1;     // the system's items
+    int w0, waves;  // the system's waves
+    double mstar;
+};
+
+// SMALL: the layout has blocks of several systems.  (Looked up in every block, they cost layouts without
+// any 0.5 to 1 us a launch.)
+template <bool SMALL>
+__device__ __forceinline__ CloseWave close_wave(const CloseBlock &blk, const StepMomentum &pm, int wave)
+{
+    if (SMALL && blk.waves != CLOSE_WAVES) {
+        const int k = wave / blk.waves, s = blk.sys + min(k, blk.n - 1);
+        const int f0 = pm.item_first[s], f1 = pm.item_first[s + 1], it = f0 + wave % blk.waves;
+        return CloseWave{s, k < blk.n && it < f1 ? it : -1, 0, 1, f0, f1, k * blk.waves, blk.waves, pm.mstar[s]};
+    }
+    const int k = wave / pm.parts;
+    return CloseWave{blk.sys, k < blk.n ? blk.item + k : -1, wave % pm.parts, pm.parts, blk.f0, blk.f1, 0, CLOSE_WAVES,
+                     blk.mstar};
+}
+
+// The rows of a block's sums from its waves' (red), once every wave has stored its own.
+template <bool SMALL>
+__device__ __forceinline__ void store_rows(const CloseBlock &blk, const double (*red)[CLOSE_WAVES], double *rows)
+{
+    const int tid = threadIdx.x;
+    if (SMALL && blk.waves != CLOSE_WAVES) {
+        const int i = tid / 3, q = tid % 3;
+        if (i >= blk.n) return;
+        double s = 0.0;
+        for (int k = 0; k < blk.waves; ++k) s += red[q][i * blk.waves + k];
+        rows[3 * (size_t)(blk.row + i) + q] = s;
+    } else if (tid < 3) {
+        double s = 0.0;
+        for (int k = 0; k < CLOSE_WAVES; ++k) s += red[tid][k];
+        rows[3 * (size_t)blk.row + tid] = s;
+    }
+}
+
 // What a drift outside a step starts from, in one launch: the momentum sums of the items' blocks,
 // and, from the workgroups after them, the check and copy of a caller's pair list.
+template <bool SMALL>
 __global__ __launch_bounds__(CE_THREADS) void drift_open_kernel(const WorkItem *items, const double *vx,
                                                                 const double *vy, const double *vz, const double *m,
                                                                 StepMomentum pm, PairImport im)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x >= pm.n_blocks) {
         const int n = min(*im.src_count, im.cap), first = (blockIdx.x - pm.n_blocks) * CE_THREADS + tid;
         bool ok = true;
@@ -658,8 +700,9 @@ __global__ __launch_bounds__(CE_THREADS) void drift_open_kernel(const WorkItem *
     __shared__ double red[3][CLOSE_WAVES];
     const CloseBlock blk = pm.blocks[blockIdx.x];
     double p[3] = {0.0, 0.0, 0.0};
-    if (wave < blk.n) {
-        const WorkItem w = items[blk.item + wave];
+    const CloseWave c = close_wave<SMALL>(blk, pm, wave);
+    if (c.item >= 0 && c.part == 0) {
+        const WorkItem w = items[c.item];
         if (lane < w.ni) {
             const int i = w.i0 + lane;
             const double mi = m[i];
@@ -673,70 +716,94 @@ __global__ __launch_bounds__(CE_THREADS) void drift_open_kernel(const WorkItem *
         if (lane == 0) red[q][wave] = p[q];
     }
     __syncthreads();
-    if (tid < 3) {
-        double s = 0.0;
-        for (int k = 0; k < CLOSE_WAVES; ++k) s += red[tid][k];
-        pm.kick[3 * (size_t)blockIdx.x + tid] = s;
-    }
+    store_rows<SMALL>(blk, red, pm.kick);
 }
 
-// A thread's part of a system's momentum after the drift: by item, and by group from the system's
-// first group on, so that the order of the sum depends on the system alone (groups are in system
-// order).  gs: the system of group tid, loaded ahead; first: a word of LDS.
-__device__ __forceinline__ void drift_momentum(const StepMomentum &pm, const CloseBlock &blk, int G, int gs, int *first,
-                                               double P[3])
+// The first of the G groups (in system order) whose system is not below s, by a wave in two rounds of
+// loads.
+__device__ __forceinline__ int first_group(const int32_t *group_sys, int G, int s)
 {
-    const int tid = threadIdx.x;
-    if (tid == 0) *first = G;
-    __syncthreads();
-    for (int k = tid; k < G; k += CE_THREADS) {
-        if (k != tid) gs = pm.group_sys[k];
-        if (gs == blk.sys) {
-            atomicMin(first, k);
-            break;
-        }
-    }
-    __syncthreads();
-    for (int k = *first + tid; k < G && pm.group_sys[k] == blk.sys; k += CE_THREADS)
-        for (int q = 0; q < 3; ++q) P[q] += pm.group[3 * (size_t)k + q];
+    static_assert(CE_MAX_GROUPS <= 64 * 64, "two rounds of 64");
+    const int lane = threadIdx.x & 63, step = (G + 63) / 64;
+    const auto below = [&](int k, bool on) { return __popcll(__ballot(on && k < G && group_sys[k] < s)); };
+    const int n = below(lane * step, true);
+    if (n == 0) return 0;
+    return (n - 1) * step + below((n - 1) * step + lane, lane < step);
 }
 
-// The second half of the Sun drift after a drift outside a step: positions + tau P / Mstar.
-__global__ __launch_bounds__(CE_THREADS) void drift_close_kernel(const WorkItem *items, double *x, double *y, double *z,
-                                                                 StepMomentum pm)
+// The second half of a Sun drift, tau P / Mstar of the wave's system, P summed after the drift by item
+// and by group from the system's first group on, so that the order of the sum depends on the system
+// alone (groups are in system order).  Every thread of the workgroup calls it.  G: the drift's groups;
+// gs: the system of group tid, loaded ahead; red: LDS; first: a word of LDS.
+template <bool SMALL>
+__device__ __forceinline__ void close_shift(const StepMomentum &pm, const CloseWave &c, int G, int gs, int *first,
+                                            double (*red)[CLOSE_WAVES], double sh[3])
 {
-    __shared__ double red[3][CLOSE_WAVES];
-    __shared__ int first;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const CloseBlock blk = pm.blocks[blockIdx.x];
-    const int G = *pm.group_n, gs = pm.group_sys[tid];
-    const WorkItem w = wave < blk.n ? items[blk.item + wave] : WorkItem{0, 0, 0, 0};
-    const bool on = lane < w.ni;
-    const int i = w.i0 + lane;
-    double P[3] = {0.0, 0.0, 0.0}, X[3] = {0.0, 0.0, 0.0};
-    for (int k = blk.f0 + tid; k < blk.f1; k += CE_THREADS)
-        for (int q = 0; q < 3; ++q) P[q] += pm.kepler[3 * (size_t)k + q];
-    if (on) {
-        X[0] = x[i];
-        X[1] = y[i];
-        X[2] = z[i];
+    double P[3] = {0.0, 0.0, 0.0};
+    const auto add = [&](const double *part, int k) {
+        for (int q = 0; q < 3; ++q) P[q] += part[3 * (size_t)k + q];
+    };
+    if (!SMALL || c.waves == CLOSE_WAVES) { // the whole workgroup
+        for (int k = c.f0 + tid; k < c.f1; k += CE_THREADS) add(pm.kepler, k);
+        if (tid == 0) *first = G;
+        __syncthreads();
+        for (int k = tid; k < G; k += CE_THREADS) {
+            if (k != tid) gs = pm.group_sys[k];
+            if (gs == c.sys) {
+                atomicMin(first, k);
+                break;
+            }
+        }
+        __syncthreads();
+        for (int k = *first + tid; k < G && pm.group_sys[k] == c.sys; k += CE_THREADS) add(pm.group, k);
+    } else if (wave == c.w0) { // the system's first wave: as many items as lanes at most
+        if (c.f0 + lane < c.f1) add(pm.kepler, c.f0 + lane);
+        if (G > 0)
+            for (int k = first_group(pm.group_sys, G, c.sys) + lane; k < G && pm.group_sys[k] == c.sys; k += 64)
+                add(pm.group, k);
     }
-    drift_momentum(pm, blk, G, gs, &first, P);
     for (int q = 0; q < 3; ++q) {
         P[q] = wave_sum(P[q]);
         if (lane == 0) red[q][wave] = P[q];
     }
     __syncthreads();
-    const double f = pm.tau / blk.mstar;
+    const double f = pm.tau / c.mstar;
     for (int q = 0; q < 3; ++q) {
         double s = 0.0;
-        for (int k = 0; k < CLOSE_WAVES; ++k) s += red[q][k];
-        X[q] += f * s;
+        if (SMALL)
+            for (int k = 0; k < c.waves; ++k) s += red[q][c.w0 + k];
+        else
+            for (int k = 0; k < CLOSE_WAVES; ++k) s += red[q][k];
+        sh[q] = f * s;
     }
+}
+
+// The second half of the Sun drift after a drift outside a step: positions + tau P / Mstar.
+template <bool SMALL>
+__global__ __launch_bounds__(CE_THREADS) void drift_close_kernel(const WorkItem *items, double *x, double *y, double *z,
+                                                                 StepMomentum pm)
+{
+    __shared__ double red[3][CLOSE_WAVES];
+    __shared__ int first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const CloseBlock blk = pm.blocks[blockIdx.x];
+    const int G = *pm.group_n, gs = pm.group_sys[tid];
+    const CloseWave c = close_wave<SMALL>(blk, pm, wave);
+    const WorkItem w = c.item >= 0 && c.part == 0 ? items[c.item] : WorkItem{0, 0, 0, 0};
+    const bool on = lane < w.ni;
+    const int i = w.i0 + lane;
+    double X[3] = {0.0, 0.0, 0.0}, sh[3];
     if (on) {
-        x[i] = X[0];
-        y[i] = X[1];
-        z[i] = X[2];
+        X[0] = x[i];
+        X[1] = y[i];
+        X[2] = z[i];
+    }
+    close_shift<SMALL>(pm, c, G, gs, &first, red, sh);
+    if (on) {
+        x[i] = X[0] + sh[0];
+        y[i] = X[1] + sh[1];
+        z[i] = X[2] + sh[2];
     }
 }
 
@@ -750,16 +817,17 @@ __device__ __forceinline__ void wave_momentum(const int32_t *first, const double
 }
 
 // The end of a kick inside a step (launch_kick_close).  Workgroup 0 builds the groups, the others
-// take a block of items each, pm.parts waves an item, which share its tasks (20040 bodies in FP64, 39
-// tasks an item: 14 us with four waves, 26 with one).  Latency bound, a chain of loads of what other launches wrote: everything a wave needs is loaded before
+// take a block of items each, of which those of a large system have up to four waves an item, which
+// share its tasks (20040 bodies in FP64, 39 tasks an item: 14 us with four waves, 26 with one).
+// Latency bound, a chain of loads of what other launches wrote: everything a wave needs is loaded before
 // the first barrier, in three rounds.
+template <bool SMALL>
 __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, double *x, double *y, double *z,
                                                                 StepMomentum pm, GroupBuild g, int with_groups)
 {
     __shared__ GroupLds S;
     constexpr int NW = CLOSE_WAVES;
     static_assert(NW == CE_THREADS / 64, "the block's waves");
-    const int parts = pm.parts;
     if (blockIdx.x == 0) {
         if (with_groups) build_groups(g, S);
         return;
@@ -767,24 +835,19 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
     double(*red)[NW] = reinterpret_cast<double(*)[NW]>(S.keys);                     // [6][NW]
     double(*share)[NW][64] = reinterpret_cast<double(*)[NW][64]>(S.keys + 6 * NW); // [3][NW][64]
     static_assert((6 + 3 * 64) * NW <= CE_MAX_MEMBERS, "the sums fit");
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), part = wave % parts;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const bool shift = pm.tau != 0.0;
     // first round: the block, the drift's groups (one per thread; more below)
     const CloseBlock blk = pm.blocks[blockIdx.x - 1];
     const int G = shift ? *pm.group_n : 0;
     const int gs = shift ? pm.group_sys[tid] : -1;
-    // second round: the item, its tasks, P after the drift by item
-    const int it = blk.item + wave / parts;
-    const bool mine = wave / parts < blk.n;
-    const WorkItem w = mine ? a.items[it] : WorkItem{0, 0, 0, 0};
-    const bool on = lane < w.ni, lead = on && part == 0;
+    // second round: the item, its tasks
+    const CloseWave c = close_wave<SMALL>(blk, pm, wave);
+    const WorkItem w = c.item >= 0 ? a.items[c.item] : WorkItem{0, 0, 0, 0};
+    const bool on = lane < w.ni, lead = on && c.part == 0;
     const int i = w.i0 + lane;
-    double P[3] = {0.0, 0.0, 0.0};
-    if (shift)
-        for (int k = blk.f0 + tid; k < blk.f1; k += CE_THREADS)
-            for (int q = 0; q < 3; ++q) P[q] += pm.kepler[3 * (size_t)k + q];
     // third: the shares and the body
-    double t[3] = {0.0, 0.0, 0.0}, X[3] = {0.0, 0.0, 0.0}, V[3] = {0.0, 0.0, 0.0}, mi = 0.0;
+    double t[3] = {0.0, 0.0, 0.0}, X[3] = {0.0, 0.0, 0.0}, V[3] = {0.0, 0.0, 0.0}, sh[3] = {0.0, 0.0, 0.0}, mi = 0.0;
     if (lead) {
         mi = a.m[i];
         V[0] = a.vx[i];
@@ -796,26 +859,13 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
             X[2] = z[i];
         }
     }
-    if (on) item_shares(a, it, w, lane, t, part, parts);
+    if (on) item_shares(a, c.item, w, lane, t, c.part, c.parts);
     for (int q = 0; q < 3; ++q) share[q][wave][lane] = t[q];
-    if (shift) {
-        drift_momentum(pm, blk, G, gs, &S.ng, P);
-        for (int q = 0; q < 3; ++q) {
-            P[q] = wave_sum(P[q]);
-            if (lane == 0) red[q][wave] = P[q];
-        }
-        __syncthreads();
-        const double f = pm.tau / blk.mstar;
-        for (int q = 0; q < 3; ++q) {
-            double s = 0.0;
-            for (int k = 0; k < NW; ++k) s += red[q][k];
-            X[q] += f * s;
-        }
-    }
+    if (shift) close_shift<SMALL>(pm, c, G, gs, &S.ng, red, sh);
     __syncthreads();
     double p[3] = {0.0, 0.0, 0.0};
     if (lead) {
-        for (int k = 1; k < parts; ++k)
+        for (int k = 1; k < c.parts; ++k)
             for (int q = 0; q < 3; ++q) t[q] += share[q][wave + k][lane];
         a.ax[i] = t[0];
         a.ay[i] = t[1];
@@ -829,9 +879,9 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
         a.vy[i] = V[1];
         a.vz[i] = V[2];
         if (shift) {
-            x[i] = X[0];
-            y[i] = X[1];
-            z[i] = X[2];
+            x[i] = X[0] + sh[0];
+            y[i] = X[1] + sh[1];
+            z[i] = X[2] + sh[2];
         }
     }
     for (int q = 0; q < 3; ++q) {
@@ -839,11 +889,7 @@ __global__ __launch_bounds__(CE_THREADS) void kick_close_kernel(KickArgs a, doub
         if (lane == 0) red[3 + q][wave] = p[q];
     }
     __syncthreads();
-    if (tid < 3) {
-        double s = 0.0;
-        for (int k = 0; k < NW; ++k) s += red[3 + tid][k];
-        pm.kick[3 * (size_t)(blockIdx.x - 1) + tid] = s;
-    }
+    store_rows<SMALL>(blk, red + 3, pm.kick);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1377,7 +1423,7 @@ __device__ __forceinline__ void sun_shift_of(const StepMomentum &pm, const doubl
     sh[0] = sh[1] = sh[2] = 0.0;
     if (!pm.kick) return;
     double P[3];
-    wave_momentum(pm.block_first, pm.kick, s, P);
+    wave_momentum(pm.row_first, pm.kick, s, P);
     const double f = pm.tau / mstar[s];
     for (int q = 0; q < 3; ++q) sh[q] = f * P[q];
 }
@@ -1649,7 +1695,7 @@ static int import_blocks(const PairImport &p) { return std::max(1, std::min(256,
 
 hipError_t launch_import_pairs(const PairImport &p, hipStream_t stream)
 {
-    drift_open_kernel<<<import_blocks(p), CE_THREADS, 0, stream>>>(nullptr, nullptr, nullptr, nullptr, nullptr,
+    drift_open_kernel<false><<<import_blocks(p), CE_THREADS, 0, stream>>>(nullptr, nullptr, nullptr, nullptr, nullptr,
                                                                    StepMomentum{}, p);
     import_finish_kernel<<<1, 64, 0, stream>>>(p);
     return hipGetLastError();
@@ -1665,7 +1711,7 @@ hipError_t launch_drift_open(const WorkItem *items, const double *vx, const doub
                              const double *m, const StepMomentum &pm, const PairImport *import, hipStream_t stream)
 {
     const int grid = pm.n_blocks + (import ? import_blocks(*import) : 0);
-    drift_open_kernel<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
+    (pm.small ? drift_open_kernel<true> : drift_open_kernel<false>)<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
     return hipGetLastError();
 }
 
@@ -1686,15 +1732,16 @@ hipError_t launch_drifted(const WorkItem *items, int n_items, const double *vx, 
 hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
                               hipStream_t stream)
 {
-    drift_close_kernel<<<pm.n_blocks, CE_THREADS, 0, stream>>>(items, x, y, z, pm);
+    (pm.small ? drift_close_kernel<true> : drift_close_kernel<false>)<<<pm.n_blocks, CE_THREADS, 0, stream>>>(items, x, y,
+                                                                                                              z, pm);
     return hipGetLastError();
 }
 
 hipError_t launch_kick_close(const KickArgs &a, double *x, double *y, double *z, const StepMomentum &pm,
                              const GroupBuild *groups, hipStream_t stream)
 {
-    kick_close_kernel<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(a, x, y, z, pm, groups ? *groups : GroupBuild{},
-                                                                  groups != nullptr);
+    (pm.small ? kick_close_kernel<true> : kick_close_kernel<false>)<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(
+        a, x, y, z, pm, groups ? *groups : GroupBuild{}, groups != nullptr);
     return hipGetLastError();
 }
 

@@ -1023,16 +1023,32 @@ int upload_plan(genga_ctx *ctx)
                                      cfst[sy], cfst[sy + 1], b, row});
         tfirst[k + 1] = (int32_t)tasks.size();
     }
-    // blocks of items of one system, for the end of a step's kick
+    // blocks for the end of a step's kick: of items of one system, or of several small systems in a row
     std::vector<CloseBlock> cb;
-    std::vector<int32_t> cfirst(n_sys + 1, 0);
+    std::vector<int32_t> rfirst(n_sys + 1, 0);
     const int cparts = close_parts((int)it.size(), ctx->n_cu), citems = CLOSE_WAVES / cparts;
+    int rows_kick = 0;
+    bool small = false;
     for (int s = 0; s < n_sys; ++s) {
-        cfirst[s] = (int32_t)cb.size();
-        for (int k = first[s]; k < first[s + 1]; k += citems)
-            cb.push_back(CloseBlock{s, k, std::min(citems, first[s + 1] - k), first[s], first[s + 1], ctx->mstar_h[s]});
+        rfirst[s] = rows_kick;
+        const int c = first[s + 1] - first[s];
+        if (c > CLOSE_SMALL) {
+            for (int k = first[s]; k < first[s + 1]; k += citems)
+                cb.push_back(CloseBlock{s, CLOSE_WAVES, k, std::min(citems, first[s + 1] - k), first[s], first[s + 1],
+                                        rows_kick++, ctx->mstar_h[s]});
+            continue;
+        }
+        if (cb.empty() || c > cb.back().waves || cb.back().waves == CLOSE_WAVES ||
+            (cb.back().n + 1) * cb.back().waves > CLOSE_WAVES) {
+            int w = 1;
+            while (w < c) w *= 2;
+            cb.push_back(CloseBlock{s, w, 0, 0, 0, 0, rows_kick, 0.0});
+            small = true;
+        }
+        ++cb.back().n;
+        ++rows_kick;
     }
-    cfirst[n_sys] = (int32_t)cb.size();
+    rfirst[n_sys] = rows_kick;
     // energy tasks: the sources after an item's first body (a test item has none: test pairs have
     // no energy), in runs as the kick's
     std::vector<EnergyTask> et;
@@ -1074,9 +1090,10 @@ int upload_plan(genga_ctx *ctx)
         if (bytes) std::copy_n(reinterpret_cast<const char *>(v.data()), bytes, host.data() + at);
         return at;
     };
-    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_cfirst = put(cfirst);
+    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_rfirst = put(rfirst),
+                 o_first = put(first);
     const size_t o_et = put(et), o_efirst = put(efirst), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
-    const size_t o_kick = place(3 * cb.size() * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
+    const size_t o_kick = place(3 * (size_t)rows_kick * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
     const size_t o_group = place(3 * (size_t)CE_MAX_GROUPS * sizeof(double));
     const size_t o_gsys = place((size_t)CE_MAX_GROUPS * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
     const size_t o_epart = place(9 * et.size() * sizeof(double));
@@ -1103,8 +1120,11 @@ int upload_plan(genga_ctx *ctx)
     ctx->L.n_massive = reinterpret_cast<int32_t *>(plan + o_nm);
     ctx->sort_seg = reinterpret_cast<int32_t *>(plan + o_seg);
     ctx->pm.blocks = reinterpret_cast<CloseBlock *>(plan + o_cb);
-    ctx->pm.block_first = reinterpret_cast<int32_t *>(plan + o_cfirst);
+    ctx->pm.row_first = reinterpret_cast<int32_t *>(plan + o_rfirst);
+    ctx->pm.item_first = reinterpret_cast<int32_t *>(plan + o_first);
+    ctx->pm.mstar = ctx->L.mstar;
     ctx->pm.n_blocks = (int32_t)cb.size();
+    ctx->pm.small = small;
     ctx->pm.parts = cparts;
     ctx->pm.kick = reinterpret_cast<double *>(plan + o_kick);
     ctx->pm.kepler = reinterpret_cast<double *>(plan + o_kepler);

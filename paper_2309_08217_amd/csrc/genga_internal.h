@@ -91,11 +91,15 @@ struct KickArgs {
     const int32_t *status;        // with collisions: bodies with status != 0 are in no pair
 };
 
-// A run of items of one system: a workgroup of launch_kick_close, of CLOSE_WAVES waves.  Each item
-// takes four waves, two or one, the most with which the blocks fit one per CU: 40000 bodies (625
-// items of 20 tasks) take 13 us with four and 18 with one, 64 systems of 4096 (4096 items of one
-// task) 21 with one and 39 with four.
+// A workgroup of launch_kick_close and of the launches around a drift alone, of CLOSE_WAVES waves: a
+// run of items of one system, or several systems of up to CLOSE_SMALL items, each with the same number
+// of waves, one an item.  (With a workgroup for every system 100000 systems of ten bodies took 2435 us a
+// kick's close, now 120.)
 constexpr int CLOSE_WAVES = 16;
+constexpr int CLOSE_SMALL = 8;
+// Each item of a run takes four waves, two or one, the most with which the blocks fit one per CU: 40000
+// bodies (625 items of 20 tasks) take 13 us with four and 18 with one, 64 systems of 4096 (4096 items of
+// one task) 21 with one and 39 with four.
 inline int close_parts(int n_items, int n_cu)
 {
     int p = 4;
@@ -103,18 +107,23 @@ inline int close_parts(int n_items, int n_cu)
     return p;
 }
 struct CloseBlock {
-    int32_t sys, item, n; // items [item, item + n)
-    int32_t f0, f1;       // the system's items
-    double mstar;
+    int32_t sys, waves; // a system's waves: CLOSE_WAVES (a run of items), else systems [sys, sys + n)
+    int32_t item, n;    // a run: items [item, item + n)
+    int32_t f0, f1;     // a run: the system's items
+    int32_t row;        // where its sums go in StepMomentum::kick: a run has one, else each system
+    double mstar;       // a run: the system's
 };
 
 // Momentum sums that the launches of a step hand on to each other instead of passes of their own.
 struct StepMomentum {
     const CloseBlock *blocks = nullptr;  // [n_blocks], systems in order
-    const int32_t *block_first = nullptr; // [n_sys + 1]
+    const int32_t *row_first = nullptr;  // [n_sys + 1] a system's rows of kick
+    const int32_t *item_first = nullptr; // [n_sys + 1] a system's items
+    const double *mstar = nullptr;       // [n_sys]
     int32_t n_blocks = 0;
-    int32_t parts = 1;                   // waves per item
-    double *kick = nullptr;    // [n_blocks][3] sum m v after the kick
+    bool small = false;                  // there are blocks of several systems
+    int32_t parts = 1;                   // a run's waves per item
+    double *kick = nullptr;    // [rows][3] sum m v after the kick
     double *kepler = nullptr;  // [n_items][3] sum m v after the drift, bodies outside groups
     double *group = nullptr;   // [CE_MAX_GROUPS][3] the same of the groups, which are in system order
     int32_t *group_sys = nullptr;

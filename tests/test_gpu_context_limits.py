@@ -194,3 +194,43 @@ def test_memory_of_a_layout(n_sys, n):
     assert per_body <= 400
     e.close()
     c.close()
+
+
+# systems of every number of items (blocks of 64 bodies) that shares a workgroup with others, of none
+# and of more; more of one item in a row than a workgroup has waves
+SIZES = [5, 64, 65, 130, 1, 0, 512, 513, 300, 0] + [40] * 19 + [200, 3, 200, 64, 700, 7]
+
+
+@pytest.mark.parametrize("call", ["step", "drift"])
+def test_ensemble_of_small_systems(call):
+    """Systems of their own central mass and momentum, with encounters, against the oracle."""
+    ds = []
+    for k, n in enumerate(SIZES):
+        if n == 0:
+            ds.append(discs.Disc(**{q: np.zeros(0) for q in KEYS + ("m",)}))
+            continue
+        d = discs.make_disc(n, 0.1 * n, seed=700 + k)
+        d.mstar = 1.0 + 0.01 * k
+        d.vx += 0.001 * k
+        if n > 1:   # a close pair at least
+            for q in KEYS:
+                getattr(d, q)[n - 1] = getattr(d, q)[0] + (4e-3 if q in "xyz" else 0.0)
+        ds.append(d)
+    rc = [oracle.rcrit(d.state(), d.mstar, 3.0, 0.0, DT) if d.n else np.zeros(0) for d in ds]
+    s = System(ds, rcrit=np.concatenate(rc))
+    if call == "step":
+        genga.genga_step(s.ctx.handle, s.b, DT, 3, FP64)
+    else:
+        s.encounter_list(standalone=True)
+        genga.genga_drift(s.ctx.handle, s.b, DT)
+    assert genga.genga_poll_status(s.ctx.handle) == genga.GENGA_OK, genga.genga_last_error()
+    got, worst = s.numpy_state(), 0.0
+    for k, d in enumerate(ds):
+        if d.n == 0:
+            continue
+        ref = oracle.step(d.state(), rc[k], d.mstar, DT, 3)[0] if call == "step" else \
+            oracle.drift(d.state(), rc[k], d.mstar, DT, oracle.encounters(d.state(), rc[k]))
+        worst = max([worst] + [np.max(np.abs(got[q][s.system_slice(k)] - ref[q])) for q in KEYS])
+    print(f"[ensemble {call}] {len(ds)} systems, error {worst:.1e}", flush=True)
+    assert worst <= 1e-10
+    s.close()

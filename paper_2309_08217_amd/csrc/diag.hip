@@ -8,7 +8,8 @@
 // waves; the runs' lengths come from the whole layout's work, as the kick's do, so that a few
 // massive bodies among many test bodies do not keep four workgroups busy alone (20040 bodies in
 // TP2 mode: 72 us when every block of targets had four parts).  The tasks' partial sums are
-// reduced in a fixed order, so the result is deterministic.  Velocities may be given half a kick ahead: v_sync = v - vshift * a.
+// reduced in a fixed order, so the result is deterministic.  Velocities may be given half a kick
+// ahead: v_sync = v - vshift * a.
 #include "genga_internal.h"
 #include "pair_math.h"
 
@@ -21,10 +22,17 @@ constexpr int NPART = 9;   // pairpot, kin, sunpot, px, py, pz, lx, ly, lz
 
 using CJ64 = const __attribute__((address_space(4))) double;
 
-__device__ __forceinline__ double wave_sum(double v)
+// Each of v summed over the wave, in every lane; the exchanges of one round run side by side.
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&v)[N])
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
+    for (int o = 32; o > 0; o >>= 1) {
+        double u[N];
+#pragma unroll
+        for (int k = 0; k < N; ++k) u[k] = __shfl_xor(v[k], o, 64);
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] += u[k];
+    }
 }
 
 __global__ __launch_bounds__(64 * EW) void energy_kernel(const EnergyTask *tasks, const double *mstar, const double *x,
@@ -50,13 +58,26 @@ __global__ __launch_bounds__(64 * EW) void energy_kernel(const EnergyTask *tasks
     double s = 0.0;
     const int jmask = min(je, w.i0 + 64);
     int j = jb;
+    // sources inside the item's own range: only j > i counts (the self pair has q = 0, so it is
+    // replaced by a harmless q = 1 with zero weight); four at a time, as in a small system these are
+    // most of a wave's sources (257 and 1000 bodies one at a time 13.8 and 16.0 us, in fours 9.5 and 11.2,
+    // and in runs of ENERGY_RUN_MIN 5.1 and 5.3)
+    const auto masked = [&](int jj, double &q, double &mj) {
+        const double dx = X[jj] - xi, dy = Y[jj] - yi, dz = Z[jj] - zi;
+        const bool take = jj > i;
+        q = take ? fma(dx, dx, fma(dy, dy, dz * dz)) : 1.0;
+        mj = take ? M[jj] : 0.0;
+    };
+    for (; j + 4 <= jmask; j += 4) {
+        double q[4], mj[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) masked(j + v, q[v], mj[v]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) s = fma(mj[v], inv_sqrt64(q[v]), s);
+    }
     for (; j < jmask; ++j) {
-        // sources inside the item's own range: only j > i counts (the self pair has q = 0,
-        // so it is replaced by a harmless q = 1 with zero weight)
-        const double dx = X[j] - xi, dy = Y[j] - yi, dz = Z[j] - zi;
-        const bool take = j > i;
-        const double q = take ? fma(dx, dx, fma(dy, dy, dz * dz)) : 1.0;
-        const double mj = take ? M[j] : 0.0;
+        double q, mj;
+        masked(j, q, mj);
         s = fma(mj, inv_sqrt64(q), s);
     }
     for (; j + 4 <= je; j += 4) {
@@ -81,36 +102,40 @@ __global__ __launch_bounds__(64 * EW) void energy_kernel(const EnergyTask *tasks
 #pragma unroll
     for (int k = 0; k < EW; ++k) tot += red[k][lane];
     const double mi = valid ? m[i] : 0.0;
-    tot = wave_sum(mi * tot);
-    if (lane == 0) partial[blockIdx.x] = tot;
-    if (!w.first) return;
-    double v[NPART - 1] = {};
+    if (!w.first) {
+        double v[1] = {mi * tot};
+        wave_sums(v);
+        if (lane == 0) partial[blockIdx.x] = v[0];
+        return;
+    }
+    double v[NPART] = {};
+    v[0] = mi * tot;
     if (valid) {
         const double ux = vx[i] - vshift * ax[i];
         const double uy = vy[i] - vshift * ay[i];
         const double uz = vz[i] - vshift * az[i];
-        v[0] = 0.5 * mi * (ux * ux + uy * uy + uz * uz);
-        v[1] = -mstar[w.sys] * mi / sqrt(xi * xi + yi * yi + zi * zi);
-        v[2] = mi * ux;
-        v[3] = mi * uy;
-        v[4] = mi * uz;
-        v[5] = mi * (yi * uz - zi * uy);
-        v[6] = mi * (zi * ux - xi * uz);
-        v[7] = mi * (xi * uy - yi * ux);
+        v[1] = 0.5 * mi * (ux * ux + uy * uy + uz * uz);
+        v[2] = -mstar[w.sys] * mi / sqrt(xi * xi + yi * yi + zi * zi);
+        v[3] = mi * ux;
+        v[4] = mi * uy;
+        v[5] = mi * uz;
+        v[6] = mi * (yi * uz - zi * uy);
+        v[7] = mi * (zi * ux - xi * uz);
+        v[8] = mi * (xi * uy - yi * ux);
     }
-#pragma unroll
-    for (int k = 0; k < NPART - 1; ++k) {
-        const double t = wave_sum(v[k]);
-        if (lane == 0) partial[(size_t)(k + 1) * gridDim.x + blockIdx.x] = t;
-    }
+    wave_sums(v);
+    if (lane == 0)
+        for (int k = 0; k < NPART; ++k) partial[(size_t)k * gridDim.x + blockIdx.x] = v[k];
 }
 
 // One workgroup per system: each thread sums a strided subset of the system's task partials
 // in order (the pair sum of every task, the other parts of the tasks that have them, which are
 // the system's first), then the lanes of a wave and the waves in fixed trees.  Bound by how fast
 // one CU reads what others wrote: 20040 bodies (12 thousand tasks) took 17 us with nine sums of
-// every task.
-constexpr int EF_THREADS = 1024, EF_AHEAD = 4;
+// every task.  Systems of up to ENERGY_SMALL tasks take a wave each (SMALL, blocks of EnergyRun): with a
+// workgroup each 100000 systems of ten bodies took 1.86 ms, now 0.11.
+constexpr int EF_THREADS = 64 * ENERGY_WAVES, EF_AHEAD = 4;
+static_assert(ENERGY_SMALL <= 64, "a task per lane");
 
 __device__ __forceinline__ double strided_sum(const double *p, int t0, int t1)
 {
@@ -125,14 +150,40 @@ __device__ __forceinline__ double strided_sum(const double *p, int t0, int t1)
     return t;
 }
 
-__global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t *task_first,
-                                                                   const double *mstar,
-                                                                   const double *partial, int n_tasks, double *out)
+// t: pairpot, kin, sunpot, p, l
+__device__ __forceinline__ void store_energy(double *out, int s, double mstar, const double (&t)[NPART])
 {
-    __shared__ double red[NPART][EF_THREADS / 64];
-    const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t0 = task_first[2 * s], tk = task_first[2 * s + 1], t1 = task_first[2 * s + 2];
+    const double p2 = t[3] * t[3] + t[4] * t[4] + t[5] * t[5];
+    out[4 * (size_t)s + 0] = t[1] + p2 / (2.0 * mstar) + t[2] - t[0];
+    out[4 * (size_t)s + 1] = t[6];
+    out[4 * (size_t)s + 2] = t[7];
+    out[4 * (size_t)s + 3] = t[8];
+}
+
+template <bool SMALL>
+__global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const EnergyRun *runs, const int32_t *task_first,
+                                                                   const double *mstar, const double *partial,
+                                                                   int n_tasks, double *out)
+{
+    __shared__ double red[NPART][ENERGY_WAVES];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int s = blockIdx.x;
     double t[NPART];
+    if constexpr (SMALL) {
+        const EnergyRun r = runs[blockIdx.x];
+        s = r.sys;
+        if (r.n > 0) { // n small systems
+            if (wave >= r.n) return;
+            s += wave;
+            const int t0 = task_first[2 * s], tk = task_first[2 * s + 1], t1 = task_first[2 * s + 2], it = t0 + lane;
+            t[0] = it < t1 ? partial[it] : 0.0;
+            for (int k = 1; k < NPART; ++k) t[k] = it < tk ? partial[(size_t)k * n_tasks + it] : 0.0;
+            wave_sums(t);
+            if (lane == 0) store_energy(out, s, mstar[s], t);
+            return;
+        }
+    }
+    const int t0 = task_first[2 * s], tk = task_first[2 * s + 1], t1 = task_first[2 * s + 2];
     // the usual number of first tasks in one load each, beside the pair sums
     t[0] = strided_sum(partial, t0, t1);
     for (int k = 1; k < NPART; ++k) {
@@ -142,23 +193,19 @@ __global__ __launch_bounds__(EF_THREADS) void energy_finish_kernel(const int32_t
     }
     for (int it = t0 + (int)threadIdx.x + EF_THREADS; it < tk; it += EF_THREADS)
         for (int k = 1; k < NPART; ++k) t[k] += partial[(size_t)k * n_tasks + it];
-    for (int k = 0; k < NPART; ++k) {
-        t[k] = wave_sum(t[k]);
-        if (lane == 0) red[k][wave] = t[k];
-    }
+    wave_sums(t);
+    if (lane == 0)
+        for (int k = 0; k < NPART; ++k) red[k][wave] = t[k];
     __syncthreads();
     if (threadIdx.x < NPART) {
         double v = 0.0;
-        for (int w = 0; w < EF_THREADS / 64; ++w) v += red[threadIdx.x][w];
+        for (int w = 0; w < ENERGY_WAVES; ++w) v += red[threadIdx.x][w];
         red[threadIdx.x][0] = v;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double p2 = red[3][0] * red[3][0] + red[4][0] * red[4][0] + red[5][0] * red[5][0];
-        out[4 * s + 0] = red[1][0] + p2 / (2.0 * mstar[s]) + red[2][0] - red[0][0];
-        out[4 * s + 1] = red[6][0];
-        out[4 * s + 2] = red[7][0];
-        out[4 * s + 3] = red[8][0];
+        for (int k = 0; k < NPART; ++k) t[k] = red[k][0];
+        store_energy(out, s, mstar[s], t);
     }
 }
 
@@ -341,15 +388,19 @@ __global__ __launch_bounds__(SORT_THREADS) void sort_pairs_kernel(const int32_t 
 
 } // namespace
 
-hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tasks, const int32_t *task_first,
-                         const double *x, const double *y, const double *z, const double *vx, const double *vy,
-                         const double *vz, const double *m, const double *ax, const double *ay, const double *az,
-                         double vshift, double *partial, double *out, hipStream_t stream)
+hipError_t launch_energy(const Layout &L, const EnergyPlan &e, const double *x, const double *y, const double *z,
+                         const double *vx, const double *vy, const double *vz, const double *m, const double *ax,
+                         const double *ay, const double *az, double vshift, double *out, hipStream_t stream)
 {
-    if (n_tasks > 0)
-        energy_kernel<<<n_tasks, 64 * EW, 0, stream>>>(tasks, L.mstar, x, y, z, vx, vy, vz, m, ax, ay, az, vshift,
-                                                       partial);
-    energy_finish_kernel<<<L.n_sys, EF_THREADS, 0, stream>>>(task_first, L.mstar, partial, n_tasks, out);
+    if (e.n_tasks > 0)
+        energy_kernel<<<e.n_tasks, 64 * EW, 0, stream>>>(e.tasks, L.mstar, x, y, z, vx, vy, vz, m, ax, ay, az, vshift,
+                                                         e.partial);
+    if (e.n_runs > 0)
+        energy_finish_kernel<true><<<e.n_runs, EF_THREADS, 0, stream>>>(e.runs, e.task_first, L.mstar, e.partial,
+                                                                        e.n_tasks, out);
+    else
+        energy_finish_kernel<false><<<L.n_sys, EF_THREADS, 0, stream>>>(nullptr, e.task_first, L.mstar, e.partial,
+                                                                        e.n_tasks, out);
     return hipGetLastError();
 }
 

@@ -67,9 +67,7 @@ struct genga_ctx {
     char *plan = nullptr;
     WorkItem *items = nullptr;  // kick items, in system order
     int32_t n_items = 0;
-    EnergyTask *etasks = nullptr; // energy tasks, in system order
-    int32_t *etask_first = nullptr; // [n_sys + 1]
-    int32_t n_etasks = 0;
+    EnergyPlan energy;
     KickTask *tasks = nullptr;  // the layout's own kick plan
     int32_t *task_first = nullptr; // [n_items + 1] an item's tasks
     uint32_t *item_row = nullptr;  // [n_items] an item's first row of shares
@@ -93,7 +91,6 @@ struct genga_ctx {
     int32_t *lab = nullptr, *mark = nullptr, *members = nullptr, *group_start = nullptr;
     int32_t *n_groups = nullptr, *member_slot = nullptr;
     int32_t *wg_list = nullptr; // groups of 9..64 members of a drift (their count first)
-    double *epartial = nullptr;
     // grid-wide Bulirsch-Stoer for groups of more than CE_MAX_GROUP members (opt-in)
     int32_t large_groups = 0;
     BigBs big;
@@ -884,8 +881,8 @@ int enqueue_energy(genga_ctx *ctx, const genga_bodies *b, double vshift, double 
 {
     const Layout &L = ctx->L;
     const size_t n = (size_t)L.n_total;
-    HIP_TRY(launch_energy(L, ctx->etasks, ctx->n_etasks, ctx->etask_first, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m,
-                          ctx->acc, ctx->acc + n, ctx->acc + 2 * n, vshift, ctx->epartial, out, s));
+    HIP_TRY(launch_energy(L, ctx->energy, b->x, b->y, b->z, b->vx, b->vy, b->vz, b->m, ctx->acc, ctx->acc + n,
+                          ctx->acc + 2 * n, vshift, out, s));
     return GENGA_OK;
 }
 
@@ -1056,7 +1053,7 @@ int upload_plan(genga_ctx *ctx)
     const auto energy_end = [&](const WorkItem &w) { return std::max(ctx->sys_off_h[w.sys] + w.nsrc, w.i0); };
     visits = 0;
     for (const WorkItem &w : it) visits += energy_end(w) - w.i0;
-    const int elen = run_len(visits, ctx->n_cu);
+    const int elen = run_len(visits, ctx->n_cu, ENERGY_RUN_MIN);
     for (int s = 0; s < n_sys; ++s) {
         for (const bool head : {true, false}) { // the items' first tasks, then the others
             efirst[2 * s + !head] = (int32_t)et.size();
@@ -1069,6 +1066,15 @@ int upload_plan(genga_ctx *ctx)
         }
     }
     efirst[2 * n_sys] = (int32_t)et.size();
+    std::vector<EnergyRun> er;
+    bool any_small = false;
+    for (int s = 0; s < n_sys; ++s) {
+        const bool is = efirst[2 * s + 2] - efirst[2 * s] <= ENERGY_SMALL;
+        if (is && !er.empty() && er.back().n > 0 && er.back().n < ENERGY_WAVES) ++er.back().n;
+        else er.push_back(EnergyRun{s, is});
+        any_small |= is;
+    }
+    if (!any_small) er.clear();
     std::vector<int32_t> seg(2 * (size_t)n_sys + 1);
     for (int s = 0; s < n_sys; ++s) {
         seg[2 * s] = ctx->sys_off_h[s];
@@ -1092,7 +1098,7 @@ int upload_plan(genga_ctx *ctx)
     };
     const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_rfirst = put(rfirst),
                  o_first = put(first);
-    const size_t o_et = put(et), o_efirst = put(efirst), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
+    const size_t o_et = put(et), o_efirst = put(efirst), o_er = put(er), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
     const size_t o_kick = place(3 * (size_t)rows_kick * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
     const size_t o_group = place(3 * (size_t)CE_MAX_GROUPS * sizeof(double));
     const size_t o_gsys = place((size_t)CE_MAX_GROUPS * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
@@ -1110,13 +1116,16 @@ int upload_plan(genga_ctx *ctx)
     ctx->plan = plan;
     ctx->n_items = (int32_t)it.size();
     ctx->n_tasks = (int32_t)tasks.size();
-    ctx->n_etasks = (int32_t)et.size();
     ctx->items = reinterpret_cast<WorkItem *>(plan + o_items);
     ctx->tasks = reinterpret_cast<KickTask *>(plan + o_tasks);
     ctx->task_first = reinterpret_cast<int32_t *>(plan + o_tfirst);
     ctx->item_row = reinterpret_cast<uint32_t *>(plan + o_rows);
-    ctx->etasks = reinterpret_cast<EnergyTask *>(plan + o_et);
-    ctx->etask_first = reinterpret_cast<int32_t *>(plan + o_efirst);
+    ctx->energy.tasks = reinterpret_cast<EnergyTask *>(plan + o_et);
+    ctx->energy.task_first = reinterpret_cast<int32_t *>(plan + o_efirst);
+    ctx->energy.n_tasks = (int32_t)et.size();
+    ctx->energy.runs = reinterpret_cast<EnergyRun *>(plan + o_er);
+    ctx->energy.n_runs = (int32_t)er.size();
+    ctx->energy.partial = reinterpret_cast<double *>(plan + o_epart);
     ctx->L.n_massive = reinterpret_cast<int32_t *>(plan + o_nm);
     ctx->sort_seg = reinterpret_cast<int32_t *>(plan + o_seg);
     ctx->pm.blocks = reinterpret_cast<CloseBlock *>(plan + o_cb);
@@ -1131,7 +1140,6 @@ int upload_plan(genga_ctx *ctx)
     ctx->pm.group = reinterpret_cast<double *>(plan + o_group);
     ctx->pm.group_sys = reinterpret_cast<int32_t *>(plan + o_gsys);
     ctx->pm.group_n = reinterpret_cast<int32_t *>(plan + o_gn);
-    ctx->epartial = reinterpret_cast<double *>(plan + o_epart);
     ctx->kpart = reinterpret_cast<double *>(plan + o_kpart);
     HIP_TRY(hipDeviceSynchronize());
     return GENGA_OK;

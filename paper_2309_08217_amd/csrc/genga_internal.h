@@ -163,7 +163,7 @@ inline int default_kick_split(int n_items, int n_cu)
 // 19.4 against 15.1 us, one of 128 gives 40 massive among 20000 test bodies 52 against 35 us.
 constexpr int KICK_RUN_MIN = 256;
 constexpr int KICK_TASKS_PER_CU = 64;
-inline int run_len(int64_t source_visits, int n_cu, int len = KICK_RUN_MIN)
+inline int run_len(int64_t source_visits, int n_cu, int len)
 {
     n_cu = n_cu < 256 ? n_cu : 256;
     while (len < (1 << 30) && source_visits / len > (int64_t)KICK_TASKS_PER_CU * n_cu) len *= 2; // n <= 2^30
@@ -174,8 +174,7 @@ inline int run_len(int64_t source_visits, int n_cu, int len = KICK_RUN_MIN)
 // 42.5 / 56.4 us with 256, 38.2 / 53.5 with 512, of 16000 127 / 175 and 119 / 169, of 10 discs of
 // 2000-8000 109 / 149 and 99 / 141; of 6600, 10 tasks per CU, 34.2 / 45.3 and 34.0 / 46.8).  Not
 // where the items have few such runs each, whose lengths then differ too much (64 discs of
-// 500-1500 bodies 46.7 / 63.1 and 49.2 / 66.5 us).  The energy's pairs (half of the kick's) keep 256:
-// 8000 bodies 27 and 30 us, 64 discs of 1000 38 and 42.
+// 500-1500 bodies 46.7 / 63.1 and 49.2 / 66.5 us).
 constexpr int KICK_SHORT_PER_CU = 14;
 inline int kick_run_len(int64_t source_visits, int64_t n_items, int n_cu)
 {
@@ -184,6 +183,10 @@ inline int kick_run_len(int64_t source_visits, int64_t n_items, int n_cu)
                       source_visits >= 6 * KICK_RUN_MIN * n_items;
     return run_len(source_visits, n_cu, many ? 2 * KICK_RUN_MIN : KICK_RUN_MIN);
 }
+// The energy's, whose prologues are shorter (no r_crit, no candidates) and whose sources next to the
+// targets are masked: genga_energy with 64 / 128 / 256 takes 12.2 / 13.1 / 16.9 us for 2048 bodies, 14.1 /
+// 14.5 / 17.6 for 4000, 12.1 / 13.9 / 16.8 for 16 systems of 300, 30.5 / 29.8 / 31.2 for 9000.
+constexpr int ENERGY_RUN_MIN = 64;
 // Tasks of an item of nsrc sources at that run length, and the length of each task's run when
 // nsrc sources are cut into `parts` (a multiple of four, so that whole quads stay whole).
 inline int kick_runs(int nsrc, int len) { return nsrc < len + len / 2 ? 1 : (nsrc + len / 2) / len; }
@@ -205,6 +208,20 @@ int noalloc_prepare(int device, unsigned char **ptr_out, int *n_cu_out);
 // [task_first[2 s], task_first[2 s + 2]), first tasks up to task_first[2 s + 1].
 struct EnergyTask {
     int32_t sys, i0, ni, j0, j1, first;
+};
+// A workgroup of the energy's finishing launch: the systems [sys, sys + n) of up to ENERGY_SMALL tasks,
+// a wave each, or (n = 0) the system sys.
+constexpr int ENERGY_WAVES = 16, ENERGY_SMALL = 64;
+struct EnergyRun {
+    int32_t sys, n;
+};
+struct EnergyPlan {
+    const EnergyTask *tasks = nullptr;   // [n_tasks], systems in order
+    const int32_t *task_first = nullptr; // [2 n_sys + 1]
+    int32_t n_tasks = 0;
+    const EnergyRun *runs = nullptr;     // [n_runs]
+    int32_t n_runs = 0;                  // 0: no small system, a workgroup for each
+    double *partial = nullptr;           // [9][n_tasks]
 };
 
 // Kernel launchers (each enqueues on `stream`; return hipError_t of the launch).
@@ -495,10 +512,9 @@ hipError_t launch_collide_resolve(const CollideArgs &c, int n_total, double *x, 
 hipError_t launch_gather(const int32_t *idx, int n, const double *src, double *dst, hipStream_t stream);
 hipError_t launch_gather(const int32_t *idx, int n, const int32_t *src, int32_t *dst, hipStream_t stream);
 
-hipError_t launch_energy(const Layout &L, const EnergyTask *tasks, int32_t n_tasks, const int32_t *task_first,
-                         const double *x, const double *y, const double *z, const double *vx, const double *vy,
-                         const double *vz, const double *m, const double *ax, const double *ay, const double *az,
-                         double vshift, double *partial, double *out, hipStream_t stream);
+hipError_t launch_energy(const Layout &L, const EnergyPlan &e, const double *x, const double *y, const double *z,
+                         const double *vx, const double *vy, const double *vz, const double *m, const double *ax,
+                         const double *ay, const double *az, double vshift, double *out, hipStream_t stream);
 // The list src in lexicographic order in dst (keys: room for src_cap).
 hipError_t launch_sort_pairs(const int32_t *src, const int32_t *src_count, int32_t src_cap, int n_total,
                              int32_t *dst, int32_t dst_cap, int32_t *dst_count, uint64_t *keys,

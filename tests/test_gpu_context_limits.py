@@ -234,3 +234,20 @@ def test_ensemble_of_small_systems(call):
     print(f"[ensemble {call}] {len(ds)} systems, error {worst:.1e}", flush=True)
     assert worst <= 1e-10
     s.close()
+
+
+@pytest.mark.parametrize("sizes", [SIZES + [95, 96, 97, 650, 720, 2000], [800, 1100], [3]])
+def test_energy_of_small_and_large_systems(sizes):
+    """Runs of one length and the next, systems of less and of more than 64 tasks side by side, only
+    larger ones, one alone: E and L against the oracle, to the rounding of their sums."""
+    ds = [discs.make_disc(n, 2.5, seed=800 + k) if n else discs.Disc(**{q: np.zeros(0) for q in KEYS + ("m",)})
+          for k, n in enumerate(sizes)]
+    for k, d in enumerate(ds):
+        d.mstar = 1.0 + 0.01 * k
+    s = System(ds, rcrit=np.zeros(sum(sizes)))
+    got = s.energy()
+    for k, d in enumerate(ds):
+        ref = oracle.energy(d.state(), d.mstar) if d.n else np.zeros(4)
+        assert abs(got[k, 0] - ref[0]) <= 1e-13 * abs(ref[0])
+        assert np.max(np.abs(got[k, 1:] - ref[1:])) <= 1e-13 * np.linalg.norm(ref[1:])
+    s.close()

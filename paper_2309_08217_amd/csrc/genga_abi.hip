@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -994,6 +995,7 @@ int upload_plan(genga_ctx *ctx)
     std::vector<WorkItem> it;
     std::vector<int32_t> first(n_sys + 1, 0);
     int64_t visits = 0;
+    it.reserve((size_t)ctx->sys_off_h[n_sys] / 64 + 2 * (size_t)n_sys);
     for (int s = 0; s < n_sys; ++s) {
         first[s] = (int32_t)it.size();
         const int b = ctx->sys_off_h[s], e = ctx->sys_off_h[s + 1];
@@ -1010,6 +1012,7 @@ int upload_plan(genga_ctx *ctx)
         cfst[s + 1] = cfst[s] + (ctx->sys_off_h[s + 1] - ctx->sys_off_h[s] + CHUNK - 1) / CHUNK;
     std::vector<int32_t> tfirst(it.size() + 1, 0);
     std::vector<uint32_t> rows(it.size());
+    tasks.reserve(it.size() + it.size() / 2);
     uint32_t row = 0; // at most 64 bodies of some 64 tasks per CU and of one and a half tasks per item
     for (size_t k = 0; k < it.size(); ++k) {
         rows[k] = row;
@@ -1049,6 +1052,7 @@ int upload_plan(genga_ctx *ctx)
     // energy tasks: the sources after an item's first body (a test item has none: test pairs have
     // no energy), in runs as the kick's
     std::vector<EnergyTask> et;
+    et.reserve(it.size() + it.size() / 2);
     std::vector<int32_t> efirst(2 * n_sys + 1, 0);
     const auto energy_end = [&](const WorkItem &w) { return std::max(ctx->sys_off_h[w.sys] + w.nsrc, w.i0); };
     visits = 0;
@@ -1083,8 +1087,12 @@ int upload_plan(genga_ctx *ctx)
     seg[2 * n_sys] = ctx->sys_off_h[n_sys];
     // One allocation and one copy: as 13 allocations and 8 copies a context of 257 / 20040 bodies took
     // 318 / 465 us to make, so 183 / 320.  The plan that was there stays until the new one is complete.
-    size_t size = 0;
-    std::vector<char> host;
+    size_t size = 0, used = 0;
+    struct Section {
+        const void *data;
+        size_t at, bytes;
+    };
+    std::vector<Section> sections;
     const auto place = [&](size_t bytes) { // 256-byte aligned sections
         const size_t at = size;
         size += (bytes + 255) / 256 * 256;
@@ -1092,8 +1100,8 @@ int upload_plan(genga_ctx *ctx)
     };
     const auto put = [&](const auto &v) {
         const size_t bytes = v.size() * sizeof(v[0]), at = place(bytes);
-        host.resize(size);
-        if (bytes) std::copy_n(reinterpret_cast<const char *>(v.data()), bytes, host.data() + at);
+        if (bytes) sections.push_back(Section{v.data(), at, bytes});
+        used = at + bytes;
         return at;
     };
     const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_rfirst = put(rfirst),
@@ -1105,9 +1113,11 @@ int upload_plan(genga_ctx *ctx)
     const size_t o_epart = place(9 * et.size() * sizeof(double));
     const size_t nt = (size_t)ctx->sys_off_h[n_sys];
     const size_t o_kpart = place(3 * std::max((size_t)row, KICK_MAX_SPLIT * nt) * sizeof(double));
+    const std::unique_ptr<char[]> host(new char[used]); // (the gaps between the sections are never read)
+    for (const Section &c : sections) memcpy(host.get() + c.at, c.data, c.bytes);
     char *plan = nullptr;
     HIP_TRY(dalloc(plan, size));
-    const hipError_t copied = hipMemcpy(plan, host.data(), host.size(), hipMemcpyHostToDevice);
+    const hipError_t copied = hipMemcpy(plan, host.get(), used, hipMemcpyHostToDevice);
     if (copied != hipSuccess) {
         dfree(plan);
         return fail(GENGA_ERR_HIP, "copy of the launch plan failed: %s", hipGetErrorString(copied));

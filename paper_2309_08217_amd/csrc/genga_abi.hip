@@ -1851,44 +1851,45 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
     hipEvent_t e0, e1;
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
-    float best = 1e30f;
-    int best_w = ctx->waves[fp32], best_s = 0;
-    // The layout's own plan (sp 0) last: an idle card takes some 30 ms of launches to reach its clock,
-    // and the first candidates are timed on the way (kick of 40000 bodies 654 us then, 560 after).
-    // Timed first, the plan lost that size to 8 waves in 4 shares, 582 us at the same clock.
-    for (int sp = KICK_MAX_SPLIT; sp >= 0 && !rc; --sp) {
-        for (int w : {16, 8, 4}) {
-            ctx->waves[fp32] = w;
-            ctx->split[fp32] = sp > 0 ? sp : default_split(ctx);
-            ctx->own_plan[fp32] = sp == 0;
-            // accelerations only (velocities untouched); one warm-up then three timed launches
-            rc = enqueue_kick(ctx, b, 0.0, 0, prec, GENGA_ACC_FP64, ctx->acc, ctx->acc + n, ctx->acc + 2 * n, s);
-            if (rc) break;
+    // Candidate c: source split c / 3 (0: the layout's own plan), 4, 8 or 16 waves.  Passes over all of
+    // them: an idle card takes some 30 ms of launches to reach its clock (kick of 40000 bodies 654 us on
+    // the way, 560 after), so the passes of that time are not counted, and of each candidate the shortest
+    // of TUNE_PASSES later ones is.  (In one pass whoever came first lost by the clock alone.)
+    constexpr int TUNE_PASSES = 2, CANDIDATES = 3 * (KICK_MAX_SPLIT + 1);
+    float best[CANDIDATES];
+    std::fill_n(best, CANDIDATES, 1e30f);
+    const auto shape = [&](int c) {
+        ctx->waves[fp32] = 4 << c % 3;
+        ctx->own_plan[fp32] = c < 3;
+        ctx->split[fp32] = c < 3 ? default_split(ctx) : c / 3;
+    };
+    const auto kick = [&] { // accelerations only (velocities untouched)
+        return enqueue_kick(ctx, b, 0.0, 0, prec, GENGA_ACC_FP64, ctx->acc, ctx->acc + n, ctx->acc + 2 * n, s);
+    };
+    const auto t0 = std::chrono::steady_clock::now();
+    bool warm = false;
+    for (int pass = 0; pass < TUNE_PASSES && !rc;) {
+        for (int c = 0; c < CANDIDATES && !rc; ++c) {
+            shape(c);
+            if ((rc = kick())) break; // one launch before the three that are timed
             (void)hipEventRecord(e0, s);
-            for (int r = 0; r < 3 && !rc; ++r)
-                rc = enqueue_kick(ctx, b, 0.0, 0, prec, GENGA_ACC_FP64, ctx->acc, ctx->acc + n, ctx->acc + 2 * n, s);
+            for (int r = 0; r < 3 && !rc; ++r) rc = kick();
             (void)hipEventRecord(e1, s);
             (void)hipEventSynchronize(e1);
             float ms = 0.f;
             (void)hipEventElapsedTime(&ms, e0, e1);
-            if (ms < best) {
-                best = ms;
-                best_w = w;
-                best_s = sp;
-            }
+            if (warm && !rc) best[c] = std::min(best[c], ms);
         }
+        if (warm) ++pass;
+        warm = warm || std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(30);
     }
-    const bool own = best_s == 0;
-    if (own) best_s = default_split(ctx);
-    ctx->waves[fp32] = best_w;
-    ctx->split[fp32] = best_s;
-    ctx->own_plan[fp32] = own;
+    shape((int)(std::min_element(best, best + CANDIDATES) - best));
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (rc || !cache_path) return rc;
     FILE *f = fopen(cache_path, "a");
     if (!f) return fail(GENGA_ERR_ARG, "cannot write the autotune cache %s", cache_path);
-    const bool ok = fprintf(f, "%s%s %d %d\n", key, own ? " own" : "", best_w, best_s) > 0;
+    const bool ok = fprintf(f, "%s%s %d %d\n", key, ctx->own_plan[fp32] ? " own" : "", ctx->waves[fp32], ctx->split[fp32]) > 0;
     if (fclose(f) != 0 || !ok) return fail(GENGA_ERR_ARG, "cannot write the autotune cache %s", cache_path);
     return GENGA_OK;
 }

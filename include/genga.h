@@ -294,9 +294,10 @@ int genga_graph_launch(genga_ctx *ctx, int repeats, void *stream);
  * among them) on the current layout
  * and keep the fastest for `prec` (synchronises `stream`; computes accelerations only, the
  * velocities are not changed).  cache_path (host string, may be NULL): a text file of earlier
- * results, one line per (device, precision, layout); a line matching the device's
- * architecture and compute-unit count, prec and the layout's system sizes and TP2 counts is
- * applied without timing, otherwise the shapes are timed and a line is appended (the file is
+ * results, one line per (kick kernels, device, precision, layout); a line matching the library's
+ * kick kernels, the device's architecture and compute-unit count, prec and the layout's system
+ * sizes and TP2 counts is applied without timing, otherwise the shapes are timed (35 ms and more:
+ * the card has to reach its clock) and a line is appended (the file is
  * created if missing; a file that cannot be read or written returns GENGA_ERR_ARG, with the
  * timed shape still applied). */
 int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_path, void *stream);

@@ -1806,7 +1806,8 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
     const int fp32 = prec == GENGA_KICK_FP32;
     const size_t n = (size_t)ctx->L.n_total;
     // the cache key: device architecture and compute units, precision, and the layout (system
-    // sizes and TP2 counts, hashed with 64-bit FNV-1a)
+    // sizes and TP2 counts, hashed with 64-bit FNV-1a), with the version of the kick's kernels and
+    // plans, so that no shape timed on others is applied
     char key[256] = {0};
     if (cache_path) {
         uint64_t h = 1469598103934665603ull;
@@ -1818,7 +1819,7 @@ int genga_autotune(genga_ctx *ctx, genga_bodies *b, int prec, const char *cache_
         };
         for (int32_t v : ctx->sys_off_h) mix(v);
         for (int32_t v : ctx->n_massive_h) mix(v);
-        snprintf(key, sizeof(key), "genga-autotune v1 %s %d %d %d %d %016llx", ctx->arch, ctx->n_cu, prec,
+        snprintf(key, sizeof(key), "genga-autotune v1 kick2 %s %d %d %d %d %016llx", ctx->arch, ctx->n_cu, prec,
                  ctx->L.n_sys, ctx->L.n_total, (unsigned long long)h);
         if (FILE *f = fopen(cache_path, "r")) {
             char line[512];

@@ -251,3 +251,23 @@ def test_energy_of_small_and_large_systems(sizes):
         assert abs(got[k, 0] - ref[0]) <= 1e-13 * abs(ref[0])
         assert np.max(np.abs(got[k, 1:] - ref[1:])) <= 1e-13 * np.linalg.norm(ref[1:])
     s.close()
+
+
+def test_autotune_cache_of_other_kernels(tmp_path):
+    """A line without the version of the kick's kernels, as written before there was one, is not
+    applied: the shapes are timed, and a line of the present version is appended."""
+    d = discs.make_disc(500, 2.5, seed=41)
+    s = System([d])
+    path = tmp_path / "tune.txt"
+    genga.genga_autotune(s.ctx.handle, s.b, FP32, str(path))
+    line = path.read_text()
+    words = line.split()
+    assert words[:3] == ["genga-autotune", "v1", "kick2"]
+    key = [w for w in words[3:-2] if w != "own"]
+    path.write_text(" ".join(words[:2] + key + ["4", "1"]) + "\n")   # 4 waves, 1 share
+    genga.genga_autotune(s.ctx.handle, s.b, FP32, str(path))
+    lines = path.read_text().splitlines()
+    assert len(lines) == 2 and lines[1].split()[:3] == words[:3]
+    genga.genga_autotune(s.ctx.handle, s.b, FP32, str(path))
+    assert path.read_text().splitlines() == lines
+    s.close()

@@ -745,7 +745,11 @@ __device__ __forceinline__ void close_shift(const StepMomentum &pm, const CloseW
         for (int q = 0; q < 3; ++q) P[q] += part[3 * (size_t)k + q];
     };
     if (!SMALL || c.waves == CLOSE_WAVES) { // the whole workgroup
-        for (int k = c.f0 + tid; k < c.f1; k += CE_THREADS) add(pm.kepler, k);
+        if (pm.n_large && c.f1 - c.f0 > LARGE_ROWS * CLOSE_WAVES) { // (runs of CLOSE_WAVES items there)
+            if (tid == 0) add(pm.sys_kepler, c.sys);
+        } else {
+            for (int k = c.f0 + tid; k < c.f1; k += CE_THREADS) add(pm.kepler, k);
+        }
         if (tid == 0) *first = G;
         __syncthreads();
         for (int k = tid; k < G; k += CE_THREADS) {
@@ -814,6 +818,34 @@ __device__ __forceinline__ void wave_momentum(const int32_t *first, const double
     for (int k = first[s] + (int)(threadIdx.x & 63); k < first[s + 1]; k += 64)
         for (int q = 0; q < 3; ++q) P[q] += part[3 * (size_t)k + q];
     for (int q = 0; q < 3; ++q) P[q] = wave_sum(P[q]);
+}
+
+// The sums of part[3 first[s] ..) of the large systems s, a workgroup each.
+__global__ __launch_bounds__(CE_THREADS) void large_sums_kernel(const int32_t *large, const int32_t *first,
+                                                                const double *part, double *sums)
+{
+    __shared__ double red[3][CE_THREADS / 64];
+    const int s = large[blockIdx.x], tid = threadIdx.x, k1 = first[s + 1];
+    double P[3] = {0.0, 0.0, 0.0};
+    for (int k = first[s] + tid; k < k1; k += 4 * CE_THREADS) { // four rows in flight
+        double v[4][3];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int q = 0; q < 3; ++q) v[u][q] = part[3 * (size_t)min(k + u * CE_THREADS, k1 - 1) + q];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            for (int q = 0; q < 3; ++q) P[q] += k + u * CE_THREADS < k1 ? v[u][q] : 0.0;
+    }
+    for (int q = 0; q < 3; ++q) {
+        P[q] = wave_sum(P[q]);
+        if ((tid & 63) == 0) red[q][tid >> 6] = P[q];
+    }
+    __syncthreads();
+    if (tid < 3) {
+        double t = 0.0;
+        for (int w = 0; w < CE_THREADS / 64; ++w) t += red[tid][w];
+        sums[3 * (size_t)s + tid] = t;
+    }
 }
 
 // The end of a kick inside a step (launch_kick_close).  Workgroup 0 builds the groups, the others
@@ -1423,7 +1455,10 @@ __device__ __forceinline__ void sun_shift_of(const StepMomentum &pm, const doubl
     sh[0] = sh[1] = sh[2] = 0.0;
     if (!pm.kick) return;
     double P[3];
-    wave_momentum(pm.row_first, pm.kick, s, P);
+    if (pm.n_large && pm.row_first[s + 1] - pm.row_first[s] > LARGE_ROWS)
+        for (int q = 0; q < 3; ++q) P[q] = pm.sys_kick[3 * (size_t)s + q];
+    else
+        wave_momentum(pm.row_first, pm.kick, s, P);
     const double f = pm.tau / mstar[s];
     for (int q = 0; q < 3; ++q) sh[q] = f * P[q];
 }
@@ -1691,6 +1726,16 @@ hipError_t launch_uf_union(const int32_t *pairs, const int32_t *pair_count, int3
     return hipGetLastError();
 }
 
+// What a launch left in pm.kick or pm.kepler summed for the large systems.
+static hipError_t large_sums(const StepMomentum &pm, bool kick, hipStream_t stream)
+{
+    if (pm.n_large > 0)
+        large_sums_kernel<<<pm.n_large, CE_THREADS, 0, stream>>>(pm.large, kick ? pm.row_first : pm.item_first,
+                                                                 kick ? pm.kick : pm.kepler,
+                                                                 kick ? pm.sys_kick : pm.sys_kepler);
+    return hipGetLastError();
+}
+
 static int import_blocks(const PairImport &p) { return std::max(1, std::min(256, (p.cap + CE_THREADS - 1) / CE_THREADS)); }
 
 hipError_t launch_import_pairs(const PairImport &p, hipStream_t stream)
@@ -1712,7 +1757,7 @@ hipError_t launch_drift_open(const WorkItem *items, const double *vx, const doub
 {
     const int grid = pm.n_blocks + (import ? import_blocks(*import) : 0);
     (pm.small ? drift_open_kernel<true> : drift_open_kernel<false>)<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
-    return hipGetLastError();
+    return large_sums(pm, true, stream);
 }
 
 hipError_t launch_sun_shift(const WorkItem *items, int n_items, const double *mstar, double *x, double *y, double *z,
@@ -1726,7 +1771,7 @@ hipError_t launch_drifted(const WorkItem *items, int n_items, const double *vx, 
                           const double *m, const StepMomentum &pm, hipStream_t stream)
 {
     drifted_kernel<<<n_items, 64, 0, stream>>>(items, vx, vy, vz, m, pm);
-    return hipGetLastError();
+    return large_sums(pm, false, stream);
 }
 
 hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
@@ -1742,7 +1787,7 @@ hipError_t launch_kick_close(const KickArgs &a, double *x, double *y, double *z,
 {
     (pm.small ? kick_close_kernel<true> : kick_close_kernel<false>)<<<1 + pm.n_blocks, CE_THREADS, 0, stream>>>(
         a, x, y, z, pm, groups ? *groups : GroupBuild{}, groups != nullptr);
-    return hipGetLastError();
+    return large_sums(pm, true, stream);
 }
 
 hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, double *x, double *y, double *z,
@@ -1790,7 +1835,7 @@ hipError_t launch_drift(const Layout &L, const WorkItem *items, int n_items, dou
                                                m, rc, dt, members, group_start, wg_list, flags, rc_lv, nlev, pm);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (fork && (e = hipStreamWaitEvent(stream, side->join, 0)) != hipSuccess) return e;
-    return hipGetLastError();
+    return large_sums(pm, false, stream);
 }
 
 } // namespace genga

@@ -1049,6 +1049,9 @@ int upload_plan(genga_ctx *ctx)
         ++rows_kick;
     }
     rfirst[n_sys] = rows_kick;
+    std::vector<int32_t> large;
+    for (int s = 0; s < n_sys; ++s)
+        if (rfirst[s + 1] - rfirst[s] > LARGE_ROWS) large.push_back(s);
     // energy tasks: the sources after an item's first body (a test item has none: test pairs have
     // no energy), in runs as the kick's
     std::vector<EnergyTask> et;
@@ -1105,9 +1108,10 @@ int upload_plan(genga_ctx *ctx)
         return at;
     };
     const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_rfirst = put(rfirst),
-                 o_first = put(first);
+                 o_first = put(first), o_large = put(large);
     const size_t o_et = put(et), o_efirst = put(efirst), o_er = put(er), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
     const size_t o_kick = place(3 * (size_t)rows_kick * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
+    const size_t o_sums = place(large.empty() ? 0 : 6 * (size_t)n_sys * sizeof(double));
     const size_t o_group = place(3 * (size_t)CE_MAX_GROUPS * sizeof(double));
     const size_t o_gsys = place((size_t)CE_MAX_GROUPS * sizeof(int32_t)), o_gn = place(sizeof(int32_t));
     const size_t o_epart = place(9 * et.size() * sizeof(double));
@@ -1144,6 +1148,10 @@ int upload_plan(genga_ctx *ctx)
     ctx->pm.mstar = ctx->L.mstar;
     ctx->pm.n_blocks = (int32_t)cb.size();
     ctx->pm.small = small;
+    ctx->pm.large = reinterpret_cast<int32_t *>(plan + o_large);
+    ctx->pm.n_large = (int32_t)large.size();
+    ctx->pm.sys_kick = reinterpret_cast<double *>(plan + o_sums);
+    ctx->pm.sys_kepler = ctx->pm.sys_kick + 3 * (size_t)n_sys;
     ctx->pm.parts = cparts;
     ctx->pm.kick = reinterpret_cast<double *>(plan + o_kick);
     ctx->pm.kepler = reinterpret_cast<double *>(plan + o_kepler);

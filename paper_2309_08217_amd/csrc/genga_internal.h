@@ -106,6 +106,9 @@ inline int close_parts(int n_items, int n_cu)
     while (p > 1 && (int64_t)n_items * p > (int64_t)CLOSE_WAVES * n_cu) p /= 2;
     return p;
 }
+// (Summed by every workgroup of the system that takes it, the momentum of 4 million bodies made their
+// genga_drift 676 us; summed once 217.  1.1 million, the first it is done for: 118 and 82.)
+constexpr int LARGE_ROWS = 1024;
 struct CloseBlock {
     int32_t sys, waves; // a system's waves: CLOSE_WAVES (a run of items), else systems [sys, sys + n)
     int32_t item, n;    // a run: items [item, item + n)
@@ -122,6 +125,9 @@ struct StepMomentum {
     const double *mstar = nullptr;       // [n_sys]
     int32_t n_blocks = 0;
     bool small = false;                  // there are blocks of several systems
+    const int32_t *large = nullptr;      // [n_large] systems of more than LARGE_ROWS rows of kick: whoever
+    int32_t n_large = 0;                 //   takes their momentum reads one sum, formed by a launch of its own
+    double *sys_kick = nullptr, *sys_kepler = nullptr; // [n_sys][3] these sums (of kick, kepler)
     int32_t parts = 1;                   // a run's waves per item
     double *kick = nullptr;    // [rows][3] sum m v after the kick
     double *kepler = nullptr;  // [n_items][3] sum m v after the drift, bodies outside groups

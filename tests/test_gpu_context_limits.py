@@ -271,3 +271,39 @@ def test_autotune_cache_of_other_kernels(tmp_path):
     genga.genga_autotune(s.ctx.handle, s.b, FP32, str(path))
     assert path.read_text().splitlines() == lines
     s.close()
+
+
+# 1024 rows of 16 blocks of 64 bodies are the most that every workgroup sums for itself; systems of
+# one and of several workgroups beside it
+@pytest.mark.parametrize("sizes", [[1 << 20], [300, (1 << 20) + 64, 2000, 30]])
+def test_drift_and_step_of_a_system_of_a_million(sizes):
+    """The drift against the oracle's, and a step against its own kicks and drift: four massive bodies
+    a system, the others' momentum moves the Sun."""
+    ds, rng = [], np.random.default_rng(9)
+    for n in sizes:
+        a, ph = rng.uniform(0.5, 4.0, n), rng.uniform(0.0, 2.0 * np.pi, n)
+        v, zero = 1.0 / np.sqrt(a), np.zeros(n)
+        ds.append(discs.Disc(x=a * np.cos(ph), y=a * np.sin(ph), z=zero, vx=0.01 - v * np.sin(ph),
+                             vy=v * np.cos(ph), vz=zero.copy(), m=np.full(n, 1e-3 / n)))
+    s, t = (System(ds, rcrit=np.zeros(sum(sizes))) for _ in range(2))
+    for u in (s, t):
+        genga.genga_set_test_bodies(u.ctx.handle, [4] * len(sizes))
+    s.encounter_list(standalone=True, cap=0)
+    genga.genga_drift(s.ctx.handle, s.b, DT)
+    got = s.numpy_state()
+    for k, d in enumerate(ds):
+        ref = oracle.drift(d.state(), np.zeros(d.n), 1.0, DT, np.zeros((0, 2), np.int32))
+        err = max(np.max(np.abs(got[q][s.system_slice(k)] - ref[q])) for q in KEYS)
+        print(f"[million] system {k} of {d.n}, error {err:.1e}", flush=True)
+        assert err <= 1e-13
+    genga.genga_step(s.ctx.handle, s.b, DT, 2, FP64)
+    genga.genga_drift(t.ctx.handle, t.b, DT)
+    for tau in (0.5 * DT, DT):
+        genga.genga_kick(t.ctx.handle, t.b, tau, FP64)
+        genga.genga_drift(t.ctx.handle, t.b, DT)
+    genga.genga_kick(t.ctx.handle, t.b, 0.5 * DT, FP64)
+    assert all(genga.genga_poll_status(u.ctx.handle) == genga.GENGA_OK for u in (s, t))
+    got, ref = s.numpy_state(), t.numpy_state()
+    assert max(np.max(np.abs(got[q] - ref[q])) for q in KEYS) <= 1e-13
+    s.close()
+    t.close()

@@ -55,14 +55,14 @@ typedef enum {
 
 /* Precision of the long-range pair arithmetic (the paper's "Do Kick in single precision"
  * switch, Sect. 4).  FP32: coordinate differences are formed in FP64 and rounded to FP32,
- * the pair term is FP32, partial sums over blocks of 64 sources are FP32 and are folded into
+ * the pair term is FP32, partial sums over at most 32 sources are FP32 and are folded into
  * an FP64 accumulator.  FP64: everything FP64.  Pairs inside the changeover region are
  * always evaluated in FP64 (Sect. 1: encounter forces are always FP64). */
 typedef enum { GENGA_KICK_FP64 = 0, GENGA_KICK_FP32 = 1 } genga_kick_prec;
 
-/* Accumulator of the FP32 kick across blocks of 64 sources (the paper fixes none; the per-body
- * sum is exact enough either way, see the kick below).  FP64: each block's FP32 partial sum is
- * rounded into an FP64 accumulator.  KAHAN32: the partial sums are added into an FP32 sum with
+/* Accumulator of the FP32 kick across its partial sums (the paper fixes none; the per-body
+ * sum is exact enough either way, see the kick below).  FP64: each FP32 partial sum is
+ * added to an FP64 accumulator.  KAHAN32: the partial sums are added into an FP32 sum with
  * Kahan compensation, whose two FP32 words are combined in FP64 at the end.  The FP64 kick
  * ignores the selector. */
 typedef enum { GENGA_ACC_FP64 = 0, GENGA_ACC_KAHAN32 = 1 } genga_acc_mode;
@@ -103,7 +103,8 @@ int genga_set_test_bodies(genga_ctx *ctx, const int32_t *n_massive_host);
  * group raises GENGA_ERR_CAPACITY and its bodies are only Kepler-drifted.  enable = 1: they
  * are integrated by the same FP64 Bulirsch-Stoer method as the small groups, with the group's
  * state spread over the device; genga_drift and genga_step then synchronise the host with
- * `stream` once per step (to read the group sizes) and once per Bulirsch-Stoer attempt, so
+ * `stream` once per step (to read the group sizes) and after every Bulirsch-Stoer attempt or
+ * every few that are surely needed (up to 16), so
  * graph capture is refused (GENGA_ERR_STATE) while enabled.  Capacity: every body of the
  * layout may be in an encounter group; one group holds at most 65536 bodies.  A larger group
  * makes genga_drift return GENGA_ERR_CAPACITY before it enqueues anything (genga_step: with
@@ -175,8 +176,7 @@ int genga_compact(genga_ctx *ctx, genga_bodies *b, double *radius, int32_t *stat
  * consecutive bodies a patch about as wide as long) and azimuth, ties in the present order.
  * The paper fixes no body order; every result is the same up to the rounding order of sums.
  * What the order changes is speed where r_crit spans many neighbours: the kick's candidate
- * pairs then come in dense runs instead of one lane in every wave, and the union-find of the
- * encounter groups converges in fewer rounds.  Keplerian shear spreads each patch along its
+ * pairs then come in dense runs instead of one lane in every wave.  Keplerian shear spreads each patch along its
  * ring again (in a dense annulus at 0.7-1 au, by about a patch's width in some tens of 5-day
  * steps), so call it every few steps, between genga_step calls.
  * Permuted: the bodies' x..vz, m and rcrit (the library writes m and rcrit: const in
@@ -239,8 +239,8 @@ int genga_kick(genga_ctx *ctx, genga_bodies *b, double tau, int prec, int acc, v
 /* The close-encounter pair list (Sect. 1: the pairs closer than r_crit,ij, whose motion the
  * encounter step integrates; GENGA keeps such a list per level):
  *  - b == NULL: the list of the last genga_kick / genga_accel / genga_step of this context,
- *    which must have run on the current positions (GENGA_ERR_STATE after a genga_drift,
- *    a layout change or before any kick);
+ *    which must have run on the current positions (GENGA_ERR_STATE after a genga_drift, a
+ *    refused genga_step, a layout change or before any kick);
  *  - b != NULL: the list for b's positions and r_crit, computed standalone (FP64 decision, no
  *    forces); it also becomes the context's list, which the next genga_drift uses.
  * Writes pairs[cap][2] (device int32, global body indices, i < j, one system), sorted

@@ -13,7 +13,7 @@
 // accepted a column, or reached dt, skips the rest.  The host repeats attempts until no group is
 // active.
 //
-// The members of a group are ordered by ring and azimuth about the star (by the host, once per
+// The members of a group are ordered by ring and azimuth about the star (on the device, once per
 // step), so a tile of 64 consecutive members is compact in space.  Each state buffer carries the
 // bounding box of every tile, written by the launch that wrote the positions; a wave skips a
 // source tile whose box is farther than the group's largest r_crit from the target tile's
@@ -432,7 +432,7 @@ __device__ __forceinline__ ListMember list_member(double skin, double ms, double
     return m;
 }
 
-// Start of an attempt on the list path, one wave per tile: the positions of Y as source records,
+// Start of an attempt on the list path, one wave per tile: the positions of Y for the first round,
 // the group's position and velocity scales (max |r|, max |v|: one atomic per workgroup whose
 // tiles share a group, as 631 tiles' atomics on one address took 10 us), and, unless the lists
 // still hold, the tile's boxes in position, velocity and A and the largest S of its members.

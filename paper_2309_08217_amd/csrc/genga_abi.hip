@@ -95,7 +95,7 @@ struct genga_ctx {
     // grid-wide Bulirsch-Stoer for groups of more than CE_MAX_GROUP members (opt-in)
     int32_t large_groups = 0;
     BigBs big;
-    int32_t *pin = nullptr;            // pinned host words: [2] the union-find rounds, [4..6] the attempts' status
+    int32_t *pin = nullptr;            // pinned host words: [2] a zero for big.ovf, [4..6] the attempts' status
     hipStream_t big_stream = nullptr;  // private stream to capture one attempt
     DriftSide side;                    // the drift's second stream (groups of 9..64 members)
     // the captured attempt, replayed on the caller's stream: one per tile-launch grid (64 times
@@ -104,8 +104,6 @@ struct genga_ctx {
     hipGraphExec_t big_exec_list[64] = {}; // the same on the list path
     int32_t ce_cap = 0;                // members / group_start capacity
     GroupHeader groups_h{};            // large mode: sizes of the groups of the last pair list
-    // host scratch of the grouping and tile ordering, kept so that the per-call vectors of
-    // n_total entries are not allocated (and faulted in) again on every call
     OrderWork ow;                      // the device ring / azimuth ordering of the large groups
     // genga_sort_bodies: its ordering work, the bounds of the sorted runs (the massive and the
     // test bodies of each system: 2 n_sys + 1 offsets) and the permutation
@@ -1695,8 +1693,8 @@ int genga_drift(genga_ctx *ctx, genga_bodies *b, double dt, const int32_t *pairs
         im = PairImport{ctx->L.sys_of, ctx->L.n_total, pairs,         d_count,        ctx->pairs,
                         ctx->pair_count, ctx->pair_cap, ctx->import_bad, ctx->flags};
     if (!ctx->col.mass && !ctx->large_groups && ctx->L.n_total > 0) {
-        // four launches: the list and the momentum, the groups, the drift, the last shift (as
-        // launches of their own, and with a second stream, 20040 bodies with their list took 110 us, now 76)
+        // five launches: the list and the momentum, the groups, the drift, the groups of 9..64, the
+        // last shift (as nine, with a second stream, 20040 bodies with their list took 96 us, so 39)
         ctx->list_valid = false;
         StepMomentum pm = ctx->pm;
         pm.tau = 0.5 * dt;

@@ -7,7 +7,8 @@
 // close-encounter forces.
 //
 // Layout as in the grid-wide Bulirsch-Stoer: the members of the parent groups are ordered by
-// ring and azimuth (by the host, once per level interval) and cut into tiles of 64.  In a
+// ring and azimuth (on the device, once per step, and passed on from level to level) and cut into
+// tiles of 64.  In a
 // group of several tiles a workgroup of 16 waves (4 when such tiles outnumber the CUs, so that
 // several workgroups share a CU) takes one target tile, lists the source tiles
 // of the group whose box lies within the group's largest level-(l-1) radius of the target

@@ -21,7 +21,7 @@ constexpr int NA_MAX_TASKS = KICK_TASKS_PER_CU * 256 + NA_MAX_ITEMS;
 // byte offsets of the parts of the scratch array (each a multiple of 256)
 constexpr size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 constexpr size_t OFF_M32 = 0;
-constexpr size_t OFF_PART = OFF_M32 + align256((size_t)NA_MAX_N * sizeof(float)); // [tasks][3][64] FP64
+constexpr size_t OFF_PART = OFF_M32 + align256((size_t)NA_MAX_N * sizeof(float)); // the tasks' shares, FP64
 constexpr size_t OFF_ITEMS = OFF_PART + align256((size_t)NA_MAX_TASKS * 192 * sizeof(double));
 constexpr size_t OFF_CHUNKS = OFF_ITEMS + align256((size_t)NA_MAX_ITEMS * sizeof(WorkItem));
 constexpr size_t OFF_RC2 = OFF_CHUNKS + align256((size_t)NA_MAX_CHUNKS * sizeof(Chunk));

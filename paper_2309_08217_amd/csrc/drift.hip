@@ -1756,7 +1756,8 @@ hipError_t launch_drift_open(const WorkItem *items, const double *vx, const doub
                              const double *m, const StepMomentum &pm, const PairImport *import, hipStream_t stream)
 {
     const int grid = pm.n_blocks + (import ? import_blocks(*import) : 0);
-    (pm.small ? drift_open_kernel<true> : drift_open_kernel<false>)<<<grid, CE_THREADS, 0, stream>>>(items, vx, vy, vz, m, pm, import ? *import : PairImport{});
+    (pm.small ? drift_open_kernel<true> : drift_open_kernel<false>)<<<grid, CE_THREADS, 0, stream>>>(
+        items, vx, vy, vz, m, pm, import ? *import : PairImport{});
     return large_sums(pm, true, stream);
 }
 
@@ -1777,8 +1778,8 @@ hipError_t launch_drifted(const WorkItem *items, int n_items, const double *vx, 
 hipError_t launch_drift_close(const WorkItem *items, double *x, double *y, double *z, const StepMomentum &pm,
                               hipStream_t stream)
 {
-    (pm.small ? drift_close_kernel<true> : drift_close_kernel<false>)<<<pm.n_blocks, CE_THREADS, 0, stream>>>(items, x, y,
-                                                                                                              z, pm);
+    (pm.small ? drift_close_kernel<true> : drift_close_kernel<false>)<<<pm.n_blocks, CE_THREADS, 0, stream>>>(
+        items, x, y, z, pm);
     return hipGetLastError();
 }
 

@@ -1105,8 +1105,8 @@ int upload_plan(genga_ctx *ctx)
         used = at + bytes;
         return at;
     };
-    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows), o_cb = put(cb), o_rfirst = put(rfirst),
-                 o_first = put(first), o_large = put(large);
+    const size_t o_items = put(it), o_tasks = put(tasks), o_tfirst = put(tfirst), o_rows = put(rows);
+    const size_t o_cb = put(cb), o_rfirst = put(rfirst), o_first = put(first), o_large = put(large);
     const size_t o_et = put(et), o_efirst = put(efirst), o_er = put(er), o_nm = put(ctx->n_massive_h), o_seg = put(seg);
     const size_t o_kick = place(3 * (size_t)rows_kick * sizeof(double)), o_kepler = place(3 * it.size() * sizeof(double));
     const size_t o_sums = place(large.empty() ? 0 : 6 * (size_t)n_sys * sizeof(double));
